@@ -13,7 +13,8 @@
 //   transpose-read instruction (ds_read_b64_tr_b16), so no operand is ever transposed in HBM.
 //   Out-of-range lanes of a copy are redirected past the end of the buffer descriptor (they deliver zero),
 //   which handles ragged M, N and K without branches.
-// fp32 path: plain FMA tile kernel with generic strides (the fp32 configuration is tiny).
+// fp32 path: the 32x32x2 fp32 MFMA with the same kind of copies; a plain FMA tile kernel with generic strides for
+// operands that are not made of whole aligned 16-byte pieces.
 #include "kernels.h"
 #include "gfx950.h"
 
@@ -665,6 +666,203 @@ hipError_t mfma_ceiling(int blocks, int iters, const void* seed, float* sink, hi
 }
 
 // ------------------------------------------------------------------------------------------ fp32
+// fp32 products on the 32x32x2 fp32 MFMA instruction (inputs and accumulation in full fp32).
+//
+// What bounds it: one such MFMA multiplies 32 x 32 x 2 in 64 clocks (256 FLOP per clock and compute unit), so a matrix
+// pipe needs 16 bytes of operands from the LDS per 64 clocks and nothing about the LDS is critical; what matters is that
+// all 4 x 256 pipes have a tile to work on and that the copies are far enough ahead.
+// The kernel is the bf16 one's little sister: operands arrive in the LDS by asynchronous copies, in a ring of NS slots
+// of KD contraction indices, one barrier per slot.  A 16-byte LDS read is 4 consecutive contraction indices of a row:
+// lane half g holds indices 8 v + 4 g + j, j = 0..3, and MFMA j of the four that follow multiplies indices {8 v + j,
+// 8 v + 4 + j}; an operand that is strided in the contraction index is read one float per MFMA in the same order.
+// With WK = 4 the four waves share one 32 x 32 tile and split every slot's contraction between them (their sums meet in
+// the LDS at the end, added in wave order): small outputs then still give every matrix pipe work.
+// Measured against the FMA kernel that ran these products before: [512, 1024] x 5504 (NT) 990 -> 63 us, [256, 256] x 688
+// 126 -> 10 us with the launch; [4096, 4096] x 4096 reaches 138-140 TFLOP/s of the 157 that the instruction allows.
+template <int R, bool KC, int KD>
+struct OperandTileF32 {
+  static constexpr int BYTES = R * KD * 4, CHUNKS = BYTES / 1024, PER_WAVE = CHUNKS / 4;
+  static constexpr int GR = KD / 4;                 // KC: 16-byte granules per image row [R][KD]
+  static constexpr int GPR = R / 4;                 // KS: granules per image row [KD][R]
+  static constexpr int RPB = GR >= 16 ? 1 : 16 / GR;
+  static_assert(CHUNKS % 4 == 0, "tile must split evenly over 4 waves");
+  // KC: granule g of row r sits in slot g ^ (r / RPB) % GR (16 rows at one granule touch all 16 bank groups).
+  static __device__ __forceinline__ int kc_swz(int row) { return (row / RPB) & (GR - 1); }
+  // KS: image row `pos` holds contraction index ks_k(pos), so the two indices that one MFMA multiplies (8 v + j and
+  // 8 v + 4 + j) are neighbours; rows of 256 bytes or more swap their 128-byte halves on odd positions so that the two
+  // lane halves of a read never meet in a bank.
+  static __device__ __forceinline__ int ks_k(int pos) { return (pos & ~7) | ((pos & 1) << 2) | ((pos >> 1) & 3); }
+  static __device__ __forceinline__ constexpr int ks_flip(int pos) { return R >= 64 ? (pos & 1) << 3 : 0; }
+  static __device__ __forceinline__ void copy_plan(int c, int p, long ld, int origin, int extent, unsigned& goff, int& kidx) {
+    const int P = 64 * c + p;
+    if constexpr (KC) {
+      const int row = P / GR, g = (P % GR) ^ kc_swz(row);
+      goff = (origin + row < extent) ? (unsigned)((long)row * ld * 4 + g * 16) : kOob;
+      kidx = g * 4;
+    } else {
+      const int pos = P / GPR, g = (P % GPR) ^ ks_flip(pos), k = ks_k(pos);
+      goff = (origin + g * 4 < extent) ? (unsigned)((long)k * ld * 4 + g * 16) : kOob;
+      kidx = k;
+    }
+  }
+  // the 4 contraction indices 8 v + 4 (lane / 32) + 0..3 of row r0 + lane % 32
+  static __device__ __forceinline__ f32x4 frag(lds_u8* img, int lane, int r0, int v) {
+    if constexpr (KC) {
+      const int row = r0 + (lane & 31);
+      return *reinterpret_cast<LDS_AS const f32x4*>(img + row * (KD * 4) + (((2 * v + (lane >> 5)) ^ kc_swz(row)) << 4));
+    } else {
+      const int g = lane >> 5, col = (r0 + (lane & 31)) ^ (ks_flip(g) * 4);
+      LDS_AS const float* const q = reinterpret_cast<LDS_AS const float*>(img) + (8 * v + g) * R + col;
+      f32x4 o;
+#pragma unroll
+      for (int j = 0; j < 4; j++) o[j] = q[2 * j * R];
+      return o;
+    }
+  }
+};
+
+template <int BM, int BN, bool AKC, bool BKC, int WK, int KD, int NS>
+__global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(GemmParams p) {
+  using TA = OperandTileF32<BM, AKC, KD>;
+  using TB = OperandTileF32<BN, BKC, KD>;
+  constexpr int SW = WK == 4 ? 1 : 2;               // waves along each side of the tile
+  constexpr int TM = BM / (32 * SW), TN = BN / (32 * SW);
+  constexpr int NA = TA::PER_WAVE, NB = TB::PER_WAVE, L = NA + NB, SLOT = TA::BYTES + TB::BYTES;
+  static_assert(WK == 1 || (WK == 4 && TM == 1 && TN == 1), "wave arrangement");
+  static_assert(KD % (8 * WK) == 0 && NS >= 2 && (NS - 2) * L < 64, "slot depth, wait counter");
+
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  lds_u8* const lds = LDS_PTR(unsigned char, smem_raw);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)lds;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = WK == 4 ? 0 : wave >> 1, wn = WK == 4 ? 0 : wave & 1, wk = WK == 4 ? wave : 0;
+
+  int tm_i, tn_i;
+  if (gridDim.z == 1) tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, tm_i, tn_i);
+  else { tm_i = (int)blockIdx.x % p.tiles_m; tn_i = (int)blockIdx.x / p.tiles_m; }
+  const int m0 = tm_i * BM, n0 = tn_i * BN;
+  int k_lo = 0, k_hi = p.K;
+  if (p.causal == CAUSAL_SKIP_UPPER) {
+    if (n0 > m0 + BM - 1) return;
+  } else if (p.causal == CAUSAL_K_END) {
+    k_hi = (m0 + BM < p.K) ? m0 + BM : p.K;
+  } else if (p.causal == CAUSAL_K_BEGIN) {
+    k_lo = m0;
+  }
+  const int nk = k_hi > k_lo ? (k_hi - k_lo + KD - 1) / KD : 0;
+  const int z = blockIdx.z;
+  const int zo = z / p.batch_inner, zi = z - zo * p.batch_inner;
+  const float* A = reinterpret_cast<const float*>(p.A) + zo * p.sAo + zi * p.sAi;
+  const float* B = reinterpret_cast<const float*>(p.B) + zo * p.sBo + zi * p.sBi;
+
+  unsigned a_goff[NA], b_goff[NB];
+  int a_kidx[NA], b_kidx[NB];
+#pragma unroll
+  for (int i = 0; i < NA; i++) TA::copy_plan(wave + 4 * i, lane, p.lda, m0, p.M, a_goff[i], a_kidx[i]);
+#pragma unroll
+  for (int i = 0; i < NB; i++) TB::copy_plan(wave + 4 * i, lane, p.ldb, n0, p.N, b_goff[i], b_kidx[i]);
+  const long a_kstep = AKC ? 1 : p.lda, b_kstep = BKC ? 1 : p.ldb;
+  uint64_t a_next = reinterpret_cast<uint64_t>((AKC ? A + (long)m0 * p.lda : A + m0) + (long)k_lo * a_kstep);
+  uint64_t b_next = reinterpret_cast<uint64_t>((BKC ? B + (long)n0 * p.ldb : B + n0) + (long)k_lo * b_kstep);
+  int slot_next = 0, krem = k_hi - k_lo;
+  // Copies of the next slot.  Past the end every lane is redirected out of range: zeros, no memory traffic, and the
+  // number of operations in flight stays uniform.
+  auto issue = [&]() {
+    const u32x4 dA = make_desc(reinterpret_cast<const void*>(a_next)), dB = make_desc(reinterpret_cast<const void*>(b_next));
+    const uint32_t base = lds0 + slot_next * SLOT + wave * 1024;
+#pragma unroll
+    for (int i = 0; i < NA; i++) dma16(base + i * 4096, dA, a_kidx[i] < krem ? a_goff[i] : kOob);
+#pragma unroll
+    for (int i = 0; i < NB; i++) dma16(base + TA::BYTES + i * 4096, dB, b_kidx[i] < krem ? b_goff[i] : kOob);
+    a_next += (uint64_t)(KD * a_kstep * 4);
+    b_next += (uint64_t)(KD * b_kstep * 4);
+    slot_next = slot_next + 1 == NS ? 0 : slot_next + 1;
+    krem -= KD;
+  };
+
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
+
+  if (nk > 0) {
+#pragma unroll
+    for (int t = 0; t < NS - 1; t++) issue();
+    for (int t = 0; t < nk; t++) {
+      wait_vmem<(NS - 2) * L>();              // slot t has landed (this wave's share)
+      __syncthreads();                        // ... everyone's share; everyone is done with slot t - 1
+      issue();                                // slot t + NS - 1 in the place of slot t - 1
+      lds_u8* const ia = lds + (t % NS) * SLOT;
+      lds_u8* const ib = ia + TA::BYTES;
+#pragma unroll
+      for (int u = 0; u < KD / 8 / WK; u++) {
+        const int v = u * WK + wk;
+        f32x4 fa[TM], fb[TN];
+#pragma unroll
+        for (int i = 0; i < TM; i++) fa[i] = TA::frag(ia, lane, (wm * TM + i) * 32, v);
+#pragma unroll
+        for (int j = 0; j < TN; j++) fb[j] = TB::frag(ib, lane, (wn * TN + j) * 32, v);
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+#pragma unroll
+          for (int i = 0; i < TM; i++)
+#pragma unroll
+            for (int j = 0; j < TN; j++)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i][q], fb[j][q], acc[i][j], 0, 0, 0);
+      }
+    }
+    wait_vmem<0>();                           // (the empty copies issued past the end)
+  }
+  if constexpr (WK > 1) {                     // the waves' partial tiles, added in wave order; one quarter of the rows each
+    __syncthreads();
+    LDS_AS float* const part = reinterpret_cast<LDS_AS float*>(lds);
+    static_assert(WK * 1024 * 4 <= NS * SLOT, "the partial tiles must fit in the ring");
+#pragma unroll
+    for (int e = 0; e < 16; e++) part[(wk * 16 + e) * 64 + lane] = acc[0][0][e];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 16; e++) acc[0][0][e] = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int e = 4 * wave + q;             // registers 4 w .. 4 w + 3 = rows 8 w + 4 (lane / 32) + 0..3
+      float s = part[e * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < WK; w++) s += part[(w * 16 + e) * 64 + lane];
+      acc[0][0][q] = s;
+    }
+  }
+  // ---- epilogue: a wave-wide store is two rows of 32 consecutive floats
+  float* C = reinterpret_cast<float*>(p.C) + zo * p.sCo + zi * p.sCi;
+  const float* R = reinterpret_cast<const float*>(p.R);
+  if (R) R += zo * p.sCo + zi * p.sCi;
+  const float* const delta = p.delta ? p.delta + zo * p.sDo + zi * p.sDi : nullptr;
+#pragma unroll
+  for (int i = 0; i < TM; i++)
+#pragma unroll
+    for (int j = 0; j < TN; j++) {
+      const int col = n0 + (wn * TN + j) * 32 + (lane & 31);
+#pragma unroll
+      for (int e = 0; e < (WK > 1 ? 4 : 16); e++) {
+        const int row = m0 + (wm * TM + i) * 32 + (WK > 1 ? 8 * wave + 4 * (lane >> 5) + e : 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3));
+        if (row >= p.M || col >= p.N) continue;
+        const long idx = (long)row * p.ldc + col;
+        float v = p.alpha * acc[i][j][e];
+        if (delta) {
+          v = (!p.delta_causal || col <= row) ? R[idx] * (v - delta[(long)row * p.ldd]) : 0.f;
+        } else {
+          if (p.accumulate) v += C[idx];
+          if (R) v += R[idx];
+        }
+        C[idx] = v;
+      }
+    }
+}
+
+// The general fp32 product, for operands that the copies above cannot move in 16-byte pieces:
 // 64 x 64 x 16 tile, 256 threads, 4 x 4 outputs per thread; operands addressed through element strides so
 // one kernel serves NN, NT and TN.
 template <typename OutT>
@@ -912,6 +1110,57 @@ hipError_t gemm_tn_grouped(const GroupedProduct* prods, int n, hipStream_t s) {
   return hipSuccess;
 }
 
+// fp32: whole 16-byte pieces of A and B (pointers, leading dimensions, batch strides and contiguous extents), and a tile's
+// rows within a 31-bit buffer range.  C, the residual and ldc have no such rule.
+static bool f32_mfma_ok(const GemmArgs& g) {
+  const long a_cols = g.layout == TN ? g.M : g.K, b_cols = g.layout == NT ? g.K : g.N;
+  const long mult4 = g.lda | g.ldb | a_cols | b_cols | (g.batch > 1 ? g.sAo | g.sAi | g.sBo | g.sBi : 0);
+  return mult4 % 4 == 0 && (reinterpret_cast<uintptr_t>(g.A) | reinterpret_cast<uintptr_t>(g.B)) % 16 == 0 &&
+         g.lda < (1 << 22) && g.ldb < (1 << 22);
+}
+
+template <int BM, int BN, bool AKC, bool BKC, int WK, int KD, int NS>
+static hipError_t launch_f32(const GemmParams& p0, int batch, hipStream_t s) {
+  GemmParams p = p0;
+  p.tiles_m = (p.M + BM - 1) / BM;
+  p.tiles_n = (p.N + BN - 1) / BN;
+  constexpr size_t smem = (size_t)NS * (BM + BN) * KD * sizeof(float);
+  static_assert(smem <= 160 * 1024, "LDS budget of one gfx950 compute unit");
+  auto kern = gemm_f32_mfma_kernel<BM, BN, AKC, BKC, WK, KD, NS>;
+  static AttrOnce once;
+  if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)batch), dim3(256), smem, s, p);
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int WK, int KD, int NS>
+static hipError_t launch_f32_layout(int layout, const GemmParams& p, int batch, hipStream_t s) {
+  switch (layout) {
+    case NN: return launch_f32<BM, BN, true, false, WK, KD, NS>(p, batch, s);
+    case NT: return launch_f32<BM, BN, true, true, WK, KD, NS>(p, batch, s);
+    case TN: return launch_f32<BM, BN, false, false, WK, KD, NS>(p, batch, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+// Tile of an fp32 product: the one with the shortest time by rounds of 256 compute units, (rounds) x (tile area) / (rate).
+// The rates (TFLOP/s with every compute unit busy) are measured: 128 x 128 tiles 132-140, 64 x 64 tiles 110-125, 32 x 32
+// tiles with the contraction split over the waves 91-110 (they move 4 times the operand bytes of the first).  Times in us,
+// 128 / 64 / 32: [512, 1024] x 5504 349 / 105 / 63 (too few tiles for anything but the smallest), [512, 5504] x 1024
+// 79 / 62 / 75, [2048, 2048] x 2048 149 / 144 / 175, [4096, 4096] x 4096 998 / 1069 / 1245.
+// Rings of three or four shallower slots measured within 5 % of these (128: three slots slower, 1049; 64: four 32-deep
+// slots 1058; 32: four 64-deep slots 1260).
+static hipError_t dispatch_f32(int layout, const GemmParams& p, int batch, hipStream_t s) {
+  auto cost = [&](int t, double rate) {
+    const long tiles = (long)((p.M + t - 1) / t) * ((p.N + t - 1) / t) * batch;
+    return (double)((tiles + 255) / 256) * t * t / rate;
+  };
+  const double c128 = cost(128, 132.), c64 = cost(64, 115.), c32 = cost(32, 100.);
+  if (c32 <= c64 && c32 <= c128) return launch_f32_layout<32, 32, 4, 128, 2>(layout, p, batch, s);
+  if (c64 <= c128) return launch_f32_layout<64, 64, 1, 64, 2>(layout, p, batch, s);
+  return launch_f32_layout<128, 128, 1, 32, 2>(layout, p, batch, s);
+}
+
 hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;     // empty product: nothing to write
   GemmParams p{};
@@ -930,6 +1179,7 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
       case TN: p.sam = 1; p.sak = g.lda; p.sbk = g.ldb; p.sbn = 1; break;
       default: return hipErrorInvalidValue;
     }
+    if (f32_mfma_ok(g)) return dispatch_f32(g.layout, p, g.batch, s);
     p.tiles_m = (g.M + 63) / 64;
     p.tiles_n = (g.N + 63) / 64;
     dim3 grid((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)g.batch);

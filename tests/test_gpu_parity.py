@@ -66,6 +66,35 @@ def test_gemm_matches_definition(dtype, layout, mnk):
         assert max_rel(to_np(got), ref + R) < 4.5e-3
 
 
+@pytest.mark.parametrize("layout", [tbp.NN, tbp.NT, tbp.TN])
+@pytest.mark.parametrize("mnk", [
+    (4, 4, 4), (33, 36, 128), (36, 32, 132), (100, 68, 260),      # 32 x 32 tiles: edges, and a slot more and less than full
+    (1036, 1028, 60), (964, 1092, 68),                            # 64 x 64 tiles
+    (4100, 2052, 36), (2052, 4036, 28),                           # 128 x 128 tiles
+    (33, 65, 17), (130, 7, 3), (66, 130, 34)])                    # no whole 16-byte pieces: the general kernel
+def test_gemm_f32_tiles_and_general_path(layout, mnk):
+    """fp32 products at the edges of each tile size of the matrix-core kernel and on the general kernel, with a residual,
+    and on operands whose leading dimension is wider than the row.  Tolerance: K exact products summed in fp32, each of at
+    most K roundings 2^-24 relative to a partial sum; over the tensor's largest element 2e-5 as everywhere here."""
+    M, N, K = mnk
+    _say(f"gemm f32 layout={layout} M,N,K={mnk}")
+    a_shape = (K, M) if layout == tbp.TN else (M, K)
+    b_shape = (N, K) if layout == tbp.NT else (K, N)
+    A, B, R = _rnd(17, "A", a_shape, "f32"), _rnd(17, "B", b_shape, "f32"), _rnd(17, "R", (M, N), "f32")
+    a64, b64 = A.astype(np.float64), B.astype(np.float64)
+    ref = {tbp.NN: ops.linear_fwd, tbp.NT: ops.linear_p1, tbp.TN: ops.linear_p2}[layout](a64, b64)
+    dA, dB = to_dev(A, "f32"), to_dev(B, "f32")
+    assert max_rel(to_np(tbp.tbp_gemm(layout, dA, dB, R=to_dev(R, "f32"))), ref + R) < 2e-5
+    # column blocks of wider matrices, at an offset that keeps (4) and one that breaks (1) the 16-byte alignment
+    for off in (4, 1):
+        wide = torch.full((a_shape[0], a_shape[1] + 8), float("nan"), device=DEV)
+        wide[:, off:off + a_shape[1]] = dA
+        out = torch.full((M, N + 3), 7.0, device=DEV)
+        tbp.tbp_gemm(layout, wide[:, off:off + a_shape[1]], dB, C_out=out[:, :N])
+        assert max_rel(to_np(out[:, :N]), ref) < 2e-5
+        assert torch.all(out[:, N:] == 7.0)
+
+
 @pytest.mark.parametrize("layout", [tbp.NN, tbp.NT])
 @pytest.mark.parametrize("mnk", [(1024, 4096, 32768), (1000, 4040, 32776), (1280, 2304, 49152)])
 def test_gemm_with_split_contraction(layout, mnk):
