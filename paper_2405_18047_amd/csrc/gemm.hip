@@ -1,11 +1,11 @@
 // GEMM kernels for gfx950 (MI355X).
 //
 // bf16 path: C = alpha * op(A) op(B) on the 32x32x16 bf16 MFMA instruction, fp32 accumulation.
-//   One workgroup = 4 wavefronts (2 x 2), block tile BM x BN (256 x 256, 256 x 192 or 128 x 128, chosen per product by
-//   how well the tiles fill the 256 compute units), contraction consumed in slices of 32 through a 4-slot LDS ring, or
+//   One workgroup = 4 wavefronts (2 x 2), block tile BM x BN (256 x 256, 256 x 192, 128 x 128 or 64 x 64, chosen per
+//   product by how well the tiles fill the 256 compute units), contraction consumed in slices of 32 through a 4-slot LDS ring, or
 //   in slices of 64 through two slots where the contraction index is contiguous in memory, filled by asynchronous
 //   global -> LDS copies (no staging registers) that stay in flight while the previous slices are multiplied.
-//   Outputs too small for any of that can split the contraction over several workgroups per tile (scratch memory).
+//   Outputs with too few tiles cut the contraction over several workgroups per tile (scratch memory, a second launch).
 //   An operand whose contraction index is contiguous in memory ("KC": A of NN/NT, B of NT) is kept in
 //   LDS as [row][k] and read as 16-byte vectors; an operand whose contraction index is the slow,
 //   strided one ("KS": A of TN, B of NN/TN, i.e. both operands of dW = X^T dY) is kept as [k][row]
@@ -36,10 +36,9 @@ struct GemmParams {
   const float* delta; long ldd, sDo, sDi;
   int delta_causal;
   long a_panel;                 // see GemmArgs
-  // contraction split over `split` workgroups per tile (see SplitPlan)
-  int split;
-  float* split_ws;
-  unsigned* split_cnt;
+  // contraction cut into `split` slices of split_k indices, one workgroup per (tile, slice) (see SplitPlan); slice i leaves
+  // its partial product at C + i * sCo
+  int split, split_k;
 };
 
 constexpr int BK = 32;                     // contraction depth of one LDS slot
@@ -59,6 +58,25 @@ __device__ __forceinline__ void tile_of_block(int pid, int tiles_m, int tiles_n,
   const int width = GROUP * tiles_n;
   const int grp = id / width;
   const int first = grp * GROUP;
+  const int gsz = (tiles_m - first) < GROUP ? (tiles_m - first) : GROUP;
+  const int r = id - grp * width;
+  tm = first + r % gsz;
+  tn = r / gsz;
+}
+
+// The same for a product whose contraction is cut into slices: the sequence that is dealt out to the XCDs in contiguous
+// ranges runs over the tiles of the first slice, then of the second, and so on.  An XCD then works on one slice (or a
+// stretch of one), so each L2 fetches only its slice of the operands, and of the larger one (the weights) no other XCD
+// fetches the same part.
+__device__ __forceinline__ void tile_of_block_split(int pid, int tiles_m, int tiles_n, int split, int& tm, int& tn, int& slice) {
+  const int nt = tiles_m * tiles_n, total = nt * split;
+  const int xcd = pid & 7, q = pid >> 3;
+  const int per = total >> 3, rem = total & 7;
+  const int seq = xcd * per + (xcd < rem ? xcd : rem) + q;
+  slice = seq / nt;
+  const int id = seq - slice * nt;
+  const int GROUP = 8, width = GROUP * tiles_n;
+  const int grp = id / width, first = grp * GROUP;
   const int gsz = (tiles_m - first) < GROUP ? (tiles_m - first) : GROUP;
   const int r = id - grp * width;
   tm = first + r % gsz;
@@ -145,8 +163,7 @@ __device__ __forceinline__ bf16x8 read_frag(lds_u8* q) {
 // row, a whole cache line, where the 32-deep slot fetches every line in two halves one iteration apart and doubles
 // the number of requests to the L2.
 template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD = BK, bool SPLIT = false, int RING = 0>
-__device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, int tn_i, int z, int split_idx = 0,
-                                               int tile_seq = 0) {
+__device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, int tn_i, int z) {
   // RING == 0: the default pipeline of the slot depth (32: ring of STAGES slots; 64: two slots); RING >= 3: the ring
   // pipeline with that many slots, for either depth
   constexpr bool RINGPIPE = KD == 32 || RING >= 3;
@@ -179,14 +196,13 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, in
   } else if (p.causal == CAUSAL_K_BEGIN) {
     k_lo = m0;
   }
-  if constexpr (SPLIT) {      // this workgroup's slice of the contraction, in whole slots (may be empty)
-    const int per = ((p.K + KD - 1) / KD + p.split - 1) / p.split * KD;
-    k_lo = split_idx * per < p.K ? split_idx * per : p.K;
-    k_hi = k_lo + per < p.K ? k_lo + per : p.K;
+  if constexpr (SPLIT) {      // z: this workgroup's slice of the contraction, in whole slots (the last may be shorter)
+    k_lo = z * p.split_k;
+    k_hi = k_lo + p.split_k < p.K ? k_lo + p.split_k : p.K;
   }
   const int nk = (k_hi - k_lo + KD - 1) / KD;
 
-  const int zo = z / p.batch_inner, zi = z - zo * p.batch_inner;
+  const int zo = SPLIT ? z : z / p.batch_inner, zi = SPLIT ? 0 : z - zo * p.batch_inner;
   const bf16_t* A = reinterpret_cast<const bf16_t*>(p.A) + zo * p.sAo + zi * p.sAi;
   const bf16_t* B = reinterpret_cast<const bf16_t*>(p.B) + zo * p.sBo + zi * p.sBi;
 
@@ -363,66 +379,6 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, in
   // a lane owns single elements of many rows.  Each wave therefore passes its tile through LDS one 32-row strip at
   // a time (the ring is free by now) and reads it back row-major, so that every lane stores 16 contiguous bytes
   // and a wave-wide store covers whole rows of the tile.
-  if constexpr (SPLIT) {
-    // Partial sums meet in memory: every workgroup of a tile leaves its accumulators there in register order (lane-
-    // contiguous stores), takes a ticket, and the one that draws the last ticket adds all slices up in slice order,
-    // clears the counter for the next product and goes on to the epilogue.  Nobody waits for anybody: a workgroup that
-    // is not last is simply done.
-    // The exchange does not depend on where the workgroups run.  The partial sums are written and read with
-    // device-scope accesses (16-byte buffer stores / loads with the sc1 cache-policy bit: they go through to, and come
-    // from, the level of the memory system that all XCDs share, whatever L2 the workgroup sits behind) and the ticket
-    // is a device-scope atomic.
-    // Order: every lane waits until its own stores have completed (vmcnt(0)), the workgroup barrier collects all
-    // lanes, only then does lane 0 take the ticket; a workgroup that sees the last ticket therefore follows, in
-    // time, the completion of every slice's stores, and its loads cannot be served from a stale cached copy.  No
-    // cache-wide write-back or invalidate is involved (such a fence would flush the L2 under every other workgroup's
-    // operand panels).  The launch map still puts the slices of a tile on one XCD, but only for speed.
-    constexpr long TILE = (long)BM * BN;
-    constexpr int kDeviceScope = 16;        // cache-policy bit "sc1" of the buffer instructions: device scope
-    float* const mine = p.split_ws + ((long)tile_seq * p.split + split_idx) * TILE;
-    {
-      const __amdgpu_buffer_rsrc_t rs = make_rsrc(mine, (uint32_t)(TILE * sizeof(float)));
-#pragma unroll
-      for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++)
-#pragma unroll
-          for (int e4 = 0; e4 < 4; e4++) {
-            u32x4 v;
-#pragma unroll
-            for (int q = 0; q < 4; q++) v[q] = __float_as_uint(acc[i][j][4 * e4 + q]);
-            __builtin_amdgcn_raw_buffer_store_b128(v, rs, ((((i * TN + j) * 4 + e4) * 256 + tid) << 4), 0, kDeviceScope);
-          }
-    }
-    wait_vmem<0>();                         // this lane's partial sums have been written
-    LDS_AS int* const last_arrival = reinterpret_cast<LDS_AS int*>(lds);     // (the ring is free once all waves are here)
-    __syncthreads();
-    if (tid == 0)
-      *last_arrival = __hip_atomic_fetch_add(p.split_cnt + tile_seq, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                      (unsigned)(p.split - 1);
-    __syncthreads();
-    if (!*last_arrival) return;
-#pragma unroll
-    for (int i = 0; i < TM; i++)
-#pragma unroll
-      for (int j = 0; j < TN; j++)
-#pragma unroll
-        for (int e = 0; e < 16; e++) acc[i][j][e] = 0.f;
-    for (int sl = 0; sl < p.split; sl++) {
-      const __amdgpu_buffer_rsrc_t rs = make_rsrc(p.split_ws + ((long)tile_seq * p.split + sl) * TILE, (uint32_t)(TILE * sizeof(float)));
-#pragma unroll
-      for (int i = 0; i < TM; i++)
-#pragma unroll
-        for (int j = 0; j < TN; j++)
-#pragma unroll
-          for (int e4 = 0; e4 < 4; e4++) {
-            const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, ((((i * TN + j) * 4 + e4) * 256 + tid) << 4), 0, kDeviceScope);
-#pragma unroll
-            for (int q = 0; q < 4; q++) acc[i][j][4 * e4 + q] += __uint_as_float(v[q]);
-          }
-    }
-    if (tid == 0) __hip_atomic_store(p.split_cnt + tile_seq, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
   __syncthreads();                          // every wave is done with the ring
   OutT* C = reinterpret_cast<OutT*>(p.C) + zo * p.sCo + zi * p.sCi;
   const bf16_t* R = reinterpret_cast<const bf16_t*>(p.R);
@@ -570,27 +526,38 @@ __global__ __launch_bounds__(256) void gemm_bf16_causal_pair_kernel(GemmParams p
   }
 }
 
-// `split` workgroups per output tile, each over its slice of the contraction.  Workgroup ids that differ by 8 are made
-// the slices of one tile: where the hardware hands consecutive ids to the 8 XCDs in turn, a tile's slices then run
-// on one XCD and fetch the tile's operand panels through one L2 (a matter of speed only: the exchange of the partial
-// sums is correct wherever the workgroups run).
-template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD>
-__global__ __launch_bounds__(256) void gemm_bf16_splitk_kernel(GemmParams p) {
-  const int v = (int)blockIdx.x, xcd = v & 7, q = v >> 3;
-  const int split_idx = q % p.split;
-  const int tq = q / p.split;                 // which of this XCD's tiles
-  const int nt = p.tiles_m * p.tiles_n;
-  if (tq >= (nt >> 3) + (xcd < (nt & 7) ? 1 : 0)) return;
-  // the same tile order as the unsplit kernel: an XCD owns a contiguous stretch of it, i.e. a compact patch of tiles
-  int tm_i, tn_i;
-  tile_of_block(tq * 8 + xcd, p.tiles_m, p.tiles_n, tm_i, tn_i);
-  const int tile_seq = tn_i * p.tiles_m + tm_i;
-  gemm_bf16_tile<BM, BN, AKC, BKC, OutT, KD, true>(p, tm_i, tn_i, 0, split_idx, tile_seq);
+// One workgroup per (tile, slice of the contraction); the fp32 partial products are added up by split_sum_kernel.
+template <int BM, int BN, bool AKC, bool BKC, int KD, int RING>
+__global__ __launch_bounds__(256) void gemm_bf16_split_kernel(GemmParams p) {
+  int tm_i, tn_i, slice;
+  tile_of_block_split(blockIdx.x, p.tiles_m, p.tiles_n, p.split, tm_i, tn_i, slice);
+  gemm_bf16_tile<BM, BN, AKC, BKC, float, KD, true, RING>(p, tm_i, tn_i, slice);
 }
 
-__global__ void fill_u32_kernel(unsigned* dst, int n, unsigned value) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) dst[i] = value;
+// C = bf16(sum over the slices of parts[slice][M][N] (+ R)), slices added in order.
+__global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict__ parts, int split, int M, int N,
+                                                        const bf16_t* __restrict__ R, bf16_t* __restrict__ C, long ldc) {
+  const int nv = N / 8;
+  const long v = blockIdx.x * 256L + threadIdx.x;
+  if (v >= (long)M * nv) return;
+  const long row = v / nv, col = (v - row * nv) * 8, idx = row * ldc + col, step = (long)M * N;
+  const float* q = parts + row * N + col;
+  u32x4 r = {0, 0, 0, 0};
+  if (R) r = *reinterpret_cast<const u32x4*>(R + idx);
+  f32x4 a = {0.f, 0.f, 0.f, 0.f}, b = a;
+#pragma unroll 4
+  for (int i = 0; i < split; i++) {
+    a += *reinterpret_cast<const f32x4*>(q + i * step);
+    b += *reinterpret_cast<const f32x4*>(q + i * step + 4);
+  }
+  float o[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  bf16x8 w;
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    w[2 * i] = (bf16_t)(o[2 * i] + __uint_as_float(r[i] << 16));
+    w[2 * i + 1] = (bf16_t)(o[2 * i + 1] + __uint_as_float(r[i] & 0xffff0000u));
+  }
+  *reinterpret_cast<bf16x8*>(C + idx) = w;
 }
 
 // Several independent weight-gradient products (TN layout, fp32 output) in one launch: the tiles of all products form
@@ -973,67 +940,109 @@ static hipError_t launch_bf16_causal_pair(const GemmParams& p0, int batch, hipSt
   return hipGetLastError();
 }
 
-// Tiles 192 columns wide for the linear-layer products whose output fills the chip badly with 256 x 256 tiles (too
-// few of them, or a last round that is mostly empty): e.g. [2048, 5120] is 160 large tiles (62 % of a round) but 216
-// of the narrower ones (84 %).  Taken when the fraction of the rounds' capacity that is useful output, discounted
-// 7 % for the narrower tile's lower operand reuse, beats what the other choice gives by 8 %; the small-tile kernel,
-// which outputs of fewer than 192 large tiles otherwise use, counts as 0.60.
-static bool narrow_tiles_pay(int M, int N, int K) {
-  if (M < 256 || N < 192 || K <= 256) return false;
-  const long tiles_m = (M + 255) / 256;
-  const long t256 = tiles_m * ((N + 255) / 256), t192 = tiles_m * ((N + 191) / 192);
-  const double area = (double)M * N;
-  const double now = (N >= 256 && t256 >= 192) ? area / ((double)((t256 + 255) / 256) * 256 * 65536) : 0.60;
-  const double narrow = 0.93 * area / ((double)((t192 + 255) / 256) * 256 * 49152);
-  return t192 >= 192 && narrow > 1.08 * now;
-}
-
-// Cost model behind gemm_split_plan, fitted to measurements on this chip (microseconds): a round of large tiles costs
-// 0.0245 per contraction index plus 12 of prologue and epilogue; the exchange of partial sums costs about 30 plus
-// 0.67 per MiB of partials (they are written by every workgroup but read back by one workgroup per tile only); the
-// small-tile kernel that such outputs otherwise use sustains about 800 TFLOP/s when it has a tile for every compute
-// unit.  In practice only long contractions
-// pay: e.g. [2048, 5120] x K = 27648 runs in 590 us split three ways against 810 us.
-SplitPlan gemm_split_plan(int dtype, int layout, int M, int N, int K, int out_f32, int batch) {
-  SplitPlan none{1, 0};
-  if (dtype != 1 || out_f32 || batch != 1 || layout == TN || M < 256 || N < 256) return none;
-  const long tiles = (long)((M + 255) / 256) * ((N + 255) / 256);
-  if (tiles >= 192 || narrow_tiles_pay(M, N, K)) return none;
-  const long small_tiles = (long)((M + 127) / 128) * ((N + 127) / 128);      // (fewer than 256 of them leave CUs idle)
-  double best = 2.0 * M * N * (double)K / (800e6 * (small_tiles < 256 ? small_tiles / 256.0 : 1.0));
-  int split = 1;
-  for (int sp = 2; sp <= 8; sp++) {
-    if (K / sp < 512) break;
-    const long rounds = (tiles * sp + 255) / 256;
-    const double t = rounds * (0.0245 * K / sp + 12.0) + 30.0 + 0.67 * (tiles * sp * 0.25);
-    if (t < 0.9 * best) { best = t; split = sp; }
+// Tile and number of contraction slices of a storage-type NN / NT product (the linear layers of forward and backward-p1)
+// whose output is at most one round of 256 x 256 tiles: the choice with the shortest modelled time.  The model, in us,
+// was fitted to 2500 measured (shape, tile, slices) triples, M 64-2048, N 256-22016, K 256-22016 (8 % rms), and picks
+// within 1.6 % of the fastest measured choice on average, 13 % at worst:
+//   a round of 256 workgroups of K / slices indices costs (per index) + (fixed)
+//     128 x 128 on four 64-deep slots   0.0091   3.0   one workgroup per compute unit
+//     256 x 192                         0.0167   8.0   "
+//     256 x 256                         0.0197   9.7   "
+//     128 x 128 on two 64-deep slots    0.0126   1.5   two per compute unit: 0.0188 per round of 512
+//     64 x 64 on four 64-deep slots     0.0047   1.3   "                     0.0071
+//   but at least the time of reading both operands once at 4.9 TB/s plus 8.4;
+//   slices add 3.8 (the second launch) and 0.30 per MB of partial products, and must gain 8 %.
+// Why so many: one tile per compute unit leaves most of the chip idle on the short micro-batches.  Measured (us) against
+// what these shapes ran on before: [256, 4096] x 22016 (NT) 207 -> 76 (16 x 16 large tiles), [256, 22016] x 4096 106 -> 75
+// (256 x 192 in two slices), [360, 4096] x 11008 99 -> 52 (96 tiles of 128 in five), [1024, 4096] x 22016 212 -> 169 (64
+// large tiles in four), [512, 1024] x 2752 23 -> 16 (64 x 64); unsplit where the tiles already fill the chip, e.g.
+// [1024, 4096] x 4096 43 us on 128 x 128 tiles against 54 for the best split.
+enum ProductTile { T128_DEEP, T256_NARROW, T256, T128_PAIR, T64 };
+static bool one_round(int M, int N) { return (long)((M + 255) / 256) * ((N + 255) / 256) <= 256; }
+static SplitPlan product_plan(int M, int N, int K, bool allow_split) {
+  struct Tile { int bm, bn, per_cu; double c1, c2, fixed; };
+  static const Tile tiles[] = {{128, 128, 1, 0.0091, 0., 3.0}, {256, 192, 1, 0.0167, 0., 8.0}, {256, 256, 1, 0.0197, 0., 9.7},
+                               {128, 128, 2, 0.0126, 0.0188, 1.5}, {64, 64, 2, 0.0047, 0.0071, 1.3}};
+  static const int slices[] = {1, 2, 3, 4, 5, 6, 8, 12, 16};
+  const double memory = 2e-6 * ((double)N * K + (double)M * K) / 4.9 + 8.4;
+  SplitPlan best{T64, 1, K, 0};
+  double best_time = 1e30;
+  for (int i = 0; i < 5; i++) {
+    const Tile& t = tiles[i];
+    if (t.bm == 256 && M < 192) continue;
+    for (int sp : slices) {
+      if (sp > 1 && (!allow_split || K / sp < 256)) break;
+      const int slice = sp == 1 ? K : ((K + 63) / 64 + sp - 1) / sp * 64, split = sp == 1 ? 1 : (K + slice - 1) / slice;
+      const long n = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * split;
+      const double one = slice * t.c1 + t.fixed, two = slice * t.c2 + t.fixed;
+      double time;
+      if (t.per_cu == 1) time = (double)((n + 255) / 256) * one;
+      else time = (double)(n / 512) * two + (n % 512 == 0 ? 0. : n % 512 <= 256 ? one : two);
+      time = (time < memory ? memory : time) + 0.02 * time;       // (equally memory-bound: the one that computes faster)
+      if (split > 1) time = 1.08 * (time + 3.8 + 0.303e-6 * split * M * N * sizeof(float));
+      if (time < best_time) {
+        best_time = time;
+        best = SplitPlan{i, split, slice, split > 1 ? (size_t)split * M * N * sizeof(float) : 0};
+      }
+    }
   }
-  if (split == 1) return none;
-  return SplitPlan{split, kSplitCounterBytes + (size_t)tiles * split * 256 * 256 * sizeof(float)};
+  return best;
+}
+SplitPlan gemm_split_plan(int dtype, int layout, int M, int N, int K, int out_f32, int batch) {
+  const SplitPlan none{0, 1, 0, 0};
+  if (dtype != 1 || out_f32 || batch != 1 || layout == TN || !one_round(M, N)) return none;
+  const SplitPlan plan = product_plan(M, N, K, true);
+  return plan.split > 1 ? plan : none;
 }
 
-template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD>
-static hipError_t launch_bf16_split(const GemmParams& p0, int split, void* ws, int counters_zero, hipStream_t s) {
+template <int BM, int BN, bool AKC, bool BKC, int KD, int RING>
+static hipError_t launch_bf16_split(const GemmParams& p0, const SplitPlan& plan, void* ws, hipStream_t s) {
   GemmParams p = p0;
   p.tiles_m = (p.M + BM - 1) / BM;
   p.tiles_n = (p.N + BN - 1) / BN;
-  p.split = split;
-  p.split_cnt = static_cast<unsigned*>(ws);
-  p.split_ws = reinterpret_cast<float*>(static_cast<char*>(ws) + kSplitCounterBytes);
-  const int tiles = p.tiles_m * p.tiles_n;
-  if ((size_t)tiles * sizeof(unsigned) > kSplitCounterBytes) return hipErrorInvalidValue;
-  constexpr size_t smem = (size_t)(KD == 32 ? STAGES : 2) * (BM + BN) * KD * sizeof(bf16_t);
-  auto kern = gemm_bf16_splitk_kernel<BM, BN, AKC, BKC, OutT, KD>;
+  p.split = plan.split; p.split_k = plan.slice;
+  p.C = ws; p.ldc = p.N; p.sCo = (long)p.M * p.N; p.sCi = 0; p.R = nullptr;
+  p.sAo = p.sAi = p.sBo = p.sBi = 0;
+  constexpr size_t smem = (size_t)(RING >= 3 ? RING : (KD == 32 ? STAGES : 2)) * (BM + BN) * KD * sizeof(bf16_t);
+  auto kern = gemm_bf16_split_kernel<BM, BN, AKC, BKC, KD, RING>;
   static AttrOnce once;
   if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
-  if (!counters_zero) {
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, s, p.split_cnt, (int)(kSplitCounterBytes / 4), 0u);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-  }
-  const unsigned blocks = (unsigned)((tiles + 7) / 8 * 8 * split);
-  hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), smem, s, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_m * p.tiles_n * plan.split)), dim3(256), smem, s, p);
+  if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  const long nv = (long)p.M * (p.N / 8);
+  hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, s, static_cast<const float*>(ws),
+                     plan.split, p.M, p.N, static_cast<const bf16_t*>(p0.R), static_cast<bf16_t*>(p0.C), p0.ldc);
   return hipGetLastError();
+}
+
+template <int BM, int BN, bool BKC, int RING>
+static hipError_t launch_product(const GemmParams& p, const SplitPlan& plan, void* ws, hipStream_t s) {
+  return plan.split > 1 ? launch_bf16_split<BM, BN, true, BKC, 64, RING>(p, plan, ws, s)
+                        : launch_bf16<BM, BN, true, BKC, bf16_t, 64, RING>(p, 1, s);
+}
+template <bool BKC>
+static hipError_t dispatch_product(const GemmParams& p, const SplitPlan& plan, void* ws, hipStream_t s) {
+  switch (plan.tile) {
+    case T128_DEEP: return launch_product<128, 128, BKC, 4>(p, plan, ws, s);
+    case T256_NARROW: return launch_product<256, 192, BKC, 0>(p, plan, ws, s);
+    case T256: return launch_product<256, 256, BKC, 0>(p, plan, ws, s);
+    case T128_PAIR: return launch_product<128, 128, BKC, 0>(p, plan, ws, s);
+    case T64: return launch_product<64, 64, BKC, 4>(p, plan, ws, s);
+  }
+  return hipErrorInvalidValue;
+}
+
+// 256 x 192 tiles for outputs of more than one round of large tiles: taken when the fraction of the rounds' capacity that
+// is useful output, discounted 7 % for the narrower tile's lower operand reuse, beats what 256 x 256 tiles give by 8 %.
+// [1024, 22016] x 4096 is 344 large tiles (67 % of two rounds) but 460 of the narrower ones (90 %): 210 against 180 us.
+static bool narrow_tiles_pay(int M, int N, int K) {
+  if (M < 256 || N < 256 || K <= 256) return false;
+  const long tiles_m = (M + 255) / 256;
+  const long t256 = tiles_m * ((N + 255) / 256), t192 = tiles_m * ((N + 191) / 192);
+  const double area = (double)M * N;
+  const double now = area / ((double)((t256 + 255) / 256) * 256 * 65536);
+  const double narrow = 0.93 * area / ((double)((t192 + 255) / 256) * 256 * 49152);
+  return narrow > 1.08 * now;
 }
 
 // Slot depth by layout and tile size: operands with a contiguous contraction index get the 64-deep slots on the
@@ -1202,15 +1211,14 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   // short contractions (the per-head q k^T and do v^T, K = head_dim) are all prologue and epilogue: small tiles let
   // two or three workgroups share a compute unit and overlap them
   const bool big = g.M >= 256 && g.N >= 256 && tiles_big >= 192 && g.K > 256;
+  if (!g.out_f32 && g.batch == 1 && g.causal == CAUSAL_NONE && !g.delta && g.layout != TN && one_round(g.M, g.N)) {
+    SplitPlan plan = product_plan(g.M, g.N, g.K, g.ws && reinterpret_cast<uintptr_t>(g.ws) % 256 == 0);
+    if (plan.bytes > g.ws_bytes) plan = product_plan(g.M, g.N, g.K, false);
+    return g.layout == NN ? dispatch_product<false>(p, plan, g.ws, s) : dispatch_product<true>(p, plan, g.ws, s);
+  }
   if (!g.out_f32 && g.batch == 1 && g.causal == CAUSAL_NONE && !g.delta && g.layout != TN && narrow_tiles_pay(g.M, g.N, g.K))
     return g.layout == NN ? launch_bf16<256, 192, true, false, bf16_t, TBP_NARROW_KD, TBP_NARROW_RING>(p, 1, s)
                           : launch_bf16<256, 192, true, true, bf16_t, TBP_NARROW_KD, TBP_NARROW_RING>(p, 1, s);
-  if (g.ws && g.causal == CAUSAL_NONE && !g.delta && reinterpret_cast<uintptr_t>(g.ws) % 256 == 0) {
-    const SplitPlan plan = gemm_split_plan(dtype, g.layout, g.M, g.N, g.K, g.out_f32, g.batch);
-    if (plan.split > 1 && plan.bytes <= g.ws_bytes)
-      return g.layout == NN ? launch_bf16_split<256, 256, true, false, bf16_t, 64>(p, plan.split, g.ws, g.ws_counters_zero, s)
-                            : launch_bf16_split<256, 256, true, true, bf16_t, 64>(p, plan.split, g.ws, g.ws_counters_zero, s);
-  }
   auto run = [&](const GemmParams& q, bool use_big) -> hipError_t {
     if (!use_big && g.batch == 1 && q.K >= 1024 && (long)((q.M + 127) / 128) * ((q.N + 127) / 128) <= 256)
       return g.out_f32 ? dispatch_small_deep<float>(g.layout, q, s) : dispatch_small_deep<bf16_t>(g.layout, q, s);
@@ -1222,17 +1230,19 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   };
   // Tail quantisation: with nt large tiles on 256 compute units the last round runs nt % 256 workgroups.  When
   // that round would be at most three quarters full, the output is cut along its longer side into a part made of
-  // whole rounds of large tiles and a remainder: up to half a round's worth runs on 128 x 128 tiles (four times as
-  // many workgroups), more than that on 256 x 192 tiles where that kernel exists for the layout (4/3 as many
-  // workgroups: one nearly full round of tiles that take 3/4 of the time).
+  // whole rounds of large tiles and a remainder: of a forward or backward-p1 product on the tiles that product_plan
+  // picks; of a weight gradient, up to half a round's worth on 128 x 128 tiles (four times as many workgroups), more on
+  // 256 x 192 tiles (4/3 as many workgroups: one nearly full round of tiles that take 3/4 of the time).
   const long rem = tiles_big % 256;
   const bool has_narrow = (g.out_f32 && g.layout == TN) || (!g.out_f32 && g.layout != TN && !g.delta);
   auto run_rest = [&](const GemmParams& q) -> hipError_t {
+    if (!g.out_f32 && g.layout != TN && !g.delta) {
+      const SplitPlan plan = product_plan(q.M, q.N, q.K, false);
+      return g.layout == NN ? dispatch_product<false>(q, plan, nullptr, s) : dispatch_product<true>(q, plan, nullptr, s);
+    }
     const long t192 = (long)((q.M + 255) / 256) * ((q.N + 191) / 192);
     if (rem <= 128 || !has_narrow || t192 > 256) return run(q, rem > 128);
-    if (g.out_f32) return launch_bf16<256, 192, false, false, float, 32>(q, 1, s);
-    return g.layout == NN ? launch_bf16<256, 192, true, false, bf16_t, TBP_NARROW_KD, TBP_NARROW_RING>(q, 1, s)
-                          : launch_bf16<256, 192, true, true, bf16_t, TBP_NARROW_KD, TBP_NARROW_RING>(q, 1, s);
+    return launch_bf16<256, 192, false, false, float, 32>(q, 1, s);
   };
   const bool defer = g.defer_rest && g.out_f32 && g.layout == TN && g.alpha == 1.f && !g.a_panel;
   if (g.defer_rest) g.defer_rest->M = 0;

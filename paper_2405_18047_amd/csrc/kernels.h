@@ -40,12 +40,9 @@ struct GemmArgs {
   // delta[(zo * sDo + zi * sDi) + row * ldd] = rowsum(dP * P) = sum over the head's columns of do * o.
   const float* delta; long ldd, sDo, sDi;
   int delta_causal;
-  // Optional scratch for products whose output has too few large tiles to fill the chip (see gemm_split_plan):
-  // device memory of at least gemm_split_plan(...).bytes bytes, 256-byte aligned.  Its first kSplitCounterBytes hold
-  // per-tile arrival counters that must be zero when a product starts and are zero again when it ends;
-  // ws_counters_zero = 0 makes gemm() clear them first (a small fill launch).
+  // Optional scratch for products whose output has too few tiles to fill the chip (see gemm_split_plan): device memory of
+  // at least gemm_split_plan(...).bytes bytes, 256-byte aligned; nothing in it has to be initialised.
   void* ws; size_t ws_bytes;
-  int ws_counters_zero;
   // TN layout, storage-type operands only: A is stored in panels of kPanel output rows, element (k, m) at
   // A[(m / kPanel) * a_panel + k * lda + m % kPanel] with lda == kPanel, so that the K x kPanel slab an output tile
   // contracts over is one contiguous stream.  0: plain [K, lda] matrix.  Such a product runs on kPanel-wide tiles.
@@ -61,13 +58,10 @@ constexpr int kPanel = 128;
 // elements of one (sequence, head) entry of the fused attention's dS^T scratch, stored in such panels
 constexpr size_t attn_ds_elems(int seq) { return (size_t)((seq + kPanel - 1) / kPanel) * seq * kPanel; }
 
-// Split of the contraction over several workgroups per output tile.  An output with fewer than 192 tiles of
-// 256 x 256 leaves compute units idle (or falls back to small tiles that move twice the operand bytes per FLOP);
-// with `split` workgroups per tile, each summing a slice of the contraction into fp32 partials in the scratch buffer,
-// the chip is full again.  The workgroup that arrives last at a tile adds the partials up in slice order (so the result
-// does not depend on arrival order), and runs the ordinary epilogue.  split == 1: not worth it / not applicable.
-struct SplitPlan { int split; size_t bytes; };
-constexpr size_t kSplitCounterBytes = 1024;
+// Split of the contraction over several workgroups per output tile: slice i (contraction indices i * slice ..) leaves an
+// fp32 partial product [M][N] in the scratch buffer and a second launch adds the slices up in order (so the result does
+// not depend on timing).  split == 1: not worth it / not applicable.
+struct SplitPlan { int tile, split, slice; size_t bytes; };
 SplitPlan gemm_split_plan(int dtype, int layout, int M, int N, int K, int out_f32, int batch);
 
 inline GemmArgs gemm_args(int layout, int M, int N, int K, const void* A, long lda, const void* B, long ldb,

@@ -240,18 +240,11 @@ GemmArgs head_gemm(const Dims& c, int layout, int M, int N, int K) {
 // A linear-layer product of the forward or backward-p1 pass: handed the stage's scratch when its output is small
 // enough for the contraction to be split over several workgroups per tile.
 hipError_t linear_gemm(tbp_stage* st, GemmArgs g, hipStream_t s) {
-  const Dims& c = st->c;
   if (st->y.ws_split_bytes) {
-    const tbp::SplitPlan plan = tbp::gemm_split_plan(c.dtype, g.layout, g.M, g.N, g.K, g.out_f32, g.batch);
-    if (plan.split > 1 && plan.bytes <= st->y.ws_split_bytes) {
-      g.ws = st->ws(st->y.ws_split);
-      g.ws_bytes = st->y.ws_split_bytes;
-      // The arrival counters are cleared before every such product (one small launch) rather than once: a flag kept on
-      // the host would be wrong for a caller who records the first call into a graph and replays it later.
-      g.ws_counters_zero = 0;
-    }
+    g.ws = st->ws(st->y.ws_split);
+    g.ws_bytes = st->y.ws_split_bytes;
   }
-  return tbp::gemm(c.dtype, g, s);
+  return tbp::gemm(st->c.dtype, g, s);
 }
 
 tbp_status run_forward(tbp_stage* st, int mb, int slot, const void* x_in, void* x_out, hipStream_t s) {
@@ -708,7 +701,7 @@ tbp_status tbp_gemm_ws(int dtype, int layout, int M, int N, int K, float alpha, 
   g.alpha = alpha; g.out_f32 = out_f32; g.accumulate = accumulate; g.R = R;
   if (workspace) {
     if ((uintptr_t)workspace % 256) return fail(TBP_EINVAL, "workspace must be 256-byte aligned");
-    g.ws = workspace; g.ws_bytes = workspace_bytes; g.ws_counters_zero = 0;     // a caller's buffer: cleared here
+    g.ws = workspace; g.ws_bytes = workspace_bytes;
   }
   TBP_HIP(tbp::gemm(dtype, g, static_cast<hipStream_t>(stream)));
   return TBP_OK;

@@ -132,6 +132,31 @@ def test_gemm_with_split_contraction(layout, mnk):
     assert max_rel(to_np(tbp.tbp_gemm(layout, dA, dB, workspace=small)), ref) < 4.5e-3
 
 
+@pytest.mark.parametrize("layout", [tbp.NN, tbp.NT])
+@pytest.mark.parametrize("mnk", [
+    (64, 64, 64), (136, 1032, 2760), (72, 1032, 5512),            # 64 x 64 tiles; the last in slices
+    (1000, 2056, 3080), (1032, 1032, 4104),                       # 128 x 128 tiles, one per compute unit; in slices
+    (2000, 3464, 1160), (360, 4088, 5512),                        # 128 x 128 tiles, two per compute unit; few, long
+    (264, 22008, 1032), (264, 11016, 4104),                       # 256 x 192 tiles; in slices
+    (1032, 4088, 8200), (4088, 4088, 1096)])                      # 256 x 256 tiles in slices (ragged last slice); unsliced
+def test_gemm_tile_and_slice_choices(layout, mnk):
+    """Storage-type products of at most one round of large tiles: every tile size, with and without the contraction cut
+    into slices whose partial products a second launch adds up, ragged in M, N, K and in the last slice; output in a wider
+    matrix whose other columns stay untouched.  Tolerance: one bf16 rounding of the result (2^-8 of the element at most)."""
+    M, N, K = mnk
+    _say(f"gemm tiles layout={layout} M,N,K={mnk}")
+    A, B = _rnd(18, "A", (M, K), "bf16"), _rnd(18, "B", (N, K) if layout == tbp.NT else (K, N), "bf16")
+    R = _rnd(18, "R", (M, N + 16), "bf16", 4.0)
+    a64, b64 = A.astype(np.float64), B.astype(np.float64)
+    ref = ops.linear_p1(a64, b64) if layout == tbp.NT else ops.linear_fwd(a64, b64)
+    dA, dB, dR = to_dev(A, "bf16"), to_dev(B, "bf16"), to_dev(R, "bf16")
+    for workspace in (True, None):
+        out = torch.full((M, N + 16), 7.0, dtype=torch.bfloat16, device=DEV)
+        tbp.tbp_gemm(layout, dA, dB, C_out=out[:, :N], R=dR[:, :N], alpha=0.5, workspace=workspace)
+        assert max_rel(to_np(out[:, :N]), 0.5 * ref + R[:, :N]) < 4.5e-3
+        assert torch.all(out[:, N:] == 7.0)
+
+
 def test_gemm_strided_views_and_empty():
     # operands that are column blocks of wider matrices (leading dimension > row length), as the stage uses them
     dtype = "bf16"
