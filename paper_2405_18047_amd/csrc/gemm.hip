@@ -951,7 +951,7 @@ static hipError_t launch_bf16_causal_pair(const GemmParams& p0, int batch, hipSt
 //     128 x 128 on two 64-deep slots    0.0126   1.5   two per compute unit: 0.0188 per round of 512
 //     64 x 64 on four 64-deep slots     0.0047   1.3   "                     0.0071
 //   but at least the time of reading both operands once at 4.9 TB/s plus 8.4;
-//   slices add 3.8 (the second launch) and 0.30 per MB of partial products, and must gain 8 %.
+//   slices add 3.8 (the second launch) and 0.30 per MB of partial products, and must gain 12 %.
 // Why so many: one tile per compute unit leaves most of the chip idle on the short micro-batches.  Measured (us) against
 // what these shapes ran on before: [256, 4096] x 22016 (NT) 207 -> 76 (16 x 16 large tiles), [256, 22016] x 4096 106 -> 75
 // (256 x 192 in two slices), [360, 4096] x 11008 99 -> 52 (96 tiles of 128 in five), [1024, 4096] x 22016 212 -> 169 (64
@@ -979,10 +979,10 @@ static SplitPlan product_plan(int M, int N, int K, bool allow_split) {
       if (t.per_cu == 1) time = (double)((n + 255) / 256) * one;
       else time = (double)(n / 512) * two + (n % 512 == 0 ? 0. : n % 512 <= 256 ? one : two);
       time = (time < memory ? memory : time) + 0.02 * time;       // (equally memory-bound: the one that computes faster)
-      if (split > 1) time = 1.08 * (time + 3.8 + 0.303e-6 * split * M * N * sizeof(float));
+      if (split > 1) time = 1.12 * (time + 3.8 + 0.303e-6 * split * M * N * sizeof(float));
       if (time < best_time) {
         best_time = time;
-        best = SplitPlan{i, split, slice, split > 1 ? (size_t)split * M * N * sizeof(float) : 0};
+        best = SplitPlan{i, split, slice, split > 1 ? kSplitHead + (size_t)split * M * N * sizeof(float) : 0};
       }
     }
   }
@@ -1001,7 +1001,8 @@ static hipError_t launch_bf16_split(const GemmParams& p0, const SplitPlan& plan,
   p.tiles_m = (p.M + BM - 1) / BM;
   p.tiles_n = (p.N + BN - 1) / BN;
   p.split = plan.split; p.split_k = plan.slice;
-  p.C = ws; p.ldc = p.N; p.sCo = (long)p.M * p.N; p.sCi = 0; p.R = nullptr;
+  float* const parts = reinterpret_cast<float*>(static_cast<char*>(ws) + kSplitHead);
+  p.C = parts; p.ldc = p.N; p.sCo = (long)p.M * p.N; p.sCi = 0; p.R = nullptr;
   p.sAo = p.sAi = p.sBo = p.sBi = 0;
   constexpr size_t smem = (size_t)(RING >= 3 ? RING : (KD == 32 ? STAGES : 2)) * (BM + BN) * KD * sizeof(bf16_t);
   auto kern = gemm_bf16_split_kernel<BM, BN, AKC, BKC, KD, RING>;
@@ -1010,7 +1011,7 @@ static hipError_t launch_bf16_split(const GemmParams& p0, const SplitPlan& plan,
   hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_m * p.tiles_n * plan.split)), dim3(256), smem, s, p);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   const long nv = (long)p.M * (p.N / 8);
-  hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, s, static_cast<const float*>(ws),
+  hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, s, parts,
                      plan.split, p.M, p.N, static_cast<const bf16_t*>(p0.R), static_cast<bf16_t*>(p0.C), p0.ldc);
   return hipGetLastError();
 }
