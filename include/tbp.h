@@ -68,7 +68,8 @@ typedef enum {
 typedef enum { TBP_F32 = 0, TBP_BF16 = 1 } tbp_dtype;
 
 /* How backward-p2 walks a set of micro-batches (Section 3.2, Figure 2; Section 4.4, Table 3):
- *   LOOP     one weight-gradient product per micro-batch, accumulated in fp32;
+ *   LOOP     the weight-gradient products of the micro-batches of any set, in any order, accumulated in fp32 (in the
+ *            accumulators of one product over the rows of a run of consecutive micro-batches, in dW between runs);
  *   KCONCAT  the micro-batches are treated as one batch concatenated over the batch dimension,
  *            i.e. one product whose contraction length is n_mbs * tokens.  The stash keeps each
  *            tensor's micro-batches in consecutive rows of one slab, so no copy is made; the set

@@ -396,12 +396,13 @@ __global__ __launch_bounds__(64 * NW) void rmsnorm_p1_ring_kernel(int rows, int 
   for (int col = threadIdx.x; col < d; col += 64 * NW) partials[(long)blockIdx.x * d + col] = colbuf[col];
 }
 
-// out[col] (= or +=) sum over the first n_rows rows of parts[row][col].
+// out[col] (= or +=) sum over the first n_rows rows of parts[row][col], for the norm blockIdx.y of the table.
 // A workgroup covers kColsumCols columns with 16 row lanes each (64-byte reads; 16 partial sums folded in LDS in a
 // fixed order, so the result is reproducible).
 constexpr int kColsumCols = 16;
-__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ parts, int n_rows, int d, int accumulate,
-                                                     float* __restrict__ out) {
+__global__ __launch_bounds__(256) void colsum_kernel(GainSums g, int n_rows, int d, int accumulate) {
+  const float* __restrict__ const parts = g.parts[blockIdx.y];
+  float* __restrict__ const out = g.out[blockIdx.y];
   __shared__ float fold[16][kColsumCols + 1];
   const int c = threadIdx.x & (kColsumCols - 1), rlane = threadIdx.x / kColsumCols;
   const int col = blockIdx.x * kColsumCols + c;
@@ -811,10 +812,16 @@ static hipError_t rmsnorm_rows_t(int dtype, int rows, int d, float eps, const vo
   }
 }
 
-hipError_t gain_partials_sum(const float* partials, int n_rows, int d, int accumulate, float* out, hipStream_t s) {
-  hipLaunchKernelGGL(colsum_kernel, dim3((d + kColsumCols - 1) / kColsumCols), dim3(256), 0, s, partials, n_rows > 0 ? n_rows : 0, d,
-                     accumulate, out);
+hipError_t gain_partials_sums(const GainSums& g, int n_rows, int d, int accumulate, hipStream_t s) {
+  if (g.n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(colsum_kernel, dim3((d + kColsumCols - 1) / kColsumCols, g.n), dim3(256), 0, s, g, n_rows > 0 ? n_rows : 0, d,
+                     accumulate);
   return hipGetLastError();
+}
+hipError_t gain_partials_sum(const float* partials, int n_rows, int d, int accumulate, float* out, hipStream_t s) {
+  GainSums g{};
+  g.n = 1; g.parts[0] = partials; g.out[0] = out;
+  return gain_partials_sums(g, n_rows, d, accumulate, s);
 }
 
 hipError_t rmsnorm_p1_rows(int dtype, int rows, int d, float eps, const void* dy, const void* x, const void* g,

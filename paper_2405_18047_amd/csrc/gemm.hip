@@ -565,9 +565,12 @@ __global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict_
 // instead of idling until the slowest tile of a round has finished, and there is one launch instead of one per weight.
 // Each product's first workgroup id is a multiple of 8, which keeps the id -> XCD correspondence that the tile map
 // relies on; the surplus ids do nothing.
-// This pays for short contractions (one micro-batch per product).  For long ones it loses: the 32 tiles an XCD runs at
+// This pays for short contractions.  For long ones it loses: the 32 tiles an XCD runs at
 // a time share operand panels through its L2 only while they walk the contraction in step, which they do when a
 // launch starts them together and stop doing once tiles of different products and start times are mixed.
+// Tiles of 256 x 256 and 128 x 128 run on a ring of four 32-deep slots (one workgroup per compute unit, and two), 64 x 64
+// on four 64-deep ones (two).
+template <int TILE>
 __global__ __launch_bounds__(256) void gemm_tn_grouped_kernel(GroupedTable g) {
   int lo = 0, hi = g.n - 1;                   // last product whose first workgroup id is <= blockIdx.x
   const int bid = (int)blockIdx.x;
@@ -577,7 +580,7 @@ __global__ __launch_bounds__(256) void gemm_tn_grouped_kernel(GroupedTable g) {
   }
   const GroupedProduct& q = g.prod[lo];
   const int pid = bid - g.first_block[lo];
-  const int tiles_m = (q.M + 255) / 256, tiles_n = (q.N + 255) / 256;
+  const int tiles_m = (q.M + TILE - 1) / TILE, tiles_n = (q.N + TILE - 1) / TILE;
   if (pid >= tiles_m * tiles_n) return;
   GemmParams p{};
   p.A = q.A; p.B = q.B; p.C = q.C;
@@ -587,7 +590,7 @@ __global__ __launch_bounds__(256) void gemm_tn_grouped_kernel(GroupedTable g) {
   p.alpha = 1.f; p.accumulate = q.accumulate; p.causal = CAUSAL_NONE;
   int tm_i, tn_i;
   tile_of_block(pid, tiles_m, tiles_n, tm_i, tn_i);
-  gemm_bf16_tile<256, 256, false, false, float>(p, tm_i, tn_i, 0);
+  gemm_bf16_tile<TILE, TILE, false, false, float, (TILE == 64 ? 64 : 32), false, (TILE == 64 ? 4 : 0)>(p, tm_i, tn_i, 0);
 }
 
 // ------------------------------------------------------------------------------------------ ceiling
@@ -1097,27 +1100,114 @@ static hipError_t dispatch_layout(int layout, const GemmParams& p, int batch, hi
   return hipErrorInvalidValue;
 }
 
-hipError_t gemm_tn_grouped(const GroupedProduct* prods, int n, hipStream_t s) {
-  constexpr size_t smem = (size_t)STAGES * (256 + 256) * BK * sizeof(bf16_t);
+template <int TILE>
+static hipError_t launch_tn_grouped(const GroupedProduct* prods, int n, hipStream_t s) {
+  constexpr size_t smem = (size_t)4 * (TILE + TILE) * (TILE == 64 ? 64 : 32) * sizeof(bf16_t);
+  auto kern = gemm_tn_grouped_kernel<TILE>;
   static AttrOnce once;
-  if (hipError_t e = once.set(reinterpret_cast<const void*>(gemm_tn_grouped_kernel), smem); e != hipSuccess) return e;
-  for (int base = 0; base < n; base += kMaxGrouped) {
+  if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
+  for (int i = 0; i < n;) {
     GroupedTable g{};
     int blocks = 0;
-    for (int i = base; i < n && g.n < kMaxGrouped; i++) {
+    for (; i < n && g.n < kMaxGrouped; i++) {
       if (prods[i].M <= 0 || prods[i].N <= 0) continue;
       g.prod[g.n] = prods[i];
       g.first_block[g.n] = blocks;
-      const int tiles = ((prods[i].M + 255) / 256) * ((prods[i].N + 255) / 256);
+      const int tiles = ((prods[i].M + TILE - 1) / TILE) * ((prods[i].N + TILE - 1) / TILE);
       blocks += (tiles + 7) & ~7;
       g.n++;
     }
     if (g.n == 0) continue;
-    hipLaunchKernelGGL(gemm_tn_grouped_kernel, dim3((unsigned)blocks), dim3(256), smem, s, g);
+    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), smem, s, g);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// Modelled time (us) of n weight-gradient tiles over K contraction indices, fitted to products of [256, 256] to
+// [4096, 22016] with K 128-4096: the part that grows with K, and the part that writes (accumulating: reads and writes)
+// the fp32 output, which a workgroup does not overlap with its own products.
+static double dw_time(int tile, long n, int K, int accumulate) {
+  const int a = accumulate ? 2 : 1;
+  if (tile == 256) return (double)((n + 255) / 256) * (0.0232 * K + 22. * a);
+  const double one = tile == 128 ? 0.0105 * K + 4.5 * a : 0.0045 * K + 2. * a;
+  const double two = tile == 128 ? 0.0152 * K + 8.5 * a : 0.0073 * K + 2. * a;
+  return (double)(n / 512) * two + (n % 512 == 0 ? 0. : n % 512 <= 256 ? one : two);
+}
+static long dw_tiles(int tile, int M, int N) { return (long)((M + tile - 1) / tile) * ((N + tile - 1) / tile); }
+
+// The first `tiles` tiles of a product, in whole tile columns (or rows, if there are more of those), and the rest.
+static void cut_product(const GroupedProduct& q, long tiles, GroupedProduct& head, GroupedProduct& rest) {
+  const int tiles_m = (q.M + 255) / 256, tiles_n = (q.N + 255) / 256;
+  head = rest = q;
+  if (tiles_n >= tiles_m) {
+    const int n0 = (int)(tiles / tiles_m) * 256;
+    head.N = n0 < q.N ? n0 : q.N;
+    rest.N = q.N - head.N;
+    rest.B = static_cast<const char*>(q.B) + (size_t)n0 * 2;
+    rest.C = q.C + n0;
+  } else {
+    const int m0 = (int)(tiles / tiles_n) * 256;
+    head.M = m0 < q.M ? m0 : q.M;
+    rest.M = q.M - head.M;
+    rest.A = static_cast<const char*>(q.A) + (size_t)m0 * 2;
+    rest.C = q.C + (size_t)m0 * q.ldc;
+  }
+}
+
+// Two arrangements, taken by modelled time:
+//   large tiles: every product's whole rounds of 256 tiles as a launch of its own (tiles that start in step share operand
+//     panels through the L2), and what does not fill a round of all products together in one grouped launch.  If that
+//     pool ends with a nearly empty round, its last tiles run as a launch of smaller tiles instead;
+//   one grouped launch of 128 x 128 or 64 x 64 tiles: short contractions, where writing the output is most of the work and
+//     a second workgroup on the compute unit covers it, and small products, which have too few large tiles.
+// Measured (us), all weight gradients of a layer: d 1152, f 3080, K 4000 (990 tiles of 128): 209 as four launches of
+// 128 x 128 tiles, 155 grouped; 7B, K 256, accumulating: 589 grouped on large tiles; 7B, K 4096: 272 pooled tiles
+// 193, with the last 16 on 128 x 128 tiles 116 + 39; d 256, f 688, K 384: 62 as eight launches, 8 grouped on 64 x 64.
+hipError_t gemm_dw(const GroupedProduct* prods, int n, GroupedProduct* pool, hipStream_t s) {
+  long n64 = 0, n128 = 0, pooled = 0, whole = 0;
+  int K = 0, acc = 0;
+  for (int i = 0; i < n; i++) {
+    n64 += dw_tiles(64, prods[i].M, prods[i].N);
+    n128 += dw_tiles(128, prods[i].M, prods[i].N);
+    const long t = dw_tiles(256, prods[i].M, prods[i].N);
+    whole += t / 256 * 256;
+    pooled += t % 256;
+    K = prods[i].K; acc |= prods[i].accumulate;
+  }
+  const long last = pooled % 256;
+  const double e64 = dw_time(64, 16 * last, K, acc), e128 = dw_time(128, 4 * last, K, acc), e_end = e64 < e128 ? e64 : e128;
+  const bool small_end = pooled > 256 && last > 0 && e_end < 0.8 * dw_time(256, last, K, acc);
+  const double t64 = dw_time(64, n64, K, acc), t128 = dw_time(128, n128, K, acc);
+  const double t256 = dw_time(256, whole, K, acc) + dw_time(256, small_end ? pooled - last : pooled, K, acc) + (small_end ? e_end : 0.);
+  if (t64 <= t128 && t64 <= t256) return launch_tn_grouped<64>(prods, n, s);
+  if (t128 <= t256) return launch_tn_grouped<128>(prods, n, s);
+  int np = 0;
+  for (int i = 0; i < n; i++) {
+    const long t = dw_tiles(256, prods[i].M, prods[i].N);
+    GroupedProduct head, rest;
+    cut_product(prods[i], t / 256 * 256, head, rest);
+    if (head.M > 0 && head.N > 0) {
+      GemmParams p{};
+      p.A = head.A; p.B = head.B; p.C = head.C;
+      p.lda = head.lda; p.ldb = head.ldb; p.ldc = head.ldc;
+      p.M = head.M; p.N = head.N; p.K = head.K;
+      p.batch_inner = 1; p.alpha = 1.f; p.accumulate = head.accumulate; p.causal = CAUSAL_NONE;
+      if (hipError_t e = launch_bf16<256, 256, false, false, float, TBP_TN_DEPTH>(p, 1, s); e != hipSuccess) return e;
+    }
+    if (rest.M > 0 && rest.N > 0) pool[np++] = rest;
+  }
+  if (np == 0) return hipSuccess;
+  GroupedProduct end{};
+  if (small_end) {                            // the pool's last tiles, cut off its last product
+    const GroupedProduct q = pool[np - 1];
+    const long t = dw_tiles(256, q.M, q.N);
+    if (t > last) cut_product(q, t - last, pool[np - 1], end);
+  }
+  if (hipError_t e = launch_tn_grouped<256>(pool, np, s); e != hipSuccess) return e;
+  if (end.M <= 0 || end.N <= 0) return hipSuccess;
+  return e64 < e128 ? launch_tn_grouped<64>(&end, 1, s) : launch_tn_grouped<128>(&end, 1, s);
 }
 
 // fp32: whole 16-byte pieces of A and B (pointers, leading dimensions, batch strides and contiguous extents), and a tile's
@@ -1220,6 +1310,13 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   if (!g.out_f32 && g.batch == 1 && g.causal == CAUSAL_NONE && !g.delta && g.layout != TN && narrow_tiles_pay(g.M, g.N, g.K))
     return g.layout == NN ? launch_bf16<256, 192, true, false, bf16_t, TBP_NARROW_KD, TBP_NARROW_RING>(p, 1, s)
                           : launch_bf16<256, 192, true, true, bf16_t, TBP_NARROW_KD, TBP_NARROW_RING>(p, 1, s);
+  // a weight gradient by itself: large tiles (below) unless smaller ones are faster by the same model as in gemm_dw
+  if (g.out_f32 && g.layout == TN && g.batch == 1 && g.causal == CAUSAL_NONE && g.K > 0) {
+    const double t256 = dw_time(256, tiles_big, g.K, g.accumulate), t64 = dw_time(64, dw_tiles(64, g.M, g.N), g.K, g.accumulate);
+    const double t128 = dw_time(128, dw_tiles(128, g.M, g.N), g.K, g.accumulate);
+    if (t64 <= t128 && t64 <= t256) return launch_bf16<64, 64, false, false, float, 64, 4>(p, 1, s);
+    if (t128 <= t256) return launch_bf16<128, 128, false, false, float, 32>(p, 1, s);
+  }
   auto run = [&](const GemmParams& q, bool use_big) -> hipError_t {
     if (!use_big && g.batch == 1 && q.K >= 1024 && (long)((q.M + 127) / 128) * ((q.N + 127) / 128) <= 256)
       return g.out_f32 ? dispatch_small_deep<float>(g.layout, q, s) : dispatch_small_deep<bf16_t>(g.layout, q, s);
@@ -1245,17 +1342,8 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
     if (rem <= 128 || !has_narrow || t192 > 256) return run(q, rem > 128);
     return launch_bf16<256, 192, false, false, float, 32>(q, 1, s);
   };
-  const bool defer = g.defer_rest && g.out_f32 && g.layout == TN && g.alpha == 1.f && !g.a_panel;
-  if (g.defer_rest) g.defer_rest->M = 0;
-  auto hold_back = [&](const GemmParams& q) {       // the remainder, for the caller's grouped launch
-    GroupedProduct& r = *g.defer_rest;
-    r.A = q.A; r.B = q.B; r.C = static_cast<float*>(q.C);
-    r.M = q.M; r.N = q.N; r.K = q.K;
-    r.lda = (int)q.lda; r.ldb = (int)q.ldb; r.ldc = (int)q.ldc;
-    r.accumulate = q.accumulate;
-  };
   if (big && g.batch == 1 && g.causal == CAUSAL_NONE && tiles_big > 256 && rem != 0 &&
-      (defer || rem <= 128 || (has_narrow && rem <= 192))) {
+      (rem <= 128 || (has_narrow && rem <= 192))) {
     const long whole = tiles_big - rem;
     const size_t ce = g.out_f32 ? 4 : 2;
     GemmParams a = p, b = p;
@@ -1269,7 +1357,6 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
         b.C = (char*)p.C + n0 * ce;
         if (p.R) b.R = (const char*)p.R + n0 * 2;
         hipError_t e = run(a, true);
-        if (defer) { hold_back(b); return e; }
         return e != hipSuccess ? e : run_rest(b);
       }
     } else {                                        // cut along M
@@ -1282,7 +1369,6 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
         b.C = (char*)p.C + m0 * g.ldc * ce;
         if (p.R) b.R = (const char*)p.R + m0 * g.ldc * 2;
         hipError_t e = run(a, true);
-        if (defer) { hold_back(b); return e; }
         return e != hipSuccess ? e : run_rest(b);
       }
     }

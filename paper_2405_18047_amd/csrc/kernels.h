@@ -19,7 +19,6 @@ enum Causal {
 };
 constexpr int kCausalPad = 256;
 
-struct GroupedProduct;
 struct GemmArgs {
   int layout;            // Layout
   int M, N, K;
@@ -47,12 +46,6 @@ struct GemmArgs {
   // A[(m / kPanel) * a_panel + k * lda + m % kPanel] with lda == kPanel, so that the K x kPanel slab an output tile
   // contracts over is one contiguous stream.  0: plain [K, lda] matrix.  Such a product runs on kPanel-wide tiles.
   long a_panel;
-  // Weight-gradient products (TN layout, bf16 storage, fp32 C, alpha = 1) whose tiles do not fill whole rounds of the
-  // 256 compute units: when set, gemm() launches only the part of the output that makes whole rounds of large tiles
-  // and describes the remainder in *defer_rest (M = 0 there: nothing was held back) instead of launching it on
-  // smaller tiles.  The caller collects the remainders of several products and runs them as one gemm_tn_grouped
-  // launch, in which they fill rounds together.
-  GroupedProduct* defer_rest;
 };
 constexpr int kPanel = 128;
 // elements of one (sequence, head) entry of the fused attention's dS^T scratch, stored in such panels
@@ -77,7 +70,7 @@ inline GemmArgs gemm_args(int layout, int M, int N, int K, const void* A, long l
 // dtype: 0 = fp32 storage, 1 = bf16 storage (matches tbp_dtype).
 hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s);
 
-// Several bf16 weight-gradient products C (=, +=) A^T B (TN layout, fp32 C, alpha = 1) run as ONE launch.
+// One bf16 weight-gradient product C (=, +=) A^T B (TN layout, fp32 C, alpha = 1).
 // Same operand rules as the bf16 TN product of gemm(): 16-byte aligned pointers, extents and leading dimensions
 // multiples of 8.
 struct GroupedProduct {
@@ -92,7 +85,8 @@ struct GroupedTable {
   int first_block[kMaxGrouped];
   GroupedProduct prod[kMaxGrouped];
 };
-hipError_t gemm_tn_grouped(const GroupedProduct* prods, int n, hipStream_t s);
+// n of them, with one K; pool: host scratch for n entries.
+hipError_t gemm_dw(const GroupedProduct* prods, int n, GroupedProduct* pool, hipStream_t s);
 
 hipError_t rmsnorm_fwd(int dtype, int rows, int d, float eps, const void* x, const void* g, void* y, hipStream_t s);
 constexpr int kNormPartialBlocks = 256;     // at most this many row-block partials of the gain gradient per call
@@ -105,6 +99,10 @@ hipError_t rmsnorm_p1_rows(int dtype, int rows, int d, float eps, const void* dy
                            const void* resid, void* dx, float* partials, hipStream_t s);
 // out[d] (= or +=) sum of the first n_rows rows of partials [n_rows][d]  (n_rows == 0: zero, or out left alone)
 hipError_t gain_partials_sum(const float* partials, int n_rows, int d, int accumulate, float* out, hipStream_t s);
+// The same for several norms in one launch (the table travels as a kernel argument).
+constexpr int kMaxGainSums = 64;
+struct GainSums { int n; const float* parts[kMaxGainSums]; float* out[kMaxGainSums]; };
+hipError_t gain_partials_sums(const GainSums& g, int n_rows, int d, int accumulate, hipStream_t s);
 // Both in one call: rows, then the sum into dg_out (dg_out == nullptr: nothing is computed for the gain).
 hipError_t rmsnorm_p1(int dtype, int rows, int d, float eps, const void* dy, const void* x, const void* g,
                       const void* resid, void* dx, float* dg_out, float* partials, hipStream_t s);

@@ -205,7 +205,7 @@ struct tbp_stage {
   std::vector<int> state;       // per micro-batch
   std::vector<int> slot_of;     // per micro-batch, -1 if none
   std::vector<int> free_slots;
-  std::vector<tbp::GroupedProduct> grouped;      // loop-mode p2: the products of one micro-batch (capacity fixed at creation)
+  std::vector<tbp::GroupedProduct> grouped, pool;      // p2: the products of one run of micro-batches, their remainders (fixed at creation)
   size_t w_live, a_live, high;
 
   void* wslab(int layer, int t, int mb) const {
@@ -410,103 +410,78 @@ tbp_status run_p1(tbp_stage* st, int mb, int slot, const void* dy, void* dx, hip
   return TBP_OK;
 }
 
-// dW (=, +=) X^T dY over rows [row0, row0 + K) of the two slabs.  rests != nullptr: the part of the output that does
-// not make whole rounds of large tiles is not launched but appended to *rests, for one grouped launch at the end.
-tbp_status p2_product(tbp_stage* st, int layer, int xt, int dyt, int mb0, int K, float* dW, int accumulate,
-                      hipStream_t s, std::vector<tbp::GroupedProduct>* rests = nullptr) {
-  const Dims& c = st->c;
-  const int M = (int)w_width(c, xt), N = (int)w_width(c, dyt);
-  GemmArgs g = gemm_args(tbp::TN, M, N, K, st->wslab(layer, xt, mb0), M, st->wslab(layer, dyt, mb0), N, dW, N);
-  g.out_f32 = 1;
-  g.accumulate = accumulate;
-  tbp::GroupedProduct rest{};
-  if (rests) g.defer_rest = &rest;
-  TBP_HIP(tbp::gemm(c.dtype, g, s));
-  if (rests && rest.M > 0) rests->push_back(rest);        // (capacity reserved at creation: no allocation here)
-  return TBP_OK;
-}
-
-tbp_status run_p2(tbp_stage* st, const int* mbs, int n, int mode, int accumulate, hipStream_t s) {
+tbp_status run_p2(tbp_stage* st, const int* mbs, int n, int accumulate, hipStream_t s) {
   const Dims& c = st->c;
   struct Prod { int x, dy; float* const* dw; bool attn_only; };
-  auto prods_of = [&](Prod (&out)[4]) {
-    const Prod all[4] = {{W_H1, W_DQKV, st->dw_qkv.data(), true}, {W_A, W_DX1, st->dw_o.data(), true},
+  const Prod prods[4] = {{W_H1, W_DQKV, st->dw_qkv.data(), true}, {W_A, W_DX1, st->dw_o.data(), true},
                          {W_H2, W_DGU, st->dw_gu.data(), false}, {W_M, W_DX2, st->dw_d.data(), false}};
-    for (int i = 0; i < 4; i++) out[i] = all[i];
-  };
-  Prod prods[4];
-  prods_of(prods);
-  if (c.dtype == TBP_BF16 && mode == TBP_P2_LOOP) {
-    // bf16, one micro-batch per product: all weight-gradient products of the stage for that micro-batch go into one
-    // grouped launch, each launch accumulating on the previous one.  (The K-concatenated products are long enough
-    // that one launch per weight, which starts its tiles in step, is the faster arrangement.)
-    std::vector<tbp::GroupedProduct>& table = st->grouped;     // (no host allocation here: the capacity is reserved)
-    for (int i = 0; i < n; i++) {
-      table.clear();
-      const int mb0 = mbs[i];
-      const int K = c.T;
-      for (int l = 0; l < c.L; l++)
-        for (const Prod& p : prods) {
-          if (p.attn_only && !c.attn) continue;
-          tbp::GroupedProduct g{};
-          g.M = (int)w_width(c, p.x); g.N = (int)w_width(c, p.dy); g.K = K;
-          g.A = st->wslab(l, p.x, mb0); g.lda = g.M;
-          g.B = st->wslab(l, p.dy, mb0); g.ldb = g.N;
-          g.C = p.dw[l]; g.ldc = g.N;
-          g.accumulate = (accumulate || i > 0) ? 1 : 0;
-          table.push_back(g);
-        }
-      TBP_HIP(tbp::gemm_tn_grouped(table.data(), (int)table.size(), s));
-    }
-  } else {
-    // K-concatenated bf16 products: one launch per weight for the whole rounds of large tiles (tiles that start in step
-    // share operand panels through the L2), and the remainders of all the stage's products together in one grouped
-    // launch at the end, where they fill rounds with each other instead of each running a last, mostly empty round
-    std::vector<tbp::GroupedProduct>* rests = (mode == TBP_P2_KCONCAT && c.dtype == TBP_BF16) ? &st->grouped : nullptr;
-    if (rests) rests->clear();
+  // A run of consecutive micro-batches is one product per weight over their consecutive rows, in either mode: the products
+  // of a LOOP set add up in fp32 in the accumulators instead of reading and writing dW once per micro-batch (a 7B layer's
+  // dW is 0.8 GB: four micro-batches of 256 tokens took 4 x 589 us).
+  for (int i = 0; i < n;) {
+    int j = i + 1;
+    while (j < n && mbs[j] == mbs[j - 1] + 1) j++;
+    const int mb0 = mbs[i], K = (j - i) * c.T, acc = (accumulate || i > 0) ? 1 : 0;
+    st->grouped.clear();                      // (no host allocation here: the capacity is reserved at creation)
     for (int l = 0; l < c.L; l++)
       for (const Prod& p : prods) {
         if (p.attn_only && !c.attn) continue;
-        if (mode == TBP_P2_KCONCAT) {
-          tbp_status r = p2_product(st, l, p.x, p.dy, mbs[0], n * c.T, p.dw[l], accumulate, s, rests);
-          if (r != TBP_OK) return r;
-        } else {
-          for (int i = 0; i < n; i++) {
-            tbp_status r = p2_product(st, l, p.x, p.dy, mbs[i], c.T, p.dw[l], (accumulate || i > 0) ? 1 : 0, s);
-            if (r != TBP_OK) return r;
-          }
-        }
+        tbp::GroupedProduct g{};
+        g.M = (int)w_width(c, p.x); g.N = (int)w_width(c, p.dy); g.K = K;
+        g.A = st->wslab(l, p.x, mb0); g.lda = g.M;
+        g.B = st->wslab(l, p.dy, mb0); g.ldb = g.N;
+        g.C = p.dw[l]; g.ldc = g.N;
+        g.accumulate = acc;
+        st->grouped.push_back(g);
       }
-    if (rests && !rests->empty()) TBP_HIP(tbp::gemm_tn_grouped(rests->data(), (int)rests->size(), s));
+    if (c.dtype == TBP_BF16) {
+      TBP_HIP(tbp::gemm_dw(st->grouped.data(), (int)st->grouped.size(), st->pool.data(), s));
+    } else {
+      for (const tbp::GroupedProduct& q : st->grouped) {
+        GemmArgs g = gemm_args(tbp::TN, q.M, q.N, q.K, q.A, q.lda, q.B, q.ldb, q.C, q.ldc);
+        g.out_f32 = 1;
+        g.accumulate = q.accumulate;
+        TBP_HIP(tbp::gemm(c.dtype, g, s));
+      }
+    }
+    i = j;
   }
   if (c.literal) {
     // gain gradients from the stashed norm inputs and output derivatives (Section 3.1 treats a norm's gain like any
     // other parameter: its gradient belongs to backward-p2); rows of consecutive micro-batches are one operand
     float* part = (float*)st->ws(st->y.ws_norm_partials_p2);
-    const int runs = mode == TBP_P2_KCONCAT ? 1 : n;
-    const int rows = mode == TBP_P2_KCONCAT ? n * c.T : c.T;
     for (int l = 0; l < c.L; l++)
-      for (int i = 0; i < runs; i++) {
-        const int acc = (accumulate || i > 0) ? 1 : 0;
+      for (int i = 0; i < n;) {
+        int j = i + 1;
+        while (j < n && mbs[j] == mbs[j - 1] + 1) j++;
+        const int acc = (accumulate || i > 0) ? 1 : 0, rows = (j - i) * c.T;
         if (c.attn)
           TBP_HIP(tbp::rmsnorm_gain_p2(c.dtype, rows, c.d, c.eps, st->wslab(l, W_N1DY, mbs[i]), st->wslab(l, W_N1X, mbs[i]),
                                        acc, st->dg1[l], part, s));
         TBP_HIP(tbp::rmsnorm_gain_p2(c.dtype, rows, c.d, c.eps, st->wslab(l, W_N2DY, mbs[i]), st->wslab(l, W_N2X, mbs[i]),
                                      acc, st->dg2[l], part, s));
+        i = j;
       }
     return TBP_OK;
   }
   // gain gradients: the partial rows that backward-p1 left, added up run by run of consecutive micro-batches (whose
-  // partial rows are consecutive in the stash; a K-concatenated set is one run)
-  for (int l = 0; l < c.L; l++)
-    for (int i = 0; i < n;) {
-      int j = i + 1;
-      while (j < n && mbs[j] == mbs[j - 1] + 1) j++;
-      const int acc = (accumulate || i > 0) ? 1 : 0, nrows = (j - i) * st->y.gain_rows;
-      if (c.attn) TBP_HIP(tbp::gain_partials_sum(st->gain_part(l, 0, mbs[i]), nrows, c.d, acc, st->dg1[l], s));
-      TBP_HIP(tbp::gain_partials_sum(st->gain_part(l, 1, mbs[i]), nrows, c.d, acc, st->dg2[l], s));
-      i = j;
-    }
+  // partial rows are consecutive in the stash; a K-concatenated set is one run), all norms of the stage in one launch
+  for (int i = 0; i < n;) {
+    int j = i + 1;
+    while (j < n && mbs[j] == mbs[j - 1] + 1) j++;
+    tbp::GainSums g{};
+    const int acc = (accumulate || i > 0) ? 1 : 0, nrows = (j - i) * st->y.gain_rows;
+    for (int l = 0; l < c.L; l++)
+      for (int which = c.attn ? 0 : 1; which < 2; which++) {
+        g.parts[g.n] = st->gain_part(l, which, mbs[i]);
+        g.out[g.n++] = which ? st->dg2[l] : st->dg1[l];
+        if (g.n == tbp::kMaxGainSums || (l == c.L - 1 && which == 1)) {
+          TBP_HIP(tbp::gain_partials_sums(g, nrows, c.d, acc, s));
+          g.n = 0;
+        }
+      }
+    i = j;
+  }
   return TBP_OK;
 }
 
@@ -570,6 +545,7 @@ tbp_status tbp_stage_create(const tbp_config* cfg, const tbp_params* params, voi
     st->free_slots.reserve(c.slots);
     for (int i = c.slots - 1; i >= 0; i--) st->free_slots.push_back(i);
     st->grouped.reserve((size_t)4 * c.L);
+    st->pool.resize((size_t)4 * c.L);
   } catch (...) {
     delete st;
     return fail(TBP_ENOMEM, "host allocation failed");
@@ -632,7 +608,7 @@ tbp_status tbp_stage_backward_p2(tbp_stage* st, const int* mbs, int n_mbs, int p
   for (int i = 0; i < n_mbs; i++)            // then the state of every member: the set is taken whole or not at all
     if (st->state[mbs[i]] != MB_P1)
       return fail(TBP_ESTATE, "backward_p2: micro-batch %d has not finished backward_p1", mbs[i]);
-  tbp_status r = run_p2(st, mbs, n_mbs, p2_mode, accumulate, static_cast<hipStream_t>(stream));
+  tbp_status r = run_p2(st, mbs, n_mbs, accumulate, static_cast<hipStream_t>(stream));
   if (r != TBP_OK) return r;
   for (int i = 0; i < n_mbs; i++) {
     st->state[mbs[i]] = MB_EMPTY;

@@ -552,3 +552,42 @@ def test_activation_slots_run_out():
     assert e.value.status == 2
     torch.cuda.synchronize()
     st.close()
+
+
+@pytest.mark.parametrize("mode,sets", [(tbp.TBP_P2_LOOP, [[0, 1, 2, 3]]), (tbp.TBP_P2_LOOP, [[3, 2, 1, 0]]), (tbp.TBP_P2_LOOP, [[2, 3, 0], [1]]),
+                                       (tbp.TBP_P2_LOOP, [[1], [0], [2, 3]]), (tbp.TBP_P2_KCONCAT, [[2, 3], [0, 1]])])
+@pytest.mark.parametrize("shape", [
+    si.StageShape("sets_bf16", 2, 256, 4, 64, 688, 136, 1, 4, "bf16", 41), si.StageShape("sets_f32", 1, 72, 3, 24, 100, 20, 1, 4, "f32", 42)],
+    ids=lambda s: s.name)
+@pytest.mark.parametrize("gain_grad", [tbp.TBP_GAIN_PARTIALS, tbp.TBP_GAIN_LITERAL])
+def test_p2_sets_in_any_order(shape, mode, sets, gain_grad):
+    """Runs of consecutive micro-batches inside a backward-p2 set are contracted in one go; sets that are not one run, in
+    any order and over several accumulating calls, give the same gradients."""
+    _say(f"p2 sets {sets} mode={mode} shape={shape.name} gain_grad={gain_grad}")
+    params, xs, dys = _stage_inputs(shape)
+    outs, dxs, grads = run_oracle(shape, params, xs, dys)
+    st = make_gpu_stage(shape, params, gain_grad=gain_grad)
+    g_out = [st.forward(m, to_dev(x, shape.dtype)) for m, x in enumerate(xs)]
+    g_dx = [st.backward_p1(m, to_dev(d, shape.dtype)) for m, d in enumerate(dys)]
+    for i, mbs in enumerate(sets):
+        st.backward_p2(mbs, mode, accumulate=i > 0)
+    compare_stage(shape, g_out, g_dx, st.grads, outs, dxs, grads, stage_tolerance(shape.dtype), f"sets {sets}")
+    st.close()
+
+
+@pytest.mark.parametrize("shape", [
+    # weight gradients of 344 and 176 large tiles: one whole round, 264 pooled of which the last 8 end on small tiles
+    si.StageShape("dw_large_tiles", 1, 2048, 0, 0, 5504, 1536, 1, 1, "bf16", 43),
+    # the same over a short contraction: one launch of 128 x 128 tiles
+    si.StageShape("dw_short", 1, 2048, 0, 0, 5504, 104, 1, 2, "bf16", 44)], ids=lambda s: s.name)
+def test_weight_gradient_arrangements(shape):
+    _say(f"dW arrangements {shape.name}")
+    params, xs, dys = _stage_inputs(shape)
+    outs, dxs, grads = run_oracle(shape, params, xs, dys)
+    for mode in (tbp.TBP_P2_KCONCAT, tbp.TBP_P2_LOOP):
+        st = make_gpu_stage(shape, params)
+        g_out = [st.forward(m, to_dev(x, shape.dtype)) for m, x in enumerate(xs)]
+        g_dx = [st.backward_p1(m, to_dev(d, shape.dtype)) for m, d in enumerate(dys)]
+        st.backward_p2(range(len(xs)), mode, accumulate=mode == tbp.TBP_P2_LOOP)          # (gradients start at zero)
+        compare_stage(shape, g_out, g_dx, st.grads, outs, dxs, grads, stage_tolerance(shape.dtype), shape.name)
+        st.close()
