@@ -158,11 +158,13 @@ __device__ __forceinline__ bf16x8 read_frag(lds_u8* q) {
 }
 
 // One output tile (tm_i, tn_i) of batch entry z of the product described by p.
+// ACC: C += (fp32 output).  A template parameter, because the registers that the old values take cost the overwriting
+// 256 x 256 kernel 2-3 %.
 // KD = contraction depth of one LDS slot: 32 with a ring of 4 slots, or 64 with 2 slots.  The deeper slot is for
 // operands whose contraction index is contiguous in memory: their copies then fetch 128 contiguous bytes per tile
 // row, a whole cache line, where the 32-deep slot fetches every line in two halves one iteration apart and doubles
 // the number of requests to the L2.
-template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD = BK, bool SPLIT = false, int RING = 0>
+template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD = BK, bool SPLIT = false, int RING = 0, bool ACC = false>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, int tn_i, int z) {
   // RING == 0: the default pipeline of the slot depth (32: ring of STAGES slots; 64: two slots); RING >= 3: the ring
   // pipeline with that many slots, for either depth
@@ -392,6 +394,23 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, in
   // a wave-wide store covers whole rows when LPR divides 64 and consecutive rows otherwise (WN = 96).
   constexpr int LPR = WN / V, NVEC = 32 * LPR;
   static_assert(NVEC % 64 == 0, "a strip must be a whole number of wave-wide stores");
+  // fp32 +=: the old value that store u of strip i adds is requested where store u of strip i - 1 has used its own, so a
+  // whole strip of requests is in flight (without branches: lanes outside the output read the tile's first element).
+  // Read in place, one at a time, they made an accumulating round of 256 large tiles 22 us longer than an overwriting one;
+  // now 14.  [4096, 22016] x 256 (128 x 128 tiles) 260 -> 210 us, x 1024 377 -> 336, [2048, 11008] x 2048 141 -> 125.
+  constexpr int OLD = ACC ? NVEC / 64 : 1;
+  static_assert(!ACC || sizeof(OutT) == 4, "only an fp32 output accumulates");
+  u32x4 old[OLD];
+  auto request_old = [&](int i, int u) {
+    const int q = u * 64 + lane;
+    const int grow = m0 + wm * WM + i * 32 + q / LPR, gcol = n0 + wn * WN + (q % LPR) * V;
+    const bool in = grow < p.M && gcol < p.N;
+    old[u] = *reinterpret_cast<const u32x4*>(C + (in ? (long)grow * p.ldc + gcol : (long)m0 * p.ldc + n0));
+  };
+  if constexpr (ACC) {
+#pragma unroll
+    for (int u = 0; u < OLD; u++) request_old(0, u);
+  }
 #pragma unroll
   for (int i = 0; i < TM; i++) {
 #pragma unroll
@@ -404,7 +423,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, in
     constexpr int NIT = NVEC / 64;                            // stores per strip, and per request batch:
     constexpr int GRP = NIT <= 8 ? NIT : (NIT % 8 == 0 ? 8 : (NIT % 6 == 0 ? 6 : (NIT % 5 == 0 ? 5 : 4)));
     static_assert(NIT % GRP == 0, "request batches must tile the strip");
-    const bool need_pre = (sizeof(OutT) == 4) ? false : (R != nullptr);   // (fp32 += reads its old value in place)
+    const bool need_pre = (sizeof(OutT) == 4) ? false : (R != nullptr);
     __builtin_amdgcn_sched_barrier(0);      // keep the next strip's requests from being hoisted over this one
 #pragma unroll
     for (int g0 = 0; g0 < NIT; g0 += GRP) {
@@ -434,9 +453,9 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, in
             v[q] = t4[0]; v[q + 1] = t4[1]; v[q + 2] = t4[2]; v[q + 3] = t4[3];
           }
           if constexpr (sizeof(OutT) == 4) {
-            if (p.accumulate) {
-              const f32x4 o = *reinterpret_cast<const f32x4*>(C + idx);
-              v[0] += o[0]; v[1] += o[1]; v[2] += o[2]; v[3] += o[3];
+            if constexpr (ACC) {
+#pragma unroll
+              for (int q = 0; q < 4; q++) v[q] += __uint_as_float(old[g0 + u][q]);
             }
             f32x4 w4;
             w4[0] = v[0]; w4[1] = v[1]; w4[2] = v[2]; w4[3] = v[3];
@@ -462,13 +481,16 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, in
             *reinterpret_cast<bf16x8*>(C + idx) = o;
           }
         }
+        if constexpr (ACC) {
+          if (i + 1 < TM) request_old(i + 1, g0 + u);
+        }
       }
       __builtin_amdgcn_sched_barrier(0);
     }
   }
 }
 
-template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD, int RING = 0>
+template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD, int RING = 0, bool ACC = false>
 __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams p) {
   int tm_i, tn_i, z = (int)blockIdx.z;
   if (gridDim.z == 1) {
@@ -502,7 +524,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams p) {
       tn_i = id / p.tiles_m;
     }
   }
-  gemm_bf16_tile<BM, BN, AKC, BKC, OutT, KD, false, RING>(p, tm_i, tn_i, z);
+  gemm_bf16_tile<BM, BN, AKC, BKC, OutT, KD, false, RING, ACC>(p, tm_i, tn_i, z);
 }
 
 // Batched product with a causal contraction end (rows of tile i contract over (i + 1) * BM indices) and one tile column:
@@ -570,7 +592,7 @@ __global__ __launch_bounds__(256) void split_sum_kernel(const float* __restrict_
 // launch starts them together and stop doing once tiles of different products and start times are mixed.
 // Tiles of 256 x 256 and 128 x 128 run on a ring of four 32-deep slots (one workgroup per compute unit, and two), 64 x 64
 // on four 64-deep ones (two).
-template <int TILE>
+template <int TILE, bool ACC>
 __global__ __launch_bounds__(256) void gemm_tn_grouped_kernel(GroupedTable g) {
   int lo = 0, hi = g.n - 1;                   // last product whose first workgroup id is <= blockIdx.x
   const int bid = (int)blockIdx.x;
@@ -587,10 +609,10 @@ __global__ __launch_bounds__(256) void gemm_tn_grouped_kernel(GroupedTable g) {
   p.lda = q.lda; p.ldb = q.ldb; p.ldc = q.ldc;
   p.M = q.M; p.N = q.N; p.K = q.K;
   p.batch_inner = 1; p.tiles_m = tiles_m; p.tiles_n = tiles_n;
-  p.alpha = 1.f; p.accumulate = q.accumulate; p.causal = CAUSAL_NONE;
+  p.alpha = 1.f; p.causal = CAUSAL_NONE;
   int tm_i, tn_i;
   tile_of_block(pid, tiles_m, tiles_n, tm_i, tn_i);
-  gemm_bf16_tile<TILE, TILE, false, false, float, (TILE == 64 ? 64 : 32), false, (TILE == 64 ? 4 : 0)>(p, tm_i, tn_i, 0);
+  gemm_bf16_tile<TILE, TILE, false, false, float, (TILE == 64 ? 64 : 32), false, (TILE == 64 ? 4 : 0), ACC>(p, tm_i, tn_i, 0);
 }
 
 // ------------------------------------------------------------------------------------------ ceiling
@@ -911,14 +933,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
 }
 
 // ------------------------------------------------------------------------------------------ host
-template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD, int RING = 0>
-static hipError_t launch_bf16(const GemmParams& p0, int batch, hipStream_t s) {
+template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD, int RING, bool ACC>
+static hipError_t launch_bf16_acc(const GemmParams& p0, int batch, hipStream_t s) {
   GemmParams p = p0;
   p.tiles_m = (p.M + BM - 1) / BM;
   p.tiles_n = (p.N + BN - 1) / BN;
   constexpr size_t smem = (size_t)(RING >= 3 ? RING : (KD == 32 ? STAGES : 2)) * (BM + BN) * KD * sizeof(bf16_t);
   static_assert(smem <= 160 * 1024, "LDS budget of one gfx950 compute unit");
-  auto kern = gemm_bf16_kernel<BM, BN, AKC, BKC, OutT, KD, RING>;
+  auto kern = gemm_bf16_kernel<BM, BN, AKC, BKC, OutT, KD, RING, ACC>;
   static AttrOnce once;
   if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
   unsigned nt = (unsigned)(p.tiles_m * p.tiles_n);
@@ -927,6 +949,12 @@ static hipError_t launch_bf16(const GemmParams& p0, int batch, hipStream_t s) {
   dim3 grid(nt, 1, (unsigned)batch);
   hipLaunchKernelGGL(kern, grid, dim3(256), smem, s, p);
   return hipGetLastError();
+}
+template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD, int RING = 0>
+static hipError_t launch_bf16(const GemmParams& p, int batch, hipStream_t s) {
+  if constexpr (sizeof(OutT) == 4)
+    if (p.accumulate) return launch_bf16_acc<BM, BN, AKC, BKC, OutT, KD, RING, true>(p, batch, s);
+  return launch_bf16_acc<BM, BN, AKC, BKC, OutT, KD, RING, false>(p, batch, s);
 }
 
 template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD>
@@ -1101,11 +1129,11 @@ static hipError_t dispatch_layout(int layout, const GemmParams& p, int batch, hi
 }
 
 template <int TILE>
-static hipError_t launch_tn_grouped(const GroupedProduct* prods, int n, hipStream_t s) {
+static hipError_t launch_tn_grouped(const GroupedProduct* prods, int n, int accumulate, hipStream_t s) {
   constexpr size_t smem = (size_t)4 * (TILE + TILE) * (TILE == 64 ? 64 : 32) * sizeof(bf16_t);
-  auto kern = gemm_tn_grouped_kernel<TILE>;
-  static AttrOnce once;
-  if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
+  auto kern = accumulate ? gemm_tn_grouped_kernel<TILE, true> : gemm_tn_grouped_kernel<TILE, false>;
+  static AttrOnce once[2];
+  if (hipError_t e = once[accumulate ? 1 : 0].set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
   for (int i = 0; i < n;) {
     GroupedTable g{};
     int blocks = 0;
@@ -1128,11 +1156,10 @@ static hipError_t launch_tn_grouped(const GroupedProduct* prods, int n, hipStrea
 // Modelled time (us) of n weight-gradient tiles over K contraction indices, fitted to products of [256, 256] to
 // [4096, 22016] with K 128-4096: the part that grows with K, and the part that writes (accumulating: reads and writes)
 // the fp32 output, which a workgroup does not overlap with its own products.
-static double dw_time(int tile, long n, int K, int accumulate) {
-  const int a = accumulate ? 2 : 1;
-  if (tile == 256) return (double)((n + 255) / 256) * (0.0232 * K + 22. * a);
-  const double one = tile == 128 ? 0.0105 * K + 4.5 * a : 0.0045 * K + 2. * a;
-  const double two = tile == 128 ? 0.0152 * K + 8.5 * a : 0.0073 * K + 2. * a;
+static double dw_time(int tile, long n, int K, int acc) {
+  if (tile == 256) return (double)((n + 255) / 256) * (0.0232 * K + (acc ? 36. : 22.));
+  const double one = tile == 128 ? 0.0105 * K + (acc ? 8. : 4.5) : 0.0045 * K + (acc ? 4. : 2.);
+  const double two = tile == 128 ? 0.0152 * K + (acc ? 15.5 : 7.5) : 0.0073 * K + (acc ? 4. : 2.);
   return (double)(n / 512) * two + (n % 512 == 0 ? 0. : n % 512 <= 256 ? one : two);
 }
 static long dw_tiles(int tile, int M, int N) { return (long)((M + tile - 1) / tile) * ((N + tile - 1) / tile); }
@@ -1165,24 +1192,24 @@ static void cut_product(const GroupedProduct& q, long tiles, GroupedProduct& hea
 // Measured (us), all weight gradients of a layer: d 1152, f 3080, K 4000 (990 tiles of 128): 209 as four launches of
 // 128 x 128 tiles, 155 grouped; 7B, K 256, accumulating: 589 grouped on large tiles; 7B, K 4096: 272 pooled tiles
 // 193, with the last 16 on 128 x 128 tiles 116 + 39; d 256, f 688, K 384: 62 as eight launches, 8 grouped on 64 x 64.
-hipError_t gemm_dw(const GroupedProduct* prods, int n, GroupedProduct* pool, hipStream_t s) {
+hipError_t gemm_dw(const GroupedProduct* prods, int n, int acc, GroupedProduct* pool, hipStream_t s) {
   long n64 = 0, n128 = 0, pooled = 0, whole = 0;
-  int K = 0, acc = 0;
+  int K = 0;
   for (int i = 0; i < n; i++) {
     n64 += dw_tiles(64, prods[i].M, prods[i].N);
     n128 += dw_tiles(128, prods[i].M, prods[i].N);
     const long t = dw_tiles(256, prods[i].M, prods[i].N);
     whole += t / 256 * 256;
     pooled += t % 256;
-    K = prods[i].K; acc |= prods[i].accumulate;
+    K = prods[i].K;
   }
   const long last = pooled % 256;
   const double e64 = dw_time(64, 16 * last, K, acc), e128 = dw_time(128, 4 * last, K, acc), e_end = e64 < e128 ? e64 : e128;
   const bool small_end = pooled > 256 && last > 0 && e_end < 0.8 * dw_time(256, last, K, acc);
   const double t64 = dw_time(64, n64, K, acc), t128 = dw_time(128, n128, K, acc);
   const double t256 = dw_time(256, whole, K, acc) + dw_time(256, small_end ? pooled - last : pooled, K, acc) + (small_end ? e_end : 0.);
-  if (t64 <= t128 && t64 <= t256) return launch_tn_grouped<64>(prods, n, s);
-  if (t128 <= t256) return launch_tn_grouped<128>(prods, n, s);
+  if (t64 <= t128 && t64 <= t256) return launch_tn_grouped<64>(prods, n, acc, s);
+  if (t128 <= t256) return launch_tn_grouped<128>(prods, n, acc, s);
   int np = 0;
   for (int i = 0; i < n; i++) {
     const long t = dw_tiles(256, prods[i].M, prods[i].N);
@@ -1193,7 +1220,7 @@ hipError_t gemm_dw(const GroupedProduct* prods, int n, GroupedProduct* pool, hip
       p.A = head.A; p.B = head.B; p.C = head.C;
       p.lda = head.lda; p.ldb = head.ldb; p.ldc = head.ldc;
       p.M = head.M; p.N = head.N; p.K = head.K;
-      p.batch_inner = 1; p.alpha = 1.f; p.accumulate = head.accumulate; p.causal = CAUSAL_NONE;
+      p.batch_inner = 1; p.alpha = 1.f; p.accumulate = acc; p.causal = CAUSAL_NONE;
       if (hipError_t e = launch_bf16<256, 256, false, false, float, TBP_TN_DEPTH>(p, 1, s); e != hipSuccess) return e;
     }
     if (rest.M > 0 && rest.N > 0) pool[np++] = rest;
@@ -1205,9 +1232,9 @@ hipError_t gemm_dw(const GroupedProduct* prods, int n, GroupedProduct* pool, hip
     const long t = dw_tiles(256, q.M, q.N);
     if (t > last) cut_product(q, t - last, pool[np - 1], end);
   }
-  if (hipError_t e = launch_tn_grouped<256>(pool, np, s); e != hipSuccess) return e;
+  if (hipError_t e = launch_tn_grouped<256>(pool, np, acc, s); e != hipSuccess) return e;
   if (end.M <= 0 || end.N <= 0) return hipSuccess;
-  return e64 < e128 ? launch_tn_grouped<64>(&end, 1, s) : launch_tn_grouped<128>(&end, 1, s);
+  return e64 < e128 ? launch_tn_grouped<64>(&end, 1, acc, s) : launch_tn_grouped<128>(&end, 1, acc, s);
 }
 
 // fp32: whole 16-byte pieces of A and B (pointers, leading dimensions, batch strides and contiguous extents), and a tile's

@@ -77,7 +77,6 @@ struct GroupedProduct {
   const void* A; const void* B; float* C;     // A [K, M] (lda), B [K, N] (ldb), C [M, N] (ldc)
   int M, N, K;
   int lda, ldb, ldc;
-  int accumulate;
 };
 constexpr int kMaxGrouped = 40;               // products per launch (the table travels as a kernel argument)
 struct GroupedTable {
@@ -86,7 +85,7 @@ struct GroupedTable {
   GroupedProduct prod[kMaxGrouped];
 };
 // n of them, with one K; pool: host scratch for n entries.
-hipError_t gemm_dw(const GroupedProduct* prods, int n, GroupedProduct* pool, hipStream_t s);
+hipError_t gemm_dw(const GroupedProduct* prods, int n, int accumulate, GroupedProduct* pool, hipStream_t s);
 
 hipError_t rmsnorm_fwd(int dtype, int rows, int d, float eps, const void* x, const void* g, void* y, hipStream_t s);
 constexpr int kNormPartialBlocks = 256;     // at most this many row-block partials of the gain gradient per call

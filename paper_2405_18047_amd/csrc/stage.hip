@@ -431,16 +431,15 @@ tbp_status run_p2(tbp_stage* st, const int* mbs, int n, int accumulate, hipStrea
         g.A = st->wslab(l, p.x, mb0); g.lda = g.M;
         g.B = st->wslab(l, p.dy, mb0); g.ldb = g.N;
         g.C = p.dw[l]; g.ldc = g.N;
-        g.accumulate = acc;
         st->grouped.push_back(g);
       }
     if (c.dtype == TBP_BF16) {
-      TBP_HIP(tbp::gemm_dw(st->grouped.data(), (int)st->grouped.size(), st->pool.data(), s));
+      TBP_HIP(tbp::gemm_dw(st->grouped.data(), (int)st->grouped.size(), acc, st->pool.data(), s));
     } else {
       for (const tbp::GroupedProduct& q : st->grouped) {
         GemmArgs g = gemm_args(tbp::TN, q.M, q.N, q.K, q.A, q.lda, q.B, q.ldb, q.C, q.ldc);
         g.out_f32 = 1;
-        g.accumulate = q.accumulate;
+        g.accumulate = acc;
         TBP_HIP(tbp::gemm(c.dtype, g, s));
       }
     }
