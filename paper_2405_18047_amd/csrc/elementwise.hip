@@ -481,21 +481,25 @@ __global__ void rope_table_kernel(int seq, int half, float base, float2* __restr
 }
 
 // A thread owns one 16-byte column chunk of the rotation table row of its token (cos, sin kept in registers) and
-// applies it to kRopeHeads consecutive heads, so the table is read once per 8 heads instead of once per head.
-constexpr int kRopeHeads = 8;
-template <typename T>
-__global__ __launch_bounds__(256) void rope_kernel(long nitems, int seq, int n_heads, int head_dim, long ld,
+// applies it to HPT consecutive heads.  8 heads per thread read the table least (4096 tokens x 64 heads of 128: 26 us =
+// the device-copy rate); short inputs take fewer, down to one, until there are 4 workgroups per compute unit: 256 tokens
+// are 64 workgroups with 8 heads per thread, each a serial chain of loads and stores.  Measured against 8 heads always and
+// 64-bit index divisions: 256 tokens 7.9 -> 3.4 us, 1024 10.1 -> 6.5, 4096 26.8 -> 25.1, 128 tokens x 8 heads of 64
+// 4.6 -> 2.5.  (I: index type, 32 bits unless there are more items.)
+template <typename T, int HPT, typename I>
+__global__ __launch_bounds__(256) void rope_kernel(I nitems, int seq, int n_heads, int head_dim, long ld,
                                                    const float2* __restrict__ table, float sgn, T* __restrict__ x) {
   constexpr int N = Vec<T>::N;
   const int half = head_dim / 2;
   const int cph = half / N;                   // chunks per head half
-  const int ngrp = (n_heads + kRopeHeads - 1) / kRopeHeads;
-  for (long v = blockIdx.x * 256L + threadIdx.x; v < nitems; v += 256L * gridDim.x) {
-    const int c = (int)(v % cph);
-    const long gv = v / cph;
-    const int hg = (int)(gv % ngrp);
-    const long row = gv / ngrp;
-    const int pos = (int)(row % seq);
+  const int ngrp = (n_heads + HPT - 1) / HPT;
+  for (I v = blockIdx.x * (I)256 + threadIdx.x; v < nitems; v += (I)256 * gridDim.x) {
+    const I gv = v / (I)cph;
+    const int c = (int)(v - gv * (I)cph);
+    const I row_i = gv / (I)ngrp;
+    const int hg = (int)(gv - row_i * (I)ngrp);
+    const long row = (long)row_i;
+    const int pos = (int)(row_i % (I)seq);
     float cs[N], sn[N];
     const float2* tb = table + (long)pos * half + c * N;
 #pragma unroll
@@ -504,8 +508,8 @@ __global__ __launch_bounds__(256) void rope_kernel(long nitems, int seq, int n_h
       cs[i] = t.x;
       sn[i] = t.y * sgn;
     }
-    const int h0 = hg * kRopeHeads;
-    const int hn = (n_heads - h0) < kRopeHeads ? (n_heads - h0) : kRopeHeads;
+    const int h0 = hg * HPT;
+    const int hn = (n_heads - h0) < HPT ? (n_heads - h0) : HPT;
     T* base = x + row * ld + (long)h0 * head_dim + c * N;
 #pragma unroll 4
     for (int u = 0; u < hn; u++) {
@@ -879,17 +883,29 @@ hipError_t rope_table(int seq, int head_dim, float base, float2* table, hipStrea
   hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, s, seq, head_dim / 2, base, table);
   return hipGetLastError();
 }
+template <typename T, int HPT>
+static hipError_t rope_t(long nitems, int seq, int n_heads, int head_dim, long ld, const float2* table, float sgn, T* x, hipStream_t s) {
+  const dim3 grid(grid_for(nitems)), block(256);
+  if (nitems < (1L << 31)) hipLaunchKernelGGL((rope_kernel<T, HPT, unsigned>), grid, block, 0, s, nitems, seq, n_heads, head_dim, ld, table, sgn, x);
+  else hipLaunchKernelGGL((rope_kernel<T, HPT, long>), grid, block, 0, s, nitems, seq, n_heads, head_dim, ld, table, sgn, x);
+  return hipGetLastError();
+}
+template <typename T>
+static hipError_t rope_heads(int rows, int seq, int n_heads, int head_dim, long ld, const float2* table, float sgn, T* x, hipStream_t s) {
+  const long per_head_group = (long)rows * (head_dim / 2 / Vec<T>::N);
+  auto items = [&](int hpt) { return per_head_group * ((n_heads + hpt - 1) / hpt); };
+  constexpr long kEnough = 1024L * 256;       // threads: 4 workgroups per compute unit
+  if (items(8) >= kEnough) return rope_t<T, 8>(items(8), seq, n_heads, head_dim, ld, table, sgn, x, s);
+  if (items(4) >= kEnough) return rope_t<T, 4>(items(4), seq, n_heads, head_dim, ld, table, sgn, x, s);
+  if (items(2) >= kEnough) return rope_t<T, 2>(items(2), seq, n_heads, head_dim, ld, table, sgn, x, s);
+  return rope_t<T, 1>(items(1), seq, n_heads, head_dim, ld, table, sgn, x, s);
+}
 hipError_t rope(int dtype, int rows, int seq, int n_heads, int head_dim, long ld, const float2* table, int inverse,
                 void* x, hipStream_t s) {
   if (rows <= 0 || n_heads <= 0) return hipSuccess;
-  const int n = dtype ? 8 : 4;
-  const long nvec = (long)rows * ((n_heads + kRopeHeads - 1) / kRopeHeads) * (head_dim / 2 / n);
   const float sgn = inverse ? -1.f : 1.f;
-  if (dtype) hipLaunchKernelGGL(rope_kernel<bf16_t>, dim3(grid_for(nvec)), dim3(256), 0, s, nvec, seq, n_heads,
-                                head_dim, ld, table, sgn, (bf16_t*)x);
-  else hipLaunchKernelGGL(rope_kernel<float>, dim3(grid_for(nvec)), dim3(256), 0, s, nvec, seq, n_heads, head_dim,
-                          ld, table, sgn, (float*)x);
-  return hipGetLastError();
+  return dtype ? rope_heads<bf16_t>(rows, seq, n_heads, head_dim, ld, table, sgn, (bf16_t*)x, s)
+               : rope_heads<float>(rows, seq, n_heads, head_dim, ld, table, sgn, (float*)x, s);
 }
 
 // chunks per lane needed for a row pair: the two zero-filled rows hold at most min(2 S, S + 2 * kCausalPad) elements
