@@ -81,10 +81,29 @@ __device__ __forceinline__ float wave_max(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), 63));
 }
 
+// table[p][i] = (cos, sin)(p * base^(-2i/dh)), evaluated in fp64.
+__device__ __forceinline__ void rope_table_entry(int idx, int seq, int half, float base, float2* __restrict__ table) {
+  if (idx >= seq * half) return;
+  const int p = idx / half, i = idx - p * half;
+  const double theta = pow((double)base, -(double)i / (double)half);
+  const double ang = (double)p * theta;
+  table[idx] = make_float2((float)cos(ang), (float)sin(ang));
+}
+
 // ---- RMSNorm forward: one 256-thread workgroup per row ----------------------------------------------
-template <typename T, int MAXC>
+// FIRST: the first norm of a stage's forward call.  It also leaves a copy of its input in the stash (x_copy), and the
+// workgroups behind the last row build the rotation table (if any): the copy and the table as launches of their own were
+// 5 us each at 256 to 1024 tokens, 2 to 3 of them just the launch, and the copy read the input a second time.
+struct FirstNorm { void* x_copy; float2* table; int seq, half; float base; };
+template <typename T, int MAXC, bool FIRST = false>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(int rows, int d, float eps, const T* __restrict__ x,
-                                                          const T* __restrict__ g, T* __restrict__ y) {
+                                                          const T* __restrict__ g, T* __restrict__ y, FirstNorm first) {
+  if constexpr (FIRST) {
+    if ((int)blockIdx.x >= rows) {            // (uniform over the workgroup, before its barrier)
+      rope_table_entry(((int)blockIdx.x - rows) * 256 + (int)threadIdx.x, first.seq, first.half, first.base, first.table);
+      return;
+    }
+  }
   constexpr int N = Vec<T>::N;
   __shared__ float red[4];
   const int row = blockIdx.x;
@@ -96,7 +115,9 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(int rows, int d, float
   for (int c = 0; c < MAXC; c++) {
     const int ch = threadIdx.x + 256 * c;
     if (ch < nchunk) {
-      Vec<T>::load(xr + ch * N, xv[c]);
+      const typename Vec<T>::Raw raw = Vec<T>::load_raw(xr + ch * N);
+      if constexpr (FIRST) *reinterpret_cast<typename Vec<T>::Raw*>(static_cast<T*>(first.x_copy) + (long)row * d + ch * N) = raw;
+      Vec<T>::unpack(raw, xv[c]);
 #pragma unroll
       for (int i = 0; i < N; i++) ss += xv[c][i] * xv[c][i];
     }
@@ -128,11 +149,13 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(int rows, int d, float
 // per workgroup, which colsum_kernel adds up.
 // GAIN_ONLY (the gain gradient as a backward-p2 operation): only x and dy are read, and only the partials written.
 // partials == nullptr (backward-p1 of a stage that computes the gain gradient in p2): nothing is written for the gain.
+// resid_copy (optional): receives a copy of resid (the upstream gradient of a stage, which backward-p2 needs; as a copy of
+// its own it took 5 us at 1024 tokens, 14 at 4096).
 template <typename T, int MAXC, int WPR, bool GAIN_ONLY = false, int NW = 8>
 __global__ __launch_bounds__(64 * NW) void rmsnorm_p1_kernel(int rows, int d, float eps, const T* __restrict__ dy,
                                                          const T* __restrict__ x, const T* __restrict__ g,
                                                          const T* __restrict__ resid, T* __restrict__ dx,
-                                                         float* __restrict__ partials) {
+                                                         float* __restrict__ partials, T* __restrict__ resid_copy) {
   constexpr int N = Vec<T>::N, G = NW / WPR, TPR = 64 * WPR;     // groups per workgroup, threads per row
   typedef typename Vec<T>::Raw Raw;
   extern __shared__ float lds[];              // [2][NW waves][2 sums] reduction slots, then [d] column buffer
@@ -224,8 +247,10 @@ __global__ __launch_bounds__(64 * NW) void rmsnorm_p1_kernel(int rows, int d, fl
         if constexpr (!GAIN_ONLY) {
           float gv[N], o[N];
           Vec<T>::load(gp + ch * N, gv);
-          if (resid) Vec<T>::unpack(rr[c], o);
-          else {
+          if (resid) {
+            Vec<T>::unpack(rr[c], o);
+            if (resid_copy) *reinterpret_cast<Raw*>(resid_copy + base + ch * N) = rr[c];
+          } else {
 #pragma unroll
             for (int i = 0; i < N; i++) o[i] = 0.f;
           }
@@ -268,7 +293,7 @@ template <typename T, int MAXC, int WPR, bool GAIN_ONLY, int NW, int PD>
 __global__ __launch_bounds__(64 * NW) void rmsnorm_p1_ring_kernel(int rows, int d, float eps, const T* __restrict__ dy,
                                                                   const T* __restrict__ x, const T* __restrict__ g,
                                                                   const T* __restrict__ resid, T* __restrict__ dx,
-                                                                  float* __restrict__ partials) {
+                                                                  float* __restrict__ partials, T* __restrict__ resid_copy) {
   constexpr int N = Vec<T>::N, G = NW / WPR, TPR = 64 * WPR;
   typedef typename Vec<T>::Raw Raw;
   extern __shared__ float lds[];              // [2][NW waves][2 sums] reduction slots, then [d] column buffer
@@ -362,8 +387,10 @@ __global__ __launch_bounds__(64 * NW) void rmsnorm_p1_ring_kernel(int rows, int 
           for (int i = 0; i < N; i++) cacc[c][i] += yv[i] * xv[i] * r;
           if constexpr (!GAIN_ONLY) {
             float o[N];
-            if (resid) Vec<T>::unpack(rr[c], o);
-            else {
+            if (resid) {
+              Vec<T>::unpack(rr[c], o);
+              if (resid_copy) *reinterpret_cast<Raw*>(resid_copy + base + ch * N) = rr[c];
+            } else {
 #pragma unroll
               for (int i = 0; i < N; i++) o[i] = 0.f;
             }
@@ -470,14 +497,8 @@ __global__ __launch_bounds__(256) void swiglu_p1_kernel(long nvec, int fchunks, 
 }
 
 // ---- rotary embedding ---------------------------------------------------------------------------------
-// table[p][i] = (cos, sin)(p * base^(-2i/dh)), evaluated in fp64 once.
 __global__ void rope_table_kernel(int seq, int half, float base, float2* __restrict__ table) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= seq * half) return;
-  const int p = idx / half, i = idx - p * half;
-  const double theta = pow((double)base, -(double)i / (double)half);
-  const double ang = (double)p * theta;
-  table[idx] = make_float2((float)cos(ang), (float)sin(ang));
+  rope_table_entry(blockIdx.x * blockDim.x + threadIdx.x, seq, half, base, table);
 }
 
 // A thread owns one 16-byte column chunk of the rotation table row of its token (cos, sin kept in registers) and
@@ -716,19 +737,28 @@ __global__ __launch_bounds__(256) void head_rowdot_kernel(int n_heads, int head_
 // ------------------------------------------------------------------------------------------ host
 static inline int chunks_per_thread(int d, int n) { return (d / n + 255) / 256; }
 
-template <typename T>
-static hipError_t rmsnorm_fwd_t(int rows, int d, float eps, const void* x, const void* g, void* y, hipStream_t s) {
+template <typename T, bool FIRST>
+static hipError_t rmsnorm_fwd_t(int rows, int d, float eps, const void* x, const void* g, void* y, const FirstNorm& first, hipStream_t s) {
   const int c = chunks_per_thread(d, Vec<T>::N);
   auto X = (const T*)x; auto G = (const T*)g; auto Y = (T*)y;
-  if (c <= 1) hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, 1>), dim3(rows), dim3(256), 0, s, rows, d, eps, X, G, Y);
-  else if (c <= 2) hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, 2>), dim3(rows), dim3(256), 0, s, rows, d, eps, X, G, Y);
-  else if (c <= 4) hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, 4>), dim3(rows), dim3(256), 0, s, rows, d, eps, X, G, Y);
+  const dim3 grid(rows + (FIRST && first.table ? (first.seq * first.half + 255) / 256 : 0)), block(256);
+  if (c <= 1) hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, 1, FIRST>), grid, block, 0, s, rows, d, eps, X, G, Y, first);
+  else if (c <= 2) hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, 2, FIRST>), grid, block, 0, s, rows, d, eps, X, G, Y, first);
+  else if (c <= 4) hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, 4, FIRST>), grid, block, 0, s, rows, d, eps, X, G, Y, first);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 hipError_t rmsnorm_fwd(int dtype, int rows, int d, float eps, const void* x, const void* g, void* y, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  return dtype ? rmsnorm_fwd_t<bf16_t>(rows, d, eps, x, g, y, s) : rmsnorm_fwd_t<float>(rows, d, eps, x, g, y, s);
+  return dtype ? rmsnorm_fwd_t<bf16_t, false>(rows, d, eps, x, g, y, FirstNorm{}, s)
+               : rmsnorm_fwd_t<float, false>(rows, d, eps, x, g, y, FirstNorm{}, s);
+}
+hipError_t rmsnorm_fwd_first(int dtype, int rows, int d, float eps, const void* x, const void* g, void* y, void* x_copy,
+                             float2* table, int seq, int head_dim, float base, hipStream_t s) {
+  if (rows <= 0) return hipSuccess;
+  const FirstNorm first{x_copy, table, seq, head_dim / 2, base};
+  return dtype ? rmsnorm_fwd_t<bf16_t, true>(rows, d, eps, x, g, y, first, s)
+               : rmsnorm_fwd_t<float, true>(rows, d, eps, x, g, y, first, s);
 }
 
 // Which kernel a (storage type, width) pair runs on, and how many rows a workgroup has in work at a time.  The number
@@ -766,24 +796,24 @@ int rmsnorm_partial_rows(int dtype, int rows, int d) {
 
 template <typename T, int WPR, bool GAIN_ONLY>
 static hipError_t rmsnorm_p1_w(int rows, int d, float eps, const T* dy, const T* x, const T* g, const T* resid, T* dx,
-                               float* partials, int nblk, hipStream_t s) {
+                               float* partials, T* resid_copy, int nblk, hipStream_t s) {
   constexpr int NW = 8;
   const int c = (d / Vec<T>::N + 64 * WPR - 1) / (64 * WPR);      // vectors per lane
   const size_t smem = (4 * NW + (size_t)d) * sizeof(float);
   const dim3 grid(nblk), block(64 * NW);
-  if (c <= 1) hipLaunchKernelGGL((rmsnorm_p1_kernel<T, 1, WPR, GAIN_ONLY, NW>), grid, block, smem, s, rows, d, eps, dy, x, g, resid, dx, partials);
-  else if (c <= 2) hipLaunchKernelGGL((rmsnorm_p1_kernel<T, 2, WPR, GAIN_ONLY, NW>), grid, block, smem, s, rows, d, eps, dy, x, g, resid, dx, partials);
-  else if (c <= 4) hipLaunchKernelGGL((rmsnorm_p1_kernel<T, 4, WPR, GAIN_ONLY, NW>), grid, block, smem, s, rows, d, eps, dy, x, g, resid, dx, partials);
+  if (c <= 1) hipLaunchKernelGGL((rmsnorm_p1_kernel<T, 1, WPR, GAIN_ONLY, NW>), grid, block, smem, s, rows, d, eps, dy, x, g, resid, dx, partials, resid_copy);
+  else if (c <= 2) hipLaunchKernelGGL((rmsnorm_p1_kernel<T, 2, WPR, GAIN_ONLY, NW>), grid, block, smem, s, rows, d, eps, dy, x, g, resid, dx, partials, resid_copy);
+  else if (c <= 4) hipLaunchKernelGGL((rmsnorm_p1_kernel<T, 4, WPR, GAIN_ONLY, NW>), grid, block, smem, s, rows, d, eps, dy, x, g, resid, dx, partials, resid_copy);
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 template <typename T, bool GAIN_ONLY>
 static hipError_t rmsnorm_p1_ring(int rows, int d, float eps, const T* dy, const T* x, const T* g, const T* resid, T* dx,
-                                  float* partials, int nblk, int wpr, hipStream_t s) {
+                                  float* partials, T* resid_copy, int nblk, int wpr, hipStream_t s) {
   if (wpr == 4) {       // at most 256 vectors per row: one per lane
     const size_t smem4 = (4 * 16 + (size_t)d) * sizeof(float);
-    hipLaunchKernelGGL((rmsnorm_p1_ring_kernel<T, 1, 4, GAIN_ONLY, 16, TBP_RING_PD1>), dim3(nblk), dim3(1024), smem4, s, rows, d, eps, dy, x, g, resid, dx, partials);
+    hipLaunchKernelGGL((rmsnorm_p1_ring_kernel<T, 1, 4, GAIN_ONLY, 16, TBP_RING_PD1>), dim3(nblk), dim3(1024), smem4, s, rows, d, eps, dy, x, g, resid, dx, partials, resid_copy);
     return hipGetLastError();
   }
   constexpr int WPR = 8;
@@ -792,8 +822,8 @@ static hipError_t rmsnorm_p1_ring(int rows, int d, float eps, const T* dy, const
   const int NW = c == 1 ? TBP_RING_NW1 : 8;
   const size_t smem = (4 * NW + (size_t)d) * sizeof(float);
   const dim3 grid(nblk), block(64 * NW);
-  if (c == 1) hipLaunchKernelGGL((rmsnorm_p1_ring_kernel<T, 1, WPR, GAIN_ONLY, TBP_RING_NW1, TBP_RING_PD1>), grid, block, smem, s, rows, d, eps, dy, x, g, resid, dx, partials);
-  else hipLaunchKernelGGL((rmsnorm_p1_ring_kernel<T, 2, WPR, GAIN_ONLY, 8, TBP_RING_PD2>), grid, block, smem, s, rows, d, eps, dy, x, g, resid, dx, partials);
+  if (c == 1) hipLaunchKernelGGL((rmsnorm_p1_ring_kernel<T, 1, WPR, GAIN_ONLY, TBP_RING_NW1, TBP_RING_PD1>), grid, block, smem, s, rows, d, eps, dy, x, g, resid, dx, partials, resid_copy);
+  else hipLaunchKernelGGL((rmsnorm_p1_ring_kernel<T, 2, WPR, GAIN_ONLY, 8, TBP_RING_PD2>), grid, block, smem, s, rows, d, eps, dy, x, g, resid, dx, partials, resid_copy);
   return hipGetLastError();
 }
 
@@ -801,18 +831,18 @@ static hipError_t rmsnorm_p1_ring(int rows, int d, float eps, const T* dy, const
 // the gain gradient.
 template <typename T, bool GAIN_ONLY>
 static hipError_t rmsnorm_rows_t(int dtype, int rows, int d, float eps, const void* dy, const void* x, const void* g,
-                                 const void* resid, void* dx, float* partials, hipStream_t s) {
+                                 const void* resid, void* dx, float* partials, void* resid_copy, hipStream_t s) {
   auto DY = (const T*)dy; auto X = (const T*)x; auto G = (const T*)g; auto RS = (const T*)resid; auto DX = (T*)dx;
   const NormPlan pl = norm_plan(dtype, d);
   const int nblk = rmsnorm_partial_rows(dtype, rows, d);
   if constexpr (sizeof(T) == 2) {
-    if (pl.kind == 1) return rmsnorm_p1_ring<T, GAIN_ONLY>(rows, d, eps, DY, X, G, RS, DX, partials, nblk, pl.wpr, s);
+    if (pl.kind == 1) return rmsnorm_p1_ring<T, GAIN_ONLY>(rows, d, eps, DY, X, G, RS, DX, partials, (T*)resid_copy, nblk, pl.wpr, s);
   }
   switch (pl.wpr) {
-    case 1: return rmsnorm_p1_w<T, 1, GAIN_ONLY>(rows, d, eps, DY, X, G, RS, DX, partials, nblk, s);
-    case 2: return rmsnorm_p1_w<T, 2, GAIN_ONLY>(rows, d, eps, DY, X, G, RS, DX, partials, nblk, s);
-    case 4: return rmsnorm_p1_w<T, 4, GAIN_ONLY>(rows, d, eps, DY, X, G, RS, DX, partials, nblk, s);
-    default: return rmsnorm_p1_w<T, 8, GAIN_ONLY>(rows, d, eps, DY, X, G, RS, DX, partials, nblk, s);
+    case 1: return rmsnorm_p1_w<T, 1, GAIN_ONLY>(rows, d, eps, DY, X, G, RS, DX, partials, (T*)resid_copy, nblk, s);
+    case 2: return rmsnorm_p1_w<T, 2, GAIN_ONLY>(rows, d, eps, DY, X, G, RS, DX, partials, (T*)resid_copy, nblk, s);
+    case 4: return rmsnorm_p1_w<T, 4, GAIN_ONLY>(rows, d, eps, DY, X, G, RS, DX, partials, (T*)resid_copy, nblk, s);
+    default: return rmsnorm_p1_w<T, 8, GAIN_ONLY>(rows, d, eps, DY, X, G, RS, DX, partials, (T*)resid_copy, nblk, s);
   }
 }
 
@@ -829,10 +859,10 @@ hipError_t gain_partials_sum(const float* partials, int n_rows, int d, int accum
 }
 
 hipError_t rmsnorm_p1_rows(int dtype, int rows, int d, float eps, const void* dy, const void* x, const void* g,
-                           const void* resid, void* dx, float* partials, hipStream_t s) {
+                           const void* resid, void* dx, float* partials, hipStream_t s, void* resid_copy) {
   if (rows <= 0) return hipSuccess;
-  return dtype ? rmsnorm_rows_t<bf16_t, false>(dtype, rows, d, eps, dy, x, g, resid, dx, partials, s)
-               : rmsnorm_rows_t<float, false>(dtype, rows, d, eps, dy, x, g, resid, dx, partials, s);
+  return dtype ? rmsnorm_rows_t<bf16_t, false>(dtype, rows, d, eps, dy, x, g, resid, dx, partials, resid_copy, s)
+               : rmsnorm_rows_t<float, false>(dtype, rows, d, eps, dy, x, g, resid, dx, partials, resid_copy, s);
 }
 
 hipError_t rmsnorm_p1(int dtype, int rows, int d, float eps, const void* dy, const void* x, const void* g,
@@ -845,8 +875,8 @@ hipError_t rmsnorm_p1(int dtype, int rows, int d, float eps, const void* dy, con
 hipError_t rmsnorm_gain_p2(int dtype, int rows, int d, float eps, const void* dy, const void* x, int accumulate,
                            float* dg_out, float* partials, hipStream_t s) {
   if (rows <= 0) return accumulate ? hipSuccess : gain_partials_sum(partials, 0, d, 0, dg_out, s);
-  hipError_t e = dtype ? rmsnorm_rows_t<bf16_t, true>(dtype, rows, d, eps, dy, x, nullptr, nullptr, nullptr, partials, s)
-                       : rmsnorm_rows_t<float, true>(dtype, rows, d, eps, dy, x, nullptr, nullptr, nullptr, partials, s);
+  hipError_t e = dtype ? rmsnorm_rows_t<bf16_t, true>(dtype, rows, d, eps, dy, x, nullptr, nullptr, nullptr, partials, nullptr, s)
+                       : rmsnorm_rows_t<float, true>(dtype, rows, d, eps, dy, x, nullptr, nullptr, nullptr, partials, nullptr, s);
   if (e != hipSuccess) return e;
   return gain_partials_sum(partials, rmsnorm_partial_rows(dtype, rows, d), d, accumulate, dg_out, s);
 }

@@ -88,14 +88,18 @@ struct GroupedTable {
 hipError_t gemm_dw(const GroupedProduct* prods, int n, int accumulate, GroupedProduct* pool, hipStream_t s);
 
 hipError_t rmsnorm_fwd(int dtype, int rows, int d, float eps, const void* x, const void* g, void* y, hipStream_t s);
+// The same, leaving a copy of x in x_copy and, if table is not null, the rotation table of (seq, head_dim, base) in it.
+hipError_t rmsnorm_fwd_first(int dtype, int rows, int d, float eps, const void* x, const void* g, void* y, void* x_copy,
+                             float2* table, int seq, int head_dim, float base, hipStream_t s);
 constexpr int kNormPartialBlocks = 256;     // at most this many row-block partials of the gain gradient per call
 // RMSNorm backward-p1.  The gain gradient dg = sum over rows of dy * x * r leaves the row kernel as
 // rmsnorm_partial_rows(dtype, rows, d) <= kNormPartialBlocks partial rows [d] fp32 (one per workgroup, each a sum over
 // that workgroup's rows in a fixed order); gain_partials_sum adds partial rows up.
 int rmsnorm_partial_rows(int dtype, int rows, int d);
-// dx = resid + dL/dx; partials (may be null: nothing is computed for the gain) receives the partial rows.
+// dx = resid + dL/dx; partials (may be null: nothing is computed for the gain) receives the partial rows; resid_copy
+// (may be null) a copy of resid.
 hipError_t rmsnorm_p1_rows(int dtype, int rows, int d, float eps, const void* dy, const void* x, const void* g,
-                           const void* resid, void* dx, float* partials, hipStream_t s);
+                           const void* resid, void* dx, float* partials, hipStream_t s, void* resid_copy = nullptr);
 // out[d] (= or +=) sum of the first n_rows rows of partials [n_rows][d]  (n_rows == 0: zero, or out left alone)
 hipError_t gain_partials_sum(const float* partials, int n_rows, int d, int accumulate, float* out, hipStream_t s);
 // The same for several norms in one launch (the table travels as a kernel argument).

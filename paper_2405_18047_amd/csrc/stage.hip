@@ -251,24 +251,29 @@ tbp_status run_forward(tbp_stage* st, int mb, int slot, const void* x_in, void* 
   const Dims& c = st->c;
   const int dt = c.dtype, T = c.T, d = c.d, f = c.f;
   const size_t act_bytes = (size_t)T * d * c.e;
-  // The rotation table is rebuilt by every forward call (a few microseconds) instead of once behind a host-side flag:
+  // The layer-0 input is kept for the RMSNorm backward: its first norm leaves the copy and builds the rotation table.  An
+  // input that the norm cannot read in 16-byte pieces is copied first.
+  // The rotation table is rebuilt by every forward call instead of once behind a host-side flag:
   // the flag would be wrong for a caller who records the first call into a graph and replays it later, and for one who
   // moves to another stream without synchronising.  (Every build writes the same values, so a backward-p1 call that
   // reads the table on another stream meanwhile reads them either way.)
-  if (c.attn) TBP_HIP(tbp::rope_table(c.S, c.dh, c.base, (float2*)st->ws(st->y.ws_rope), s));
-  const void* x_cur = x_in;
+  float2* const table = c.attn ? (float2*)st->ws(st->y.ws_rope) : nullptr;
+  const bool direct = reinterpret_cast<uintptr_t>(x_in) % 16 == 0;
+  auto first_norm = [&](void* kept, const void* gain, void* h) -> hipError_t {
+    if (direct) return tbp::rmsnorm_fwd_first(dt, T, d, c.eps, x_in, gain, h, kept, table, c.S, c.dh, c.base, s);
+    hipError_t e = hipMemcpyAsync(kept, x_in, act_bytes, hipMemcpyDeviceToDevice, s);
+    if (e == hipSuccess && table) e = tbp::rope_table(c.S, c.dh, c.base, table, s);
+    return e != hipSuccess ? e : tbp::rmsnorm_fwd(dt, T, d, c.eps, kept, gain, h, s);
+  };
   for (int l = 0; l < c.L; l++) {
     void* x1 = st->x1_of(l, mb, slot);
     if (c.attn) {
       void* x0 = st->x0_of(l, mb, slot);
-      // the layer input is kept for the RMSNorm backward; for layer 0 it is copied from the caller
-      if (l == 0) TBP_HIP(hipMemcpyAsync(x0, x_in, act_bytes, hipMemcpyDeviceToDevice, s));
-      (void)x_cur;
       void* h1 = st->wslab(l, W_H1, mb);
       void* qkv = st->aslot(l, A_QKV, slot);
       void* P = st->aslot(l, A_P, slot);
       void* a = st->wslab(l, W_A, mb);
-      TBP_HIP(tbp::rmsnorm_fwd(dt, T, d, c.eps, x0, st->g1[l], h1, s));
+      TBP_HIP(l == 0 ? first_norm(x0, st->g1[l], h1) : tbp::rmsnorm_fwd(dt, T, d, c.eps, x0, st->g1[l], h1, s));
       TBP_HIP(linear_gemm(st, gemm_args(tbp::NN, T, 3 * d, d, h1, d, st->w_qkv[l], 3 * d, qkv, 3 * d), s));
       TBP_HIP(tbp::rope(dt, T, c.S, 2 * c.H, c.dh, 3 * d, (const float2*)st->ws(st->y.ws_rope), 0, qkv, s));
       if (c.fused) {
@@ -299,13 +304,11 @@ tbp_status run_forward(tbp_stage* st, int mb, int slot, const void* x_in, void* 
         g.R = x0;
         TBP_HIP(linear_gemm(st, g, s));
       }
-    } else if (l == 0) {
-      TBP_HIP(hipMemcpyAsync(x1, x_in, act_bytes, hipMemcpyDeviceToDevice, s));
     }
     void* h2 = st->wslab(l, W_H2, mb);
     void* gu = st->aslot(l, A_GU, slot);
     void* m = st->wslab(l, W_M, mb);
-    TBP_HIP(tbp::rmsnorm_fwd(dt, T, d, c.eps, x1, st->g2[l], h2, s));
+    TBP_HIP(l == 0 && !c.attn ? first_norm(x1, st->g2[l], h2) : tbp::rmsnorm_fwd(dt, T, d, c.eps, x1, st->g2[l], h2, s));
     TBP_HIP(linear_gemm(st, gemm_args(tbp::NN, T, 2 * f, d, h2, d, st->w_gu[l], 2 * f, gu, 2 * f), s));
     TBP_HIP(tbp::swiglu_fwd(dt, T, f, gu, m, s));
     {  // x2 = x1 + m Wd, written where the next layer (or the caller) wants its input
@@ -322,10 +325,17 @@ tbp_status run_p1(tbp_stage* st, int mb, int slot, const void* dy, void* dx, hip
   const Dims& c = st->c;
   const int dt = c.dtype, T = c.T, d = c.d, f = c.f;
   const size_t act_bytes = (size_t)T * d * c.e;
-  // the stage's upstream gradient is the output derivative of the last layer's down projection: keep it
-  TBP_HIP(hipMemcpyAsync(st->wslab(c.L - 1, W_DX2, mb), dy, act_bytes, hipMemcpyDeviceToDevice, s));
+  // The stage's upstream gradient is the output derivative of the last layer's down projection and is kept for p2: by the
+  // norm that reads it anyway, or copied first where the kernels cannot read it in 16-byte pieces, or where that norm
+  // already writes dx (one layer without attention) and the two buffers overlap.
+  const uintptr_t dy0 = reinterpret_cast<uintptr_t>(dy), dx0 = reinterpret_cast<uintptr_t>(dx);
+  const bool overlap = dy0 < dx0 + act_bytes && dx0 < dy0 + act_bytes;
+  const bool direct = dy0 % 16 == 0 && !(overlap && c.L == 1 && !c.attn);
+  if (!direct) TBP_HIP(hipMemcpyAsync(st->wslab(c.L - 1, W_DX2, mb), dy, act_bytes, hipMemcpyDeviceToDevice, s));
   for (int l = c.L - 1; l >= 0; l--) {
-    void* dx2 = st->wslab(l, W_DX2, mb);
+    void* const dx2_slab = st->wslab(l, W_DX2, mb);
+    const bool from_caller = l == c.L - 1 && direct;
+    const void* dx2 = from_caller ? dy : dx2_slab;
     void* dm = st->ws(st->y.ws_t_f);
     void* dgu = st->wslab(l, W_DGU, mb);
     // derivative of a norm's output: a temporary, or (literal gain gradient) a slab that p2 reads
@@ -342,7 +352,7 @@ tbp_status run_p1(tbp_stage* st, int mb, int slot, const void* dy, void* dx, hip
     void* dx1 = c.attn ? st->wslab(l, W_DX1, mb) : dx_out;
     // (the partial rows of the gain gradient stay in the stash as they leave the row kernel: backward-p2 adds them up)
     TBP_HIP(tbp::rmsnorm_p1_rows(dt, T, d, c.eps, dh, x1, st->g2[l], dx2, dx1,
-                                 c.literal ? nullptr : st->gain_part(l, 1, mb), s));
+                                 c.literal ? nullptr : st->gain_part(l, 1, mb), s, from_caller ? dx2_slab : nullptr));
     if (!c.attn) continue;
     void* da = st->ws(st->y.ws_t_d1);
     void* qkv = st->aslot(l, A_QKV, slot);

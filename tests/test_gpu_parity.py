@@ -591,3 +591,37 @@ def test_weight_gradient_arrangements(shape):
         st.backward_p2(range(len(xs)), mode, accumulate=mode == tbp.TBP_P2_LOOP)          # (gradients start at zero)
         compare_stage(shape, g_out, g_dx, st.grads, outs, dxs, grads, stage_tolerance(shape.dtype), shape.name)
         st.close()
+
+
+@pytest.mark.parametrize("shape", [
+    si.StageShape("ptr_bf16", 2, 256, 4, 64, 688, 136, 1, 1, "bf16", 45), si.StageShape("ptr_f32", 1, 72, 3, 24, 100, 20, 1, 1, "f32", 46),
+    si.StageShape("ptr_mlp", 1, 264, 0, 0, 520, 1000, 1, 1, "bf16", 47)], ids=lambda s: s.name)
+@pytest.mark.parametrize("gain_grad", [tbp.TBP_GAIN_PARTIALS, tbp.TBP_GAIN_LITERAL])
+def test_stage_inputs_at_any_address(shape, gain_grad):
+    """The stage keeps copies of its input and of its upstream gradient, made by the norms that read them or (inputs that
+    are not 16-byte aligned, an output that overlaps the upstream gradient) ahead of them: the same bits either way, also
+    when the caller overwrites its buffers right after the calls and when dx is written over dy, in place or shifted."""
+    _say(f"stage inputs at any address {shape.name} gain_grad={gain_grad}")
+    params, xs, dys = _stage_inputs(shape)
+    x, dy = to_dev(xs[0], shape.dtype), to_dev(dys[0], shape.dtype)
+    n, rows, d = x.numel(), x.shape[0], x.shape[1]
+
+    def run(x_off, dy_off, dx_off):
+        st = make_gpu_stage(shape, params, gain_grad=gain_grad)
+        xb, gb = (torch.zeros(2 * n + 64, dtype=x.dtype, device=DEV) for _ in range(2))
+        xv, dyv = xb[x_off:x_off + n].view(rows, d).copy_(x), gb[dy_off:dy_off + n].view(rows, d).copy_(dy)
+        out = st.forward(0, xv)
+        xb.zero_()
+        dx = st.backward_p1(0, dyv, out=gb[dx_off:dx_off + n].view(rows, d)).clone()
+        gb.zero_()
+        st.backward_p2([0], tbp.TBP_P2_LOOP, accumulate=False)
+        res = [out, dx] + [g.clone() for v in st.grads.values() for g in v]
+        st.close()
+        return res
+
+    q = 16 // x.element_size()
+    want = run(0, 0, n + 64 - n % 64)
+    assert all(torch.all(torch.isfinite(t)) for t in want) and all(t.abs().max() > 0 for t in want)
+    for offs in ((1, 1, n + 64 - n % 64), (0, 0, 0), (0, 0, 2 * q), (q, 4 * q, 0)):
+        for a, b in zip(run(*offs), want):
+            assert torch.equal(a, b), offs
