@@ -87,11 +87,18 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& c, int u) {
 
 // ------------------------------------------------------------------------------------------ forward
 // One workgroup = 4 waves x 32 queries of one (sequence, head); keys and values stream through LDS in blocks of 64,
-// double-buffered.  Per block and wave: S^T (64 keys x 32 queries), online softmax per lane, O^T += V^T P^T.
+// double-buffered, K one block ahead of V.  Per block and wave: online softmax of S^T (64 keys x 32 queries) per lane,
+// O^T += V^T P^T, and S^T of the next block.
+// Bound: per block and wave 32 MFMAs of 32 clocks, about 900 clocks of vector ALU (32 exponentials at 16 clocks, the rest at
+// 4), and 32 KiB of LDS reads, which two waves per SIMD turn into 2000 clocks of each.  Computing a block's scores, softmax
+// and PV product one after the other, the units hardly overlapped; with the scores of the next block computed beside the
+// exponentials of this one, in a pinned order, B 2, H 32, S 2048, dh 128 takes 87 us instead of 100 (S 4096, B 1: 153 for
+// 182; dh 64: 52 for 64; without the causal mask, H 16: 70 for 82).  64 queries per wave (half the LDS reads, one wave per
+// SIMD) was tried: 72 us for 53 at dh 64, spilled registers at 128.
 template <int DH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_kernel(AttnParams p) {
   using HT = HeadTile<DH>;
-  constexpr int KS = DH / 16, DT = DH / 32, BKV = 64;
+  constexpr int KS = DH / 16, DT = DH / 32, BKV = 64, BQ = 128;
   constexpr int IMG = BKV * HT::RB, SLOT = 2 * IMG;
   constexpr int NCH = IMG / 1024 / 4;                 // copies per wave per operand per block
 
@@ -105,13 +112,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // causal masking the work of a block grows with its index, and the blocks still to start near the end are short ones
   const int qb = (int)gridDim.y - 1 - (int)blockIdx.y;
   const int h = (int)blockIdx.x % p.H, b = (int)blockIdx.x / p.H;
-  const int q0 = qb * 128, qw0 = q0 + 32 * wave, query = qw0 + ql;
+  const int q0 = qb * BQ, qw0 = q0 + 32 * wave, query = qw0 + ql;
   const int d = p.H * DH;
   const long tok0 = (long)b * p.S;
 
   const typename HT::Offsets fo = HT::offsets(lane);
-  // ---- the block's 128 query rows: copied (coalesced) into the second slot, which the loop fills only after its first
-  // barrier; fetched per lane they would be 32-byte pieces of 32 rows per instruction
+  // ---- the block's query rows: copied (coalesced) into the second slot, which nothing else uses until they have been read;
+  // fetched per lane they would be 32-byte pieces of 32 rows per instruction
   {
     const u32x4 dq = make_desc(p.qkv + (tok0 + q0) * p.ld_qkv + h * DH, (uint32_t)((long)(p.S - q0) * p.ld_qkv * 2));
 #pragma unroll
@@ -126,20 +133,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   unsigned c_off[NCH];
 #pragma unroll
   for (int i = 0; i < NCH; i++) HT::plan(wave + 4 * i, lane, p.ld_qkv, c_row[i], c_off[i]);
-  const int kv_end = p.causal ? (q0 + 128 < p.S ? q0 + 128 : p.S) : p.S;
+  const int kv_end = p.causal ? (q0 + BQ < p.S ? q0 + BQ : p.S) : p.S;
   const int nblk = (kv_end + BKV - 1) / BKV;
-  auto issue = [&](int j) {
+  auto issue = [&](int j, int which) {      // which: 0 the K image, 1 the V image of block j
     const int kv0 = j * BKV;
-    const bf16_t* kb = p.qkv + (tok0 + kv0) * p.ld_qkv + d + h * DH;
-    const uint32_t bytes = (uint32_t)((long)(p.S - kv0) * p.ld_qkv * 2);     // rows of this sequence only
-    const u32x4 dk = make_desc(kb, bytes), dv = make_desc(kb + d, bytes);
-    const uint32_t base = lds0 + (j & 1) * SLOT + wave * 1024;
+    const bf16_t* src = p.qkv + (tok0 + kv0) * p.ld_qkv + (which ? 2 * d : d) + h * DH;
+    const u32x4 desc = make_desc(src, (uint32_t)((long)(p.S - kv0) * p.ld_qkv * 2));      // rows of this sequence only
+    const uint32_t base = lds0 + (j & 1) * SLOT + which * IMG + wave * 1024;
 #pragma unroll
-    for (int i = 0; i < NCH; i++) {
-      const unsigned off = (kv0 + c_row[i] < p.S) ? c_off[i] : kOob;
-      dma16(base + i * 4096, dk, off);
-      dma16(base + IMG + i * 4096, dv, off);
-    }
+    for (int i = 0; i < NCH; i++) dma16(base + i * 4096, desc, (kv0 + c_row[i] < p.S) ? c_off[i] : kOob);
   };
 
   f32x16 ot[DT];
@@ -147,41 +149,47 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int t = 0; t < DT; t++)
 #pragma unroll
     for (int e = 0; e < 16; e++) ot[t][e] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  // m: reference point of the row's exponentials (the same in both lane halves); l: this lane half's share of the row sum
+  float m = -INFINITY, l[2] = {0.f, 0.f};
 
-  issue(0);
+  issue(0, 0);
+  issue(0, 1);
   wait_vmem<0>();
   __syncthreads();
   // ---- this lane's query row as B operand of S^T = K Q^T: 8 consecutive head-dim values per k-step
   bf16x8 qf[KS];
 #pragma unroll
   for (int s = 0; s < KS; s++) qf[s] = HT::rows_frag(lds + SLOT, fo, 32 * wave, s);
-  for (int j = 0; j < nblk; j++) {
-    wait_vmem<0>();
-    __syncthreads();                   // block j has landed; every wave is done with the other slot (and has its query row)
-    if (j + 1 < nblk) issue(j + 1);
-    const int kv0 = j * BKV;
-    if (p.causal && kv0 > qw0 + 31) continue;          // every key of the block is after every query of this wave
-    lds_u8* const kimg = lds + (j & 1) * SLOT;
-    lds_u8* const vimg = kimg + IMG;
-    // S^T for the two key tiles of the block as two interleaved accumulation chains (consecutive MFMAs are
-    // independent), fragments fetched one k-step ahead
-    f32x16 st[2];
+  f32x16 sa[2], sb[2];                 // S^T of the block whose softmax is in work, and of the next one
+#pragma unroll
+  for (int kt = 0; kt < 2; kt++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) sa[kt][e] = 0.f;
+#pragma unroll
+  for (int s = 0; s < KS; s++)
 #pragma unroll
     for (int kt = 0; kt < 2; kt++)
+      sa[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(HT::rows_frag(lds, fo, 32 * kt, s), qf[s], sa[kt], 0, 0, 0);
+  __syncthreads();                     // every wave has its query row: the second slot is free
+  if (nblk > 1) issue(1, 0);
+
+  // Block j: softmax of its scores (st) and O^T += V^T P^T, with the scores of block j + 1 (nx) computed on the way.
+  // The order of the instructions is pinned: the MFMAs of the next block's scores and the first three quarters of the PV
+  // MFMAs each carry a share of the exponentials, so that the matrix pipe and the vector ALU work side by side.
+  auto block = [&](f32x16 (&st)[2], f32x16 (&nx)[2], int j) {
+    wait_vmem<0>();
+    __syncthreads();                   // K of block j + 1 and V of block j have landed; every wave is done with block j - 1
+    if (j + 2 < nblk) issue(j + 2, 0);
+    if (j + 1 < nblk) issue(j + 1, 1);
+    const int kv0 = j * BKV;
+    if (p.causal && kv0 > qw0 + 31) return;            // every key of the block is after every query of this wave
+    lds_u8* const kimg = lds + ((j + 1) & 1) * SLOT;   // (after the last block: an older one, whose scores nobody uses)
+    lds_u8* const vimg = lds + (j & 1) * SLOT + IMG;
+    bf16x8 kf[2][2];
 #pragma unroll
-      for (int e = 0; e < 16; e++) st[kt][e] = 0.f;
-    {
-      bf16x8 k0 = HT::rows_frag(kimg, fo, 0, 0), k1 = HT::rows_frag(kimg, fo, 32, 0);
+    for (int s = 0; s < 2; s++)
 #pragma unroll
-      for (int s = 0; s < KS; s++) {
-        bf16x8 n0 = k0, n1 = k1;
-        if (s + 1 < KS) { n0 = HT::rows_frag(kimg, fo, 0, s + 1); n1 = HT::rows_frag(kimg, fo, 32, s + 1); }
-        st[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k0, qf[s], st[0], 0, 0, 0);
-        st[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k1, qf[s], st[1], 0, 0, 0);
-        k0 = n0; k1 = n1;
-      }
-    }
+      for (int kt = 0; kt < 2; kt++) kf[s][kt] = HT::rows_frag(kimg, fo, 32 * kt, s);
     // keys beyond the query (causal) or beyond the sequence do not take part (blocks on the diagonal / at the end only)
     if ((p.causal && kv0 + BKV - 1 > qw0) || kv0 + BKV > p.S) {
       const int last = p.causal ? (query < p.S - 1 ? query : p.S - 1) : p.S - 1;      // last key this lane's query sees
@@ -192,65 +200,83 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int e = 0; e < 16; e++)
           st[kt][e] = (32 * kt + 8 * (e >> 2) + (e & 3) > rel) ? -INFINITY : st[kt][e];
     }
+    // The reference point m of the exponentials only has to stay within a safe distance of the running maximum, not
+    // on it: o / l and lse = m + log2 l are the same for any m.  It is moved (and what is accumulated rescaled) only
+    // when some query's maximum has risen by more than kSlack octaves above it; until then p <= 2^kSlack, far inside
+    // the range of fp32 sums and of the storage type.  With the maximum itself as reference nearly every block moves
+    // some lane's maximum and pays 16 * DT multiplications per lane; this way typically only the first block does, and
+    // the two halves of a row need not exchange their maxima to find out.
+    constexpr float kSlack = 8.f;
     float mx = -INFINITY;
 #pragma unroll
     for (int kt = 0; kt < 2; kt++)
 #pragma unroll
       for (int e = 0; e < 16; e++) mx = fmaxf(mx, st[kt][e]);
-    mx = fmaxf(mx, xor32(mx)) * p.scale_log2e;          // scale > 0: the maximum commutes with it
-    // The reference point m of the exponentials only has to stay within a safe distance of the running maximum, not
-    // on it: o / l and lse = m + log2 l are the same for any m.  It is moved (and what is accumulated rescaled) only
-    // when some query's maximum has risen by more than kSlack octaves above it; until then p <= 2^kSlack, far inside
-    // the range of fp32 sums and of the storage type.  With the maximum itself as reference nearly every block moves
-    // some lane's maximum and pays 16 * DT multiplications per lane; this way typically only the first block does.
-    constexpr float kSlack = 8.f;
-    const float mnew = fmaxf(m, mx);
-    if (__any(mnew > m + kSlack)) {
+    mx *= p.scale_log2e;                                // scale > 0: the maximum commutes with it
+    if (__any(mx > m + kSlack)) {
+      const float mnew = fmaxf(m, fmaxf(mx, xor32(mx)));
       const float alpha = __builtin_amdgcn_exp2f(m - mnew);    // first block: m = -inf, exp2(-inf) = 0
-      l *= alpha;
+      l[0] *= alpha;
+      l[1] *= alpha;
 #pragma unroll
       for (int t = 0; t < DT; t++)
 #pragma unroll
         for (int e = 0; e < 16; e++) ot[t][e] *= alpha;
       m = mnew;
     }
-    float rs = 0.f;
+    bf16x8 pb[4], vf[DT];
+    auto elements = [&](int e0, int e1) {               // exponentials of elements e0 .. e1 - 1 of the lane's 32
+#pragma unroll
+      for (int e = e0; e < e1; e++) {
+        const float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e >> 4][e & 15], p.scale_log2e, -m));
+        st[e >> 4][e & 15] = pe;
+        l[e & 1] += pe;
+        if (e % 8 == 7) pb[e >> 3] = pack8(st[e >> 4], (e >> 3) & 1);
+      }
+    };
+    constexpr int NA = 2 * KS, EA = 18;        // MFMAs of the scores; elements done beside them, the rest beside 3 PV k-steps
+    static_assert(EA >= 8 && EA + (32 - EA) / 3 >= 16 && EA + (32 - EA) * 2 / 3 >= 24, "P must be ready in time");
 #pragma unroll
     for (int kt = 0; kt < 2; kt++)
 #pragma unroll
-      for (int e = 0; e < 16; e++) {
-        const float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(st[kt][e], p.scale_log2e, -m));
-        st[kt][e] = pe;
-        rs += pe;
-      }
-    l += rs + xor32(rs);
-    // O^T += V^T P^T: 4 (kt, u) steps x DT independent accumulators, fragments one step ahead
-    bf16x8 vf[DT];
+      for (int e = 0; e < 16; e++) nx[kt][e] = 0.f;
+    __builtin_amdgcn_s_setprio(1);             // (the SIMD's other wave fills in: 1-4 % faster than without)
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int t = 0; t < DT; t++) vf[t] = HT::cols_frag(vimg, fo, 0, 0, t);
-#pragma unroll
-    for (int ku = 0; ku < 4; ku++) {
-      const bf16x8 pb = pack8(st[ku >> 1], ku & 1);
-      bf16x8 nf[DT];
-#pragma unroll
-      for (int t = 0; t < DT; t++) nf[t] = ku < 3 ? HT::cols_frag(vimg, fo, 32 * ((ku + 1) >> 1), (ku + 1) & 1, t) : vf[t];
-#pragma unroll
-      for (int t = 0; t < DT; t++) ot[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t], pb, ot[t], 0, 0, 0);
-#pragma unroll
-      for (int t = 0; t < DT; t++) vf[t] = nf[t];
+    for (int i = 0; i < NA; i++) {
+      const int s = i >> 1, kt = i & 1;
+      nx[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s & 1][kt], qf[s], nx[kt], 0, 0, 0);
+      if (s + 2 < KS) kf[s & 1][kt] = HT::rows_frag(kimg, fo, 32 * kt, s + 2);
+      if (i >= NA - DT) vf[i - (NA - DT)] = HT::cols_frag(vimg, fo, 0, 0, i - (NA - DT));
+      elements(EA * i / NA, EA * (i + 1) / NA);
+      __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int i = 0; i < 4 * DT; i++) {
+      const int ku = i / DT, t = i % DT;
+      ot[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t], pb[ku], ot[t], 0, 0, 0);
+      if (ku < 3) vf[t] = HT::cols_frag(vimg, fo, 32 * ((ku + 1) >> 1), (ku + 1) & 1, t);
+      if (ku < 3) elements(EA + (32 - EA) * i / (3 * DT), EA + (32 - EA) * (i + 1) / (3 * DT));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_s_setprio(0);
+  };
+  for (int j = 0; j < nblk; j += 2) {
+    block(sa, sb, j);
+    if (j + 1 < nblk) block(sb, sa, j + 1);
   }
 
   // ---- o = O^T / l, transposed back on the way out.  A lane holds 4 consecutive head-dim values of its query per
-  // register group (8 bytes, 32 rows per instruction if stored directly): each wave passes its 32 rows through LDS
-  // (the ring is free after one more barrier; rows padded to DH * 2 + 16 bytes against bank conflicts) and writes them
+  // register group (8 bytes, 32 rows per instruction if stored directly): each wave passes its rows through LDS
+  // (free after one more barrier; rows padded to DH * 2 + 16 bytes against bank conflicts) and writes them
   // whole, 16 bytes per lane.
   __syncthreads();
   constexpr int EROW = DH * 2 + 16;
-  static_assert(128 * EROW <= 2 * SLOT, "the output tile must fit in the ring");
+  static_assert(BQ * EROW <= 2 * SLOT, "the output tile must fit in the ring");
   lds_u8* const erow = lds + 32 * wave * EROW;
   {
-    const float inv = 1.f / l;
+    const float lq = (l[0] + l[1]) + xor32(l[0] + l[1]);
+    const float inv = 1.f / lq;
 #pragma unroll
     for (int t = 0; t < DT; t++)
 #pragma unroll
@@ -260,7 +286,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int r = 0; r < 4; r++) v[r] = (bf16_t)(ot[t][4 * e4 + r] * inv);
         *reinterpret_cast<LDS_AS bf16x4*>(erow + ql * EROW + (32 * t + 8 * e4 + 4 * g) * 2) = v;
       }
-    if (g == 0 && query < p.S) p.lse[((long)b * p.H + h) * p.S + query] = m + __builtin_amdgcn_logf(l);
+    if (g == 0 && query < p.S) p.lse[((long)b * p.H + h) * p.S + query] = m + __builtin_amdgcn_logf(lq);
   }
   {  // (LDS operations of a wave execute in order: the reads below see this wave's own writes above)
     constexpr int LPR = DH / 8, RPI = 64 / LPR;
