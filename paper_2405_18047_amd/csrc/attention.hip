@@ -401,32 +401,38 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
         f32x16 sa, da;
 #pragma unroll
         for (int e = 0; e < 16; e++) { sa[e] = 0.f; da[e] = 0.f; }
+        // The order is pinned: left to itself the compiler fetches a fragment right before the MFMA that wants it, and
+        // the latency of the LDS is then paid at every one of the KS steps.
         constexpr int PF = KS < 4 ? KS : 4;
         bf16x8 fq[KS], fd[KS];
+        f32x4 ls[4], dl[4];
 #pragma unroll
         for (int s = 0; s < PF; s++) { fq[s] = HT::rows_frag(qimg, fo, 0, s); fd[s] = HT::rows_frag(dimg, fo, 0, s); }
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int s = 0; s < KS; s++) {
           if (s + PF < KS) { fq[s + PF] = HT::rows_frag(qimg, fo, 0, s + PF); fd[s + PF] = HT::rows_frag(dimg, fo, 0, s + PF); }
+          if (s >= KS - 4) {
+            const int e4 = s - (KS - 4);
+            ls[e4] = *reinterpret_cast<const LDS_AS f32x4*>(stat + 8 * e4 + 4 * g);
+            dl[e4] = *reinterpret_cast<const LDS_AS f32x4*>(stat + BQ + 8 * e4 + 4 * g);
+          }
           sa = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fq[s], kfb[s], sa, 0, 0, 0);
           da = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fd[s], vfb[s], da, 0, 0, 0);
+          __builtin_amdgcn_sched_barrier(0);
         }
-        // register e of the tile is query qt0 + 8 (e / 4) + 4 g + e % 4
-        const int rel = p.causal ? key - qt0 - 4 * g : -1;
+        // register e of the tile is query qt0 + 8 (e / 4) + 4 g + e % 4.  Only a tile on the diagonal has a query before
+        // one of the wave's keys: the others skip the two instructions per element of the comparison.
         float pv[16], sv[16];
 #pragma unroll
-        for (int e4 = 0; e4 < 4; e4++) {
-          const f32x4 ls = *reinterpret_cast<const LDS_AS f32x4*>(stat + 8 * e4 + 4 * g);
-          const f32x4 dl = *reinterpret_cast<const LDS_AS f32x4*>(stat + BQ + 8 * e4 + 4 * g);
+        for (int e = 0; e < 16; e++) pv[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sa[e], p.scale_log2e, -ls[e >> 2][e & 3]));
+        if (p.causal && qt0 < kw0 + 31) {
+          const int rel = key - qt0 - 4 * g;
 #pragma unroll
-          for (int q = 0; q < 4; q++) {
-            const int e = 4 * e4 + q;
-            float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(sa[e], p.scale_log2e, -ls[q]));
-            pe = (8 * e4 + q < rel) ? 0.f : pe;
-            pv[e] = pe;
-            sv[e] = pe * (da[e] - dl[q]);
-          }
+          for (int e = 0; e < 16; e++) pv[e] = (8 * (e >> 2) + (e & 3) < rel) ? 0.f : pv[e];
         }
+#pragma unroll
+        for (int e = 0; e < 16; e++) sv[e] = pv[e] * (da[e] - dl[e >> 2][e & 3]);
         bf16x8 kp[2], ks[2];
 #pragma unroll
         for (int u = 0; u < 2; u++)
@@ -539,23 +545,30 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
       const int tile = tp - 1;
       lds_u8* const qimg = lds + (((tile >> 1) - step0) % 3) * SLOT + (tile & 1) * HALF;
       lds_u8* const dimg = qimg + IMG;
-      // this wave's 32 head-dim columns of dO^T and Q^T (two k-steps of 16 queries), then every key block's P and dS
-      bf16x8 fo_d[2], fo_q[2];
-#pragma unroll
-      for (int u = 0; u < 2; u++) { fo_d[u] = my_cols(dimg, u); fo_q[u] = my_cols(qimg, u); }
+      // this wave's 32 head-dim columns of dO^T and Q^T (two k-steps of 16 queries), then every key block's P and dS, each
+      // fetched one key block ahead of its MFMAs (pinned, as on the left)
+      bf16x8 fo_d[2], fo_q[2], kp[2][2], ks[2][2];
       const lds_u8* const in = hand + (tile & 1) * HAND + lane * 16;
-#pragma unroll
-      for (int kbk = 0; kbk < 4; kbk++) {
-        bf16x8 kp[2], ks[2];
-        kp[0] = *reinterpret_cast<const LDS_AS bf16x8*>(in + kbk * 4096);
-        kp[1] = *reinterpret_cast<const LDS_AS bf16x8*>(in + kbk * 4096 + 1024);
-        ks[0] = *reinterpret_cast<const LDS_AS bf16x8*>(in + kbk * 4096 + 2048);
-        ks[1] = *reinterpret_cast<const LDS_AS bf16x8*>(in + kbk * 4096 + 3072);
+      auto fetch = [&](int kbk) {
 #pragma unroll
         for (int u = 0; u < 2; u++) {
-          dvt[kbk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo_d[u], kp[u], dvt[kbk], 0, 0, 0);
-          dkt[kbk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo_q[u], ks[u], dkt[kbk], 0, 0, 0);
+          kp[kbk & 1][u] = *reinterpret_cast<const LDS_AS bf16x8*>(in + kbk * 4096 + 1024 * u);
+          ks[kbk & 1][u] = *reinterpret_cast<const LDS_AS bf16x8*>(in + kbk * 4096 + 2048 + 1024 * u);
         }
+      };
+#pragma unroll
+      for (int u = 0; u < 2; u++) { fo_d[u] = my_cols(dimg, u); fo_q[u] = my_cols(qimg, u); }
+      fetch(0);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int kbk = 0; kbk < 4; kbk++) {
+        if (kbk < 3) fetch(kbk + 1);
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+          dvt[kbk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo_d[u], kp[kbk & 1][u], dvt[kbk], 0, 0, 0);
+          dkt[kbk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo_q[u], ks[kbk & 1][u], dkt[kbk], 0, 0, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
     // step (tp + 1) / 2 + 1 is what the left waves start two barriers from now, when tp is odd: it was issued three
@@ -711,7 +724,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // keys beyond the query (causal) or beyond the sequence do not take part: their probability is zero
     const bool edge = (p.causal && kv0 + BKV - 1 > qw0) || kv0 + BKV > p.S;
     const int last = p.causal ? (query < p.S - 1 ? query : p.S - 1) : p.S - 1;
-    const int rel = edge ? last - kv0 - 4 * g : 1 << 20;
+    const int rel = last - kv0 - 4 * g;
     // one 32-key tile at a time (both tiles at once would need 64 more accumulator registers than a wave has):
     // S^T and dP^T as two interleaved accumulation chains, fragments one k-step ahead; then dS^T in place and
     // dQ^T += K^T dS^T over the tile's two k-steps on DT independent accumulators
@@ -720,24 +733,30 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       f32x16 st, dp;
 #pragma unroll
       for (int e = 0; e < 16; e++) { st[e] = 0.f; dp[e] = 0.f; }
-      bf16x8 kf = HT::rows_frag(kimg, fo, 32 * kt, 0), vf = HT::rows_frag(vimg, fo, 32 * kt, 0);
+      // (the order is pinned: the compiler would fetch each fragment right before its MFMA)
+      constexpr int PF = 3;
+      bf16x8 kf[PF], vf[PF], ktf[DT];
+#pragma unroll
+      for (int s = 0; s < PF; s++) { kf[s] = HT::rows_frag(kimg, fo, 32 * kt, s); vf[s] = HT::rows_frag(vimg, fo, 32 * kt, s); }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int s = 0; s < KS; s++) {
-        bf16x8 nk = kf, nv = vf;
-        if (s + 1 < KS) { nk = HT::rows_frag(kimg, fo, 32 * kt, s + 1); nv = HT::rows_frag(vimg, fo, 32 * kt, s + 1); }
-        st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf, qf[s], st, 0, 0, 0);
-        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf, dof[s], dp, 0, 0, 0);
-        kf = nk; vf = nv;
+        st = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s % PF], qf[s], st, 0, 0, 0);
+        dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[s % PF], dof[s], dp, 0, 0, 0);
+        if (s + PF < KS) { kf[s % PF] = HT::rows_frag(kimg, fo, 32 * kt, s + PF); vf[s % PF] = HT::rows_frag(vimg, fo, 32 * kt, s + PF); }
+        if (s >= KS - DT) ktf[s - (KS - DT)] = HT::cols_frag(kimg, fo, 32 * kt, 0, s - (KS - DT));
+        __builtin_amdgcn_sched_barrier(0);
       }
-      bf16x8 ktf[DT];
-#pragma unroll
-      for (int t = 0; t < DT; t++) ktf[t] = HT::cols_frag(kimg, fo, 32 * kt, 0, t);
 #pragma unroll
       for (int e = 0; e < 16; e++) {
-        float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e], p.scale_log2e, -lse_q));
-        pe = (32 * kt + 8 * (e >> 2) + (e & 3) > rel) ? 0.f : pe;
-        st[e] = pe * (dp[e] - dl_q);                         // dS^T
+        st[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e], p.scale_log2e, -lse_q));
       }
+      if (edge) {
+#pragma unroll
+        for (int e = 0; e < 16; e++) st[e] = (32 * kt + 8 * (e >> 2) + (e & 3) > rel) ? 0.f : st[e];
+      }
+#pragma unroll
+      for (int e = 0; e < 16; e++) st[e] *= dp[e] - dl_q;    // dS^T
 #pragma unroll
       for (int u = 0; u < 2; u++) {
         const bf16x8 sb = pack8(st, u);
@@ -745,6 +764,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int t = 0; t < DT; t++) {
           dqt[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ktf[t], sb, dqt[t], 0, 0, 0);
           if (u == 0) ktf[t] = HT::cols_frag(kimg, fo, 32 * kt, 1, t);     // the second k-step's fragment, behind the MFMA that used the first
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
     }
@@ -832,8 +852,12 @@ hipError_t attention_p1(int batch, int n_heads, int seq, int head_dim, int causa
   p.B = batch; p.H = n_heads; p.S = seq; p.causal = causal;
   p.scale = 1.f / sqrtf((float)head_dim);
   p.scale_log2e = 1.4426950408889634f * p.scale;
-  if (!ds_t) {
-    // no dS^T buffer: dQ by the recompute pass
+  // dQ by the recompute pass where there is no dS^T buffer, and where there are at least four workgroups of 128 keys per
+  // compute unit: dS^T is then several times the on-package cache (0.5 GB at B 2, H 32, S 2048) and its round trip costs
+  // more than the two products it saves.  Whole backward, us, dS^T / recompute: B 2, H 32, S 2048 326 / 298, dh 64
+  // 213 / 177; B 1, S 4096 507 / 487; below that the recompute pass leaves the chip emptier than one product over
+  // 128 x 128 tiles: B 1, H 32, S 2048 142 / 155, S 1024 62 / 72, H 16, S 2048 100 / 123.
+  if (!ds_t || (long)batch * n_heads * ((seq + 127) / 128) >= 1024) {
     if (head_dim == 128) e = launch_bwd_kv_split<128, false>(p, s);
     else if (head_dim == 64) e = launch_bwd_kv_split<64, false>(p, s);
     else return hipErrorInvalidValue;

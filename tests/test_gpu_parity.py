@@ -625,3 +625,23 @@ def test_stage_inputs_at_any_address(shape, gain_grad):
     for offs in ((1, 1, n + 64 - n % 64), (0, 0, 0), (0, 0, 2 * q), (q, 4 * q, 0)):
         for a, b in zip(run(*offs), want):
             assert torch.equal(a, b), offs
+
+
+@pytest.mark.parametrize("dh,causal", [(64, True), (128, False)])
+def test_fused_attention_backward_on_many_workgroups(dh, causal):
+    """With four workgroups of 128 keys per compute unit or more, dq comes from the recompute pass also where there is room
+    for dS^T: the same bits as the call that asks for it, and the oracle's values."""
+    seq, nb, H = 264, 4, 86                                   # 344 (sequence, head) pairs x 3 key blocks, the last ragged
+    _say(f"attention p1 on 1032 workgroups dh={dh} causal={causal}")
+    d = H * dh
+    q, k, v, do = (_rnd(48, n, (nb * seq, d), "bf16") for n in ("q", "k", "v", "do"))
+    q64, k64, v64 = q.astype(np.float64), k.astype(np.float64), v.astype(np.float64)
+    _, P = ops.attention_fwd(q64, k64, v64, seq, H, dh, causal)
+    dq, dk, dv = ops.attention_p1(do.astype(np.float64), q64, k64, v64, P, seq, H, dh)
+    qkv = to_dev(np.concatenate([q, k, v], axis=1), "bf16")
+    out, lse2 = tbp.tbp_attention_fwd(qkv, seq, H, dh, causal)
+    got = tbp.tbp_attention_p1(qkv, out, to_dev(do, "bf16"), lse2, seq, H, dh, causal)
+    assert torch.equal(got, tbp.tbp_attention_p1(qkv, out, to_dev(do, "bf16"), lse2, seq, H, dh, causal, recompute=True))
+    got = to_np(got)
+    for name, ref, blk in (("dq", dq, got[:, :d]), ("dk", dk, got[:, d:2 * d]), ("dv", dv, got[:, 2 * d:])):
+        assert max_rel(blk, ref) < 1.5e-2, name
