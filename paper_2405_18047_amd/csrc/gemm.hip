@@ -90,7 +90,8 @@ __device__ __forceinline__ void tile_of_block_split(int pid, int tiles_m, int ti
 //       in slot g ^ ((r >> 2) & 3) (depth 32) or g ^ ((r >> 1) & 7) (depth 64): the 16 lanes served per clock (256
 //       bytes) then touch 16 different 16-byte bank groups.  A fragment read is one ds_read_b128 per lane.
 //   KS (contraction index strided in memory): image [BK][R] as in memory, R/8 granules per row; granule
-//       pairs (32 bytes = 16 columns) are swizzled: pair q of row k sits in pair slot q ^ (k & 3).  A fragment
+//       pairs (32 bytes = 16 columns) are swizzled: pair q of row k sits in pair slot q ^ (k & 3) (tiles of 32 columns have
+//       two pairs per row and need no swizzle: four rows cover the banks).  A fragment
 //       read is two ds_read_b64_tr_b16 (transpose reads), each covering 4 k x 16 columns per 16-lane group:
 //       within a group lane j addresses row k + j/4, columns 4*(j%4)..+3 and receives 4 consecutive k of column j.
 template <int R, bool KC, int KD = BK>
@@ -107,6 +108,7 @@ struct OperandTile {
   // KC swizzle: granule g of row r sits in slot g ^ ((r / RPB) % GR), so 16 consecutive rows at one logical granule
   // cover the 16 bank groups once.
   static __device__ __forceinline__ int kc_swz(int row) { return (row / RPB) & (GR - 1); }
+  static __device__ __forceinline__ int ks_swz(int k) { return R >= 64 ? (k & 3) : 0; }
 
   // Global byte offset (relative to the tile origin) and contraction index covered by lane p of chunk c.
   static __device__ __forceinline__ void copy_plan(int c, int p, long ld, int origin, int extent, unsigned& goff,
@@ -119,7 +121,7 @@ struct OperandTile {
     } else {
       const int P = 64 * c + p;
       const int k = P / GPR, sl = P % GPR;
-      const int g = ((((sl >> 1) ^ (k & 3)) << 1) | (sl & 1));
+      const int g = ((((sl >> 1) ^ ks_swz(k)) << 1) | (sl & 1));
       goff = (origin + g * 8 < extent) ? (unsigned)((long)k * ld * 2 + g * 16) : kOob;
       kidx = k;
     }
@@ -134,7 +136,7 @@ struct OperandTile {
     } else {
       const int k = 8 * (lane >> 5) + ((lane & 15) >> 2);
       const int q = w0 / 16 + ((lane >> 4) & 1) + 2 * v;
-      return k * (R * 2) + ((q ^ (k & 3)) << 5) + 8 * (lane & 3);
+      return k * (R * 2) + ((q ^ ks_swz(k)) << 5) + 8 * (lane & 3);
     }
   }
   static constexpr int VARIANTS = KC ? KD / 16 : 2;
@@ -554,6 +556,108 @@ __global__ __launch_bounds__(256) void gemm_bf16_split_kernel(GemmParams p) {
   int tm_i, tn_i, slice;
   tile_of_block_split(blockIdx.x, p.tiles_m, p.tiles_n, p.split, tm_i, tn_i, slice);
   gemm_bf16_tile<BM, BN, AKC, BKC, float, KD, true, RING>(p, tm_i, tn_i, slice);
+}
+
+constexpr int kSmallSlots = 4;                 // ring slots per wave of the small-output kernel
+
+// Outputs of at most one 32 x 32 tile per compute unit (storage-type NN / NT products of short micro-batches).  What bounds
+// such a product is latency: a workgroup has few slots to walk, and every barrier and every slot that is not yet in flight
+// adds to them.  The four waves of a workgroup share one 32 x 32 tile and take the 64-deep slots of the contraction in
+// turn, each through a ring of its own that it fills with its own copies: no barrier until the waves' partial sums meet in
+// the LDS (added in wave order), and 12 slots on their way at once.
+// Measured against 64 x 64 tiles (us): [128, 256] x 256 4.2 -> 3.7, x 768 6.0 -> 4.2, x 1376 8.4 -> 4.7, [256, 1024] x 5504
+// 14.5 -> 11.9, [64, 4096] x 4096 22 -> 11; at more than one tile per compute unit it loses ([200, 1536] x 512 5.4 -> 6.9).
+template <bool BKC>
+__global__ __launch_bounds__(256) void gemm_bf16_small_kernel(GemmParams p) {
+  using TA = OperandTile<32, true, 64>;
+  using TB = OperandTile<32, BKC, 64>;
+  constexpr int KD = 64, NS = kSmallSlots, L = 8;
+  static_assert(TA::BYTES == 4096 && TB::BYTES == 4096 && (NS - 2) * L < 64, "slot layout, wait counter");
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  lds_u8* const lds = LDS_PTR(unsigned char, smem_raw);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  lds_u8* const ring = lds + wave * (NS * 8192);
+  const uint32_t ring0 = (uint32_t)(uintptr_t)lds + wave * (NS * 8192);
+
+  int tm_i, tn_i;
+  tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, tm_i, tn_i);
+  const int m0 = tm_i * 32, n0 = tn_i * 32;
+  const bf16_t* A = reinterpret_cast<const bf16_t*>(p.A);
+  const bf16_t* B = reinterpret_cast<const bf16_t*>(p.B);
+
+  unsigned a_goff[4], b_goff[4];
+  int a_kidx[4], b_kidx[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    TA::copy_plan(i, lane, p.lda, m0, p.M, a_goff[i], a_kidx[i]);
+    TB::copy_plan(i, lane, p.ldb, n0, p.N, b_goff[i], b_kidx[i]);
+  }
+  const long b_kstep = BKC ? 1 : p.ldb;
+  const int k0 = wave * KD;                   // this wave's slots: k0, k0 + 4 KD, ...
+  uint64_t a_next = reinterpret_cast<uint64_t>(A + (long)m0 * p.lda + k0);
+  uint64_t b_next = reinterpret_cast<uint64_t>((BKC ? B + (long)n0 * p.ldb : B + n0) + (long)k0 * b_kstep);
+  int slot_next = 0, krem = p.K - k0;
+  const int nk = krem > 0 ? (krem + 4 * KD - 1) / (4 * KD) : 0;
+  auto issue = [&]() {                        // past the end: every lane out of range, zeros, no traffic
+    const u32x4 dA = make_desc(reinterpret_cast<const void*>(a_next)), dB = make_desc(reinterpret_cast<const void*>(b_next));
+    const uint32_t base = ring0 + slot_next * 8192;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      dma16(base + i * 1024, dA, a_kidx[i] < krem ? a_goff[i] : kOob);
+      dma16(base + 4096 + i * 1024, dB, b_kidx[i] < krem ? b_goff[i] : kOob);
+    }
+    a_next += (uint64_t)(4 * KD * 2);
+    b_next += (uint64_t)(4 * KD * b_kstep * 2);
+    slot_next = slot_next + 1 == NS ? 0 : slot_next + 1;
+    krem -= 4 * KD;
+  };
+  f32x16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; e++) acc[e] = 0.f;
+  if (nk > 0) {
+#pragma unroll
+    for (int t = 0; t < NS - 1; t++) issue();
+    for (int t = 0; t < nk; t++) {
+      wait_vmem<(NS - 2) * L>();              // this wave's slot t has landed
+      asm volatile("" ::: "memory");          // (its fragments must not be fetched earlier)
+      __builtin_amdgcn_sched_barrier(0);
+      lds_u8* const ia = ring + (t % NS) * 8192;
+      lds_u8* const ib = ia + 4096;
+      issue();                                // slot t + NS - 1 in the place of slot t - 1, whose fragments have been used
+      bf16x8 fa[4], fb[4];
+#pragma unroll
+      for (int v = 0; v < 4; v++) {
+        fa[v] = read_frag<32, true>(ia + TA::frag_base(lane, 0, TA::variant(v, 0)) + TA::frag_step(v, 0));
+        fb[v] = read_frag<32, BKC>(ib + TB::frag_base(lane, 0, TB::variant(v, 0)) + TB::frag_step(v, 0));
+      }
+      __builtin_amdgcn_sched_barrier(0);    // (all fetched before the first MFMA, one LDS latency per slot)
+#pragma unroll
+      for (int v = 0; v < 4; v++) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[v], fb[v], acc, 0, 0, 0);
+    }
+    wait_vmem<0>();                           // (the empty copies issued past the end)
+  }
+  __syncthreads();                            // every wave is done with its ring
+  LDS_AS float* const part = reinterpret_cast<LDS_AS float*>(lds);
+#pragma unroll
+  for (int e = 0; e < 16; e++) part[(wave * 16 + e) * 64 + lane] = acc[e];
+  __syncthreads();
+  // each wave adds up and stores 8 rows: registers 4 w .. 4 w + 3 are rows 8 w + 4 (lane / 32) + 0..3
+  const bf16_t* R = reinterpret_cast<const bf16_t*>(p.R);
+  bf16_t* C = reinterpret_cast<bf16_t*>(p.C);
+  const int col = n0 + (lane & 31);
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const int e = 4 * wave + q, row = m0 + 8 * wave + 4 * (lane >> 5) + q;
+    float v = part[e * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < 4; w++) v += part[(w * 16 + e) * 64 + lane];
+    if (row >= p.M || col >= p.N) continue;
+    const long idx = (long)row * p.ldc + col;
+    v *= p.alpha;
+    if (R) v += (float)R[idx];
+    C[idx] = (bf16_t)v;
+  }
 }
 
 // C = bf16(sum over the slices of parts[slice][M][N] (+ R)), slices added in order.
@@ -982,13 +1086,14 @@ static hipError_t launch_bf16_causal_pair(const GemmParams& p0, int batch, hipSt
 //     128 x 128 on two 64-deep slots    0.0126   1.5   two per compute unit: 0.0188 per round of 512
 //     64 x 64 on four 64-deep slots     0.0047   1.3   "                     0.0071
 //   but at least the time of reading both operands once at 4.9 TB/s plus 8.4;
+//   outputs of at most 256 tiles of 32 x 32 can run on gemm_bf16_small_kernel: 0.0018 K + 3.0;
 //   slices add 3.8 (the second launch) and 0.30 per MB of partial products, and must gain 12 %.
 // Why so many: one tile per compute unit leaves most of the chip idle on the short micro-batches.  Measured (us) against
 // what these shapes ran on before: [256, 4096] x 22016 (NT) 207 -> 76 (16 x 16 large tiles), [256, 22016] x 4096 106 -> 75
 // (256 x 192 in two slices), [360, 4096] x 11008 99 -> 52 (96 tiles of 128 in five), [1024, 4096] x 22016 212 -> 169 (64
 // large tiles in four), [512, 1024] x 2752 23 -> 16 (64 x 64); unsplit where the tiles already fill the chip, e.g.
 // [1024, 4096] x 4096 43 us on 128 x 128 tiles against 54 for the best split.
-enum ProductTile { T128_DEEP, T256_NARROW, T256, T128_PAIR, T64 };
+enum ProductTile { T128_DEEP, T256_NARROW, T256, T128_PAIR, T64, T32 };
 static bool one_round(int M, int N) { return (long)((M + 255) / 256) * ((N + 255) / 256) <= 256; }
 static SplitPlan product_plan(int M, int N, int K, bool allow_split) {
   struct Tile { int bm, bn, per_cu; double c1, c2, fixed; };
@@ -998,6 +1103,10 @@ static SplitPlan product_plan(int M, int N, int K, bool allow_split) {
   const double memory = 2e-6 * ((double)N * K + (double)M * K) / 4.9 + 8.4;
   SplitPlan best{T64, 1, K, 0};
   double best_time = 1e30;
+  if ((long)((M + 31) / 32) * ((N + 31) / 32) <= 256) {
+    best_time = 0.0018 * K + 3.0;
+    best.tile = T32;
+  }
   for (int i = 0; i < 5; i++) {
     const Tile& t = tiles[i];
     if (t.bm == 256 && M < 192) continue;
@@ -1024,6 +1133,19 @@ SplitPlan gemm_split_plan(int dtype, int layout, int M, int N, int K, int out_f3
   if (dtype != 1 || out_f32 || batch != 1 || layout == TN || !one_round(M, N)) return none;
   const SplitPlan plan = product_plan(M, N, K, true);
   return plan.split > 1 ? plan : none;
+}
+
+template <bool BKC>
+static hipError_t launch_small(const GemmParams& p0, hipStream_t s) {
+  GemmParams p = p0;
+  p.tiles_m = (p.M + 31) / 32;
+  p.tiles_n = (p.N + 31) / 32;
+  constexpr size_t smem = (size_t)4 * kSmallSlots * 8192;
+  auto kern = gemm_bf16_small_kernel<BKC>;
+  static AttrOnce once;
+  if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(256), smem, s, p);
+  return hipGetLastError();
 }
 
 template <int BM, int BN, bool AKC, bool BKC, int KD, int RING>
@@ -1060,6 +1182,7 @@ static hipError_t dispatch_product(const GemmParams& p, const SplitPlan& plan, v
     case T256: return launch_product<256, 256, BKC, 0>(p, plan, ws, s);
     case T128_PAIR: return launch_product<128, 128, BKC, 0>(p, plan, ws, s);
     case T64: return launch_product<64, 64, BKC, 4>(p, plan, ws, s);
+    case T32: return launch_small<BKC>(p, s);
   }
   return hipErrorInvalidValue;
 }

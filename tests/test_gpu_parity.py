@@ -134,7 +134,8 @@ def test_gemm_with_split_contraction(layout, mnk):
 
 @pytest.mark.parametrize("layout", [tbp.NN, tbp.NT])
 @pytest.mark.parametrize("mnk", [
-    (64, 64, 64), (136, 1032, 2760), (72, 1032, 5512),            # 64 x 64 tiles; the last in slices
+    (8, 8, 8), (64, 72, 264), (136, 1032, 2760), (256, 1024, 1000),       # 32 x 32 tiles
+    (264, 1032, 1000), (264, 1032, 5512),                         # 64 x 64 tiles; the last in slices
     (1000, 2056, 3080), (1032, 1032, 4104),                       # 128 x 128 tiles, one per compute unit; in slices
     (2000, 3464, 1160), (360, 4088, 5512),                        # 128 x 128 tiles, two per compute unit; few, long
     (264, 22008, 1032), (264, 11016, 4104),                       # 256 x 192 tiles; in slices
