@@ -958,6 +958,144 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(GemmParams p) {
     }
 }
 
+// Outputs of at most two 16 x 16 tiles per compute unit.  What bounds such a product on 32 x 32 tiles is the chain of MFMAs
+// itself (64 clocks per two indices, and a quarter of the contraction per wave): a quarter of the tile is a quarter of the
+// chain (the 16x16x4 MFMA takes 32 clocks per four indices) on four times as many workgroups.  As in the bf16 kernel for
+// small outputs the four waves take the slots of the contraction (32 indices, 2 KiB per operand) in turn, each through a
+// ring of its own, with no barrier until their partial sums meet in the LDS (added in wave order).
+// Lane group g = lane / 16 holds contraction indices 16 v + 4 g + j, j = 0..3 (one 16-byte read where they are contiguous),
+// and MFMA j of the four that follow multiplies the indices 16 v + {0, 4, 8, 12} + j; an operand that is strided in the
+// contraction index keeps the four indices of one MFMA in neighbouring image rows (64 bytes each: no bank conflicts).
+// Measured against 32 x 32 tiles (us): [256, 256] x 256 4.7 -> 3.3, x 768 7.2 -> 4.0, x 1376 10.6 -> 5.3, [64, 1024] x 2752
+// 19.2 -> 9.5; at three tiles per compute unit it loses ([256, 688] x 256 4.7 -> 5.9, [256, 768] x 256 4.9 -> 6.3).
+template <bool KC>
+struct SmallTileF32 {
+  static __device__ __forceinline__ void copy_plan(int c, int p, long ld, int origin, int extent, unsigned& goff, int& kidx) {
+    const int P = 64 * c + p;
+    if constexpr (KC) {                       // [16 rows][32]: granule g of row r in slot g ^ (r / 2) % 8
+      const int row = P / 8, g = (P % 8) ^ ((row >> 1) & 7);
+      goff = (origin + row < extent) ? (unsigned)((long)row * ld * 4 + g * 16) : kOob;
+      kidx = g * 4;
+    } else {                                  // [32][16 columns]
+      const int pos = P / 4, g = P % 4, k = (pos & ~15) | ((pos & 3) << 2) | ((pos >> 2) & 3);
+      goff = (origin + g * 4 < extent) ? (unsigned)((long)k * ld * 4 + g * 16) : kOob;
+      kidx = k;
+    }
+  }
+  static __device__ __forceinline__ f32x4 frag(lds_u8* img, int lane, int v) {
+    const int row = lane & 15, g = lane >> 4;
+    if constexpr (KC) {
+      return *reinterpret_cast<LDS_AS const f32x4*>(img + row * 128 + (((4 * v + g) ^ ((row >> 1) & 7)) << 4));
+    } else {
+      LDS_AS const float* const q = reinterpret_cast<LDS_AS const float*>(img) + (16 * v + g) * 16 + row;
+      f32x4 o;
+#pragma unroll
+      for (int j = 0; j < 4; j++) o[j] = q[64 * j];
+      return o;
+    }
+  }
+};
+
+template <bool AKC, bool BKC>
+__global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmParams p) {
+  using TA = SmallTileF32<AKC>;
+  using TB = SmallTileF32<BKC>;
+  constexpr int KD = 32, NS = kSmallSlots, L = 4, SLOT = 4096;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  lds_u8* const lds = LDS_PTR(unsigned char, smem_raw);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  lds_u8* const ring = lds + wave * (NS * SLOT);
+  const uint32_t ring0 = (uint32_t)(uintptr_t)lds + wave * (NS * SLOT);
+
+  int tm_i, tn_i;
+  if (gridDim.z == 1) tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, tm_i, tn_i);
+  else { tm_i = (int)blockIdx.x % p.tiles_m; tn_i = (int)blockIdx.x / p.tiles_m; }
+  const int m0 = tm_i * 16, n0 = tn_i * 16;
+  int k_lo = 0, k_hi = p.K;
+  if (p.causal == CAUSAL_SKIP_UPPER) {
+    if (n0 > m0 + 15) return;                 // (uniform over the workgroup)
+  } else if (p.causal == CAUSAL_K_END) {
+    k_hi = (m0 + 16 < p.K) ? m0 + 16 : p.K;
+  } else if (p.causal == CAUSAL_K_BEGIN) {
+    k_lo = m0;
+  }
+  const int z = blockIdx.z;
+  const int zo = z / p.batch_inner, zi = z - zo * p.batch_inner;
+  const float* A = reinterpret_cast<const float*>(p.A) + zo * p.sAo + zi * p.sAi;
+  const float* B = reinterpret_cast<const float*>(p.B) + zo * p.sBo + zi * p.sBi;
+
+  unsigned a_goff[2], b_goff[2];
+  int a_kidx[2], b_kidx[2];
+#pragma unroll
+  for (int i = 0; i < 2; i++) {
+    TA::copy_plan(i, lane, p.lda, m0, p.M, a_goff[i], a_kidx[i]);
+    TB::copy_plan(i, lane, p.ldb, n0, p.N, b_goff[i], b_kidx[i]);
+  }
+  const long a_kstep = AKC ? 1 : p.lda, b_kstep = BKC ? 1 : p.ldb;
+  const int k0 = k_lo + wave * KD;            // this wave's slots: k0, k0 + 4 KD, ...
+  uint64_t a_next = reinterpret_cast<uint64_t>((AKC ? A + (long)m0 * p.lda : A + m0) + (long)k0 * a_kstep);
+  uint64_t b_next = reinterpret_cast<uint64_t>((BKC ? B + (long)n0 * p.ldb : B + n0) + (long)k0 * b_kstep);
+  int slot_next = 0, krem = k_hi - k0;
+  const int nk = krem > 0 ? (krem + 4 * KD - 1) / (4 * KD) : 0;
+  auto issue = [&]() {                        // past the end: every lane out of range, zeros, no traffic
+    const u32x4 dA = make_desc(reinterpret_cast<const void*>(a_next)), dB = make_desc(reinterpret_cast<const void*>(b_next));
+    const uint32_t base = ring0 + slot_next * SLOT;
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+      dma16(base + i * 1024, dA, a_kidx[i] < krem ? a_goff[i] : kOob);
+      dma16(base + 2048 + i * 1024, dB, b_kidx[i] < krem ? b_goff[i] : kOob);
+    }
+    a_next += (uint64_t)(4 * KD * a_kstep * 4);
+    b_next += (uint64_t)(4 * KD * b_kstep * 4);
+    slot_next = slot_next + 1 == NS ? 0 : slot_next + 1;
+    krem -= 4 * KD;
+  };
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  if (nk > 0) {
+#pragma unroll
+    for (int t = 0; t < NS - 1; t++) issue();
+    for (int t = 0; t < nk; t++) {
+      wait_vmem<(NS - 2) * L>();              // this wave's slot t has landed
+      asm volatile("" ::: "memory");          // (its fragments must not be fetched earlier)
+      __builtin_amdgcn_sched_barrier(0);
+      lds_u8* const ia = ring + (t % NS) * SLOT;
+      issue();                                // slot t + NS - 1 in the place of slot t - 1, whose fragments have been used
+      f32x4 fa[2], fb[2];
+#pragma unroll
+      for (int v = 0; v < 2; v++) { fa[v] = TA::frag(ia, lane, v); fb[v] = TB::frag(ia + 2048, lane, v); }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int v = 0; v < 2; v++)
+#pragma unroll
+        for (int j = 0; j < 4; j++) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[v][j], fb[v][j], acc, 0, 0, 0);
+    }
+    wait_vmem<0>();                           // (the empty copies issued past the end)
+  }
+  __syncthreads();                            // every wave is done with its ring
+  LDS_AS float* const part = reinterpret_cast<LDS_AS float*>(lds);
+#pragma unroll
+  for (int e = 0; e < 4; e++) part[(wave * 4 + e) * 64 + lane] = acc[e];
+  __syncthreads();
+  // wave w adds up and stores register w of the tile: rows 4 (lane / 16) + w
+  float v = part[wave * 64 + lane];
+#pragma unroll
+  for (int w = 1; w < 4; w++) v += part[(w * 4 + wave) * 64 + lane];
+  const int row = m0 + 4 * (lane >> 4) + wave, col = n0 + (lane & 15);
+  if (row >= p.M || col >= p.N) return;
+  float* const C = reinterpret_cast<float*>(p.C) + zo * p.sCo + zi * p.sCi;
+  const float* const R = p.R ? reinterpret_cast<const float*>(p.R) + zo * p.sCo + zi * p.sCi : nullptr;
+  const long idx = (long)row * p.ldc + col;
+  v *= p.alpha;
+  if (p.delta) {
+    v = (!p.delta_causal || col <= row) ? R[idx] * (v - p.delta[zo * p.sDo + zi * p.sDi + (long)row * p.ldd]) : 0.f;
+  } else {
+    if (p.accumulate) v += C[idx];
+    if (R) v += R[idx];
+  }
+  C[idx] = v;
+}
+
 // The general fp32 product, for operands that the copies above cannot move in 16-byte pieces:
 // 64 x 64 x 16 tile, 256 threads, 4 x 4 outputs per thread; operands addressed through element strides so
 // one kernel serves NN, NT and TN.
@@ -1393,7 +1531,19 @@ static hipError_t launch_f32_layout(int layout, const GemmParams& p, int batch, 
   return hipErrorInvalidValue;
 }
 
-// Tile of an fp32 product: the one with the shortest time by rounds of 256 compute units, (rounds) x (tile area) / (rate).
+static hipError_t launch_f32_small(int layout, const GemmParams& p0, int batch, hipStream_t s) {
+  GemmParams p = p0;
+  p.tiles_m = (p.M + 15) / 16;
+  p.tiles_n = (p.N + 15) / 16;
+  constexpr size_t smem = (size_t)4 * kSmallSlots * 4096;
+  auto kern = layout == NN ? gemm_f32_small_kernel<true, false> : layout == NT ? gemm_f32_small_kernel<true, true> : gemm_f32_small_kernel<false, false>;
+  static AttrOnce once[3];
+  if (hipError_t e = once[layout].set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)batch), dim3(256), smem, s, p);
+  return hipGetLastError();
+}
+
+// Tile of an fp32 product: 16 x 16 up to two of them per compute unit, else the one with the shortest time by rounds of 256 compute units, (rounds) x (tile area) / (rate).
 // The rates (TFLOP/s with every compute unit busy) are measured: 128 x 128 tiles 132-140, 64 x 64 tiles 110-125, 32 x 32
 // tiles with the contraction split over the waves 91-110 (they move 4 times the operand bytes of the first).  Times in us,
 // 128 / 64 / 32: [512, 1024] x 5504 349 / 105 / 63 (too few tiles for anything but the smallest), [512, 5504] x 1024
@@ -1405,6 +1555,7 @@ static hipError_t dispatch_f32(int layout, const GemmParams& p, int batch, hipSt
     const long tiles = (long)((p.M + t - 1) / t) * ((p.N + t - 1) / t) * batch;
     return (double)((tiles + 255) / 256) * t * t / rate;
   };
+  if ((long)((p.M + 15) / 16) * ((p.N + 15) / 16) * batch <= 512) return launch_f32_small(layout, p, batch, s);
   const double c128 = cost(128, 132.), c64 = cost(64, 115.), c32 = cost(32, 100.);
   if (c32 <= c64 && c32 <= c128) return launch_f32_layout<32, 32, 4, 128, 2>(layout, p, batch, s);
   if (c64 <= c128) return launch_f32_layout<64, 64, 1, 64, 2>(layout, p, batch, s);

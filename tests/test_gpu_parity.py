@@ -68,7 +68,8 @@ def test_gemm_matches_definition(dtype, layout, mnk):
 
 @pytest.mark.parametrize("layout", [tbp.NN, tbp.NT, tbp.TN])
 @pytest.mark.parametrize("mnk", [
-    (4, 4, 4), (33, 36, 128), (36, 32, 132), (100, 68, 260),      # 32 x 32 tiles: edges, and a slot more and less than full
+    (4, 4, 4), (33, 36, 128), (36, 32, 132), (100, 68, 260),      # 16 x 16 tiles: edges, and a slot more and less than full
+    (260, 516, 260), (388, 420, 124),                             # 32 x 32 tiles
     (1036, 1028, 60), (964, 1092, 68),                            # 64 x 64 tiles
     (4100, 2052, 36), (2052, 4036, 28),                           # 128 x 128 tiles
     (33, 65, 17), (130, 7, 3), (66, 130, 34)])                    # no whole 16-byte pieces: the general kernel
