@@ -2,9 +2,10 @@
 //
 // bf16 path: C = alpha * op(A) op(B) on the 32x32x16 bf16 MFMA instruction, fp32 accumulation.
 //   One workgroup = 4 wavefronts (2 x 2), block tile BM x BN (256 x 256, 256 x 192, 128 x 128 or 64 x 64, chosen per
-//   product by how well the tiles fill the 256 compute units), contraction consumed in slices of 32 through a 4-slot LDS ring, or
-//   in slices of 64 through two slots where the contraction index is contiguous in memory, filled by asynchronous
-//   global -> LDS copies (no staging registers) that stay in flight while the previous slices are multiplied.
+//   product by how well the tiles fill the 256 compute units), contraction consumed in slices of 32 through a 4-slot LDS
+//   ring, or in slices of 64 through two slots (four for the small tiles) where the contraction index is contiguous in
+//   memory, filled by asynchronous global -> LDS copies (no staging registers) that stay in flight while the previous
+//   slices are multiplied.  The smallest outputs run on 32 x 32 tiles that the four waves share, each through its own ring.
 //   Outputs with too few tiles cut the contraction over several workgroups per tile (scratch memory, a second launch).
 //   An operand whose contraction index is contiguous in memory ("KC": A of NN/NT, B of NT) is kept in
 //   LDS as [row][k] and read as 16-byte vectors; an operand whose contraction index is the slow,
@@ -13,7 +14,7 @@
 //   transpose-read instruction (ds_read_b64_tr_b16), so no operand is ever transposed in HBM.
 //   Out-of-range lanes of a copy are redirected past the end of the buffer descriptor (they deliver zero),
 //   which handles ragged M, N and K without branches.
-// fp32 path: the 32x32x2 fp32 MFMA with the same kind of copies; a plain FMA tile kernel with generic strides for
+// fp32 path: the 32x32x2 (small outputs: 16x16x4) fp32 MFMA with the same kind of copies; a plain FMA tile kernel with generic strides for
 // operands that are not made of whole aligned 16-byte pieces.
 #include "kernels.h"
 #include "gfx950.h"
@@ -1221,22 +1222,26 @@ static hipError_t launch_bf16_causal_pair(const GemmParams& p0, int batch, hipSt
 //     128 x 128 on four 64-deep slots   0.0091   3.0   one workgroup per compute unit
 //     256 x 192                         0.0167   8.0   "
 //     256 x 256                         0.0197   9.7   "
+//     128 x 128 on four 32-deep slots   0.0112   2.05  one per compute unit, whole contractions only
 //     128 x 128 on two 64-deep slots    0.0126   1.5   two per compute unit: 0.0188 per round of 512
 //     64 x 64 on four 64-deep slots     0.0047   1.3   "                     0.0071
 //   but at least the time of reading both operands once at 4.9 TB/s plus 8.4;
 //   outputs of at most 256 tiles of 32 x 32 can run on gemm_bf16_small_kernel: 0.0018 K + 3.0;
 //   slices add 3.8 (the second launch) and 0.30 per MB of partial products, and must gain 12 %.
+// The ring of 32-deep slots starts a short contraction sooner and is ahead up to K = 450 or so: [1688, 1560] x 400 9.4 us,
+// 9.7 on the 64-deep ring; [376, 8840] x 320 8.8, 9.0; [1024, 4096] x 512 10.2, 10.0.  Two 64-deep slots need a second
+// workgroup to cover their latency (the same shapes 10.2, 9.3, 10.9), so they are left out up to one per compute unit.
 // Why so many: one tile per compute unit leaves most of the chip idle on the short micro-batches.  Measured (us) against
 // what these shapes ran on before: [256, 4096] x 22016 (NT) 207 -> 76 (16 x 16 large tiles), [256, 22016] x 4096 106 -> 75
 // (256 x 192 in two slices), [360, 4096] x 11008 99 -> 52 (96 tiles of 128 in five), [1024, 4096] x 22016 212 -> 169 (64
 // large tiles in four), [512, 1024] x 2752 23 -> 16 (64 x 64); unsplit where the tiles already fill the chip, e.g.
 // [1024, 4096] x 4096 43 us on 128 x 128 tiles against 54 for the best split.
-enum ProductTile { T128_DEEP, T256_NARROW, T256, T128_PAIR, T64, T32 };
+enum ProductTile { T128_DEEP, T256_NARROW, T256, T128_PAIR, T64, T128_SHALLOW, T32 };
 static bool one_round(int M, int N) { return (long)((M + 255) / 256) * ((N + 255) / 256) <= 256; }
 static SplitPlan product_plan(int M, int N, int K, bool allow_split) {
   struct Tile { int bm, bn, per_cu; double c1, c2, fixed; };
   static const Tile tiles[] = {{128, 128, 1, 0.0091, 0., 3.0}, {256, 192, 1, 0.0167, 0., 8.0}, {256, 256, 1, 0.0197, 0., 9.7},
-                               {128, 128, 2, 0.0126, 0.0188, 1.5}, {64, 64, 2, 0.0047, 0.0071, 1.3}};
+                               {128, 128, 2, 0.0126, 0.0188, 1.5}, {64, 64, 2, 0.0047, 0.0071, 1.3}, {128, 128, 1, 0.0112, 0., 2.05}};
   static const int slices[] = {1, 2, 3, 4, 5, 6, 8, 12, 16};
   const double memory = 2e-6 * ((double)N * K + (double)M * K) / 4.9 + 8.4;
   SplitPlan best{T64, 1, K, 0};
@@ -1245,13 +1250,14 @@ static SplitPlan product_plan(int M, int N, int K, bool allow_split) {
     best_time = 0.0018 * K + 3.0;
     best.tile = T32;
   }
-  for (int i = 0; i < 5; i++) {
+  for (int i = 0; i < 6; i++) {
     const Tile& t = tiles[i];
     if (t.bm == 256 && M < 192) continue;
     for (int sp : slices) {
-      if (sp > 1 && (!allow_split || K / sp < 256)) break;
+      if (sp > 1 && (!allow_split || K / sp < 256 || i == T128_SHALLOW)) break;
       const int slice = sp == 1 ? K : ((K + 63) / 64 + sp - 1) / sp * 64, split = sp == 1 ? 1 : (K + slice - 1) / slice;
       const long n = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * split;
+      if (i == T128_PAIR && n <= 256) continue;
       const double one = slice * t.c1 + t.fixed, two = slice * t.c2 + t.fixed;
       double time;
       if (t.per_cu == 1) time = (double)((n + 255) / 256) * one;
@@ -1320,6 +1326,7 @@ static hipError_t dispatch_product(const GemmParams& p, const SplitPlan& plan, v
     case T256: return launch_product<256, 256, BKC, 0>(p, plan, ws, s);
     case T128_PAIR: return launch_product<128, 128, BKC, 0>(p, plan, ws, s);
     case T64: return launch_product<64, 64, BKC, 4>(p, plan, ws, s);
+    case T128_SHALLOW: return launch_bf16<128, 128, true, BKC, bf16_t, 32>(p, 1, s);
     case T32: return launch_small<BKC>(p, s);
   }
   return hipErrorInvalidValue;
@@ -1543,13 +1550,13 @@ static hipError_t launch_f32_small(int layout, const GemmParams& p0, int batch, 
   return hipGetLastError();
 }
 
-// Tile of an fp32 product: 16 x 16 up to two of them per compute unit, else the one with the shortest time by rounds of 256 compute units, (rounds) x (tile area) / (rate).
-// The rates (TFLOP/s with every compute unit busy) are measured: 128 x 128 tiles 132-140, 64 x 64 tiles 110-125, 32 x 32
-// tiles with the contraction split over the waves 91-110 (they move 4 times the operand bytes of the first).  Times in us,
-// 128 / 64 / 32: [512, 1024] x 5504 349 / 105 / 63 (too few tiles for anything but the smallest), [512, 5504] x 1024
-// 79 / 62 / 75, [2048, 2048] x 2048 149 / 144 / 175, [4096, 4096] x 4096 998 / 1069 / 1245.
-// Rings of three or four shallower slots measured within 5 % of these (128: three slots slower, 1049; 64: four 32-deep
-// slots 1058; 32: four 64-deep slots 1260).
+// Tile of an fp32 product: 16 x 16 up to two of them per compute unit, else the one with the shortest time by rounds of
+// 256 compute units, (rounds) x (tile area) / (rate).  The rates (TFLOP/s with every compute unit busy) are measured:
+// 128 x 128 tiles 132-140, 64 x 64 tiles 110-125, 32 x 32 tiles with the contraction split over the waves 91-110 (they move
+// 4 times the operand bytes of the first).  Times in us, 128 / 64 / 32: [512, 1024] x 5504 349 / 105 / 63 (too few tiles for
+// anything but the smallest), [512, 5504] x 1024 79 / 62 / 75, [2048, 2048] x 2048 149 / 144 / 175, [4096, 4096] x 4096
+// 998 / 1069 / 1245.  Rings of three or four shallower slots measured within 5 % of these (128: three slots slower, 1049;
+// 64: four 32-deep slots 1058; 32: four 64-deep slots 1260).
 static hipError_t dispatch_f32(int layout, const GemmParams& p, int batch, hipStream_t s) {
   auto cost = [&](int t, double rate) {
     const long tiles = (long)((p.M + t - 1) / t) * ((p.N + t - 1) / t) * batch;

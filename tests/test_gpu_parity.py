@@ -138,6 +138,7 @@ def test_gemm_with_split_contraction(layout, mnk):
     (8, 8, 8), (64, 72, 264), (136, 1032, 2760), (256, 1024, 1000),       # 32 x 32 tiles
     (264, 1032, 1000), (264, 1032, 5512),                         # 64 x 64 tiles; the last in slices
     (1000, 2056, 3080), (1032, 1032, 4104),                       # 128 x 128 tiles, one per compute unit; in slices
+    (1688, 1560, 400), (2040, 2040, 8),                           # the same with a short contraction
     (2000, 3464, 1160), (360, 4088, 5512),                        # 128 x 128 tiles, two per compute unit; few, long
     (264, 22008, 1032), (264, 11016, 4104),                       # 256 x 192 tiles; in slices
     (1032, 4088, 8200), (4088, 4088, 1096)])                      # 256 x 256 tiles in slices (ragged last slice); unsliced
