@@ -1231,6 +1231,9 @@ static hipError_t launch_bf16_causal_pair(const GemmParams& p0, int batch, hipSt
 // The ring of 32-deep slots starts a short contraction sooner and is ahead up to K = 450 or so: [1688, 1560] x 400 9.4 us,
 // 9.7 on the 64-deep ring; [376, 8840] x 320 8.8, 9.0; [1024, 4096] x 512 10.2, 10.0.  Two 64-deep slots need a second
 // workgroup to cover their latency (the same shapes 10.2, 9.3, 10.9), so they are left out up to one per compute unit.
+// A K that is no multiple of 64 puts every 128-byte piece of a tile row across two cache lines.  The 64 x 64 tiles fetch the
+// most per product and pay for it, 8 % on a CU of their own and 38 % beside a second one: [296, 4488] x 3920 40 us, where two
+// slices of 128 x 128 tiles take 28; [168, 5280] x 7592 44 us, three slices 35; [360, 3072] x 4096 (whole lines) 25.
 // Why so many: one tile per compute unit leaves most of the chip idle on the short micro-batches.  Measured (us) against
 // what these shapes ran on before: [256, 4096] x 22016 (NT) 207 -> 76 (16 x 16 large tiles), [256, 22016] x 4096 106 -> 75
 // (256 x 192 in two slices), [360, 4096] x 11008 99 -> 52 (96 tiles of 128 in five), [1024, 4096] x 22016 212 -> 169 (64
@@ -1246,6 +1249,7 @@ static SplitPlan product_plan(int M, int N, int K, bool allow_split) {
   const double memory = 2e-6 * ((double)N * K + (double)M * K) / 4.9 + 8.4;
   SplitPlan best{T64, 1, K, 0};
   double best_time = 1e30;
+  const bool half_lines = K % 64 != 0;
   if ((long)((M + 31) / 32) * ((N + 31) / 32) <= 256) {
     best_time = 0.0018 * K + 3.0;
     best.tile = T32;
@@ -1258,7 +1262,8 @@ static SplitPlan product_plan(int M, int N, int K, bool allow_split) {
       const int slice = sp == 1 ? K : ((K + 63) / 64 + sp - 1) / sp * 64, split = sp == 1 ? 1 : (K + slice - 1) / slice;
       const long n = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * split;
       if (i == T128_PAIR && n <= 256) continue;
-      const double one = slice * t.c1 + t.fixed, two = slice * t.c2 + t.fixed;
+      const double lines1 = half_lines && i == T64 ? 1.08 : 1., lines2 = half_lines && i == T64 ? 1.38 : 1.;
+      const double one = slice * t.c1 * lines1 + t.fixed, two = slice * t.c2 * lines2 + t.fixed;
       double time;
       if (t.per_cu == 1) time = (double)((n + 255) / 256) * one;
       else time = (double)(n / 512) * two + (n % 512 == 0 ? 0. : n % 512 <= 256 ? one : two);
