@@ -35,7 +35,7 @@ struct GemmParams {
   long sam, sak, sbk, sbn;
   // fused softmax backward (see GemmArgs)
   const float* delta; long ldd, sDo, sDi;
-  int delta_causal;
+  int delta_causal, causal_fill;
   long a_panel;                 // see GemmArgs
   // contraction cut into `split` slices of split_k indices, one workgroup per (tile, slice) (see SplitPlan); slice i leaves
   // its partial product at C + i * sCo
@@ -82,6 +82,15 @@ __device__ __forceinline__ void tile_of_block_split(int pid, int tiles_m, int ti
   const int r = id - grp * width;
   tm = first + r % gsz;
   tn = r / gsz;
+}
+
+// SKIP_UPPER: is the tile at (m0, n0) left out?  Tiles wholly above the diagonal are, except for those within the range that
+// has to hold zeros (see GemmArgs::causal_fill); `empty` tells of one of those that there is nothing to contract.
+template <int BM>
+__device__ __forceinline__ bool tile_skipped(const GemmParams& p, int m0, int n0, bool& empty) {
+  empty = n0 >= m0 + BM;
+  const int fill = p.causal_fill > BM ? p.causal_fill : BM;
+  return n0 >= (m0 & -fill) + fill;
 }
 
 // LDS image of one operand tile (R rows/columns of the output x BK of the contraction), laid out so that
@@ -195,7 +204,9 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, in
 
   int k_lo = 0, k_hi = p.K;
   if (p.causal == CAUSAL_SKIP_UPPER) {
-    if (n0 > m0 + BM - 1) return;
+    bool empty;
+    if (tile_skipped<BM>(p, m0, n0, empty)) return;
+    if (empty) k_hi = 0;
   } else if (p.causal == CAUSAL_K_END) {
     k_hi = (m0 + BM < p.K) ? m0 + BM : p.K;
   } else if (p.causal == CAUSAL_K_BEGIN) {
@@ -516,7 +527,7 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmParams p) {
       // otherwise rotating the map by the batch index at least keeps one XCD from getting all the long tiles
       id = ((int)blockIdx.x + 3 * z) % nt;
     }
-    if (p.causal == CAUSAL_SKIP_UPPER && p.tiles_m == p.tiles_n) {
+    if (p.causal == CAUSAL_SKIP_UPPER && p.tiles_m == p.tiles_n && p.causal_fill <= BM) {
       // only the lower-triangular tiles are launched: id = tm (tm + 1) / 2 + tn
       tm_i = (int)((__builtin_sqrtf(8.f * (float)id + 1.f) - 1.f) * 0.5f);
       while (tm_i * (tm_i + 1) / 2 > id) tm_i--;
@@ -841,7 +852,9 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(GemmParams p) {
   const int m0 = tm_i * BM, n0 = tn_i * BN;
   int k_lo = 0, k_hi = p.K;
   if (p.causal == CAUSAL_SKIP_UPPER) {
-    if (n0 > m0 + BM - 1) return;
+    bool empty;
+    if (tile_skipped<BM>(p, m0, n0, empty)) return;
+    if (empty) k_hi = 0;
   } else if (p.causal == CAUSAL_K_END) {
     k_hi = (m0 + BM < p.K) ? m0 + BM : p.K;
   } else if (p.causal == CAUSAL_K_BEGIN) {
@@ -1015,7 +1028,9 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmParams p) {
   const int m0 = tm_i * 16, n0 = tn_i * 16;
   int k_lo = 0, k_hi = p.K;
   if (p.causal == CAUSAL_SKIP_UPPER) {
-    if (n0 > m0 + 15) return;                 // (uniform over the workgroup)
+    bool empty;                               // (uniform over the workgroup)
+    if (tile_skipped<16>(p, m0, n0, empty)) return;
+    if (empty) k_hi = 0;
   } else if (p.causal == CAUSAL_K_END) {
     k_hi = (m0 + 16 < p.K) ? m0 + 16 : p.K;
   } else if (p.causal == CAUSAL_K_BEGIN) {
@@ -1111,7 +1126,9 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmParams p) {
   const int m0 = tm_i * TB, n0 = tn_i * TB;
   int k_lo = 0, k_hi = p.K;
   if (p.causal == CAUSAL_SKIP_UPPER) {
-    if (n0 > m0 + TB - 1) return;
+    bool empty;
+    if (tile_skipped<TB>(p, m0, n0, empty)) return;
+    if (empty) k_hi = 0;
   } else if (p.causal == CAUSAL_K_END) {
     k_hi = (m0 + TB < p.K) ? m0 + TB : p.K;
   } else if (p.causal == CAUSAL_K_BEGIN) {
@@ -1187,7 +1204,7 @@ static hipError_t launch_bf16_acc(const GemmParams& p0, int batch, hipStream_t s
   static AttrOnce once;
   if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
   unsigned nt = (unsigned)(p.tiles_m * p.tiles_n);
-  if (batch > 1 && p.causal == CAUSAL_SKIP_UPPER && p.tiles_m == p.tiles_n)
+  if (batch > 1 && p.causal == CAUSAL_SKIP_UPPER && p.tiles_m == p.tiles_n && p.causal_fill <= BM)
     nt = (unsigned)(p.tiles_m * (p.tiles_m + 1) / 2);       // lower-triangular tiles only
   dim3 grid(nt, 1, (unsigned)batch);
   hipLaunchKernelGGL(kern, grid, dim3(256), smem, s, p);
@@ -1562,16 +1579,34 @@ static hipError_t launch_f32_small(int layout, const GemmParams& p0, int batch, 
 // anything but the smallest), [512, 5504] x 1024 79 / 62 / 75, [2048, 2048] x 2048 149 / 144 / 175, [4096, 4096] x 4096
 // 998 / 1069 / 1245.  Rings of three or four shallower slots measured within 5 % of these (128: three slots slower, 1049;
 // 64: four 32-deep slots 1058; 32: four 64-deep slots 1260).
-static hipError_t dispatch_f32(int layout, const GemmParams& p, int batch, hipStream_t s) {
+static int f32_tile(int M, int N, int batch) {
   auto cost = [&](int t, double rate) {
-    const long tiles = (long)((p.M + t - 1) / t) * ((p.N + t - 1) / t) * batch;
+    const long tiles = (long)((M + t - 1) / t) * ((N + t - 1) / t) * batch;
     return (double)((tiles + 255) / 256) * t * t / rate;
   };
-  if ((long)((p.M + 15) / 16) * ((p.N + 15) / 16) * batch <= 512) return launch_f32_small(layout, p, batch, s);
+  if ((long)((M + 15) / 16) * ((N + 15) / 16) * batch <= 512) return 16;
   const double c128 = cost(128, 132.), c64 = cost(64, 115.), c32 = cost(32, 100.);
-  if (c32 <= c64 && c32 <= c128) return launch_f32_layout<32, 32, 4, 128, 2>(layout, p, batch, s);
-  if (c64 <= c128) return launch_f32_layout<64, 64, 1, 64, 2>(layout, p, batch, s);
+  return c32 <= c64 && c32 <= c128 ? 32 : c64 <= c128 ? 64 : 128;
+}
+static hipError_t dispatch_f32(int layout, const GemmParams& p, int batch, hipStream_t s) {
+  switch (f32_tile(p.M, p.N, batch)) {
+    case 16: return launch_f32_small(layout, p, batch, s);
+    case 32: return launch_f32_layout<32, 32, 4, 128, 2>(layout, p, batch, s);
+    case 64: return launch_f32_layout<64, 64, 1, 64, 2>(layout, p, batch, s);
+  }
   return launch_f32_layout<128, 128, 1, 32, 2>(layout, p, batch, s);
+}
+
+// bf16: large tiles when the output is big enough to fill 256 compute units with them.  Short contractions (the per-head
+// q k^T and do v^T, K = head_dim) are all prologue and epilogue: small tiles let two or three workgroups share a compute
+// unit and overlap them.
+static bool large_tiles(const GemmArgs& g) {
+  return g.M >= 256 && g.N >= 256 && (long)((g.M + 255) / 256) * ((g.N + 255) / 256) * g.batch >= 192 && g.K > 256;
+}
+
+int gemm_row_tile(int dtype, const GemmArgs& g) {
+  if (dtype == 0) return f32_mfma_ok(g) ? f32_tile(g.M, g.N, g.batch) : 64;
+  return !g.a_panel && large_tiles(g) ? 256 : 128;
 }
 
 hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
@@ -1584,6 +1619,7 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   p.batch_inner = g.batch_inner > 0 ? g.batch_inner : 1;
   p.alpha = g.alpha; p.accumulate = g.accumulate; p.causal = g.causal;
   p.delta = g.delta; p.ldd = g.ldd; p.sDo = g.sDo; p.sDi = g.sDi; p.delta_causal = g.delta_causal;
+  p.causal_fill = g.delta && g.delta_causal ? g.causal_fill : 0;
   if (dtype == 0) {
     if (g.a_panel) return hipErrorInvalidValue;
     switch (g.layout) {
@@ -1609,12 +1645,9 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
     return g.out_f32 ? launch_bf16<kPanel, 128, false, false, float, 32>(p, g.batch, s)
                      : launch_bf16<kPanel, 128, false, false, bf16_t, 32>(p, g.batch, s);
   }
-  // bf16: large tiles when the output is big enough to fill 256 compute units with them
   const int tiles_m = (g.M + 255) / 256, tiles_n = (g.N + 255) / 256;
   const long tiles_big = (long)tiles_m * tiles_n * g.batch;
-  // short contractions (the per-head q k^T and do v^T, K = head_dim) are all prologue and epilogue: small tiles let
-  // two or three workgroups share a compute unit and overlap them
-  const bool big = g.M >= 256 && g.N >= 256 && tiles_big >= 192 && g.K > 256;
+  const bool big = large_tiles(g);
   if (!g.out_f32 && g.batch == 1 && g.causal == CAUSAL_NONE && !g.delta && g.layout != TN && one_round(g.M, g.N)) {
     SplitPlan plan = product_plan(g.M, g.N, g.K, g.ws && reinterpret_cast<uintptr_t>(g.ws) % 256 == 0);
     if (plan.bytes > g.ws_bytes) plan = product_plan(g.M, g.N, g.K, false);

@@ -8,9 +8,11 @@ namespace tbp {
 
 enum Layout { NN = 0, NT = 1, TN = 2 };
 
-// How a product that involves the causal probability matrix restricts its work.  Rows of the
-// probability (and score-gradient) matrices are zero-filled from the diagonal to the next multiple
-// of kCausalPad columns, which is what lets whole K-tiles be skipped safely.
+// How a product that involves the causal probability matrix restricts its work.  A K_END or K_BEGIN product contracts over
+// whole row tiles of its own (16 to 256 rows), so it reads its first operand beyond the diagonal, up to the end of the row
+// tile: there that operand has to hold zeros.  The softmax zero-fills the probabilities P from the diagonal to the next
+// multiple of kCausalPad columns, as far as any tile reads.  The score gradients dS come out of a SKIP_UPPER product, which
+// leaves out tiles above the diagonal by a tile size of its own and writes zeros as far as GemmArgs::causal_fill says.
 enum Causal {
   CAUSAL_NONE = 0,
   CAUSAL_SKIP_UPPER = 1,  // output [S,S] tiles strictly above the diagonal are not computed (q k^T, do v^T)
@@ -39,6 +41,10 @@ struct GemmArgs {
   // delta[(zo * sDo + zi * sDi) + row * ldd] = rowsum(dP * P) = sum over the head's columns of do * o.
   const float* delta; long ldd, sDo, sDi;
   int delta_causal;
+  // With SKIP_UPPER and delta_causal: rows are written (zeros above the diagonal) up to the next multiple of causal_fill
+  // columns, a power of two: the largest gemm_row_tile of the products that read dS.  Tiles that lie wholly above the
+  // diagonal but inside that range store their zeros without contracting anything.
+  int causal_fill;
   // Optional scratch for products whose output has too few tiles to fill the chip (see gemm_split_plan): device memory of
   // at least gemm_split_plan(...).bytes bytes, 256-byte aligned; nothing in it has to be initialised.
   void* ws; size_t ws_bytes;
@@ -69,6 +75,8 @@ inline GemmArgs gemm_args(int layout, int M, int N, int K, const void* A, long l
 
 // dtype: 0 = fp32 storage, 1 = bf16 storage (matches tbp_dtype).
 hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s);
+// Rows of the output tiles that gemm() runs a product with a causal contraction (K_END, K_BEGIN) on.
+int gemm_row_tile(int dtype, const GemmArgs& g);
 
 // One bf16 weight-gradient product C (=, +=) A^T B (TN layout, fp32 C, alpha = 1).
 // Same operand rules as the bf16 TN product of gemm(): 16-byte aligned pointers, extents and leading dimensions

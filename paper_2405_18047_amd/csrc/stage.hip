@@ -373,6 +373,19 @@ tbp_status run_p1(tbp_stage* st, int mb, int slot, const void* dy, void* dx, hip
       // rowsum(dP * P) per (token, head) = rowsum(da * a): no S x S tensor needed for it
       float* delta = (float*)st->ws(st->y.ws_delta);
       TBP_HIP(tbp::head_rowdot(dt, T, c.H, c.dh, da, st->wslab(l, W_A, mb), delta, s));
+      // dq = dS k / sqrt(dh) and dk = dS^T q / sqrt(dh), described first: their tiles say how far dS has to be written
+      GemmArgs gq = head_gemm(c, tbp::NN, c.S, c.dh, c.S);
+      gq.alpha = scale;
+      gq.A = dP; gq.lda = c.S; gq.sAo = bs; gq.sAi = hs;
+      gq.B = (const char*)qkv + (size_t)d * c.e; gq.ldb = 3 * d; gq.sBo = tok3; gq.sBi = c.dh;
+      gq.C = dqkv; gq.ldc = 3 * d; gq.sCo = tok3; gq.sCi = c.dh;
+      gq.causal = c.causal ? tbp::CAUSAL_K_END : tbp::CAUSAL_NONE;
+      GemmArgs gk = head_gemm(c, tbp::TN, c.S, c.dh, c.S);
+      gk.alpha = scale;
+      gk.A = dP; gk.lda = c.S; gk.sAo = bs; gk.sAi = hs;
+      gk.B = qkv; gk.ldb = 3 * d; gk.sBo = tok3; gk.sBi = c.dh;
+      gk.C = (char*)dqkv + (size_t)d * c.e; gk.ldc = 3 * d; gk.sCo = tok3; gk.sCi = c.dh;
+      gk.causal = c.causal ? tbp::CAUSAL_K_BEGIN : tbp::CAUSAL_NONE;
       {  // dS = P * (da v^T - delta): the softmax backward is the epilogue of the dP product (dP is never stored)
         GemmArgs g = head_gemm(c, tbp::NT, c.S, c.S, c.dh);
         g.A = da; g.lda = d; g.sAo = (long)c.S * d; g.sAi = c.dh;
@@ -381,6 +394,7 @@ tbp_status run_p1(tbp_stage* st, int mb, int slot, const void* dy, void* dx, hip
         g.R = P;
         g.delta = delta; g.ldd = c.H; g.sDo = (long)c.S * c.H; g.sDi = 1; g.delta_causal = c.causal;
         g.causal = c.causal ? tbp::CAUSAL_SKIP_UPPER : tbp::CAUSAL_NONE;
+        g.causal_fill = std::max(tbp::gemm_row_tile(dt, gq), tbp::gemm_row_tile(dt, gk));
         TBP_HIP(tbp::gemm(dt, g, s));
       }
       {  // dv = P^T da
@@ -391,24 +405,8 @@ tbp_status run_p1(tbp_stage* st, int mb, int slot, const void* dy, void* dx, hip
         g.causal = c.causal ? tbp::CAUSAL_K_BEGIN : tbp::CAUSAL_NONE;
         TBP_HIP(tbp::gemm(dt, g, s));
       }
-      {  // dq = dS k / sqrt(dh)
-        GemmArgs g = head_gemm(c, tbp::NN, c.S, c.dh, c.S);
-        g.alpha = scale;
-        g.A = dP; g.lda = c.S; g.sAo = bs; g.sAi = hs;
-        g.B = (const char*)qkv + (size_t)d * c.e; g.ldb = 3 * d; g.sBo = tok3; g.sBi = c.dh;
-        g.C = dqkv; g.ldc = 3 * d; g.sCo = tok3; g.sCi = c.dh;
-        g.causal = c.causal ? tbp::CAUSAL_K_END : tbp::CAUSAL_NONE;
-        TBP_HIP(tbp::gemm(dt, g, s));
-      }
-      {  // dk = dS^T q / sqrt(dh)
-        GemmArgs g = head_gemm(c, tbp::TN, c.S, c.dh, c.S);
-        g.alpha = scale;
-        g.A = dP; g.lda = c.S; g.sAo = bs; g.sAi = hs;
-        g.B = qkv; g.ldb = 3 * d; g.sBo = tok3; g.sBi = c.dh;
-        g.C = (char*)dqkv + (size_t)d * c.e; g.ldc = 3 * d; g.sCo = tok3; g.sCi = c.dh;
-        g.causal = c.causal ? tbp::CAUSAL_K_BEGIN : tbp::CAUSAL_NONE;
-        TBP_HIP(tbp::gemm(dt, g, s));
-      }
+      TBP_HIP(tbp::gemm(dt, gq, s));
+      TBP_HIP(tbp::gemm(dt, gk, s));
     }
     TBP_HIP(tbp::rope(dt, T, c.S, 2 * c.H, c.dh, 3 * d, (const float2*)st->ws(st->y.ws_rope), 1, dqkv, s));
     // dh1 = [dq, dk, dv] Wqkv^T

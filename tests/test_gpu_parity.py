@@ -648,3 +648,37 @@ def test_fused_attention_backward_on_many_workgroups(dh, causal):
     got = to_np(got)
     for name, ref, blk in (("dq", dq, got[:, :d]), ("dk", dk, got[:, d:2 * d]), ("dv", dv, got[:, 2 * d:])):
         assert max_rel(blk, ref) < 1.5e-2, name
+
+
+# (seq, head_dim, heads, micro_batch, dtype): the tiles of the score-gradient product and of the products that read it
+SCORE_TILES = [
+    (64, 128, 2, 16, "f32"),      # fp32: 16 x 16 read by 32 x 32
+    (136, 128, 3, 13, "f32"),     # 32 by 64, ragged
+    (520, 128, 2, 24, "f32"),     # 32 by 128, ragged
+    (560, 128, 2, 24, "f32"),     # 64 by 128, ragged
+    (128, 64, 4, 16, "f32"),      # 64 by 32
+    (256, 64, 4, 16, "f32"),      # 128 by 64
+    (1000, 64, 4, 3, "f32"),      # 128 by 32, ragged
+    (264, 256, 2, 48, "bf16"),    # bf16: 128 x 128 read by 256 x 256, ragged
+    (520, 256, 2, 32, "bf16"),    # the same with an odd number of 128-row tiles
+]
+
+
+@pytest.mark.parametrize("case", SCORE_TILES, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("causal", [True, False])
+def test_materialised_attention_reads_nothing_unwritten(case, causal):
+    """Materialised attention whose per-head products run on different tiles: the causal dq and dk products contract over
+    whole row tiles and so read score gradients above the diagonal, which must be there (zeros) whatever the arena held
+    before.  The arena is filled with NaN patterns first; every tensor against the oracle."""
+    seq, dh, heads, batch, dtype = case
+    shape = si.StageShape("score_tiles", 1, heads * dh, heads, dh, 64, seq, batch, 1, dtype, 49, causal=causal)
+    _say(f"materialised attention {case} causal={causal}")
+    params, xs, dys = _stage_inputs(shape)
+    outs, dxs, grads = run_oracle(shape, params, xs, dys)
+    st = make_gpu_stage(shape, params, attention=tbp.TBP_ATTN_MATERIALISED)
+    st.arena.fill_(0xFF)
+    g_out = [st.forward(0, to_dev(xs[0], dtype))]
+    g_dx = [st.backward_p1(0, to_dev(dys[0], dtype))]
+    st.backward_p2([0], tbp.TBP_P2_LOOP, accumulate=False)
+    compare_stage(shape, g_out, g_dx, st.grads, outs, dxs, grads, stage_tolerance(dtype), f"score tiles {case}")
+    st.close()
