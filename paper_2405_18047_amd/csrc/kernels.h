@@ -164,6 +164,15 @@ struct AttrOnce {
   }
 };
 
+// Index behind the run of consecutive micro-batches that starts at mbs[i] and that backward-p2 contracts over in one go.
+// The rows of a run are one contraction length, an int in the kernels with room for a slot beyond: longer runs are cut.
+constexpr long kMaxRunRows = 1L << 30;
+inline int run_end(const int* mbs, int n, int i, int tokens) {
+  int j = i + 1;
+  while (j < n && mbs[j] == mbs[j - 1] + 1 && (long)(j + 1 - i) * tokens <= kMaxRunRows) j++;
+  return j;
+}
+
 // Limits enforced by the host before any launch.
 inline int max_d_model(int dtype) { return dtype == 1 ? 8192 : 4096; }
 constexpr int kMaxSeq = 4096;

@@ -427,8 +427,7 @@ tbp_status run_p2(tbp_stage* st, const int* mbs, int n, int accumulate, hipStrea
   // of a LOOP set add up in fp32 in the accumulators instead of reading and writing dW once per micro-batch (a 7B layer's
   // dW is 0.8 GB: four micro-batches of 256 tokens took 4 x 589 us).
   for (int i = 0; i < n;) {
-    int j = i + 1;
-    while (j < n && mbs[j] == mbs[j - 1] + 1) j++;
+    const int j = tbp::run_end(mbs, n, i, c.T);
     const int mb0 = mbs[i], K = (j - i) * c.T, acc = (accumulate || i > 0) ? 1 : 0;
     st->grouped.clear();                      // (no host allocation here: the capacity is reserved at creation)
     for (int l = 0; l < c.L; l++)
@@ -459,8 +458,7 @@ tbp_status run_p2(tbp_stage* st, const int* mbs, int n, int accumulate, hipStrea
     float* part = (float*)st->ws(st->y.ws_norm_partials_p2);
     for (int l = 0; l < c.L; l++)
       for (int i = 0; i < n;) {
-        int j = i + 1;
-        while (j < n && mbs[j] == mbs[j - 1] + 1) j++;
+        const int j = tbp::run_end(mbs, n, i, c.T);
         const int acc = (accumulate || i > 0) ? 1 : 0, rows = (j - i) * c.T;
         if (c.attn)
           TBP_HIP(tbp::rmsnorm_gain_p2(c.dtype, rows, c.d, c.eps, st->wslab(l, W_N1DY, mbs[i]), st->wslab(l, W_N1X, mbs[i]),
@@ -474,8 +472,7 @@ tbp_status run_p2(tbp_stage* st, const int* mbs, int n, int accumulate, hipStrea
   // gain gradients: the partial rows that backward-p1 left, added up run by run of consecutive micro-batches (whose
   // partial rows are consecutive in the stash; a K-concatenated set is one run), all norms of the stage in one launch
   for (int i = 0; i < n;) {
-    int j = i + 1;
-    while (j < n && mbs[j] == mbs[j - 1] + 1) j++;
+    const int j = tbp::run_end(mbs, n, i, c.T);
     tbp::GainSums g{};
     const int acc = (accumulate || i > 0) ? 1 : 0, nrows = (j - i) * st->y.gain_rows;
     for (int l = 0; l < c.L; l++)

@@ -3,6 +3,7 @@
 import ctypes as C
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -196,3 +197,40 @@ def test_gemm_workspace_policy_and_checks():
     assert L.tbp_gemm_ws(1, tbp.NT, 1024, 4096, 32768, 1.0, fake, 32768, fake, 32768, fake, 4096, 0, 0, None,
                          C.c_void_p(0x3000010), need, None) == 1
     assert "aligned" in L.tbp_last_error().decode()
+
+
+def test_backward_p2_runs_fit_the_contraction_length(tmp_path):
+    """backward-p2 contracts over the rows of a run of consecutive micro-batches in one product, whose length is an int:
+    sets of any accepted size are cut into runs that fit (128 micro-batches of 2^24 tokens are 2^31 rows)."""
+    src = tmp_path / "runs.cpp"
+    src.write_text("""
+#include <cstdio>
+#include <vector>
+#include "kernels.h"
+int main() {
+  for (int tokens : {1, 2048, 1 << 20, 1 << 24}) {
+    for (int n : {1, 4, 127, 128, 300}) {
+      std::vector<int> mbs(n);
+      for (int k = 0; k < n; k++) mbs[k] = k + (k >= n / 2 ? 1 : 0);          // two runs
+      long rows = 0, longest = 0;
+      int runs = 0;
+      for (int i = 0; i < n;) {
+        const int j = tbp::run_end(mbs.data(), n, i, tokens);
+        for (int k = i + 1; k < j; k++) if (mbs[k] != mbs[k - 1] + 1) return 1;
+        if ((long)(j - i) * tokens > longest) longest = (long)(j - i) * tokens;
+        rows += (long)(j - i) * tokens; runs++; i = j;
+      }
+      if (rows != (long)n * tokens) return 2;
+      std::printf("%d %d %d %ld\\n", tokens, n, runs, longest);
+    }
+  }
+}
+""")
+    exe = tmp_path / "runs"
+    subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I",
+                    os.path.join(ROOT, "paper_2405_18047_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    got = subprocess.run([str(exe)], check=True, capture_output=True, text=True).stdout.split("\n")
+    got = {tuple(map(int, l.split()[:2])): tuple(map(int, l.split()[2:])) for l in got if l}
+    assert all(longest <= 2**31 - 64 for _, longest in got.values())
+    assert got[2048, 300] == (2, 150 * 2048) and got[2048, 1] == (1, 2048)          # ordinary sets: the runs themselves
+    assert got[1 << 24, 128] == (2, 64 << 24) and got[1 << 24, 300][0] == 6
