@@ -737,16 +737,26 @@ __global__ __launch_bounds__(256) void head_rowdot_kernel(int n_heads, int head_
 // ------------------------------------------------------------------------------------------ host
 static inline int chunks_per_thread(int d, int n) { return (d / n + 255) / 256; }
 
+// (a launch has fewer than 2^32 threads, and one that asks for more is not refused but cut: more rows take several launches)
 template <typename T, bool FIRST>
-static hipError_t rmsnorm_fwd_t(int rows, int d, float eps, const void* x, const void* g, void* y, const FirstNorm& first, hipStream_t s) {
+static hipError_t rmsnorm_fwd_t(int rows, int d, float eps, const void* x, const void* g, void* y, FirstNorm first, hipStream_t s) {
+  constexpr int kLaunchRows = 1 << 23;
   const int c = chunks_per_thread(d, Vec<T>::N);
-  auto X = (const T*)x; auto G = (const T*)g; auto Y = (T*)y;
-  const dim3 grid(rows + (FIRST && first.table ? (first.seq * first.half + 255) / 256 : 0)), block(256);
-  if (c <= 1) hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, 1, FIRST>), grid, block, 0, s, rows, d, eps, X, G, Y, first);
-  else if (c <= 2) hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, 2, FIRST>), grid, block, 0, s, rows, d, eps, X, G, Y, first);
-  else if (c <= 4) hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, 4, FIRST>), grid, block, 0, s, rows, d, eps, X, G, Y, first);
-  else return hipErrorInvalidValue;
-  return hipGetLastError();
+  auto G = (const T*)g;
+  const dim3 block(256);
+  for (int row0 = 0; row0 < rows; row0 += kLaunchRows) {
+    const int n = rows - row0 < kLaunchRows ? rows - row0 : kLaunchRows;
+    auto X = (const T*)x + (long)row0 * d; auto Y = (T*)y + (long)row0 * d;
+    const dim3 grid(n + (FIRST && first.table ? (first.seq * first.half + 255) / 256 : 0));
+    if (c <= 1) hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, 1, FIRST>), grid, block, 0, s, n, d, eps, X, G, Y, first);
+    else if (c <= 2) hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, 2, FIRST>), grid, block, 0, s, n, d, eps, X, G, Y, first);
+    else if (c <= 4) hipLaunchKernelGGL((rmsnorm_fwd_kernel<T, 4, FIRST>), grid, block, 0, s, n, d, eps, X, G, Y, first);
+    else return hipErrorInvalidValue;
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+    first.table = nullptr;
+    if (FIRST) first.x_copy = static_cast<T*>(first.x_copy) + (long)n * d;
+  }
+  return hipSuccess;
 }
 hipError_t rmsnorm_fwd(int dtype, int rows, int d, float eps, const void* x, const void* g, void* y, hipStream_t s) {
   if (rows <= 0) return hipSuccess;

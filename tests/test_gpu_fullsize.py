@@ -295,3 +295,25 @@ def test_eight_layer_end_to_end_within_stated_tolerance(name, n_mb):
     fp64) end to end."""
     err = _depth8_errors(name, n_mb)
     assert max(err.values()) <= stage_tolerance("bf16"), {k: v for k, v in err.items() if v > stage_tolerance("bf16")}
+
+
+def test_forward_at_the_most_tokens():
+    """Close to 2^24 tokens per micro-batch, the limit: a workgroup per row, and some more that build the rotation table, are
+    more than the 2^32 threads of one launch, and such a launch silently does a part of its work.  The
+    first and the last sequence against a stage that runs them by themselves (other tiles, so other orders of the fp32
+    sums: two bf16 roundings of the output apart at most)."""
+    seq, batch, d, f = 4088, 4104, 64, 8
+    shape = si.StageShape("most_tokens", 1, d, 1, 64, f, seq, batch, 1, "bf16", 50)
+    print(f"forward at the most tokens {shape}", flush=True)
+    params = _params(shape)
+    gen = torch.Generator(device="cuda:0").manual_seed(50)
+    x = torch.randn((shape.tokens, d), generator=gen, device="cuda:0", dtype=torch.bfloat16)
+    st = make_gpu_stage(shape, params, attention=tbp.TBP_ATTN_FUSED_RECOMPUTE)
+    out = st.forward(0, x)
+    torch.cuda.synchronize()
+    for rows in (slice(0, seq), slice(shape.tokens - seq, shape.tokens)):
+        one = make_gpu_stage(shape.replace(micro_batch=1), params, attention=tbp.TBP_ATTN_FUSED_RECOMPUTE)
+        want = one.forward(0, x[rows].contiguous())
+        assert max_rel(to_np(out[rows]), to_np(want)) < 2 * 2.0 ** -8
+        one.close()
+    st.close()
