@@ -1443,15 +1443,22 @@ static hipError_t launch_tn_grouped(const GroupedProduct* prods, int n, int accu
   return hipSuccess;
 }
 
-// Modelled time (us) of n weight-gradient tiles over K contraction indices, fitted to products of [256, 256] to
-// [4096, 22016] with K 128-4096: the part that grows with K, and the part that writes (accumulating: reads and writes)
-// the fp32 output, which a workgroup does not overlap with its own products.
+// Modelled time (us) of n weight-gradient tiles over K contraction indices in one launch.  A round of workgroups costs (per
+// index) K + (fixed part, which reads and writes the fp32 output; more of it where the whole output is larger than the
+// on-package cache).  The small tiles run two workgroups per compute unit: `one` up to 256 of them, `two` for 512, and already
+// 0.6 of the difference once some compute units have two.  The constants were fitted to make the right choice: over 459 stages
+// (all weight gradients, K 64-6500) and 578 single products, each measured on all three tile sizes, overwriting and
+// accumulating, the tile that the model picks costs 0.9 % more than the fastest on average (more than 10 % in one case of 50).
 static double dw_time(int tile, long n, int K, int acc) {
-  if (tile == 256) return (double)((n + 255) / 256) * (0.0232 * K + (acc ? 36. : 22.));
-  const double one = tile == 128 ? 0.0105 * K + (acc ? 8. : 4.5) : 0.0045 * K + (acc ? 4. : 2.);
-  const double two = tile == 128 ? 0.0152 * K + (acc ? 15.5 : 7.5) : 0.0073 * K + (acc ? 4. : 2.);
-  return (double)(n / 512) * two + (n % 512 == 0 ? 0. : n % 512 <= 256 ? one : two);
+  const bool large = n * tile * tile > (1L << 26);          // output above 256 MB
+  if (tile == 256) return (double)((n + 255) / 256) * (0.0217 * K + (acc ? (large ? 26.8 : 25.5) : (large ? 11.8 : 13.0)));
+  const double one = tile == 128 ? 0.0087 * K + (acc ? 6.9 : 6.3) : 0.0043 * K + (acc ? 5.1 : 4.6);
+  const double two = tile == 128 ? 0.0171 * K + (acc ? (large ? 12.5 : 9.0) : (large ? 6.2 : 5.1)) : 0.0084 * K + 4.3;
+  const long r = n % 512;
+  return (double)(n / 512) * two + (r == 0 ? 0. : r <= 256 ? one : one + (two - one) * (0.6 + 0.4 * (double)(r - 256) / 256));
 }
+constexpr double kLargeTileStart = 4.3;         // us that an arrangement on large tiles takes longer to get going
+constexpr double kEndLaunch = 9.7;              // us that a second launch for the last tiles costs beside their own time
 static long dw_tiles(int tile, int M, int N) { return (long)((M + tile - 1) / tile) * ((N + tile - 1) / tile); }
 
 // The first `tiles` tiles of a product, in whole tile columns (or rows, if there are more of those), and the rest.
@@ -1473,15 +1480,17 @@ static void cut_product(const GroupedProduct& q, long tiles, GroupedProduct& hea
   }
 }
 
-// Two arrangements, taken by modelled time:
-//   large tiles: every product's whole rounds of 256 tiles as a launch of its own (tiles that start in step share operand
-//     panels through the L2), and what does not fill a round of all products together in one grouped launch.  If that
-//     pool ends with a nearly empty round, its last tiles run as a launch of smaller tiles instead;
-//   one grouped launch of 128 x 128 or 64 x 64 tiles: short contractions, where writing the output is most of the work and
-//     a second workgroup on the compute unit covers it, and small products, which have too few large tiles.
-// Measured (us), all weight gradients of a layer: d 1152, f 3080, K 4000 (990 tiles of 128): 209 as four launches of
-// 128 x 128 tiles, 155 grouped; 7B, K 256, accumulating: 589 grouped on large tiles; 7B, K 4096: 272 pooled tiles
-// 193, with the last 16 on 128 x 128 tiles 116 + 39; d 256, f 688, K 384: 62 as eight launches, 8 grouped on 64 x 64.
+// Arrangements, taken by modelled time:
+//   one grouped launch of 64 x 64 or 128 x 128 tiles: short contractions, where writing the output is most of the work and a
+//     second workgroup on the compute unit covers it, and outputs that have too few larger tiles;
+//   large tiles, all products pooled in one grouped launch.  If it ends with a nearly empty round, its last tiles run as a
+//     launch of smaller tiles instead;
+//   for long contractions, every product's whole rounds of 256 large tiles as a launch of its own (tiles that start in step
+//     share operand panels through the L2), and only what does not fill a round of all products in the pool.
+// Measured (us), all weight gradients of a stage, 128 x 128 / large pooled / large in whole rounds: 7B layer, K 456 333 / 266 /
+// 304, K 1440 707 / 569 / 592, K 4096 - / 1416 / 1423, K 8192 - / 2735 / 2676, K 32768 - / 11712 / 10366; four MLP blocks of d 2048,
+// K 6144 - / 1464 / 1449, K 32768 - / 8100 / 7324; two layers of d 768, f 2456, accumulating, K 368 40 / 55 / -.
+constexpr int kWholeRoundsK = 4096;             // contractions longer than this in whole rounds
 hipError_t gemm_dw(const GroupedProduct* prods, int n, int acc, GroupedProduct* pool, hipStream_t s) {
   long n64 = 0, n128 = 0, pooled = 0, whole = 0;
   int K = 0;
@@ -1493,18 +1502,19 @@ hipError_t gemm_dw(const GroupedProduct* prods, int n, int acc, GroupedProduct* 
     pooled += t % 256;
     K = prods[i].K;
   }
+  if (K <= kWholeRoundsK) { pooled += whole; whole = 0; }
   const long last = pooled % 256;
-  const double e64 = dw_time(64, 16 * last, K, acc), e128 = dw_time(128, 4 * last, K, acc), e_end = e64 < e128 ? e64 : e128;
+  const double e64 = dw_time(64, 16 * last, K, acc), e128 = dw_time(128, 4 * last, K, acc), e_end = (e64 < e128 ? e64 : e128) + kEndLaunch;
   const bool small_end = pooled > 256 && last > 0 && e_end < 0.8 * dw_time(256, last, K, acc);
   const double t64 = dw_time(64, n64, K, acc), t128 = dw_time(128, n128, K, acc);
-  const double t256 = dw_time(256, whole, K, acc) + dw_time(256, small_end ? pooled - last : pooled, K, acc) + (small_end ? e_end : 0.);
+  const double t256 = dw_time(256, whole, K, acc) + dw_time(256, small_end ? pooled - last : pooled, K, acc) + (small_end ? e_end : 0.) + kLargeTileStart;
   if (t64 <= t128 && t64 <= t256) return launch_tn_grouped<64>(prods, n, acc, s);
   if (t128 <= t256) return launch_tn_grouped<128>(prods, n, acc, s);
   int np = 0;
   for (int i = 0; i < n; i++) {
     const long t = dw_tiles(256, prods[i].M, prods[i].N);
-    GroupedProduct head, rest;
-    cut_product(prods[i], t / 256 * 256, head, rest);
+    GroupedProduct head{}, rest = prods[i];
+    if (K > kWholeRoundsK) cut_product(prods[i], t / 256 * 256, head, rest);
     if (head.M > 0 && head.N > 0) {
       GemmParams p{};
       p.A = head.A; p.B = head.B; p.C = head.C;
@@ -1656,10 +1666,20 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   if (!g.out_f32 && g.batch == 1 && g.causal == CAUSAL_NONE && !g.delta && g.layout != TN && narrow_tiles_pay(g.M, g.N, g.K))
     return g.layout == NN ? launch_bf16<256, 192, true, false, bf16_t, TBP_NARROW_KD, TBP_NARROW_RING>(p, 1, s)
                           : launch_bf16<256, 192, true, true, bf16_t, TBP_NARROW_KD, TBP_NARROW_RING>(p, 1, s);
-  // a weight gradient by itself: large tiles (below) unless smaller ones are faster by the same model as in gemm_dw
+  // a weight gradient by itself: large tiles (below, with the last round on smaller ones where it is at most three quarters
+  // full) unless smaller ones are faster by the same model as in gemm_dw.  [7264, 7208] x 1896: 841 large tiles are three
+  // rounds and 73 tiles, 210 us, 128 x 128 tiles 247; [4128, 920] x 3824: 264 tiles of 128 x 128 58, 64 x 64 69; [600, 544] x
+  // 5880, accumulating: 64 x 64 29, 128 x 128 50.
   if (g.out_f32 && g.layout == TN && g.batch == 1 && g.causal == CAUSAL_NONE && g.K > 0) {
-    const double t256 = dw_time(256, tiles_big, g.K, g.accumulate), t64 = dw_time(64, dw_tiles(64, g.M, g.N), g.K, g.accumulate);
-    const double t128 = dw_time(128, dw_tiles(128, g.M, g.N), g.K, g.accumulate);
+    const double t64 = dw_time(64, dw_tiles(64, g.M, g.N), g.K, g.accumulate), t128 = dw_time(128, dw_tiles(128, g.M, g.N), g.K, g.accumulate);
+    double t256 = 1e30;
+    if (big) {
+      const long whole = tiles_big / 256 * 256, r = tiles_big - whole;
+      t256 = dw_time(256, tiles_big, g.K, g.accumulate);
+      if (whole > 0 && r > 0 && r <= 192)
+        t256 = dw_time(256, whole, g.K, g.accumulate) + (r <= 128 ? dw_time(128, 4 * r, g.K, g.accumulate) : 0.75 * dw_time(256, r, g.K, g.accumulate));
+    }
+    t256 += kLargeTileStart;
     if (t64 <= t128 && t64 <= t256) return launch_bf16<64, 64, false, false, float, 64, 4>(p, 1, s);
     if (t128 <= t256) return launch_bf16<128, 128, false, false, float, 32>(p, 1, s);
   }

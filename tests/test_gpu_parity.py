@@ -579,8 +579,10 @@ def test_p2_sets_in_any_order(shape, mode, sets, gain_grad):
 
 
 @pytest.mark.parametrize("shape", [
-    # weight gradients of 344 and 176 large tiles: one whole round, 264 pooled of which the last 8 end on small tiles
+    # weight gradients of 344 and 176 large tiles: 520 pooled, of which the last 8 end on small tiles
     si.StageShape("dw_large_tiles", 1, 2048, 0, 0, 5504, 1536, 1, 1, "bf16", 43),
+    # a long contraction, 258 and 132 large tiles, ragged: a whole round by itself and 134 pooled
+    si.StageShape("dw_whole_rounds", 1, 1288, 0, 0, 5496, 1368, 1, 3, "bf16", 51),
     # the same over a short contraction: one launch of 128 x 128 tiles
     si.StageShape("dw_short", 1, 2048, 0, 0, 5504, 104, 1, 2, "bf16", 44)], ids=lambda s: s.name)
 def test_weight_gradient_arrangements(shape):
