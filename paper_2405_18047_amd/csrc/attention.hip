@@ -92,10 +92,15 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& c, int u) {
 // Bound: per block and wave 32 MFMAs of 32 clocks, about 900 clocks of vector ALU (32 exponentials at 16 clocks, the rest at
 // 4), and 32 KiB of LDS reads, which two waves per SIMD turn into 2000 clocks of each.  Computing a block's scores, softmax
 // and PV product one after the other, the units hardly overlapped; with the scores of the next block computed beside the
-// exponentials of this one, in a pinned order, B 2, H 32, S 2048, dh 128 takes 87 us instead of 100 (S 4096, B 1: 153 for
-// 182; dh 64: 52 for 64; without the causal mask, H 16: 70 for 82).  64 queries per wave (half the LDS reads, one wave per
+// exponentials of this one, in a pinned order, B 2, H 32, S 2048, dh 128 takes 77 us instead of 90 (S 4096, B 1: 136 for
+// 162; dh 64: 46 for 57; without the causal mask: 131 for 149; calls in a row on inputs that take turns).  64 queries per wave (half the LDS reads, one wave per
 // SIMD) was tried: 72 us for 53 at dh 64, spilled registers at 128.
-template <int DH>
+// AHEAD = false, for sequences of at most 256 keys (four blocks): a block's own scores first, then its softmax and PV product.
+// There are few next blocks to compute ahead, and the scores after the last one, which nobody uses, and a barrier more at the
+// start cost more than the overlap gives.  us, ahead / not: B 32, H 32, dh 128, S 64 17.3 / 16.7, S 128 28.1 / 27.0, S 256 63.9 / 63.2;
+// B 1, H 8, dh 64, S 192 5.94 / 5.62, S 256 6.80 / 6.58; beyond that either is ahead by 1-3 % up to S 512 (B 8, H 16, dh 128, S 264
+// 13.0 / 13.3, S 512 19.4 / 19.7).  (Skipping the last scores by a branch in the pinned order instead: spilled registers.)
+template <int DH, bool AHEAD>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_kernel(AttnParams p) {
   using HT = HeadTile<DH>;
   constexpr int KS = DH / 16, DT = DH / 32, BKV = 64, BQ = 128;
@@ -161,17 +166,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 #pragma unroll
   for (int s = 0; s < KS; s++) qf[s] = HT::rows_frag(lds + SLOT, fo, 32 * wave, s);
   f32x16 sa[2], sb[2];                 // S^T of the block whose softmax is in work, and of the next one
-#pragma unroll
-  for (int kt = 0; kt < 2; kt++)
-#pragma unroll
-    for (int e = 0; e < 16; e++) sa[kt][e] = 0.f;
-#pragma unroll
-  for (int s = 0; s < KS; s++)
+  auto scores = [&](f32x16 (&st)[2], lds_u8* kimg) {
 #pragma unroll
     for (int kt = 0; kt < 2; kt++)
-      sa[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(HT::rows_frag(lds, fo, 32 * kt, s), qf[s], sa[kt], 0, 0, 0);
-  __syncthreads();                     // every wave has its query row: the second slot is free
-  if (nblk > 1) issue(1, 0);
+#pragma unroll
+      for (int e = 0; e < 16; e++) st[kt][e] = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; s++)
+#pragma unroll
+      for (int kt = 0; kt < 2; kt++)
+        st[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(HT::rows_frag(kimg, fo, 32 * kt, s), qf[s], st[kt], 0, 0, 0);
+  };
+  if constexpr (AHEAD) {
+    scores(sa, lds);
+    __syncthreads();                   // every wave has its query row: the second slot is free
+    if (nblk > 1) issue(1, 0);
+  }
 
   // Block j: softmax of its scores (st) and O^T += V^T P^T, with the scores of block j + 1 (nx) computed on the way.
   // The order of the instructions is pinned: the MFMAs of the next block's scores and the first three quarters of the PV
@@ -179,17 +189,21 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   auto block = [&](f32x16 (&st)[2], f32x16 (&nx)[2], int j) {
     wait_vmem<0>();
     __syncthreads();                   // K of block j + 1 and V of block j have landed; every wave is done with block j - 1
-    if (j + 2 < nblk) issue(j + 2, 0);
+    if (AHEAD ? j + 2 < nblk : j + 1 < nblk) issue(AHEAD ? j + 2 : j + 1, 0);      // (not AHEAD: K of block j has landed)
     if (j + 1 < nblk) issue(j + 1, 1);
     const int kv0 = j * BKV;
     if (p.causal && kv0 > qw0 + 31) return;            // every key of the block is after every query of this wave
     lds_u8* const kimg = lds + ((j + 1) & 1) * SLOT;   // (after the last block: an older one, whose scores nobody uses)
     lds_u8* const vimg = lds + (j & 1) * SLOT + IMG;
     bf16x8 kf[2][2];
+    if constexpr (AHEAD) {
 #pragma unroll
-    for (int s = 0; s < 2; s++)
+      for (int s = 0; s < 2; s++)
 #pragma unroll
-      for (int kt = 0; kt < 2; kt++) kf[s][kt] = HT::rows_frag(kimg, fo, 32 * kt, s);
+        for (int kt = 0; kt < 2; kt++) kf[s][kt] = HT::rows_frag(kimg, fo, 32 * kt, s);
+    } else {
+      scores(st, lds + (j & 1) * SLOT);
+    }
     // keys beyond the query (causal) or beyond the sequence do not take part (blocks on the diagonal / at the end only)
     if ((p.causal && kv0 + BKV - 1 > qw0) || kv0 + BKV > p.S) {
       const int last = p.causal ? (query < p.S - 1 ? query : p.S - 1) : p.S - 1;      // last key this lane's query sees
@@ -236,20 +250,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     };
     constexpr int NA = 2 * KS, EA = 18;        // MFMAs of the scores; elements done beside them, the rest beside 3 PV k-steps
     static_assert(EA >= 8 && EA + (32 - EA) / 3 >= 16 && EA + (32 - EA) * 2 / 3 >= 24, "P must be ready in time");
+    if constexpr (AHEAD) {
 #pragma unroll
-    for (int kt = 0; kt < 2; kt++)
+      for (int kt = 0; kt < 2; kt++)
 #pragma unroll
-      for (int e = 0; e < 16; e++) nx[kt][e] = 0.f;
+        for (int e = 0; e < 16; e++) nx[kt][e] = 0.f;
+    }
     __builtin_amdgcn_s_setprio(1);             // (the SIMD's other wave fills in: 1-4 % faster than without)
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (AHEAD) {
 #pragma unroll
-    for (int i = 0; i < NA; i++) {
-      const int s = i >> 1, kt = i & 1;
-      nx[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s & 1][kt], qf[s], nx[kt], 0, 0, 0);
-      if (s + 2 < KS) kf[s & 1][kt] = HT::rows_frag(kimg, fo, 32 * kt, s + 2);
-      if (i >= NA - DT) vf[i - (NA - DT)] = HT::cols_frag(vimg, fo, 0, 0, i - (NA - DT));
-      elements(EA * i / NA, EA * (i + 1) / NA);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int i = 0; i < NA; i++) {
+        const int s = i >> 1, kt = i & 1;
+        nx[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s & 1][kt], qf[s], nx[kt], 0, 0, 0);
+        if (s + 2 < KS) kf[s & 1][kt] = HT::rows_frag(kimg, fo, 32 * kt, s + 2);
+        if (i >= NA - DT) vf[i - (NA - DT)] = HT::cols_frag(vimg, fo, 0, 0, i - (NA - DT));
+        elements(EA * i / NA, EA * (i + 1) / NA);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+#pragma unroll
+      for (int t = 0; t < DT; t++) vf[t] = HT::cols_frag(vimg, fo, 0, 0, t);
+      elements(0, EA);
     }
 #pragma unroll
     for (int i = 0; i < 4 * DT; i++) {
@@ -797,10 +819,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
-template <int DH>
+template <int DH, bool AHEAD>
 static hipError_t launch_fwd(const AttnParams& p, hipStream_t s) {
   constexpr size_t smem = 2 * 2 * 64 * DH * 2;
-  auto kern = attn_fwd_kernel<DH>;
+  auto kern = attn_fwd_kernel<DH, AHEAD>;
   static AttrOnce once;
   if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)(p.H * p.B), (unsigned)((p.S + 127) / 128)), dim3(256), smem, s, p);
@@ -814,8 +836,8 @@ hipError_t attention_fwd(int batch, int n_heads, int seq, int head_dim, int caus
   p.qkv = (const bf16_t*)qkv; p.ld_qkv = ld_qkv; p.out = (bf16_t*)out; p.ld_out = ld_out; p.lse = lse;
   p.B = batch; p.H = n_heads; p.S = seq; p.causal = causal;
   p.scale_log2e = 1.4426950408889634f / sqrtf((float)head_dim);
-  if (head_dim == 128) return launch_fwd<128>(p, s);
-  if (head_dim == 64) return launch_fwd<64>(p, s);
+  if (head_dim == 128) return seq > 256 ? launch_fwd<128, true>(p, s) : launch_fwd<128, false>(p, s);
+  if (head_dim == 64) return seq > 256 ? launch_fwd<64, true>(p, s) : launch_fwd<64, false>(p, s);
   return hipErrorInvalidValue;
 }
 

@@ -328,7 +328,10 @@ def test_fused_attention_backward(seq, nb, H, dh, causal, recompute):
 # ------------------------------------------------------------------------------------------- whole stage
 @pytest.mark.parametrize("seq,nb,H,dh,causal", [(256, 1, 2, 128, True), (136, 2, 3, 64, True), (520, 1, 2, 128, True),
                                                 (200, 1, 2, 64, False), (1024, 1, 4, 128, True), (8, 1, 1, 64, True),
-                                                (4096, 1, 1, 128, True)])
+                                                (4096, 1, 1, 128, True),
+                                                # both sides of the line between the two kernels, whole and ragged blocks
+                                                (256, 1, 2, 64, False), (264, 1, 2, 64, False), (264, 2, 2, 128, True),
+                                                (64, 3, 2, 128, True), (72, 1, 3, 128, False)])
 def test_fused_attention_forward(seq, nb, H, dh, causal):
     """Fused attention against the oracle's materialised form; the row log-sum-exp against what the oracle's
     probabilities imply (lse_i = s_ii - log P_ii on the diagonal, which is never masked)."""
