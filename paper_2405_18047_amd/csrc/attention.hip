@@ -853,7 +853,7 @@ static hipError_t launch_bwd_dq(const AttnDqParams& p, hipStream_t s) {
 
 template <int DH, bool WRITE_DST>
 static hipError_t launch_bwd_kv_split(const AttnBwdParams& p, hipStream_t s) {
-  constexpr size_t smem = 3 * (2 * 64 * DH * 2 + 1024) + 2 * 4 * 4096 + 4 * 32 * 144;     // three slots, two hand-over buffers, dS^T staging
+  constexpr size_t smem = 3 * (2 * 64 * DH * 2 + 1024) + 2 * 4 * 4096 + (WRITE_DST ? 4 * 32 * 144 : 0);     // three slots, two hand-over buffers, dS^T staging
   auto kern = attn_bwd_kv_split_kernel<DH, WRITE_DST>;
   static AttrOnce once;
   if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
@@ -874,12 +874,7 @@ hipError_t attention_p1(int batch, int n_heads, int seq, int head_dim, int causa
   p.B = batch; p.H = n_heads; p.S = seq; p.causal = causal;
   p.scale = 1.f / sqrtf((float)head_dim);
   p.scale_log2e = 1.4426950408889634f * p.scale;
-  // dQ by the recompute pass where there is no dS^T buffer, and where there are at least four workgroups of 128 keys per
-  // compute unit: dS^T is then several times the on-package cache (0.5 GB at B 2, H 32, S 2048) and its round trip costs
-  // more than the two products it saves.  Whole backward, us, dS^T / recompute: B 2, H 32, S 2048 326 / 298, dh 64
-  // 213 / 177; B 1, S 4096 507 / 487; below that the recompute pass leaves the chip emptier than one product over
-  // 128 x 128 tiles: B 1, H 32, S 2048 142 / 155, S 1024 62 / 72, H 16, S 2048 100 / 123.
-  if (!ds_t || (long)batch * n_heads * ((seq + 127) / 128) >= 1024) {
+  if (!ds_t || attn_rebuilds_dq(batch, n_heads, seq, head_dim)) {
     if (head_dim == 128) e = launch_bwd_kv_split<128, false>(p, s);
     else if (head_dim == 64) e = launch_bwd_kv_split<64, false>(p, s);
     else return hipErrorInvalidValue;

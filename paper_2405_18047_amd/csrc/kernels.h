@@ -135,11 +135,23 @@ hipError_t head_rowdot(int dtype, int rows, int n_heads, int head_dim, const voi
 hipError_t attention_fwd(int batch, int n_heads, int seq, int head_dim, int causal, const void* qkv, long ld_qkv,
                          void* out, long ld_out, float* lse, hipStream_t s);
 
+// Does the backward compute dq by a pass that rebuilds S and dP rather than from dS^T written to memory?  Where there are at
+// least four workgroups of 128 keys per compute unit (below that the pass leaves the chip emptier than one product over
+// 128 x 128 tiles), and at head_dim 128 only for sequences above 512: shorter ones write little dS^T per workgroup, and its
+// round trip then costs less than the two products that the pass adds (at head_dim 64 these are cheap).  Whole backward, us,
+// dS^T / rebuilt, causal and not: dh 128, B 2, H 32, S 2048 281 / 276, 494 / 478; B 4, H 12, S 4096 748 / 704, 1355 / 1322;
+// B 4, H 40, S 896 196 / 184, 291 / 281; B 8, H 32, S 512 131 / 138, 169 / 175; B 32, H 32, S 128 97 / 103, 98 / 104; dh 64, the
+// first 216 / 180, 393 / 301, the last 67 / 62, 67 / 60; fewer workgroups: B 1, H 32, dh 128, S 2048 142 / 155, S 1024 62 / 72.
+inline bool attn_rebuilds_dq(int batch, int n_heads, int seq, int head_dim) {
+  return (long)batch * n_heads * ((seq + 127) / 128) >= 1024 && (head_dim == 64 || seq > 512);
+}
+
 // Backward-p1 of the same: dq, dk, dv into the column blocks of dqkv from qkv, the forward's output and lse and the
 // output derivative d_out (dense rows: ld_out == n_heads*head_dim).  delta: scratch [batch*seq, n_heads] fp32;
 // ds_t: scratch of batch * n_heads * attn_ds_elems(seq) storage-type elements (receives dS^T in panels of kPanel
 // queries: per (sequence, head) [ceil(seq / kPanel)][seq keys][kPanel queries]; dq is then one batched product
-// dS K), or nullptr: dq is computed by a second pass over the keys that rebuilds S and dP (no dS^T anywhere).
+// dS K), or nullptr: dq is computed by a second pass over the keys that rebuilds S and dP (no dS^T anywhere), as it is
+// with attn_rebuilds_dq in any case (ds_t is then not touched).
 hipError_t attention_p1(int batch, int n_heads, int seq, int head_dim, int causal, const void* qkv, long ld_qkv,
                         const void* out, const void* d_out, long ld_out, const float* lse, void* dqkv, long ld_dqkv,
                         float* delta, void* ds_t, hipStream_t s);
