@@ -181,12 +181,12 @@ tbp_status check_config(const tbp_config* cfg, Dims* out) {
     if ((cfg->attention == TBP_ATTN_FUSED || cfg->attention == TBP_ATTN_FUSED_RECOMPUTE) && c.attn && !can_fuse)
       return fail(TBP_EINVAL, "fused attention needs bf16 storage and head_dim 64 or 128");
     c.fused = can_fuse && cfg->attention != TBP_ATTN_MATERIALISED;
-    c.dq_recompute = c.fused && cfg->attention == TBP_ATTN_FUSED_RECOMPUTE;
   }
   if (cfg->gain_grad != TBP_GAIN_PARTIALS && cfg->gain_grad != TBP_GAIN_LITERAL) return fail(TBP_EINVAL, "gain_grad must be a tbp_gain_grad value");
   c.literal = cfg->gain_grad == TBP_GAIN_LITERAL;
   if (!(c.eps >= 0.f)) return fail(TBP_EINVAL, "rms_eps must be >= 0");
   if ((long)c.S * c.B > (1L << 24)) return fail(TBP_EINVAL, "tokens per micro-batch above 2^24");
+  c.dq_recompute = c.fused && (cfg->attention == TBP_ATTN_FUSED_RECOMPUTE || tbp::attn_rebuilds_dq(c.B, c.H, c.S, c.dh));
   c.T = c.S * c.B;
   *out = c;
   return TBP_OK;

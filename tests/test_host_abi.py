@@ -67,6 +67,15 @@ def test_stash_sizes_follow_the_stash_rule():
     s = si.CONFIGS["llama7b_s1024"]
     assert _sizes(s, act_slots=1)["a_stash_bytes"] * 4 == _sizes(s)["a_stash_bytes"]
     assert _sizes(s, act_slots=1)["w_stash_bytes"] == _sizes(s)["w_stash_bytes"]
+    # where the backward rebuilds dq on its own account, no dS^T workspace is asked for: from 1024 workgroups of 128 keys on,
+    # at head_dim 128 above 512 keys
+    for heads, dh, seq, batch, rebuilt in ((32, 128, 2048, 2, True), (31, 128, 2048, 2, False), (32, 128, 512, 8, False), (32, 128, 520, 8, True),
+                                           (32, 64, 128, 32, True), (32, 64, 128, 31, False), (32, 64, 512, 8, True)):
+        s = si.StageShape("dst", 1, heads * dh, heads, dh, 256, seq, batch, 1, "bf16", 1)
+        saved = _sizes(s, attention=tbp.TBP_ATTN_FUSED)["workspace_bytes"] - _sizes(s, attention=tbp.TBP_ATTN_FUSED_RECOMPUTE)["workspace_bytes"]
+        assert saved == (0 if rebuilt else batch * heads * seq * ((seq + 127) // 128 * 128) * 2), (heads, dh, seq, batch)
+        # the single operation's scratch stays large enough for any smaller call
+        assert tbp.lib().tbp_attention_p1_scratch_bytes(batch, heads, seq) >= batch * heads * seq * seq * 2
     # 13B stage: everything fits the 288 GB of one MI355X
     assert _sizes(si.CONFIGS["llama13b_s2048"])["arena_bytes"] < 150 * 2**30
 
