@@ -1582,24 +1582,34 @@ static hipError_t launch_f32_small(int layout, const GemmParams& p0, int batch, 
   return hipGetLastError();
 }
 
-// Tile of an fp32 product: 16 x 16 up to two of them per compute unit, else the one with the shortest time by rounds of
-// 256 compute units, (rounds) x (tile area) / (rate).  The rates (TFLOP/s with every compute unit busy) are measured:
-// 128 x 128 tiles 132-140, 64 x 64 tiles 110-125, 32 x 32 tiles with the contraction split over the waves 91-110 (they move
-// 4 times the operand bytes of the first).  Times in us, 128 / 64 / 32: [512, 1024] x 5504 349 / 105 / 63 (too few tiles for
-// anything but the smallest), [512, 5504] x 1024 79 / 62 / 75, [2048, 2048] x 2048 149 / 144 / 175, [4096, 4096] x 4096
-// 998 / 1069 / 1245.  Rings of three or four shallower slots measured within 5 % of these (128: three slots slower, 1049;
-// 64: four 32-deep slots 1058; 32: four 64-deep slots 1260).
-static int f32_tile(int M, int N, int batch) {
-  auto cost = [&](int t, double rate) {
-    const long tiles = (long)((M + t - 1) / t) * ((N + t - 1) / t) * batch;
-    return (double)((tiles + 255) / 256) * t * t / rate;
-  };
-  if ((long)((M + 15) / 16) * ((N + 15) / 16) * batch <= 512) return 16;
-  const double c128 = cost(128, 132.), c64 = cost(64, 115.), c32 = cost(32, 100.);
-  return c32 <= c64 && c32 <= c128 ? 32 : c64 <= c128 ? 64 : 128;
+// Tile of an fp32 product: the one with the shortest modelled time.  Every kind runs two workgroups per compute unit (64 KiB of
+// LDS each), so a launch is rounds of 512 workgroups, `two` us each, and a last one that costs `one` if it has at most 256; both
+// have a part per contraction index (the matrix pipes: 132 TFLOP/s on 128 x 128 tiles, 110 on the smaller ones, which move more
+// operand bytes) and a fixed one (start, store).  Fitted to 471 products, M and N 64-6000, K 32-4096, each measured on all four
+// tiles (5 % rms; 8 % on 16 x 16): the choice costs 0.4 % more than the fastest on average, 4 % with the rule before, which
+// had no fixed part and so took 32 x 32 tiles for short contractions ([1544, 3268] x 64: 36 us; 64 x 64 tiles 19).
+// us, 16 / 32 / 64 / 128: [512, 1024] x 5504 - / 63 / 105 / 349 (too few tiles for the large ones), [512, 5504] x 1024 - / 75 / 62 / 79,
+// [2048, 2048] x 2048 - / 175 / 144 / 149, [4096, 4096] x 4096 - / 1245 / 1069 / 998.  Rings of
+// three or four shallower slots measured within 5 % of these (128: three slots slower, 1049; 64: four 32-deep slots 1058; 32: four
+// 64-deep slots 1260).
+static int f32_tile(int M, int N, int K, int batch) {
+  struct Tile { int t; double one_k, one, two_k, two, share; };
+  static const Tile tiles[] = {{128, 0.0614, 6.3, 0.1226, 10.9, 1.0}, {64, 0.0184, 2.4, 0.0347, 4.4, 1.0},
+                               {32, 0.0054, 1.8, 0.0100, 2.8, 1.0}, {16, 0.0017, 0.9, 0.0040, 1.3, 0.7}};
+  int best = 0;
+  double best_time = 1e30;
+  for (const Tile& x : tiles) {
+    const long n = (long)((M + x.t - 1) / x.t) * ((N + x.t - 1) / x.t) * batch, r = n % 512;
+    if (x.t == 16 && n > 512) continue;             // ([2436, 100] x 3448 (TN), 1071 of them: 55 us, 32 x 32 tiles 41)
+    const double one = x.one_k * K + x.one, two = x.two_k * K + x.two;
+    const double share = x.share + (1.0 - x.share) * (double)(r - 256) / 256;       // (16 x 16: 0.7 of the difference at 257)
+    const double time = (double)(n / 512) * two + (r == 0 ? 0. : r <= 256 ? one : one + (two - one) * share);
+    if (time < best_time) { best_time = time; best = x.t; }
+  }
+  return best;
 }
 static hipError_t dispatch_f32(int layout, const GemmParams& p, int batch, hipStream_t s) {
-  switch (f32_tile(p.M, p.N, batch)) {
+  switch (f32_tile(p.M, p.N, p.K, batch)) {
     case 16: return launch_f32_small(layout, p, batch, s);
     case 32: return launch_f32_layout<32, 32, 4, 128, 2>(layout, p, batch, s);
     case 64: return launch_f32_layout<64, 64, 1, 64, 2>(layout, p, batch, s);
@@ -1615,7 +1625,7 @@ static bool large_tiles(const GemmArgs& g) {
 }
 
 int gemm_row_tile(int dtype, const GemmArgs& g) {
-  if (dtype == 0) return f32_mfma_ok(g) ? f32_tile(g.M, g.N, g.batch) : 64;
+  if (dtype == 0) return f32_mfma_ok(g) ? f32_tile(g.M, g.N, g.K, g.batch) : 64;
   return !g.a_panel && large_tiles(g) ? 256 : 128;
 }
 
