@@ -950,14 +950,40 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(GemmParams p) {
   const float* R = reinterpret_cast<const float*>(p.R);
   if (R) R += zo * p.sCo + zi * p.sCi;
   const float* const delta = p.delta ? p.delta + zo * p.sDo + zi * p.sDi : nullptr;
+  constexpr int NE = WK > 1 ? 4 : 16;               // registers of an MFMA tile that this wave stores
+  auto row_of = [&](int i, int e) {
+    return m0 + (wm * TM + i) * 32 + (WK > 1 ? 8 * wave + 4 * (lane >> 5) + e : 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3));
+  };
+  if (p.accumulate && !R && !delta) {
+    // the old values of an MFMA tile are requested together: one at a time, between stores that the compiler must take to
+    // alias the next load, they made an accumulating [2616, 4084] x 64 product 66 us; now 38
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++) {
+        const int col = n0 + (wn * TN + j) * 32 + (lane & 31);
+        float old[NE];
+#pragma unroll
+        for (int e = 0; e < NE; e++) {              // (without branches: outside the output the tile's first element)
+          const int row = row_of(i, e);
+          old[e] = C[row < p.M && col < p.N ? (long)row * p.ldc + col : (long)m0 * p.ldc + n0];
+        }
+#pragma unroll
+        for (int e = 0; e < NE; e++) {
+          const int row = row_of(i, e);
+          if (row < p.M && col < p.N) C[(long)row * p.ldc + col] = old[e] + p.alpha * acc[i][j][e];
+        }
+      }
+    return;
+  }
 #pragma unroll
   for (int i = 0; i < TM; i++)
 #pragma unroll
     for (int j = 0; j < TN; j++) {
       const int col = n0 + (wn * TN + j) * 32 + (lane & 31);
 #pragma unroll
-      for (int e = 0; e < (WK > 1 ? 4 : 16); e++) {
-        const int row = m0 + (wm * TM + i) * 32 + (WK > 1 ? 8 * wave + 4 * (lane >> 5) + e : 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3));
+      for (int e = 0; e < NE; e++) {
+        const int row = row_of(i, e);
         if (row >= p.M || col >= p.N) continue;
         const long idx = (long)row * p.ldc + col;
         float v = p.alpha * acc[i][j][e];

@@ -96,6 +96,22 @@ def test_gemm_f32_tiles_and_general_path(layout, mnk):
         assert torch.all(out[:, N:] == 7.0)
 
 
+@pytest.mark.parametrize("mnk", [(36, 52, 40), (260, 516, 260), (964, 1092, 68), (2052, 4036, 28)])      # 16, 32, 64, 128
+def test_gemm_f32_accumulates_on_every_tile(mnk):
+    """fp32 weight gradients added to what is there, ragged on every tile size of the matrix-core kernels, into the columns
+    of a wider matrix whose others stay; and with a residual on top.  Tolerance as above."""
+    M, N, K = mnk
+    _say(f"gemm f32 accumulate M,N,K={mnk}")
+    A, B, R, C = (_rnd(19, n, sh, "f32") for n, sh in (("A", (K, M)), ("B", (K, N)), ("R", (M, N + 3)), ("C", (M, N + 3))))
+    ref = C[:, :N] + ops.linear_p2(A.astype(np.float64), B.astype(np.float64))
+    for resid in (False, True):
+        out = to_dev(C, "f32")
+        tbp.tbp_gemm(tbp.TN, to_dev(A, "f32"), to_dev(B, "f32"), C_out=out[:, :N], accumulate=True,
+                     R=to_dev(R, "f32")[:, :N] if resid else None)
+        assert max_rel(to_np(out[:, :N]), ref + R[:, :N] if resid else ref) < 2e-5
+        assert torch.equal(out[:, N:], to_dev(C, "f32")[:, N:])
+
+
 @pytest.mark.parametrize("layout", [tbp.NN, tbp.NT])
 @pytest.mark.parametrize("mnk", [(1024, 4096, 32768), (1000, 4040, 32776), (1280, 2304, 49152)])
 def test_gemm_with_split_contraction(layout, mnk):
