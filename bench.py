@@ -130,7 +130,11 @@ def main() -> int:
             st.backward_p1(m, dys[m], dx_out)
             if e: e[5 + 2 * m].record()
         if e: e[2].record()
-        st.backward_p2(range(M), mode, accumulate=False)
+        if mode is None:           # one call per micro-batch, each adding to the one before
+            for m in range(M):
+                st.backward_p2([m], tbp.TBP_P2_LOOP, accumulate=m > 0)
+        else:
+            st.backward_p2(range(M), mode, accumulate=False)
         if e: e[3].record()
         if record is not None:
             record.append(e)
@@ -166,11 +170,12 @@ def main() -> int:
     p1_ms = [e[4 + 2 * m].elapsed_time(e[5 + 2 * m]) for e in recs for m in range(M)]
     stats = st.stats()
 
-    # the same stash walked as M accumulating products per weight (outside the timed steps)
+    # the same stash walked as M accumulating products per weight, by one call per micro-batch (a LOOP call over the whole
+    # set is, like the K-concatenated one, a single product per weight, since the set is one run); outside the timed steps
     loop_recs = []
     if not args.no_loop_compare:
         for _ in range(max(2, min(args.steps, 3))):
-            step(tbp.TBP_P2_LOOP, loop_recs)
+            step(None, loop_recs)
         torch.cuda.synchronize()
     p2_loop_ms = [e[2].elapsed_time(e[3]) for e in loop_recs] or [float("nan")]
 

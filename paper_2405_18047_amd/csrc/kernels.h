@@ -61,7 +61,7 @@ constexpr size_t attn_ds_elems(int seq) { return (size_t)((seq + kPanel - 1) / k
 // fp32 partial product [M][N] in the scratch buffer and a second launch adds the slices up in order (so the result does
 // not depend on timing).  split == 1: not worth it / not applicable.
 struct SplitPlan { int tile, split, slice; size_t bytes; };
-constexpr size_t kSplitHead = 1024;           // unused head of the scratch: part of the size that callers are told
+constexpr size_t kSplitHead = 1024;           // unused: part of the size that tbp_gemm_workspace_bytes has always told callers
 SplitPlan gemm_split_plan(int dtype, int layout, int M, int N, int K, int out_f32, int batch);
 
 inline GemmArgs gemm_args(int layout, int M, int N, int K, const void* A, long lda, const void* B, long ldb,

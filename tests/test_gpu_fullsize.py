@@ -101,7 +101,7 @@ def test_13b_mlp_block_shape_full_compare():
 def test_stage_with_split_contraction():
     """A stage whose backward-p1 product dh2 = [dg, du] Wgu^T has a small output ([1024, 1024]: 16 large tiles) and a
     very long contraction (2 x 24576): the stage runs it with the contraction split over several workgroups per tile,
-    using scratch from its own workspace, whose arrival counters are cleared before every such product."""
+    using scratch from its own workspace."""
     shape = si.StageShape("mlp_long_k", 1, 1024, 0, 0, 24576, 1024, 1, 2, "bf16", 20240525)
     assert tbp.lib().tbp_gemm_workspace_bytes(tbp.TBP_BF16, tbp.NT, shape.tokens, shape.d_model, 2 * shape.d_ffn, 0) > 0
     params, xs, dys = _inputs(shape)
@@ -153,6 +153,8 @@ def test_full_benchmark_configuration_properties():
     # same stash contents, different p2 call patterns
     _, dxs2, g_loop = run([(range(M), tbp.TBP_P2_LOOP, False)])
     _, _, g_split = run([([0, 1], tbp.TBP_P2_KCONCAT, False), ([2, 3], tbp.TBP_P2_KCONCAT, True)])
+    # (a LOOP set that is one run of micro-batches is one product, like the concatenated one: here one per micro-batch)
+    _, _, g_each = run([([m], tbp.TBP_P2_LOOP, m > 0) for m in range(M)])
     for a, b in zip(dxs, dxs2):
         assert torch.equal(a, b)                      # the path is deterministic
     for k in g_cat:
@@ -160,6 +162,7 @@ def test_full_benchmark_configuration_properties():
             ref = to_np(g_cat[k][l])
             assert max_rel(to_np(g_loop[k][l]), ref) < 1e-4, (k, l)
             assert max_rel(to_np(g_split[k][l]), ref) < 1e-4, (k, l)
+            assert max_rel(to_np(g_each[k][l]), ref) < 1e-4, (k, l)
     st.close()
 
 
@@ -212,6 +215,8 @@ def test_headline_layer_shape_full_compare():
     compare_stage(shape, g_outs, g_dxs, st.grads, outs, dxs, grads, tol, "7B seq 2048 x mb 2, K-concat")
     g_outs, g_dxs = _gpu_step(st, xs, dys, [([0, 1], tbp.TBP_P2_LOOP, False)])
     compare_stage(shape, g_outs, g_dxs, st.grads, outs, dxs, grads, tol, "7B seq 2048 x mb 2, loop")
+    g_outs, g_dxs = _gpu_step(st, xs, dys, [([0], tbp.TBP_P2_LOOP, False), ([1], tbp.TBP_P2_LOOP, True)])
+    compare_stage(shape, g_outs, g_dxs, st.grads, outs, dxs, grads, tol, "7B seq 2048 x mb 2, one call per micro-batch")
     st.close()
 
 

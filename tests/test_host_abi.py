@@ -188,7 +188,7 @@ def test_single_op_argument_checks():
 def test_gemm_workspace_policy_and_checks():
     """tbp_gemm_workspace_bytes is host arithmetic: scratch is asked for only where splitting the contraction pays
     (a bf16 NN / NT product with a storage-type output that neither tile shape can spread over the chip, and a long
-    contraction), and it is exactly the arrival counters plus one fp32 tile per slice."""
+    contraction), and it is exactly a head of 1 KiB plus one fp32 partial product per slice."""
     L = tbp.lib()
     need = L.tbp_gemm_workspace_bytes(1, tbp.NT, 1024, 4096, 32768, 0)
     assert need == 1024 + 64 * 4 * 256 * 256 * 4                          # 64 tiles, four slices
