@@ -411,7 +411,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, in
   // fp32 +=: the old value that store u of strip i adds is requested where store u of strip i - 1 has used its own, so a
   // whole strip of requests is in flight (without branches: lanes outside the output read the tile's first element).
   // Read in place, one at a time, they made an accumulating round of 256 large tiles 22 us longer than an overwriting one;
-  // now 14.  [4096, 22016] x 256 (128 x 128 tiles) 260 -> 210 us, x 1024 377 -> 336, [2048, 11008] x 2048 141 -> 125.
+  // now 14.  [4096, 22016] x 256 (128 x 128 tiles) 260 -> 198 us, x 1024 374 -> 321, [2048, 11008] x 2048 141 -> 121 (with the
+  // tile that is chosen now 193, 303, 108).
   constexpr int OLD = ACC ? NVEC / 64 : 1;
   static_assert(!ACC || sizeof(OutT) == 4, "only an fp32 output accumulates");
   u32x4 old[OLD];
@@ -1416,13 +1417,13 @@ static bool narrow_tiles_pay(int M, int N, int K) {
 #ifndef TBP_SMALL_DEEP_KD
 #define TBP_SMALL_DEEP_KD 64
 #endif
-// Small tiles with a deep ring: when the whole output is at most one small tile per compute unit (e.g. [1024, 4096]),
-// no second workgroup shares the CU to cover the first one's waits, and a 32-deep slot of a 128 x 128 tile is
-// multiplied in 256 clocks, so the three slots that a ring of four keeps in flight cover under 800 clocks of memory
-// latency.  Such products get a ring of four 64-deep slots (128 KiB of LDS; one workgroup per CU anyway): three
-// times 512 clocks of cover, and K-contiguous operands are fetched in whole 128-byte lines.  Measured on
-// [1024, 4096] outputs: K = 12288 (NT) 126 -> 107 us, K = 22016 (NT) 237 -> 216 us, K = 11008 (NN) 104 -> 93 us;
-// a ring of eight 32-deep slots gains 3 %, three 64-deep slots lose 5 %, five (all 160 KiB) lose too.
+// Small tiles with a deep ring, for outputs of at most one small tile per compute unit that product_plan does not take: the
+// last, nearly empty round of a large weight gradient, and causal products of a single head.  No second workgroup shares the
+// CU to cover the first one's waits, and a 32-deep slot of a 128 x 128 tile is multiplied in 256 clocks, so the three slots
+// that a ring of four keeps in flight cover under 800 clocks of memory latency; four 64-deep slots (128 KiB of LDS; eight 32-deep
+// ones where the contraction index is strided in memory) cover three times 512.  Measured on [1024, 4096] outputs when they
+// ran here (product_plan's T128_DEEP is the same kernel): K = 12288 (NT) 126 -> 107 us, K = 22016 (NT) 237 -> 216 us, K = 11008
+// (NN) 104 -> 93 us; a ring of eight 32-deep slots gains 3 %, three 64-deep slots lose 5 %, five (all 160 KiB) lose too.
 template <typename OutT>
 static hipError_t dispatch_small_deep(int layout, const GemmParams& p, hipStream_t s) {
   switch (layout) {
@@ -1516,8 +1517,10 @@ static void cut_product(const GroupedProduct& q, long tiles, GroupedProduct& hea
 // Measured (us), all weight gradients of a stage, 128 x 128 / large pooled / large in whole rounds: 7B layer, K 456 333 / 266 /
 // 304, K 1440 707 / 569 / 592, K 4096 - / 1416 / 1423, K 8192 - / 2735 / 2676, K 32768 - / 11712 / 10366; four MLP blocks of d 2048,
 // K 6144 - / 1464 / 1449, K 32768 - / 8100 / 7324; two layers of d 768, f 2456, accumulating, K 368 40 / 55 / -.
-constexpr int kWholeRoundsK = 4096;             // contractions longer than this in whole rounds
+// Large pooled over large in whole rounds, overwriting / accumulating: eight 7B layers, K 512 0.91 / 0.77, K 2048 0.99 / 0.89, K 3072
+// 1.00 / 0.96, K 4096 1.02 / 1.00, K 6144 1.04 / 1.04; twelve of d 2048, f 5504, K 4096 0.99 / 0.99.
 hipError_t gemm_dw(const GroupedProduct* prods, int n, int acc, GroupedProduct* pool, hipStream_t s) {
+  const int whole_rounds_k = acc ? 4096 : 3072;             // contractions longer than this in whole rounds
   long n64 = 0, n128 = 0, pooled = 0, whole = 0;
   int K = 0;
   for (int i = 0; i < n; i++) {
@@ -1528,7 +1531,7 @@ hipError_t gemm_dw(const GroupedProduct* prods, int n, int acc, GroupedProduct* 
     pooled += t % 256;
     K = prods[i].K;
   }
-  if (K <= kWholeRoundsK) { pooled += whole; whole = 0; }
+  if (K <= whole_rounds_k) { pooled += whole; whole = 0; }
   const long last = pooled % 256;
   const double e64 = dw_time(64, 16 * last, K, acc), e128 = dw_time(128, 4 * last, K, acc), e_end = (e64 < e128 ? e64 : e128) + kEndLaunch;
   const bool small_end = pooled > 256 && last > 0 && e_end < 0.8 * dw_time(256, last, K, acc);
@@ -1540,7 +1543,7 @@ hipError_t gemm_dw(const GroupedProduct* prods, int n, int acc, GroupedProduct* 
   for (int i = 0; i < n; i++) {
     const long t = dw_tiles(256, prods[i].M, prods[i].N);
     GroupedProduct head{}, rest = prods[i];
-    if (K > kWholeRoundsK) cut_product(prods[i], t / 256 * 256, head, rest);
+    if (K > whole_rounds_k) cut_product(prods[i], t / 256 * 256, head, rest);
     if (head.M > 0 && head.N > 0) {
       GemmParams p{};
       p.A = head.A; p.B = head.B; p.C = head.C;
