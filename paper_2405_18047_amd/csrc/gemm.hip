@@ -1615,16 +1615,17 @@ static hipError_t launch_f32_small(int layout, const GemmParams& p0, int batch, 
 // LDS each), so a launch is rounds of 512 workgroups, `two` us each, and a last one that costs `one` if it has at most 256; both
 // have a part per contraction index (the matrix pipes: 132 TFLOP/s on 128 x 128 tiles, 110 on the smaller ones, which move more
 // operand bytes) and a fixed one (start, store).  Fitted to 471 products, M and N 64-6000, K 32-4096, each measured on all four
-// tiles (5 % rms; 8 % on 16 x 16): the choice costs 0.4 % more than the fastest on average, 4 % with the rule before, which
-// had no fixed part and so took 32 x 32 tiles for short contractions ([1544, 3268] x 64: 36 us; 64 x 64 tiles 19).
+// tiles (5 % rms; 8 % on 16 x 16).  A larger tile has to be 5 % faster in the model, which is its error (without that [3360, 2944] x
+// 440 (NT) ran on 128 x 128 tiles: 98 us, 90 on 64 x 64; [2072, 328] x 640 (NN) on 64 x 64: 17.1, 16.2 on 32 x 32).  The choice
+// costs 0.4 % more than the fastest on average; a rule by rounds and rates alone, 4 % (it took 32 x 32 tiles for short
+// contractions, [1544, 3268] x 64: 36 us; 64 x 64 tiles 19).
 // us, 16 / 32 / 64 / 128: [512, 1024] x 5504 - / 63 / 105 / 349 (too few tiles for the large ones), [512, 5504] x 1024 - / 75 / 62 / 79,
-// [2048, 2048] x 2048 - / 175 / 144 / 149, [4096, 4096] x 4096 - / 1245 / 1069 / 998.  Rings of
-// three or four shallower slots measured within 5 % of these (128: three slots slower, 1049; 64: four 32-deep slots 1058; 32: four
-// 64-deep slots 1260).
+// [2048, 2048] x 2048 - / 175 / 144 / 149, [4096, 4096] x 4096 - / 1245 / 1069 / 998.  Rings of three or four shallower slots
+// measured within 5 % of these (128: three slots slower, 1049; 64: four 32-deep slots 1058; 32: four 64-deep slots 1260).
 static int f32_tile(int M, int N, int K, int batch) {
   struct Tile { int t; double one_k, one, two_k, two, share; };
-  static const Tile tiles[] = {{128, 0.0614, 6.3, 0.1226, 10.9, 1.0}, {64, 0.0184, 2.4, 0.0347, 4.4, 1.0},
-                               {32, 0.0054, 1.8, 0.0100, 2.8, 1.0}, {16, 0.0017, 0.9, 0.0040, 1.3, 0.7}};
+  static const Tile tiles[] = {{16, 0.0017, 0.9, 0.0040, 1.3, 0.7}, {32, 0.0054, 1.8, 0.0100, 2.8, 1.0},
+                               {64, 0.0184, 2.4, 0.0347, 4.4, 1.0}, {128, 0.0614, 6.3, 0.1226, 10.9, 1.0}};
   int best = 0;
   double best_time = 1e30;
   for (const Tile& x : tiles) {
@@ -1633,7 +1634,7 @@ static int f32_tile(int M, int N, int K, int batch) {
     const double one = x.one_k * K + x.one, two = x.two_k * K + x.two;
     const double share = x.share + (1.0 - x.share) * (double)(r - 256) / 256;       // (16 x 16: 0.7 of the difference at 257)
     const double time = (double)(n / 512) * two + (r == 0 ? 0. : r <= 256 ? one : one + (two - one) * share);
-    if (time < best_time) { best_time = time; best = x.t; }
+    if (time < 0.95 * best_time) { best_time = time; best = x.t; }
   }
   return best;
 }

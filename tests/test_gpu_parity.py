@@ -678,7 +678,9 @@ def test_fused_attention_backward_on_many_workgroups(seq, nb, H, dh, causal, reb
 SCORE_TILES = [
     (64, 128, 2, 16, "f32"),      # fp32: 16 x 16 read by 32 x 32
     (136, 128, 3, 13, "f32"),     # 32 by 64, ragged
-    (80, 256, 3, 13, "f32"),      # 16 by 64, ragged
+    (80, 256, 3, 13, "f32"),      # 32 by 32, ragged
+    (24, 128, 5, 13, "f32"),      # 16 by 64, ragged
+    (264, 256, 1, 41, "f32"),     # 32 by 128, ragged
     (568, 256, 1, 24, "f32"),     # 64 by 128, ragged
     (128, 64, 4, 16, "f32"),      # 64 by 32
     (256, 64, 4, 16, "f32"),      # 128 by 64
