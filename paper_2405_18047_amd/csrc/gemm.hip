@@ -1271,7 +1271,13 @@ static hipError_t launch_bf16_causal_pair(const GemmParams& p0, int batch, hipSt
 //     64 x 64 on four 64-deep slots     0.0047   1.3   "                     0.0071
 //   but at least the time of reading both operands once at 4.9 TB/s plus 8.4;
 //   outputs of at most 256 tiles of 32 x 32 can run on gemm_bf16_small_kernel: 0.0018 K + 3.0;
-//   slices add 3.8 (the second launch) and 0.30 per MB of partial products, and must gain 12 %.
+//   slices add 3.8 (the second launch) and 0.30 per MB of partial products, and must gain 12 % (3 % up to 128 rows).
+// Up to 128 rows the weight is read for one row of tiles, from HBM, and the tiles differ in the rate at which they
+// fetch it: 5.9 TB/s on 128 x 128 tiles and 4.5 on 64 x 64 ones where its columns are contiguous (pieces of 256 and of 128 bytes),
+// 4.9 on both where the contraction is; each has its own start (`start`, us), and rings of few slots take longer per index
+// (`thin`).  Fitted to 510 products, M 8-128, N 256-24000, K 64-16000, weights that no cache holds, on all tiles and slices (11 %
+// rms): the choice costs 2 % more than the fastest on average, 8 with the constants above, which did not tell the tiles apart
+// ([64, 22016] x 4096 (NN) 58.7 us on 64 x 64 tiles, 44.9 on 128 x 128; [16, 17072] x 5952 61 and, on 128 x 128 in three slices, 47).
 // The ring of 32-deep slots starts a short contraction sooner and is ahead up to K = 450 or so: [1688, 1560] x 400 9.4 us,
 // 9.7 on the 64-deep ring; [376, 8840] x 320 8.8, 9.0; [1024, 4096] x 512 10.2, 10.0.  Two 64-deep slots need a second
 // workgroup to cover their latency (the same shapes 10.2, 9.3, 10.9), so they are left out up to one per compute unit.
@@ -1285,34 +1291,37 @@ static hipError_t launch_bf16_causal_pair(const GemmParams& p0, int batch, hipSt
 // [1024, 4096] x 4096 43 us on 128 x 128 tiles against 54 for the best split.
 enum ProductTile { T128_DEEP, T256_NARROW, T256, T128_PAIR, T64, T128_SHALLOW, T32 };
 static bool one_round(int M, int N) { return (long)((M + 255) / 256) * ((N + 255) / 256) <= 256; }
-static SplitPlan product_plan(int M, int N, int K, bool allow_split) {
-  struct Tile { int bm, bn, per_cu; double c1, c2, fixed; };
-  static const Tile tiles[] = {{128, 128, 1, 0.0091, 0., 3.0}, {256, 192, 1, 0.0167, 0., 8.0}, {256, 256, 1, 0.0197, 0., 9.7},
-                               {128, 128, 2, 0.0126, 0.0188, 1.5}, {64, 64, 2, 0.0047, 0.0071, 1.3}, {128, 128, 1, 0.0112, 0., 2.05}};
+static SplitPlan product_plan(int layout, int M, int N, int K, bool allow_split) {
+  struct Tile { int bm, bn, per_cu; double c1, c2, fixed, thin, start; };
+  static const Tile tiles[] = {{128, 128, 1, 0.0091, 0., 3.0, 1.04, 4.9}, {256, 192, 1, 0.0167, 0., 8.0, 0., 0.},
+                               {256, 256, 1, 0.0197, 0., 9.7, 0., 0.}, {128, 128, 2, 0.0126, 0.0188, 1.5, 1.17, 5.4},
+                               {64, 64, 2, 0.0047, 0.0071, 1.3, 1.3, 3.9}, {128, 128, 1, 0.0112, 0., 2.05, 1.25, 4.75}};
   static const int slices[] = {1, 2, 3, 4, 5, 6, 8, 12, 16};
-  const double memory = 2e-6 * ((double)N * K + (double)M * K) / 4.9 + 8.4;
+  const double bytes = 2e-6 * ((double)N * K + (double)M * K);
+  const bool thin = M <= 128, nn = layout == NN;
   SplitPlan best{T64, 1, K, 0};
   double best_time = 1e30;
   const bool half_lines = K % 64 != 0;
   if ((long)((M + 31) / 32) * ((N + 31) / 32) <= 256) {
-    best_time = 0.0018 * K + 3.0;
+    best_time = !thin ? 0.0018 * K + 3.0 : (nn ? 0.0022 : 0.0014) * K + 2.9 + 0.26e-6 * N * K;
     best.tile = T32;
   }
   for (int i = 0; i < 6; i++) {
     const Tile& t = tiles[i];
     if (t.bm == 256 && M < 192) continue;
+    const double per_index = thin ? t.thin : 1., memory = thin ? bytes / (!nn ? 4.9 : i == T64 ? 4.5 : 5.9) + t.start : bytes / 4.9 + 8.4;
     for (int sp : slices) {
       if (sp > 1 && (!allow_split || K / sp < 256 || i == T128_SHALLOW)) break;
       const int slice = sp == 1 ? K : ((K + 63) / 64 + sp - 1) / sp * 64, split = sp == 1 ? 1 : (K + slice - 1) / slice;
       const long n = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * split;
       if (i == T128_PAIR && n <= 256) continue;
       const double lines1 = half_lines && i == T64 ? 1.08 : 1., lines2 = half_lines && i == T64 ? 1.38 : 1.;
-      const double one = slice * t.c1 * lines1 + t.fixed, two = slice * t.c2 * lines2 + t.fixed;
+      const double one = slice * t.c1 * per_index * lines1 + t.fixed, two = slice * t.c2 * per_index * lines2 + t.fixed;
       double time;
       if (t.per_cu == 1) time = (double)((n + 255) / 256) * one;
       else time = (double)(n / 512) * two + (n % 512 == 0 ? 0. : n % 512 <= 256 ? one : two);
       time = (time < memory ? memory : time) + 0.02 * time;       // (equally memory-bound: the one that computes faster)
-      if (split > 1) time = 1.12 * (time + 3.8 + 0.303e-6 * split * M * N * sizeof(float));
+      if (split > 1) time = (thin ? 1.03 : 1.12) * (time + 3.8 + 0.303e-6 * split * M * N * sizeof(float));
       if (time < best_time) {
         best_time = time;
         best = SplitPlan{i, split, slice, split > 1 ? kSplitHead + (size_t)split * M * N * sizeof(float) : 0};
@@ -1324,7 +1333,7 @@ static SplitPlan product_plan(int M, int N, int K, bool allow_split) {
 SplitPlan gemm_split_plan(int dtype, int layout, int M, int N, int K, int out_f32, int batch) {
   const SplitPlan none{0, 1, 0, 0};
   if (dtype != 1 || out_f32 || batch != 1 || layout == TN || !one_round(M, N)) return none;
-  const SplitPlan plan = product_plan(M, N, K, true);
+  const SplitPlan plan = product_plan(layout, M, N, K, true);
   return plan.split > 1 ? plan : none;
 }
 
@@ -1699,8 +1708,8 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   const long tiles_big = (long)tiles_m * tiles_n * g.batch;
   const bool big = large_tiles(g);
   if (!g.out_f32 && g.batch == 1 && g.causal == CAUSAL_NONE && !g.delta && g.layout != TN && one_round(g.M, g.N)) {
-    SplitPlan plan = product_plan(g.M, g.N, g.K, g.ws && reinterpret_cast<uintptr_t>(g.ws) % 256 == 0);
-    if (plan.bytes > g.ws_bytes) plan = product_plan(g.M, g.N, g.K, false);
+    SplitPlan plan = product_plan(g.layout, g.M, g.N, g.K, g.ws && reinterpret_cast<uintptr_t>(g.ws) % 256 == 0);
+    if (plan.bytes > g.ws_bytes) plan = product_plan(g.layout, g.M, g.N, g.K, false);
     return g.layout == NN ? dispatch_product<false>(p, plan, g.ws, s) : dispatch_product<true>(p, plan, g.ws, s);
   }
   if (!g.out_f32 && g.batch == 1 && g.causal == CAUSAL_NONE && !g.delta && g.layout != TN && narrow_tiles_pay(g.M, g.N, g.K))
@@ -1741,7 +1750,7 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   const bool has_narrow = (g.out_f32 && g.layout == TN) || (!g.out_f32 && g.layout != TN && !g.delta);
   auto run_rest = [&](const GemmParams& q) -> hipError_t {
     if (!g.out_f32 && g.layout != TN && !g.delta) {
-      const SplitPlan plan = product_plan(q.M, q.N, q.K, false);
+      const SplitPlan plan = product_plan(g.layout, q.M, q.N, q.K, false);
       return g.layout == NN ? dispatch_product<false>(q, plan, nullptr, s) : dispatch_product<true>(q, plan, nullptr, s);
     }
     const long t192 = (long)((q.M + 255) / 256) * ((q.N + 191) / 192);

@@ -157,6 +157,7 @@ def test_gemm_with_split_contraction(layout, mnk):
     (1688, 1560, 400), (2040, 2040, 8),                           # the same with a short contraction
     (2000, 3464, 1160), (360, 4088, 5512),                        # 128 x 128 tiles, two per compute unit; few, long
     (264, 22008, 1032), (264, 11016, 4104),                       # 256 x 192 tiles; in slices
+    (40, 11000, 4104), (24, 16696, 6088), (8, 4104, 4104),        # one row of tiles: by layout 128 x 128 or 64 x 64, or 32 x 32, in slices
     (1032, 4088, 8200), (4088, 4088, 1096)])                      # 256 x 256 tiles in slices (ragged last slice); unsliced
 def test_gemm_tile_and_slice_choices(layout, mnk):
     """Storage-type products of at most one round of large tiles: every tile size, with and without the contraction cut
