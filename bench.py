@@ -538,7 +538,7 @@ def kernel_rates(shape, tbp, torch, dev, tdt, probe=False) -> dict:
         timeit(mk_rope, 4 * T * d * e, "rope_p1")
         if shape.dtype == "bf16" and shape.head_dim in (64, 128):
             # the softmax backward of the hot path lives inside the fused attention backward (no S x S tensor is read
-            # or written by it): that kernel pair is what is timed here.  Algorithmic bytes: q, k, v, o, do in, dq, dk,
+            # or written by it): those kernels are what is timed here.  Algorithmic bytes: q, k, v, o, do in, dq, dk,
             # dv out (8 T d e) + the row log-sum-exp; FLOPs: five products of 2 S^2 dh per (sequence, head), the causal
             # half of which is live.
             nbytes = 8 * T * d * e + B * H * S * 4
@@ -556,8 +556,9 @@ def kernel_rates(shape, tbp, torch, dev, tdt, probe=False) -> dict:
             r = res["attention_p1_fused"]
             r["TFLOP/s_live_causal_half"] = round(flops_live / (r["us"] * 1e-6) / 1e12, 1)
             r["frac_of_bf16_mfma_peak"] = round(r["TFLOP/s_live_causal_half"] / PEAK_BF16_TFLOPS, 4)
-            r["what"] = ("fused attention backward (softmax backward inside), per layer and micro-batch: row dot + dK/dV/dS^T "
-                         "kernel + dQ product; GB/s on the algorithmic bytes (the pair also moves dS^T out and back)")
+            r["what"] = ("fused attention backward (softmax backward inside), per layer and micro-batch: row dot + dK/dV kernel "
+                         "+ dQ, by the recompute pass on large grids, else as a product with the dS^T that the first kernel "
+                         "writes; GB/s on the algorithmic bytes")
         else:
             causal_bytes = 3 * B * H * (S * (S + 1) // 2) * e      # live lower triangle only
 
