@@ -955,11 +955,22 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(GemmParams p) {
   auto row_of = [&](int i, int e) {
     return m0 + (wm * TM + i) * 32 + (WK > 1 ? 8 * wave + 4 * (lane >> 5) + e : 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3));
   };
-  if (p.accumulate && !R && !delta) {
-    // the old values of an MFMA tile are requested together: one at a time, between stores that the compiler must take to
-    // alias the next load, they made an accumulating [2616, 4084] x 64 product 66 us; now 38
+  // What an epilogue reads (old values, a residual, or the probabilities and delta of the softmax backward) is requested for a
+  // whole MFMA tile at a time: one value at a time, between stores that the compiler must take to alias the next load, old
+  // values made an accumulating [2616, 4084] x 64 product 66 us (now 38), and P and delta the 16 x [512, 512] x 64 product of a
+  // score gradient 40 us (now 15).  The overwriting kernel keeps a branch of its own: sharing this one cost it 20-30 %.
+  if ((p.accumulate || R) && !(p.accumulate && R && !delta)) {
+    const float* const src = R ? R : C;
 #pragma unroll
-    for (int i = 0; i < TM; i++)
+    for (int i = 0; i < TM; i++) {
+      float dl[NE];
+      if (delta) {
+#pragma unroll
+        for (int e = 0; e < NE; e++) {
+          const int row = row_of(i, e);
+          dl[e] = delta[(long)(row < p.M ? row : m0) * p.ldd];
+        }
+      }
 #pragma unroll
       for (int j = 0; j < TN; j++) {
         const int col = n0 + (wn * TN + j) * 32 + (lane & 31);
@@ -967,14 +978,17 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(GemmParams p) {
 #pragma unroll
         for (int e = 0; e < NE; e++) {              // (without branches: outside the output the tile's first element)
           const int row = row_of(i, e);
-          old[e] = C[row < p.M && col < p.N ? (long)row * p.ldc + col : (long)m0 * p.ldc + n0];
+          old[e] = src[row < p.M && col < p.N ? (long)row * p.ldc + col : (long)m0 * p.ldc + n0];
         }
 #pragma unroll
         for (int e = 0; e < NE; e++) {
           const int row = row_of(i, e);
-          if (row < p.M && col < p.N) C[(long)row * p.ldc + col] = old[e] + p.alpha * acc[i][j][e];
+          const float v = p.alpha * acc[i][j][e];
+          if (row < p.M && col < p.N)
+            C[(long)row * p.ldc + col] = !delta ? old[e] + v : (!p.delta_causal || col <= row) ? old[e] * (v - dl[e]) : 0.f;
         }
       }
+    }
     return;
   }
 #pragma unroll
@@ -988,11 +1002,9 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(GemmParams p) {
         if (row >= p.M || col >= p.N) continue;
         const long idx = (long)row * p.ldc + col;
         float v = p.alpha * acc[i][j][e];
-        if (delta) {
-          v = (!p.delta_causal || col <= row) ? R[idx] * (v - delta[(long)row * p.ldd]) : 0.f;
-        } else {
-          if (p.accumulate) v += C[idx];
-          if (R) v += R[idx];
+        if (p.accumulate) {
+          v += C[idx];
+          v += R[idx];
         }
         C[idx] = v;
       }
