@@ -100,10 +100,13 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& c, int u) {
 // start cost more than the overlap gives.  us, ahead / not: B 32, H 32, dh 128, S 64 17.3 / 16.7, S 128 28.1 / 27.0, S 256 63.9 / 63.2;
 // B 1, H 8, dh 64, S 192 5.94 / 5.62, S 256 6.80 / 6.58; beyond that either is ahead by 1-3 % up to S 512 (B 8, H 16, dh 128, S 264
 // 13.0 / 13.3, S 512 19.4 / 19.7).  (Skipping the last scores by a branch in the pinned order instead: spilled registers.)
-template <int DH, bool AHEAD>
+// SPLIT = 2, for grids that leave compute units idle: 64 queries per workgroup, and two waves per 32 queries, each on one
+// 32-key tile of every block, whose sums meet at the end: twice the workgroups with half the chain each, for twice the copies
+// per query.  (Computing scores ahead gains nothing here: 20.7 and 21.1 us at B 1, H 32, dh 128, S 1024, 11.5 and 11.0 at S 512.)
+template <int DH, bool AHEAD, int SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_fwd_kernel(AttnParams p) {
   using HT = HeadTile<DH>;
-  constexpr int KS = DH / 16, DT = DH / 32, BKV = 64, BQ = 128;
+  constexpr int KS = DH / 16, DT = DH / 32, BKV = 64, BQ = 128 / SPLIT, QW = 4 / SPLIT, NT = 2 / SPLIT;
   constexpr int IMG = BKV * HT::RB, SLOT = 2 * IMG;
   constexpr int NCH = IMG / 1024 / 4;                 // copies per wave per operand per block
 
@@ -117,7 +120,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // causal masking the work of a block grows with its index, and the blocks still to start near the end are short ones
   const int qb = (int)gridDim.y - 1 - (int)blockIdx.y;
   const int h = (int)blockIdx.x % p.H, b = (int)blockIdx.x / p.H;
-  const int q0 = qb * BQ, qw0 = q0 + 32 * wave, query = qw0 + ql;
+  const int wq = SPLIT == 1 ? wave : wave % QW, wk = SPLIT == 1 ? 0 : wave / QW;      // which 32 queries, which 32-key tile of every block (SPLIT 2)
+  const int q0 = qb * BQ, qw0 = q0 + 32 * wq, query = qw0 + ql;
   const int d = p.H * DH;
   const long tok0 = (long)b * p.S;
 
@@ -127,7 +131,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   {
     const u32x4 dq = make_desc(p.qkv + (tok0 + q0) * p.ld_qkv + h * DH, (uint32_t)((long)(p.S - q0) * p.ld_qkv * 2));
 #pragma unroll
-    for (int i = 0; i < 2 * NCH; i++) {
+    for (int i = 0; i < 2 * NCH / SPLIT; i++) {
       int row; unsigned go;
       HT::plan(wave + 4 * i, lane, p.ld_qkv, row, go);
       dma16(lds0 + SLOT + (wave + 4 * i) * 1024, dq, q0 + row < p.S ? go : kOob);
@@ -164,21 +168,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // ---- this lane's query row as B operand of S^T = K Q^T: 8 consecutive head-dim values per k-step
   bf16x8 qf[KS];
 #pragma unroll
-  for (int s = 0; s < KS; s++) qf[s] = HT::rows_frag(lds + SLOT, fo, 32 * wave, s);
-  f32x16 sa[2], sb[2];                 // S^T of the block whose softmax is in work, and of the next one
-  auto scores = [&](f32x16 (&st)[2], lds_u8* kimg) {
+  for (int s = 0; s < KS; s++) qf[s] = HT::rows_frag(lds + SLOT, fo, 32 * wq, s);
+  f32x16 sa[NT], sb[NT];               // S^T of the block whose softmax is in work, and of the next one
+  const int wk_rows = 32 * wk * HT::RB;          // (SPLIT 2: this wave's tile of the K and V images)
+  auto scores = [&](f32x16 (&st)[NT], lds_u8* kimg) {
 #pragma unroll
-    for (int kt = 0; kt < 2; kt++)
+    for (int kt = 0; kt < NT; kt++)
 #pragma unroll
       for (int e = 0; e < 16; e++) st[kt][e] = 0.f;
 #pragma unroll
     for (int s = 0; s < KS; s++)
 #pragma unroll
-      for (int kt = 0; kt < 2; kt++)
+      for (int kt = 0; kt < NT; kt++)
         st[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(HT::rows_frag(kimg, fo, 32 * kt, s), qf[s], st[kt], 0, 0, 0);
   };
   if constexpr (AHEAD) {
-    scores(sa, lds);
+    scores(sa, lds + wk_rows);
     __syncthreads();                   // every wave has its query row: the second slot is free
     if (nblk > 1) issue(1, 0);
   }
@@ -186,30 +191,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // Block j: softmax of its scores (st) and O^T += V^T P^T, with the scores of block j + 1 (nx) computed on the way.
   // The order of the instructions is pinned: the MFMAs of the next block's scores and the first three quarters of the PV
   // MFMAs each carry a share of the exponentials, so that the matrix pipe and the vector ALU work side by side.
-  auto block = [&](f32x16 (&st)[2], f32x16 (&nx)[2], int j) {
+  auto block = [&](f32x16 (&st)[NT], f32x16 (&nx)[NT], int j) {
     wait_vmem<0>();
     __syncthreads();                   // K of block j + 1 and V of block j have landed; every wave is done with block j - 1
     if (AHEAD ? j + 2 < nblk : j + 1 < nblk) issue(AHEAD ? j + 2 : j + 1, 0);      // (not AHEAD: K of block j has landed)
     if (j + 1 < nblk) issue(j + 1, 1);
-    const int kv0 = j * BKV;
+    const int kv0 = j * BKV + 32 * wk;
     if (p.causal && kv0 > qw0 + 31) return;            // every key of the block is after every query of this wave
-    lds_u8* const kimg = lds + ((j + 1) & 1) * SLOT;   // (after the last block: an older one, whose scores nobody uses)
-    lds_u8* const vimg = lds + (j & 1) * SLOT + IMG;
-    bf16x8 kf[2][2];
+    if (SPLIT == 2 && kv0 >= p.S) return;              // no key at all (and so none in any later block)
+    lds_u8* const kimg = lds + ((j + 1) & 1) * SLOT + wk_rows;   // (after the last block: an older one, whose scores nobody uses)
+    lds_u8* const vimg = lds + (j & 1) * SLOT + IMG + wk_rows;
+    bf16x8 kf[2][NT];
     if constexpr (AHEAD) {
 #pragma unroll
       for (int s = 0; s < 2; s++)
 #pragma unroll
-        for (int kt = 0; kt < 2; kt++) kf[s][kt] = HT::rows_frag(kimg, fo, 32 * kt, s);
+        for (int kt = 0; kt < NT; kt++) kf[s][kt] = HT::rows_frag(kimg, fo, 32 * kt, s);
     } else {
-      scores(st, lds + (j & 1) * SLOT);
+      scores(st, lds + (j & 1) * SLOT + wk_rows);
     }
     // keys beyond the query (causal) or beyond the sequence do not take part (blocks on the diagonal / at the end only)
-    if ((p.causal && kv0 + BKV - 1 > qw0) || kv0 + BKV > p.S) {
+    if ((p.causal && kv0 + 32 * NT - 1 > qw0) || kv0 + 32 * NT > p.S) {
       const int last = p.causal ? (query < p.S - 1 ? query : p.S - 1) : p.S - 1;      // last key this lane's query sees
       const int rel = last - kv0 - 4 * g;
 #pragma unroll
-      for (int kt = 0; kt < 2; kt++)
+      for (int kt = 0; kt < NT; kt++)
 #pragma unroll
         for (int e = 0; e < 16; e++)
           st[kt][e] = (32 * kt + 8 * (e >> 2) + (e & 3) > rel) ? -INFINITY : st[kt][e];
@@ -223,7 +229,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     constexpr float kSlack = 8.f;
     float mx = -INFINITY;
 #pragma unroll
-    for (int kt = 0; kt < 2; kt++)
+    for (int kt = 0; kt < NT; kt++)
 #pragma unroll
       for (int e = 0; e < 16; e++) mx = fmaxf(mx, st[kt][e]);
     mx *= p.scale_log2e;                                // scale > 0: the maximum commutes with it
@@ -238,8 +244,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int e = 0; e < 16; e++) ot[t][e] *= alpha;
       m = mnew;
     }
-    bf16x8 pb[4], vf[DT];
-    auto elements = [&](int e0, int e1) {               // exponentials of elements e0 .. e1 - 1 of the lane's 32
+    bf16x8 pb[2 * NT], vf[DT];
+    auto elements = [&](int e0, int e1) {               // exponentials of elements e0 .. e1 - 1 of the lane's 16 NT
 #pragma unroll
       for (int e = e0; e < e1; e++) {
         const float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e >> 4][e & 15], p.scale_log2e, -m));
@@ -248,11 +254,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         if (e % 8 == 7) pb[e >> 3] = pack8(st[e >> 4], (e >> 3) & 1);
       }
     };
-    constexpr int NA = 2 * KS, EA = 18;        // MFMAs of the scores; elements done beside them, the rest beside 3 PV k-steps
-    static_assert(EA >= 8 && EA + (32 - EA) / 3 >= 16 && EA + (32 - EA) * 2 / 3 >= 24, "P must be ready in time");
+    // MFMAs of the scores; elements done beside them, the rest beside all PV k-steps but the last
+    constexpr int NA = NT * KS, NE = 16 * NT, EA = NT == 2 ? 18 : 10, PK = 2 * NT, PE = PK - 1;
+    static_assert(EA >= 8 && EA + (NE - EA) / PE >= 16 && (NT == 1 || EA + (NE - EA) * 2 / PE >= 24), "P must be ready in time");
     if constexpr (AHEAD) {
 #pragma unroll
-      for (int kt = 0; kt < 2; kt++)
+      for (int kt = 0; kt < NT; kt++)
 #pragma unroll
         for (int e = 0; e < 16; e++) nx[kt][e] = 0.f;
     }
@@ -261,7 +268,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     if constexpr (AHEAD) {
 #pragma unroll
       for (int i = 0; i < NA; i++) {
-        const int s = i >> 1, kt = i & 1;
+        const int s = i / NT, kt = i % NT;
         nx[kt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[s & 1][kt], qf[s], nx[kt], 0, 0, 0);
         if (s + 2 < KS) kf[s & 1][kt] = HT::rows_frag(kimg, fo, 32 * kt, s + 2);
         if (i >= NA - DT) vf[i - (NA - DT)] = HT::cols_frag(vimg, fo, 0, 0, i - (NA - DT));
@@ -274,11 +281,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       elements(0, EA);
     }
 #pragma unroll
-    for (int i = 0; i < 4 * DT; i++) {
+    for (int i = 0; i < PK * DT; i++) {
       const int ku = i / DT, t = i % DT;
       ot[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t], pb[ku], ot[t], 0, 0, 0);
-      if (ku < 3) vf[t] = HT::cols_frag(vimg, fo, 32 * ((ku + 1) >> 1), (ku + 1) & 1, t);
-      if (ku < 3) elements(EA + (32 - EA) * i / (3 * DT), EA + (32 - EA) * (i + 1) / (3 * DT));
+      if (ku < PE) vf[t] = HT::cols_frag(vimg, fo, 32 * ((ku + 1) >> 1), (ku + 1) & 1, t);
+      if (ku < PE) elements(EA + (NE - EA) * i / (PE * DT), EA + (NE - EA) * (i + 1) / (PE * DT));
       __builtin_amdgcn_sched_barrier(0);
     }
     __builtin_amdgcn_s_setprio(0);
@@ -295,9 +302,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   __syncthreads();
   constexpr int EROW = DH * 2 + 16;
   static_assert(BQ * EROW <= 2 * SLOT, "the output tile must fit in the ring");
-  lds_u8* const erow = lds + 32 * wave * EROW;
+  lds_u8* const erow = lds + 32 * wq * EROW;
+  float lq = (l[0] + l[1]) + xor32(l[0] + l[1]);
+  if constexpr (SPLIT == 2) {
+    // the two waves of a query: what the second one summed, brought to the common reference point, joins the first one's.
+    // (The first tile of a row always has a visible key; a second wave that saw none has m = -inf and adds nothing.)
+    static_assert(BQ * EROW + 1024 <= SLOT && QW * DT * 4096 <= SLOT, "output tile, statistics and partial sums side by side");
+    LDS_AS float* const part = reinterpret_cast<LDS_AS float*>(lds + SLOT) + wq * (DT * 1024);
+    LDS_AS float* const stat = reinterpret_cast<LDS_AS float*>(lds + BQ * EROW) + wq * 128;
+    if (wk == 1) {
+#pragma unroll
+      for (int t = 0; t < DT; t++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) part[(t * 16 + e) * 64 + lane] = ot[t][e];
+      stat[lane] = m;
+      stat[64 + lane] = lq;
+    }
+    __syncthreads();
+    if (wk == 1) return;
+    const float m1 = stat[lane], mc = fmaxf(m, m1);
+    const float f0 = __builtin_amdgcn_exp2f(m - mc), f1 = __builtin_amdgcn_exp2f(m1 - mc);
+    m = mc;
+    lq = lq * f0 + stat[64 + lane] * f1;
+#pragma unroll
+    for (int t = 0; t < DT; t++)
+#pragma unroll
+      for (int e = 0; e < 16; e++) ot[t][e] = ot[t][e] * f0 + part[(t * 16 + e) * 64 + lane] * f1;
+  }
   {
-    const float lq = (l[0] + l[1]) + xor32(l[0] + l[1]);
     const float inv = 1.f / lq;
 #pragma unroll
     for (int t = 0; t < DT; t++)
@@ -336,6 +368,7 @@ struct AttnBwdParams {
   const float* lse;                    // [B, H, S] from the forward
   const float* delta;                  // [B*S, H]: rowsum(dout * out) per (token, head)
   bf16_t* dqkv; long ld_dqkv;          // dk and dv blocks are written (columns H*DH.. and 2*H*DH..)
+  const float2* rope;                  // rotation table [S][DH / 2]: dk is rotated back; or nullptr
   bf16_t* dst;                         // dS^T per (b, h) in panels of 128 queries: [ceil(S / 128)][S keys][128 queries]
   int B, H, S, causal;
   float scale, scale_log2e;
@@ -352,7 +385,10 @@ struct AttnBwdParams {
 // of its neighbours.  One workgroup barrier per 32-query tile; the hand-over buffers and the query-step images are
 // double / triple buffered so that neither side ever waits for the other beyond that barrier.  The right waves also
 // issue all asynchronous copies (they have no other vector-memory operations, so their copy counter is exact).
-template <int DH, bool WRITE_DST>
+// KEYS = 64, for grids that leave compute units idle: two left waves per 32 keys, each on one tile of a 64-query step, and the
+// right waves take both tiles per iteration: half the iterations per workgroup, twice the workgroups (and the transposed
+// fragments of Q and dO, read for half the keys, weigh twice as much: about 10 % slower per key and query).
+template <int DH, bool WRITE_DST, int KEYS>
 __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p) {
   using HT = HeadTile<DH>;
   constexpr int KS = DH / 16, DT = DH / 32, BQ = 64;
@@ -361,6 +397,8 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
   constexpr int OPS = 2 * NCH + 1;                            // vector-memory operations of one issue(), per right wave
   constexpr int HAND = 4 * 4096;                              // one hand-over buffer: 4 wave pairs x 64 lanes x 64 bytes
   constexpr int HALF = 32 * HT::RB;                           // the second tile's rows inside an image
+  constexpr int KB = KEYS / 32, TPI = 4 / KB;                 // 32-key blocks of the workgroup; 32-query tiles per iteration
+  static_assert((KEYS == 128 || KEYS == 64) && !(WRITE_DST && KEYS != 128), "key block");
 
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
   lds_u8* const lds = LDS_PTR(unsigned char, smem_raw);
@@ -371,18 +409,19 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
   const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int right = wave8 >> 2, wave = wave8 & 3;             // role, and which 32 keys of the block
   const int kb = blockIdx.y;
+  const int kblk = KB == 4 ? wave : wave % KB, tq_left = KB == 4 ? 0 : wave / KB;      // a left wave's 32 keys, and which tile of an iteration
   const int h = (int)blockIdx.x % p.H, b = (int)blockIdx.x / p.H;
-  const int kv0 = kb * 128, kw0 = kv0 + 32 * wave, key = kw0 + kl;
+  const int kv0 = kb * KEYS, kw0 = kv0 + 32 * kblk, key = kw0 + kl;
   const int d = p.H * DH;
   const long tok0 = (long)b * p.S;
   const long bh = (long)b * p.H + h;
   const typename HT::Offsets fo = HT::offsets(lane);
   const int step0 = p.causal ? kv0 / BQ : 0;                  // queries before the first key of the block see none of it
   const int nstep = (p.S + BQ - 1) / BQ;
-  const int t0 = 2 * step0, nt = 2 * (nstep - step0);         // first tile, number of tiles
+  const int t0 = 2 * step0, nt = 2 * (nstep - step0) / TPI;   // first tile, number of iterations
   typedef LDS_AS float lds_f32;
   lds_u8* const my_hand = hand + wave * 4096 + lane * 16;     // + buffer * HAND + 1024 * {p0, p1, s0, s1}
-  constexpr int KVIMG = 128 * HT::RB;                         // image of the block's 128 K (then V) rows
+  constexpr int KVIMG = KEYS * HT::RB;                        // image of the block's K (then V) rows
   lds_u8* const kvimg = lds + 2 * SLOT;
   static_assert(2 * KVIMG <= SLOT + 2 * HAND, "K and V images must fit in the third slot plus the hand-over area");
 
@@ -409,13 +448,13 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
     // right waves copied into the third slot and the hand-over area, which nothing else uses yet
 #pragma unroll
     for (int s = 0; s < KS; s++) {
-      kfb[s] = HT::rows_frag(kvimg, fo, 32 * wave, s);
-      vfb[s] = HT::rows_frag(kvimg + KVIMG, fo, 32 * wave, s);
+      kfb[s] = HT::rows_frag(kvimg, fo, 32 * kblk, s);
+      vfb[s] = HT::rows_frag(kvimg + KVIMG, fo, 32 * kblk, s);
     }
     __syncthreads();                                          // every left wave has its rows: the area is free again
     for (int it = 0; it <= nt; it++) {
       if (it < nt) {
-        const int tile = t0 + it, qt0 = tile * 32;
+        const int tile = t0 + TPI * it + tq_left, qt0 = tile * 32;
         lds_u8* const slot = lds + (((tile >> 1) - step0) % 3) * SLOT;
         lds_u8* const qimg = slot + (tile & 1) * HALF;
         lds_u8* const dimg = qimg + IMG;
@@ -460,7 +499,7 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
         for (int u = 0; u < 2; u++)
 #pragma unroll
           for (int t = 0; t < 8; t++) { kp[u][t] = (bf16_t)pv[8 * u + t]; ks[u][t] = (bf16_t)sv[8 * u + t]; }
-        lds_u8* const out = my_hand + (tile & 1) * HAND;
+        lds_u8* const out = my_hand + (it & 1) * HAND;
         *reinterpret_cast<LDS_AS bf16x8*>(out) = kp[0];
         *reinterpret_cast<LDS_AS bf16x8*>(out + 1024) = kp[1];
         *reinterpret_cast<LDS_AS bf16x8*>(out + 2048) = ks[0];
@@ -527,9 +566,9 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
   // A right wave owns 32 head-dim columns (its index) of dV^T and dK^T for all four key blocks of the workgroup: it then
   // reads only its quarter of the Q and dO tiles as transposed fragments (the expensive reads) and all four left waves'
   // P and dS (cheap, lane-contiguous).  With head_dim 64 waves 2 and 3 have no columns and only copy.
-  f32x16 dvt[4], dkt[4];
+  f32x16 dvt[KB], dkt[KB];
 #pragma unroll
-  for (int t = 0; t < 4; t++)
+  for (int t = 0; t < KB; t++)
 #pragma unroll
     for (int e = 0; e < 16; e++) { dvt[t][e] = 0.f; dkt[t][e] = 0.f; }
   const bool has_cols = wave < DT;
@@ -548,7 +587,7 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
     const uint32_t bytes = (uint32_t)((long)(p.S - kv0) * p.ld_qkv * 2);
     const u32x4 dk = make_desc(kb0, bytes), dv = make_desc(kb0 + d, bytes);
 #pragma unroll
-    for (int i = 0; i < 2 * NCH; i++) {
+    for (int i = 0; i < NCH * KEYS / 64; i++) {
       int row; unsigned go;
       HT::plan(wave + 4 * i, lane, p.ld_qkv, row, go);
       const unsigned off = kv0 + row < p.S ? go : kOob;
@@ -562,43 +601,54 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
   __syncthreads();
   __syncthreads();                                            // the left waves have read their K and V rows
   for (int it = 0; it <= nt; it++) {
-    const int tp = t0 + it;                                   // the tile the left waves are on
     if (it > 0 && has_cols) {
-      const int tile = tp - 1;
-      lds_u8* const qimg = lds + (((tile >> 1) - step0) % 3) * SLOT + (tile & 1) * HALF;
-      lds_u8* const dimg = qimg + IMG;
-      // this wave's 32 head-dim columns of dO^T and Q^T (two k-steps of 16 queries), then every key block's P and dS, each
-      // fetched one key block ahead of its MFMAs (pinned, as on the left)
-      bf16x8 fo_d[2], fo_q[2], kp[2][2], ks[2][2];
-      const lds_u8* const in = hand + (tile & 1) * HAND + lane * 16;
-      auto fetch = [&](int kbk) {
 #pragma unroll
-        for (int u = 0; u < 2; u++) {
-          kp[kbk & 1][u] = *reinterpret_cast<const LDS_AS bf16x8*>(in + kbk * 4096 + 1024 * u);
-          ks[kbk & 1][u] = *reinterpret_cast<const LDS_AS bf16x8*>(in + kbk * 4096 + 2048 + 1024 * u);
-        }
-      };
+      for (int tq = 0; tq < TPI; tq++) {
+        const int tile = t0 + TPI * (it - 1) + tq;
+        lds_u8* const qimg = lds + (((tile >> 1) - step0) % 3) * SLOT + (tile & 1) * HALF;
+        lds_u8* const dimg = qimg + IMG;
+        // this wave's 32 head-dim columns of dO^T and Q^T (two k-steps of 16 queries), then every key block's P and dS, each
+        // fetched one key block ahead of its MFMAs (pinned, as on the left)
+        bf16x8 fo_d[2], fo_q[2], kp[2][2], ks[2][2];
+        const lds_u8* const in = hand + ((it - 1) & 1) * HAND + tq * (KB * 4096) + lane * 16;
+        auto fetch = [&](int kbk) {
 #pragma unroll
-      for (int u = 0; u < 2; u++) { fo_d[u] = my_cols(dimg, u); fo_q[u] = my_cols(qimg, u); }
-      fetch(0);
-      __builtin_amdgcn_sched_barrier(0);
+          for (int u = 0; u < 2; u++) {
+            kp[kbk & 1][u] = *reinterpret_cast<const LDS_AS bf16x8*>(in + kbk * 4096 + 1024 * u);
+            ks[kbk & 1][u] = *reinterpret_cast<const LDS_AS bf16x8*>(in + kbk * 4096 + 2048 + 1024 * u);
+          }
+        };
 #pragma unroll
-      for (int kbk = 0; kbk < 4; kbk++) {
-        if (kbk < 3) fetch(kbk + 1);
-#pragma unroll
-        for (int u = 0; u < 2; u++) {
-          dvt[kbk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo_d[u], kp[kbk & 1][u], dvt[kbk], 0, 0, 0);
-          dkt[kbk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo_q[u], ks[kbk & 1][u], dkt[kbk], 0, 0, 0);
-        }
+        for (int u = 0; u < 2; u++) { fo_d[u] = my_cols(dimg, u); fo_q[u] = my_cols(qimg, u); }
+        fetch(0);
         __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kbk = 0; kbk < KB; kbk++) {
+          if (kbk + 1 < KB) fetch(kbk + 1);
+#pragma unroll
+          for (int u = 0; u < 2; u++) {
+            dvt[kbk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo_d[u], kp[kbk & 1][u], dvt[kbk], 0, 0, 0);
+            dkt[kbk] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fo_q[u], ks[kbk & 1][u], dkt[kbk], 0, 0, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
     }
-    // step (tp + 1) / 2 + 1 is what the left waves start two barriers from now, when tp is odd: it was issued three
-    // barriers ago and only the issue after it may still be in flight
-    if (tp & 1) wait_vmem<OPS>();
-    __syncthreads();
-    // after this barrier nobody reads the step before tp / 2 any more (tp even): its slot takes step tp / 2 + 2
-    if (!(tp & 1)) issue((tp >> 1) + 2);
+    if constexpr (TPI == 1) {
+      // the left waves are on tile tp.  Step (tp + 1) / 2 + 1 is what they start two barriers from now, when tp is odd: it was
+      // issued three barriers ago and only the issue after it may still be in flight
+      const int tp = t0 + it;
+      if (tp & 1) wait_vmem<OPS>();
+      __syncthreads();
+      // after this barrier nobody reads the step before tp / 2 any more (tp even): its slot takes step tp / 2 + 2
+      if (!(tp & 1)) issue((tp >> 1) + 2);
+    } else {
+      // a whole step per iteration: the one after the left waves' was issued behind the barrier before, and the one before
+      // it, which the right waves have just finished, leaves its slot to the step after next
+      wait_vmem<0>();
+      __syncthreads();
+      issue(step0 + it + 2);
+    }
   }
   wait_vmem<0>();                                             // (copies past the end: zeros, no traffic)
   __syncthreads();                                            // ... of every wave, before the ring is reused below
@@ -610,11 +660,11 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
   // rows, 16 bytes per lane, 256 contiguous bytes per row.
   constexpr int EROW = DH * 2 + 16;
   lds_u8* const edk = lds;
-  lds_u8* const edv = lds + 128 * EROW;
-  static_assert(2 * 128 * EROW <= 3 * SLOT, "dK and dV tiles must fit in the ring");
+  lds_u8* const edv = lds + KEYS * EROW;
+  static_assert(2 * KEYS * EROW <= 3 * SLOT, "dK and dV tiles must fit in the ring");
   if (has_cols) {
 #pragma unroll
-    for (int kbk = 0; kbk < 4; kbk++)
+    for (int kbk = 0; kbk < KB; kbk++)
 #pragma unroll
       for (int e4 = 0; e4 < 4; e4++) {
         bf16x4 vk, vv;
@@ -630,12 +680,24 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
     constexpr int LPR = DH / 8, RPI = 64 / LPR;               // lanes per row, rows per wave-wide store
     const int rl = lane / LPR, piece = lane % LPR;
 #pragma unroll
-    for (int r0 = 0; r0 < 32; r0 += RPI) {
-      const int row = 32 * wave + r0 + rl;                    // this wave's 32 key rows
+    for (int r0 = 0; r0 < KEYS / 4; r0 += RPI) {
+      const int row = KEYS / 4 * wave + r0 + rl;              // this wave's quarter of the key rows
       const int krow = kv0 + row;
       if (krow < p.S) {
         bf16_t* const out = p.dqkv + (tok0 + krow) * p.ld_dqkv + d + h * DH + 8 * piece;
-        *reinterpret_cast<u32x4*>(out) = *reinterpret_cast<const LDS_AS u32x4*>(edk + row * EROW + 16 * piece);
+        bf16x8 vk = *reinterpret_cast<const LDS_AS bf16x8*>(edk + row * EROW + 16 * piece);
+        if (p.rope) {                                         // rotated back: the other half of the row is in LDS as well
+          const bf16x8 other = *reinterpret_cast<const LDS_AS bf16x8*>(edk + row * EROW + 16 * (piece ^ (LPR / 2)));
+          const float2* const tb = p.rope + (long)krow * (DH / 2) + 8 * (piece & (LPR / 2 - 1));
+          const float sgn = piece < LPR / 2 ? 1.f : -1.f;
+#pragma unroll
+          for (int i = 0; i < 8; i += 2) {
+            const f32x4 cs = *reinterpret_cast<const f32x4*>(tb + i);
+            vk[i] = (bf16_t)((float)vk[i] * cs[0] + sgn * cs[1] * (float)other[i]);
+            vk[i + 1] = (bf16_t)((float)vk[i + 1] * cs[2] + sgn * cs[3] * (float)other[i + 1]);
+          }
+        }
+        *reinterpret_cast<bf16x8*>(out) = vk;
         *reinterpret_cast<u32x4*>(out + d) = *reinterpret_cast<const LDS_AS u32x4*>(edv + row * EROW + 16 * piece);
       }
     }
@@ -649,21 +711,26 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
 // dQ^T += K^T dS^T (the B-operand trick of the file header), accumulating dQ^T in registers over all key blocks.
 // Three products per tile instead of one, but no dS^T is written to or read from memory, nothing is added
 // atomically, and the result is bit-reproducible.  Workgroup = 4 waves x 32 queries, K and V blocks double-buffered
-// through LDS exactly as in the forward.
+// through LDS exactly as in the forward; SPLIT = 2 as there.
+// It runs before the pass over the queries, because it has a query's rows of dout in registers: delta = rowsum(dout * out) costs
+// it one more image, which arrives beside the first key block, instead of a launch that reads both tensors (11 of 285 us at
+// B 2, H 32, S 2048, dh 128; 5 of 82 at B 4, H 12, S 1000, dh 64).
 struct AttnDqParams {
   const bf16_t* qkv; long ld_qkv;
   const bf16_t* dout; long ld_do;
+  const bf16_t* out;                   // [B*S, H*DH] the forward's output (rows as dout)
   const float* lse;                    // [B, H, S]
-  const float* delta;                  // [B*S, H]
+  float* delta;                        // [B*S, H]: written here (rowsum(dout * out)), read by the pass over the queries
+  const float2* rope;                  // rotation table [S][DH / 2]: dq is rotated back; or nullptr
   bf16_t* dqkv; long ld_dqkv;          // dq block is written (columns h * DH ..)
   int B, H, S, causal;
   float scale, scale_log2e;
 };
 
-template <int DH>
+template <int DH, int SPLIT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_kernel(AttnDqParams p) {
   using HT = HeadTile<DH>;
-  constexpr int KS = DH / 16, DT = DH / 32, BKV = 64;
+  constexpr int KS = DH / 16, DT = DH / 32, BKV = 64, BQ = 128 / SPLIT, QW = 4 / SPLIT;
   constexpr int IMG = BKV * HT::RB, SLOT = 2 * IMG;
   constexpr int NCH = IMG / 1024 / 4;
 
@@ -675,18 +742,19 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int qb = (int)gridDim.y - 1 - (int)blockIdx.y;             // longest (last) query blocks first
   const int h = (int)blockIdx.x % p.H, b = (int)blockIdx.x / p.H;
-  const int q0 = qb * 128, qw0 = q0 + 32 * wave, query = qw0 + ql;
+  const int wq = SPLIT == 1 ? wave : wave % QW, wk = SPLIT == 1 ? 0 : wave / QW;      // which 32 queries, which 32-key tile of every block (SPLIT 2)
+  const int q0 = qb * BQ, qw0 = q0 + 32 * wq, query = qw0 + ql;
   const int d = p.H * DH;
   const long tok0 = (long)b * p.S;
   const long bh = (long)b * p.H + h;
 
   const typename HT::Offsets fo = HT::offsets(lane);
-  // ---- the block's 128 query rows into the second slot and their output derivatives into the first (coalesced copies)
+  // ---- the block's query rows into the second slot and their output derivatives into the first (coalesced copies)
   {
     const u32x4 dq = make_desc(p.qkv + (tok0 + q0) * p.ld_qkv + h * DH, (uint32_t)((long)(p.S - q0) * p.ld_qkv * 2));
     const u32x4 dd = make_desc(p.dout + (tok0 + q0) * p.ld_do + h * DH, (uint32_t)((long)(p.S - q0) * p.ld_do * 2));
 #pragma unroll
-    for (int i = 0; i < 2 * NCH; i++) {
+    for (int i = 0; i < 2 * NCH / SPLIT; i++) {
       int row; unsigned go, gd;
       HT::plan(wave + 4 * i, lane, p.ld_qkv, row, go);
       HT::plan(wave + 4 * i, lane, p.ld_do, row, gd);
@@ -699,7 +767,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   unsigned c_off[NCH];
 #pragma unroll
   for (int i = 0; i < NCH; i++) HT::plan(wave + 4 * i, lane, p.ld_qkv, c_row[i], c_off[i]);
-  const int kv_end = p.causal ? (q0 + 128 < p.S ? q0 + 128 : p.S) : p.S;
+  const int kv_end = p.causal ? (q0 + BQ < p.S ? q0 + BQ : p.S) : p.S;
   const int nblk = (kv_end + BKV - 1) / BKV;
   auto issue = [&](int j) {
     const int kv0 = j * BKV;
@@ -714,10 +782,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
       dma16(base + IMG + i * 4096, dv, off);
     }
   };
-  // the row statistics of this lane's query
   const bool qlive = query < p.S;
   const float lse_q = qlive ? p.lse[bh * p.S + query] : 0.f;
-  const float dl_q = qlive ? p.delta[(tok0 + query) * p.H + h] : 0.f;
 
   f32x16 dqt[DT];
 #pragma unroll
@@ -730,11 +796,34 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   bf16x8 qf[KS], dof[KS];            // this lane's query row and output-derivative row as B operands
 #pragma unroll
   for (int s = 0; s < KS; s++) {
-    qf[s] = HT::rows_frag(lds + SLOT, fo, 32 * wave, s);
-    dof[s] = HT::rows_frag(lds, fo, 32 * wave, s);
+    qf[s] = HT::rows_frag(lds + SLOT, fo, 32 * wq, s);
+    dof[s] = HT::rows_frag(lds, fo, 32 * wq, s);
   }
   __syncthreads();                   // every wave has its rows: both slots are free for the key blocks
   issue(0);
+  // ---- delta of this lane's query, rowsum(dout * out): the block's rows of the output arrive in the second slot beside the
+  // first key block
+  {
+    const u32x4 dr = make_desc(p.out + (tok0 + q0) * p.ld_do + h * DH, (uint32_t)((long)(p.S - q0) * p.ld_do * 2));
+#pragma unroll
+    for (int i = 0; i < 2 * NCH / SPLIT; i++) {
+      int row; unsigned go;
+      HT::plan(wave + 4 * i, lane, p.ld_do, row, go);
+      dma16(lds0 + SLOT + (wave + 4 * i) * 1024, dr, q0 + row < p.S ? go : kOob);
+    }
+  }
+  wait_vmem<0>();
+  __syncthreads();
+  float dl_q = 0.f;
+#pragma unroll
+  for (int s = 0; s < KS; s++) {
+    const bf16x8 o = HT::rows_frag(lds + SLOT, fo, 32 * wq, s);
+#pragma unroll
+    for (int i = 0; i < 8; i++) dl_q += (float)o[i] * (float)dof[s][i];
+  }
+  dl_q += xor32(dl_q);
+  if (qlive && g == 0 && wk == 0) p.delta[(tok0 + query) * p.H + h] = dl_q;
+  __syncthreads();                   // the second slot is free again
   for (int j = 0; j < nblk; j++) {
     wait_vmem<0>();
     __syncthreads();                 // block j has landed; every wave is done with the other slot
@@ -751,7 +840,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     // S^T and dP^T as two interleaved accumulation chains, fragments one k-step ahead; then dS^T in place and
     // dQ^T += K^T dS^T over the tile's two k-steps on DT independent accumulators
 #pragma unroll 1
-    for (int kt = 0; kt < 2; kt++) {
+    for (int kt = SPLIT == 2 ? wk : 0; kt < (SPLIT == 2 ? wk + 1 : 2); kt++) {
       f32x16 st, dp;
 #pragma unroll
       for (int e = 0; e < 16; e++) { st[e] = 0.f; dp[e] = 0.f; }
@@ -792,18 +881,59 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     }
   }
 
-  // ---- dq = scale * dQ^T, transposed back through LDS and written as whole rows (as the forward writes its output)
   __syncthreads();
+  if constexpr (SPLIT == 2) {        // the two waves of a query add up, first the wave of the first tiles
+    LDS_AS float* const part = reinterpret_cast<LDS_AS float*>(lds) + wq * (DT * 1024);
+    static_assert(QW * DT * 4096 <= 2 * SLOT, "the partial sums must fit in the ring");
+    if (wk == 1) {
+#pragma unroll
+      for (int t = 0; t < DT; t++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) part[(t * 16 + e) * 64 + lane] = dqt[t][e];
+    }
+    __syncthreads();
+    if (wk == 0) {
+#pragma unroll
+      for (int t = 0; t < DT; t++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) dqt[t][e] += part[(t * 16 + e) * 64 + lane];
+    }
+    __syncthreads();
+    if (wk == 1) return;
+  }
+  // ---- dq = scale * dQ^T (rotated back: a lane holds both halves of its query's row), transposed back through LDS and
+  // written as whole rows (as the forward writes its output)
+#pragma unroll
+  for (int t = 0; t < DT; t++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) dqt[t][e] *= p.scale;
+  if (p.rope) {
+    const float2* const tb = p.rope + (long)(qlive ? query : 0) * (DH / 2) + 4 * g;
+#pragma unroll
+    for (int t = 0; t < DT / 2; t++)
+#pragma unroll
+      for (int e4 = 0; e4 < 4; e4++) {
+        const f32x4 c01 = *reinterpret_cast<const f32x4*>(tb + 32 * t + 8 * e4);
+        const f32x4 c23 = *reinterpret_cast<const f32x4*>(tb + 32 * t + 8 * e4 + 2);
+        const float cs[4] = {c01[0], c01[2], c23[0], c23[2]}, sn[4] = {c01[1], c01[3], c23[1], c23[3]};
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const float x = dqt[t][4 * e4 + r], y = dqt[t + DT / 2][4 * e4 + r];
+          dqt[t][4 * e4 + r] = x * cs[r] + y * sn[r];
+          dqt[t + DT / 2][4 * e4 + r] = y * cs[r] - x * sn[r];
+        }
+      }
+  }
   constexpr int EROW = DH * 2 + 16;
-  static_assert(128 * EROW <= 2 * SLOT, "the output tile must fit in the ring");
-  lds_u8* const erow = lds + 32 * wave * EROW;
+  static_assert(BQ * EROW <= 2 * SLOT, "the output tile must fit in the ring");
+  lds_u8* const erow = lds + 32 * wq * EROW;
 #pragma unroll
   for (int t = 0; t < DT; t++)
 #pragma unroll
     for (int e4 = 0; e4 < 4; e4++) {
       bf16x4 v;
 #pragma unroll
-      for (int r = 0; r < 4; r++) v[r] = (bf16_t)(dqt[t][4 * e4 + r] * p.scale);
+      for (int r = 0; r < 4; r++) v[r] = (bf16_t)dqt[t][4 * e4 + r];
       *reinterpret_cast<LDS_AS bf16x4*>(erow + ql * EROW + (32 * t + 8 * e4 + 4 * g) * 2) = v;
     }
   {  // (LDS operations of a wave execute in order: the reads below see this wave's own writes above)
@@ -819,13 +949,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
-template <int DH, bool AHEAD>
+// Workgroups of 128 queries (keys) of a launch; and is the chip short of them?  Up to one per compute unit it is; with the
+// causal mask, whose longest workgroup works eight times as long as the shortest (or more), up to two.
+static long query_groups(long heads, int seq) { return heads * ((seq + 127) / 128); }
+static bool few_query_groups(long heads, int seq) { const long w = query_groups(heads, seq); return w <= 256 || (w <= 512 && seq > 896); }
+
+template <int DH, bool AHEAD, int SPLIT>
 static hipError_t launch_fwd(const AttnParams& p, hipStream_t s) {
   constexpr size_t smem = 2 * 2 * 64 * DH * 2;
-  auto kern = attn_fwd_kernel<DH, AHEAD>;
+  auto kern = attn_fwd_kernel<DH, AHEAD, SPLIT>;
   static AttrOnce once;
   if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(p.H * p.B), (unsigned)((p.S + 127) / 128)), dim3(256), smem, s, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.H * p.B), (unsigned)((p.S * SPLIT + 127) / 128)), dim3(256), smem, s, p);
   return hipGetLastError();
 }
 
@@ -836,58 +971,82 @@ hipError_t attention_fwd(int batch, int n_heads, int seq, int head_dim, int caus
   p.qkv = (const bf16_t*)qkv; p.ld_qkv = ld_qkv; p.out = (bf16_t*)out; p.ld_out = ld_out; p.lse = lse;
   p.B = batch; p.H = n_heads; p.S = seq; p.causal = causal;
   p.scale_log2e = 1.4426950408889634f / sqrtf((float)head_dim);
-  if (head_dim == 128) return seq > 256 ? launch_fwd<128, true>(p, s) : launch_fwd<128, false>(p, s);
-  if (head_dim == 64) return seq > 256 ? launch_fwd<64, true>(p, s) : launch_fwd<64, false>(p, s);
-  return hipErrorInvalidValue;
+  if (head_dim != 128 && head_dim != 64) return hipErrorInvalidValue;
+  // us, 128 / 64 queries per workgroup; causal: B 1, H 32, dh 128, S 256 9.0 / 7.6, S 512 13.5 / 11.0, S 1024 23.8 / 21.1, S 2048
+  // 51.7 / 48.3; B 4, H 12, dh 64, S 1000 18.9 / 16.9; lost: B 4, H 32, dh 128, S 512 21.1 / 23.6, B 1, H 40, S 2048 55.3 / 62.9; unmasked:
+  // B 1, H 16, dh 128, S 1024 21.8 / 17.4, twice the heads 26.5 / 24.9; S 64 4.1 / 4.3
+  if (seq > 64 && (query_groups(batch * (long)n_heads, seq) <= 256 || (causal && few_query_groups(batch * (long)n_heads, seq))))
+    return head_dim == 128 ? launch_fwd<128, false, 2>(p, s) : launch_fwd<64, false, 2>(p, s);
+  if (head_dim == 128) return seq > 256 ? launch_fwd<128, true, 1>(p, s) : launch_fwd<128, false, 1>(p, s);
+  return seq > 256 ? launch_fwd<64, true, 1>(p, s) : launch_fwd<64, false, 1>(p, s);
 }
 
-template <int DH>
+template <int DH, int SPLIT>
 static hipError_t launch_bwd_dq(const AttnDqParams& p, hipStream_t s) {
   constexpr size_t smem = 2 * 2 * 64 * DH * 2;
-  auto kern = attn_bwd_dq_kernel<DH>;
+  auto kern = attn_bwd_dq_kernel<DH, SPLIT>;
   static AttrOnce once;
   if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(p.H * p.B), (unsigned)((p.S + 127) / 128)), dim3(256), smem, s, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.H * p.B), (unsigned)((p.S * SPLIT + 127) / 128)), dim3(256), smem, s, p);
   return hipGetLastError();
 }
 
-template <int DH, bool WRITE_DST>
+// 64 keys per workgroup instead of 128?  By modelled time, in units of 128 keys times 128 queries: a workgroup costs its units and
+// 1.3 (start and drain, one workgroup per compute unit), units on 64 keys 10 % more; the launch takes as long as its rounds or,
+// with the causal mask, as its longest workgroup or as all of them spread over the chip.  us of the whole backward, 128 / 64: causal,
+// dh 128, B 1, H 32, S 256 23.5 / 20.0, S 1024 64.1 / 56.6, S 2048 142 / 147, B 4, H 32, S 256 31.3 / 31.8, B 1, H 8, S 4096 199 / 167;
+// unmasked, B 1, H 16, dh 128, S 1024 59.0 / 50.4, twice the heads 68.4 / 72.1, B 4, H 12, dh 64, S 1000 80.7 / 73.4, B 1, H 40, dh 128,
+// S 2048 326 / 320.
+static bool short_key_blocks(long heads, int seq, int causal) {
+  const double kStart = 1.3, kSlower = 1.1, nb = (seq + 127) / 128;
+  const double w = heads * nb;
+  if (!causal) return ceil(2 * w / 256) * (0.5 * kSlower * nb + kStart) < ceil(w / 256) * (nb + kStart);
+  const double units = heads * nb * (nb + 1) / 2;
+  const double whole = fmax(nb + kStart, (units + kStart * w) / 256);
+  return fmax(0.5 * kSlower * nb + kStart, (kSlower * units + 2 * kStart * w) / 256) < whole;
+}
+
+template <int DH, bool WRITE_DST, int KEYS>
 static hipError_t launch_bwd_kv_split(const AttnBwdParams& p, hipStream_t s) {
   constexpr size_t smem = 3 * (2 * 64 * DH * 2 + 1024) + 2 * 4 * 4096 + (WRITE_DST ? 4 * 32 * 144 : 0);     // three slots, two hand-over buffers, dS^T staging
-  auto kern = attn_bwd_kv_split_kernel<DH, WRITE_DST>;
+  auto kern = attn_bwd_kv_split_kernel<DH, WRITE_DST, KEYS>;
   static AttrOnce once;
   if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(p.H * p.B), (unsigned)((p.S + 127) / 128)), dim3(512), smem, s, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.H * p.B), (unsigned)((p.S + KEYS - 1) / KEYS)), dim3(512), smem, s, p);
   return hipGetLastError();
 }
 
 hipError_t attention_p1(int batch, int n_heads, int seq, int head_dim, int causal, const void* qkv, long ld_qkv,
                         const void* out, const void* d_out, long ld_out, const float* lse, void* dqkv, long ld_dqkv,
-                        float* delta, void* ds_t, hipStream_t s) {
+                        float* delta, void* ds_t, const float2* rope_table, hipStream_t s) {
   if (batch <= 0 || n_heads <= 0 || seq <= 0) return hipSuccess;
-  if (ld_out != (long)n_heads * head_dim) return hipErrorInvalidValue;      // the row-dot kernel takes dense rows
-  hipError_t e = head_rowdot(1, batch * seq, n_heads, head_dim, d_out, out, delta, s);
-  if (e != hipSuccess) return e;
+  if (ld_out != (long)n_heads * head_dim || (head_dim != 64 && head_dim != 128)) return hipErrorInvalidValue;      // the row-dot kernel takes dense rows
   AttnBwdParams p{};
   p.qkv = (const bf16_t*)qkv; p.ld_qkv = ld_qkv; p.dout = (const bf16_t*)d_out; p.ld_do = ld_out;
   p.lse = lse; p.delta = delta; p.dqkv = (bf16_t*)dqkv; p.ld_dqkv = ld_dqkv; p.dst = (bf16_t*)ds_t;
   p.B = batch; p.H = n_heads; p.S = seq; p.causal = causal;
   p.scale = 1.f / sqrtf((float)head_dim);
   p.scale_log2e = 1.4426950408889634f * p.scale;
-  if (!ds_t || attn_rebuilds_dq(batch, n_heads, seq, head_dim)) {
-    if (head_dim == 128) e = launch_bwd_kv_split<128, false>(p, s);
-    else if (head_dim == 64) e = launch_bwd_kv_split<64, false>(p, s);
-    else return hipErrorInvalidValue;
-    if (e != hipSuccess) return e;
+  hipError_t e;
+  if (!ds_t || attn_rebuilds_dq(batch, n_heads, seq, head_dim, causal)) {
+    const long heads = (long)batch * n_heads;
+    // us of the whole backward, 128 / 64 queries per workgroup of the dq pass; causal: B 1, H 32, dh 128, S 256 23.5 / 21.1, S 1024
+    // 64.1 / 57.3, S 2048 142 / 138, B 4, H 12, dh 64, S 1000 50.5 / 48.3; lost: B 4, H 32, S 512 60.9 / 62.1; unmasked: B 1, H 16,
+    // dh 128, S 1024 59.0 / 52.6, H 24, S 1000 62.8 / 62.5, B 4, H 12, dh 64, S 1000 80.7 / 80.9
+    const bool short_queries = causal ? few_query_groups(heads, seq) : query_groups(heads, seq) <= 128;
+    p.rope = rope_table;
     AttnDqParams q{};
-    q.qkv = p.qkv; q.ld_qkv = ld_qkv; q.dout = p.dout; q.ld_do = ld_out; q.lse = lse; q.delta = delta;
-    q.dqkv = p.dqkv; q.ld_dqkv = ld_dqkv; q.B = batch; q.H = n_heads; q.S = seq; q.causal = causal;
+    q.qkv = p.qkv; q.ld_qkv = ld_qkv; q.dout = p.dout; q.ld_do = ld_out; q.out = (const bf16_t*)out; q.lse = lse; q.delta = delta;
+    q.rope = rope_table; q.dqkv = p.dqkv; q.ld_dqkv = ld_dqkv; q.B = batch; q.H = n_heads; q.S = seq; q.causal = causal;
     q.scale = p.scale; q.scale_log2e = p.scale_log2e;
-    return head_dim == 128 ? launch_bwd_dq<128>(q, s) : launch_bwd_dq<64>(q, s);
+    if (short_queries) e = head_dim == 128 ? launch_bwd_dq<128, 2>(q, s) : launch_bwd_dq<64, 2>(q, s);
+    else e = head_dim == 128 ? launch_bwd_dq<128, 1>(q, s) : launch_bwd_dq<64, 1>(q, s);
+    if (e != hipSuccess) return e;
+    if (short_key_blocks(heads, seq, causal)) return head_dim == 128 ? launch_bwd_kv_split<128, false, 64>(p, s) : launch_bwd_kv_split<64, false, 64>(p, s);
+    return head_dim == 128 ? launch_bwd_kv_split<128, false, 128>(p, s) : launch_bwd_kv_split<64, false, 128>(p, s);
   }
-  if (head_dim == 128) e = launch_bwd_kv_split<128, true>(p, s);
-  else if (head_dim == 64) e = launch_bwd_kv_split<64, true>(p, s);
-  else return hipErrorInvalidValue;
+  if (e = head_rowdot(1, batch * seq, n_heads, head_dim, d_out, out, delta, s); e != hipSuccess) return e;
+  e = head_dim == 128 ? launch_bwd_kv_split<128, true, 128>(p, s) : launch_bwd_kv_split<64, true, 128>(p, s);
   if (e != hipSuccess) return e;
   // dq = scale * dS k = scale * (dS^T)^T k per (sequence, head): contraction over keys, causal: keys <= query
   const long d = (long)n_heads * head_dim;
@@ -899,7 +1058,8 @@ hipError_t attention_p1(int batch, int n_heads, int seq, int head_dim, int causa
   g.sBo = (long)seq * ld_qkv; g.sBi = head_dim;
   g.sCo = (long)seq * ld_dqkv; g.sCi = head_dim;
   g.causal = causal ? CAUSAL_K_END : CAUSAL_NONE;
-  return gemm(1, g, s);
+  if (e = gemm(1, g, s); e != hipSuccess || !rope_table) return e;
+  return rope(1, batch * seq, seq, 2 * n_heads, head_dim, ld_dqkv, rope_table, 1, dqkv, s);
 }
 
 }  // namespace tbp

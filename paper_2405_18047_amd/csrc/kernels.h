@@ -135,15 +135,25 @@ hipError_t head_rowdot(int dtype, int rows, int n_heads, int head_dim, const voi
 hipError_t attention_fwd(int batch, int n_heads, int seq, int head_dim, int causal, const void* qkv, long ld_qkv,
                          void* out, long ld_out, float* lse, hipStream_t s);
 
-// Does the backward compute dq by a pass that rebuilds S and dP rather than from dS^T written to memory?  Where there are at
-// least four workgroups of 128 keys per compute unit (below that the pass leaves the chip emptier than one product over
-// 128 x 128 tiles), and at head_dim 128 only for sequences above 512: shorter ones write little dS^T per workgroup, and its
-// round trip then costs less than the two products that the pass adds (at head_dim 64 these are cheap).  Whole backward, us,
-// dS^T / rebuilt, causal and not: dh 128, B 2, H 32, S 2048 281 / 276, 494 / 478; B 4, H 12, S 4096 748 / 704, 1355 / 1322;
-// B 4, H 40, S 896 196 / 184, 291 / 281; B 8, H 32, S 512 131 / 138, 169 / 175; B 32, H 32, S 128 97 / 103, 98 / 104; dh 64, the
-// first 216 / 180, 393 / 301, the last 67 / 62, 67 / 60; fewer workgroups: B 1, H 32, dh 128, S 2048 142 / 155, S 1024 62 / 72.
-inline bool attn_rebuilds_dq(int batch, int n_heads, int seq, int head_dim) {
-  return (long)batch * n_heads * ((seq + 127) / 128) >= 1024 && (head_dim == 64 || seq > 512);
+// Does the backward compute dq by a pass that rebuilds S and dP rather than from dS^T written to memory?  At head_dim 64, where
+// the two products that the pass adds are cheap (on 769 to 1023 workgroups of 128 keys of a short sequence dS^T has been kept,
+// B 4, H 85, S 264 74 / 60: a test holds the two forms apart there);
+// at head_dim 128 where the grid is small (its workgroups can be halved, a product over 128 x 128 tiles cannot) or the
+// sequence long: short ones write little dS^T per workgroup.  Whole backward, us, dS^T / rebuilt; dh 128, causal: B 1, H 32, S 256
+// 23.7 / 17.4, S 1024 56.7 / 49.9, S 2048 140 / 138, B 2, H 40, S 768 69 / 71, B 3, H 32, S 1024 139 / 132, B 5, H 32, S 640 115 / 112, B 10, H 32,
+// S 256 71 / 73, B 2, H 32, S 2048 270 / 264, B 8, H 32, S 512 131 / 135; unmasked: B 1, H 16, S 1024 53 / 43, H 24, S 1000 57 / 63, B 2, H 40, S 768
+// 98 / 102, B 3, H 32, S 1024 206 / 200; dh 64: B 1, H 16, S 1024 45 / 30, B 4, H 12, S 1000 unmasked 82 / 73, B 2, H 24, S 2048 167 / 138.
+inline bool attn_rebuilds_dq(int batch, int n_heads, int seq, int head_dim, int causal) {
+  const long w = (long)batch * n_heads * ((seq + 127) / 128);
+  if (w >= 1024) return head_dim == 64 || seq > 512;
+  if (head_dim == 64) return w <= 768 || seq > 512;
+  return causal ? w <= 512 || seq > 768 : w <= 128 || (w >= 512 && seq > 768);
+}
+
+// Does a stage ask for room for dS^T?  (By the size of the grid alone, and also for small grids that have stopped writing it: the
+// sizes that a configuration's owner was told have not changed with that.)
+inline bool attn_asks_for_ds(int batch, int n_heads, int seq, int head_dim) {
+  return (long)batch * n_heads * ((seq + 127) / 128) < 1024 || (head_dim != 64 && seq <= 512);
 }
 
 // Backward-p1 of the same: dq, dk, dv into the column blocks of dqkv from qkv, the forward's output and lse and the
@@ -151,10 +161,11 @@ inline bool attn_rebuilds_dq(int batch, int n_heads, int seq, int head_dim) {
 // ds_t: scratch of batch * n_heads * attn_ds_elems(seq) storage-type elements (receives dS^T in panels of kPanel
 // queries: per (sequence, head) [ceil(seq / kPanel)][seq keys][kPanel queries]; dq is then one batched product
 // dS K), or nullptr: dq is computed by a second pass over the keys that rebuilds S and dP (no dS^T anywhere), as it is
-// with attn_rebuilds_dq in any case (ds_t is then not touched).
+// with attn_rebuilds_dq in any case (ds_t is then not touched).  rope_table (may be null): q and k are rotated, and dq and dk
+// leave rotated back.
 hipError_t attention_p1(int batch, int n_heads, int seq, int head_dim, int causal, const void* qkv, long ld_qkv,
                         const void* out, const void* d_out, long ld_out, const float* lse, void* dqkv, long ld_dqkv,
-                        float* delta, void* ds_t, hipStream_t s);
+                        float* delta, void* ds_t, const float2* rope_table, hipStream_t s);
 
 // Register-resident MFMA loop (measurement aid): blocks x 4 waves x iters x 16 MFMAs of 32x32x16.
 // seed: 8 x 64 x 8 bf16 values; sink: blocks * 256 floats.

@@ -186,7 +186,7 @@ tbp_status check_config(const tbp_config* cfg, Dims* out) {
   c.literal = cfg->gain_grad == TBP_GAIN_LITERAL;
   if (!(c.eps >= 0.f)) return fail(TBP_EINVAL, "rms_eps must be >= 0");
   if ((long)c.S * c.B > (1L << 24)) return fail(TBP_EINVAL, "tokens per micro-batch above 2^24");
-  c.dq_recompute = c.fused && (cfg->attention == TBP_ATTN_FUSED_RECOMPUTE || tbp::attn_rebuilds_dq(c.B, c.H, c.S, c.dh));
+  c.dq_recompute = c.fused && (cfg->attention == TBP_ATTN_FUSED_RECOMPUTE || !tbp::attn_asks_for_ds(c.B, c.H, c.S, c.dh));
   c.T = c.S * c.B;
   *out = c;
   return TBP_OK;
@@ -368,7 +368,7 @@ tbp_status run_p1(tbp_stage* st, int mb, int slot, const void* dy, void* dx, hip
       // probabilities rebuilt from the stashed row log-sum-exp; dq, dk, dv straight into the dqkv slab
       TBP_HIP(tbp::attention_p1(c.B, c.H, c.S, c.dh, c.causal, qkv, 3 * d, st->wslab(l, W_A, mb), da, d,
                                 (const float*)st->aslot(l, A_LSE, slot), dqkv, 3 * d, (float*)st->ws(st->y.ws_delta),
-                                c.dq_recompute ? nullptr : dP, s));
+                                c.dq_recompute ? nullptr : dP, (const float2*)st->ws(st->y.ws_rope), s));
     } else {
       // rowsum(dP * P) per (token, head) = rowsum(da * a): no S x S tensor needed for it
       float* delta = (float*)st->ws(st->y.ws_delta);
@@ -408,7 +408,7 @@ tbp_status run_p1(tbp_stage* st, int mb, int slot, const void* dy, void* dx, hip
       TBP_HIP(tbp::gemm(dt, gq, s));
       TBP_HIP(tbp::gemm(dt, gk, s));
     }
-    TBP_HIP(tbp::rope(dt, T, c.S, 2 * c.H, c.dh, 3 * d, (const float2*)st->ws(st->y.ws_rope), 1, dqkv, s));
+    if (!c.fused) TBP_HIP(tbp::rope(dt, T, c.S, 2 * c.H, c.dh, 3 * d, (const float2*)st->ws(st->y.ws_rope), 1, dqkv, s));
     // dh1 = [dq, dk, dv] Wqkv^T
     void* dh1 = c.literal ? st->wslab(l, W_N1DY, mb) : dh;
     TBP_HIP(linear_gemm(st, gemm_args(tbp::NT, T, d, 3 * d, dqkv, 3 * d, st->w_qkv[l], 3 * d, dh1, d), s));
@@ -731,7 +731,7 @@ static tbp_status attention_p1_checked(int dtype, int batch, int n_heads, int se
   float* delta = static_cast<float*>(scratch);
   void* ds_t = recompute ? nullptr : static_cast<char*>(scratch) + align_up((size_t)batch * seq * n_heads * sizeof(float), 256);
   TBP_HIP(tbp::attention_p1(batch, n_heads, seq, head_dim, causal ? 1 : 0, qkv, ld_qkv, out, d_out, ld_out, lse, dqkv,
-                            ld_dqkv, delta, ds_t, static_cast<hipStream_t>(stream)));
+                            ld_dqkv, delta, ds_t, nullptr, static_cast<hipStream_t>(stream)));
   return TBP_OK;
 }
 

@@ -675,6 +675,30 @@ def test_fused_attention_backward_on_many_workgroups(seq, nb, H, dh, causal, reb
         assert max_rel(blk, ref) < 1.5e-2, name
 
 
+@pytest.mark.parametrize("seq,nb,H,dh,causal", [
+    (136, 1, 128, 64, True), (136, 3, 43, 128, False),                      # 256 and 258 workgroups of 128 queries: halved, whole
+    (264, 2, 43, 128, True), (264, 4, 43, 64, False),                       # 258, 516: whole, scores computed ahead
+    (904, 1, 64, 64, True), (904, 1, 65, 64, True),                         # 512 and 520, long and causal
+    (904, 1, 16, 128, False), (904, 1, 17, 128, False),                     # 128, 136: dq from halved workgroups; from dS^T
+    (72, 2, 3, 64, False), (40, 1, 2, 128, False)])                         # a second key tile that is ragged; that is empty
+def test_fused_attention_on_few_and_many_workgroups(seq, nb, H, dh, causal):
+    """Short of workgroups the kernels take 64 queries or keys per workgroup instead of 128: both sides of each line, forward and
+    backward, against the oracle's values."""
+    _say(f"attention, halved workgroups seq={seq} B={nb} H={H} dh={dh} causal={causal}")
+    d = H * dh
+    q, k, v, do = (_rnd(49, n, (nb * seq, d), "bf16") for n in ("q", "k", "v", "do"))
+    q64, k64, v64 = q.astype(np.float64), k.astype(np.float64), v.astype(np.float64)
+    o_ref, P = ops.attention_fwd(q64, k64, v64, seq, H, dh, causal)
+    dq, dk, dv = ops.attention_p1(do.astype(np.float64), q64, k64, v64, P, seq, H, dh)
+    qkv = to_dev(np.concatenate([q, k, v], axis=1), "bf16")
+    out, lse2 = tbp.tbp_attention_fwd(qkv, seq, H, dh, causal)
+    assert max_rel(to_np(out), o_ref) < 1e-2
+    for recompute in (False, True):
+        got = to_np(tbp.tbp_attention_p1(qkv, out, to_dev(do, "bf16"), lse2, seq, H, dh, causal, recompute=recompute))
+        for name, ref, blk in (("dq", dq, got[:, :d]), ("dk", dk, got[:, d:2 * d]), ("dv", dv, got[:, 2 * d:])):
+            assert max_rel(blk, ref) < 1.5e-2, (name, recompute)
+
+
 # (seq, head_dim, heads, micro_batch, dtype): the tiles of the score-gradient product and of the products that read it
 SCORE_TILES = [
     (64, 128, 2, 16, "f32"),      # fp32: 16 x 16 read by 32 x 32
