@@ -176,12 +176,16 @@ __device__ __forceinline__ bf16x8 read_frag(lds_u8* q) {
 // operands whose contraction index is contiguous in memory: their copies then fetch 128 contiguous bytes per tile
 // row, a whole cache line, where the 32-deep slot fetches every line in two halves one iteration apart and doubles
 // the number of requests to the L2.
-template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD = BK, bool SPLIT = false, int RING = 0, bool ACC = false>
+// COPIERS: a workgroup of 8 waves, of which 0..3 multiply and 4..7 do nothing but start the copies and wait for them.  A wave
+// that does both issues in order: while the texture path takes its 1 KiB requests one by one, its MFMAs wait.  With a wave of
+// each kind on every SIMD a 128 x 128 tile of 4096 indices takes 33.9 us instead of 36.3 ([1024, 4096] x 4096; copies alone 27,
+// MFMAs alone 25), on 256 products of all kinds 4-15 %.  The 256 x 256 and 256 x 192 tiles have no registers for a second wave.
+template <int BM, int BN, bool AKC, bool BKC, typename OutT, int KD = BK, bool SPLIT = false, int RING = 0, bool ACC = false, bool COPIERS = false>
 __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, int tn_i, int z) {
   // RING == 0: the default pipeline of the slot depth (32: ring of STAGES slots; 64: two slots); RING >= 3: the ring
   // pipeline with that many slots, for either depth
   constexpr bool RINGPIPE = KD == 32 || RING >= 3;
-  constexpr int NS = RING >= 3 ? RING : (KD == 32 ? STAGES : 2);       // ring slots
+  constexpr int NS = COPIERS || RING >= 3 ? RING : (KD == 32 ? STAGES : 2);       // ring slots
   constexpr int KSTEPS = KD / 16;
   constexpr int WM = BM / 2, WN = BN / 2;       // per-wave tile
   constexpr int TM = WM / 32, TN = WN / 32;     // MFMA tiles per wave
@@ -197,7 +201,8 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, in
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave8 = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave = COPIERS ? wave8 & 3 : wave8;
   const int wm = wave >> 1, wn = wave & 1;
 
   const int m0 = tm_i * BM, n0 = tn_i * BN;
@@ -317,7 +322,7 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, in
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  static_assert(BK == 32 && (!RINGPIPE || (NS - 2) * L < 64), "the wait counter has 6 bits");
+  static_assert(BK == 32 && ((!RINGPIPE && !COPIERS) || (NS - (COPIERS ? 1 : 2)) * L < 64), "the wait counter has 6 bits");
   bf16x8 fa0[TM], fb0[TN], fa1[TM], fb1[TN];
   auto first_fragments = [&]() {
 #pragma unroll
@@ -325,7 +330,47 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, in
 #pragma unroll
     for (int j = 0; j < TN; j++) fb0[j] = read_frag<BN, BKC>(lds + b_base[TB::variant(0, j)] + TB::frag_step(0, j));
   };
-  if constexpr (RINGPIPE) {
+  if constexpr (COPIERS) {
+    // All NS slots are in flight or landed at any time: the barrier before the last k-step of a slot, whose fragments are in
+    // registers by then, publishes the next slot and gives this one back to the copying waves.  Both kinds of wave pass
+    // 1 + nk barriers here (none if nk is 0) and one below.
+    if (wave8 >= 4) {
+      auto issue = [&]() {
+        const CopyJob j = next_job();
+#pragma unroll
+        for (int c = 0; c < L; c++) copy_one(j, c);
+      };
+      if (nk > 0) {
+#pragma unroll
+        for (int t = 0; t < NS; t++) issue();
+        wait_vmem<(NS - 1) * L>();            // tile 0 has landed (this wave's share)
+        __syncthreads();
+        for (int t = 0; t < nk; t++) {
+          wait_vmem<(NS - 2) * L>();          // tile t + 1
+          __syncthreads();
+          issue();                            // tile t + NS into the slot of tile t
+        }
+        wait_vmem<0>();                       // the (empty) copies issued past the end
+      }
+      __syncthreads();
+      return;
+    }
+    if (nk > 0) {
+      __syncthreads();
+      first_fragments();
+      for (int t = 0; t < nk; t++) {
+        lds_u8* const cur = lds + (t % NS) * STAGE_BYTES;
+#pragma unroll
+        for (int ks = 1; ks < KSTEPS; ks++) {
+          if (ks & 1) region(fa0, fb0, fa1, fb1, cur, ks, nullptr);
+          else region(fa1, fb1, fa0, fb0, cur, ks, nullptr);
+        }
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        region(fa1, fb1, fa0, fb0, lds + ((t + 1) % NS) * STAGE_BYTES, 0, nullptr);
+      }
+    }
+  } else if constexpr (RINGPIPE) {
     // Ring of NS slots, KSTEPS k-steps per slot (an even number: the two fragment register sets alternate).  While
     // k-step ks - 1 of tile t is multiplied, the fragments of k-step ks are fetched; before the last k-step of a slot
     // (its fragments are in registers by then) come the wait for tile t + 1 and the workgroup barrier, and during that
@@ -561,6 +606,20 @@ __global__ __launch_bounds__(256) void gemm_bf16_causal_pair_kernel(GemmParams p
     gemm_bf16_tile<BM, BN, AKC, BKC, OutT, KD>(p, r == 0 ? nt - 1 - id : id, 0, z);
     __syncthreads();                          // every wave has read its strip back: the ring may be refilled
   }
+}
+
+// Storage-type NN / NT products with waves of their own for the copies; WGS workgroups share a compute unit.
+template <int BM, int BN, bool BKC, int RING, int WGS>
+__global__ __launch_bounds__(512, 2 * WGS) void gemm_bf16_copiers_kernel(GemmParams p) {
+  int tm_i, tn_i;
+  tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, tm_i, tn_i);
+  gemm_bf16_tile<BM, BN, true, BKC, bf16_t, 64, false, RING, false, true>(p, tm_i, tn_i, 0);
+}
+template <int BM, int BN, bool BKC, int RING, int WGS>
+__global__ __launch_bounds__(512, 2 * WGS) void gemm_bf16_copiers_split_kernel(GemmParams p) {
+  int tm_i, tn_i, slice;
+  tile_of_block_split(blockIdx.x, p.tiles_m, p.tiles_n, p.split, tm_i, tn_i, slice);
+  gemm_bf16_tile<BM, BN, true, BKC, float, 64, true, RING, false, true>(p, tm_i, tn_i, slice);
 }
 
 // One workgroup per (tile, slice of the contraction); the fp32 partial products are added up by split_sum_kernel.
@@ -1271,73 +1330,133 @@ static hipError_t launch_bf16_causal_pair(const GemmParams& p0, int batch, hipSt
 }
 
 // Tile and number of contraction slices of a storage-type NN / NT product (the linear layers of forward and backward-p1)
-// whose output is at most one round of 256 x 256 tiles: the choice with the shortest modelled time.  The model, in us,
-// was fitted to 2500 measured (shape, tile, slices) triples, M 64-2048, N 256-22016, K 256-22016 (8 % rms), and picks
-// within 1.6 % of the fastest measured choice on average, 13 % at worst:
-//   a round of 256 workgroups of K / slices indices costs (per index) + (fixed)
-//     128 x 128 on four 64-deep slots   0.0091   3.0   one workgroup per compute unit
-//     256 x 192                         0.0167   8.0   "
-//     256 x 256                         0.0197   9.7   "
-//     128 x 128 on four 32-deep slots   0.0112   2.05  one per compute unit, whole contractions only
-//     128 x 128 on two 64-deep slots    0.0126   1.5   two per compute unit: 0.0188 per round of 512
-//     64 x 64 on four 64-deep slots     0.0047   1.3   "                     0.0071
-//   but at least the time of reading both operands once at 4.9 TB/s plus 8.4;
-//   outputs of at most 256 tiles of 32 x 32 can run on gemm_bf16_small_kernel: 0.0018 K + 3.0;
-//   slices add 3.8 (the second launch) and 0.30 per MB of partial products, and must gain 12 % (3 % up to 128 rows).
+// whose output is at most one round of 256 x 256 tiles.  Two models of a product's time, fitted to different data:
+// `coarse_plan` knows six tiles, with constants of its own for up to 128 rows, and errs little where it errs; `product_time` knows all
+// of them and more of what a product's time depends on.  The plan is the coarse one unless the other model has a choice that it
+// holds for 4 to 20 % faster, depending on how well it knows the two.  On 3900 products (M 16-4096, N 128-27648, K 64-27648, weights that no cache holds) the plan costs 0.9 % more
+// than the fastest of all tiles and slices on average, and is more than 6 % slower than the coarse one on 6 of them; the coarse
+// one alone costs 2.5 %, `product_time` alone 0.7 % with a tail of 1.3-fold misses ([16, 2560] x 3264 (NN) 13.4 us for 9.6).
+// us, with the 4-wave kernels and the coarse plan that were here / now: [256, 22016] x 4096 (NN) 71 / 57 (256 x 128), [360, 4096] x 11008
+// (NT) 52 / 46, [256, 4096] x 4096 (NN) 19.6 / 16.7 (64 x 64), [2000, 1152] x 3456 (NT) 27.3 / 23.6 (128 x 128), [1024, 4096] x 11008 (NN)
+// 90 / 87.
+enum ProductTile { T32, T64, T128X64, T128, T128_PAIR, T128X192, T256X128, T192, T256_NARROW, T256 };
+struct TileCost {
+  int bm, bn, per_cu;
+  double index, fixed;          // us per contraction index of a full round, and per round
+  double idle;                  // per_cu 1: share of `index` that an empty chip saves; per_cu 2: us per index of two workgroups
+  double nn, nt, start;         // TB/s at which the operands are fetched, by layout, and us
+  double overlap;               // us by which a round beyond the first starts early
+  double half_b, half_a;        // extra time per index for rows of B, of A (NN) that are no multiple of 64
+  double sum, sum_mb;           // us for the sum of the slices, and per MB of partial products
+  double second;                // per_cu 2: share of the second workgroup's time that the first compute units with two add
+};
+static const TileCost kTileCost[] = {
+    {32, 32, 1, 0.00174, 3.33, 0.309, 4.78, 14.0, 2.68, 5.93, 0.278, 0.270, 5.35, 0.230, 0.},        // no slices
+    {64, 64, 2, 0.00327, 3.74, 0.00805, 5.48, 8.70, 0.694, 1.39, 0.229, 0.0826, 2.03, 0.347, 1.},
+    {128, 64, 1, 0.00533, 4.77, 0.358, 4.60, 10.6, 1.91, 1.63, 0.232, 0.195, 1.89, 0.266, 0.},
+    {128, 128, 1, 0.00791, 5.21, 0.425, 6.21, 8.46, 1.83, 2.22, 0.201, 0.0773, 1.77, 0.272, 0.},
+    {128, 128, 2, 0.00979, 4.51, 0.0187, 4.67, 14.0, 1.87, 0.515, 0.110, 0.0414, 1.65, 0.306, 0.837},
+    {128, 192, 1, 0.0106, 6.66, 0.379, 6.27, 10.0, 4.52, 0.747, 0.196, 0.0480, 1.76, 0.264, 0.},
+    {256, 128, 1, 0.0122, 8.65, 0.438, 13.9, 10.0, 5.13, 1.60, 0.149, 0.134, 1.64, 0.206, 0.},
+    {192, 192, 1, 0.0140, 9.81, 0.340, 7.18, 10.5, 5.69, 1.35, 0.113, 0.0303, 1.56, 0.199, 0.},
+    {256, 192, 1, 0.0193, 9.71, 0.478, 4.72, 13.0, 15.0, 0., 0.183, 0.0324, 2.25, 0.131, 0.},
+    {256, 256, 1, 0.0241, 11.6, 0.413, 5.99, 7.64, 15.0, 0.142, 0.0678, 0.0832, 1.50, 0.140, 0.}};
+
+// A round of 256 workgroups (one per compute unit; 512 with two) costs its contraction indices and a fixed part, less per index
+// where compute units stay idle (the others' copies then go faster), and no less than reading both operands once (of the
+// shorter of these two times an eighth shows).  A row length that is no multiple of 64 puts every 128-byte piece of a tile row
+// across two cache lines.  Slices add a second launch and the partial products.
+static double product_time(const TileCost& t, int layout, int M, int N, int K, long n, int slice, int split) {
+  const double slower = 1. + ((layout == NN ? N : K) % 64 ? t.half_b : 0.) + (layout == NN && K % 64 ? t.half_a : 0.);
+  const double work = slice * t.index * slower;
+  double time;
+  if (t.per_cu == 1) {
+    const long rest = n % 256;
+    const double last = work * (1. - t.idle * (1. - (double)(n <= 256 ? n : rest) / 256)) + t.fixed;
+    time = n <= 256 ? last : (double)(n / 256) * (work + t.fixed) + (rest ? last : 0.) - (double)((n - 1) / 256) * t.overlap;
+  } else {
+    const long rest = n % 512;
+    const double one = work + t.fixed, two = slice * t.idle * slower + t.fixed;
+    time = (double)(n / 512) * two - (n > 512 ? (double)((n - 1) / 512) * t.overlap : 0.);
+    if (rest) time += rest <= 256 ? one : one + (two - one) * (t.second + (1. - t.second) * (double)(rest - 256) / 256);
+  }
+  const double memory = 2e-6 * ((double)N * K + (double)M * K) / (layout == NN ? t.nn : t.nt) * (1. + 0.5 * (slower - 1.)) + t.start;
+  time = time > memory ? time + 0.12 * memory : memory + 0.12 * time;
+  return split > 1 ? 1.03 * (time + t.sum + t.sum_mb * 4e-6 * split * M * N) : time;
+}
+static const int kSlices[] = {1, 2, 3, 4, 5, 6, 8, 12, 16};
+static SplitPlan slices_of(int tile, int M, int N, int K, int sp) {
+  const int slice = sp == 1 ? K : ((K + 63) / 64 + sp - 1) / sp * 64, split = sp == 1 ? 1 : (K + slice - 1) / slice;
+  return SplitPlan{tile, split, slice, split > 1 ? kSplitHead + (size_t)split * M * N * sizeof(float) : 0};
+}
+static long tiles_of(int tile, int M, int N) {
+  const TileCost& t = kTileCost[tile];
+  return (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+}
+// The model, in us, fitted to 2500 (shape, tile, slices) triples, M 64-2048, N 256-22016, K 256-22016: a round of 256 workgroups of
+// K / slices indices costs `one` per index (`two` with two workgroups on a compute unit) and a fixed part, but at least the time
+// of reading both operands once at 4.9 TB/s plus 8.4; slices add 3.8 and 0.30 per MB of partial products, and must gain 12 % (3 % up to 128 rows).
 // Up to 128 rows the weight is read for one row of tiles, from HBM, and the tiles differ in the rate at which they
 // fetch it: 5.9 TB/s on 128 x 128 tiles and 4.5 on 64 x 64 ones where its columns are contiguous (pieces of 256 and of 128 bytes),
 // 4.9 on both where the contraction is; each has its own start (`start`, us), and rings of few slots take longer per index
-// (`thin`).  Fitted to 510 products, M 8-128, N 256-24000, K 64-16000, weights that no cache holds, on all tiles and slices (11 %
-// rms): the choice costs 2 % more than the fastest on average, 8 with the constants above, which did not tell the tiles apart
-// ([64, 22016] x 4096 (NN) 58.7 us on 64 x 64 tiles, 44.9 on 128 x 128; [16, 17072] x 5952 61 and, on 128 x 128 in three slices, 47).
-// The ring of 32-deep slots starts a short contraction sooner and is ahead up to K = 450 or so: [1688, 1560] x 400 9.4 us,
-// 9.7 on the 64-deep ring; [376, 8840] x 320 8.8, 9.0; [1024, 4096] x 512 10.2, 10.0.  Two 64-deep slots need a second
-// workgroup to cover their latency (the same shapes 10.2, 9.3, 10.9), so they are left out up to one per compute unit.
-// A K that is no multiple of 64 puts every 128-byte piece of a tile row across two cache lines.  The 64 x 64 tiles fetch the
-// most per product and pay for it, 8 % on a CU of their own and 38 % beside a second one: [296, 4488] x 3920 40 us, where two
-// slices of 128 x 128 tiles take 28; [168, 5280] x 7592 44 us, three slices 35; [360, 3072] x 4096 (whole lines) 25.
-// Why so many: one tile per compute unit leaves most of the chip idle on the short micro-batches.  Measured (us) against
-// what these shapes ran on before: [256, 4096] x 22016 (NT) 207 -> 76 (16 x 16 large tiles), [256, 22016] x 4096 106 -> 75
-// (256 x 192 in two slices), [360, 4096] x 11008 99 -> 52 (96 tiles of 128 in five), [1024, 4096] x 22016 212 -> 169 (64
-// large tiles in four), [512, 1024] x 2752 23 -> 16 (64 x 64); unsplit where the tiles already fill the chip, e.g.
-// [1024, 4096] x 4096 43 us on 128 x 128 tiles against 54 for the best split.
-enum ProductTile { T128_DEEP, T256_NARROW, T256, T128_PAIR, T64, T128_SHALLOW, T32 };
-static bool one_round(int M, int N) { return (long)((M + 255) / 256) * ((N + 255) / 256) <= 256; }
-static SplitPlan product_plan(int layout, int M, int N, int K, bool allow_split) {
-  struct Tile { int bm, bn, per_cu; double c1, c2, fixed, thin, start; };
-  static const Tile tiles[] = {{128, 128, 1, 0.0091, 0., 3.0, 1.04, 4.9}, {256, 192, 1, 0.0167, 0., 8.0, 0., 0.},
-                               {256, 256, 1, 0.0197, 0., 9.7, 0., 0.}, {128, 128, 2, 0.0126, 0.0188, 1.5, 1.17, 5.4},
-                               {64, 64, 2, 0.0047, 0.0071, 1.3, 1.3, 3.9}, {128, 128, 1, 0.0112, 0., 2.05, 1.25, 4.75}};
-  static const int slices[] = {1, 2, 3, 4, 5, 6, 8, 12, 16};
+// (`thin`).  Fitted to 510 products, M 8-128, N 256-24000, K 64-16000, weights that no cache holds.
+// Rows of K that are no multiple of 64 cost the 64 x 64 tiles, which fetch the most per product, 8 % on a CU of their own and 38 %
+// beside a second one.
+static SplitPlan coarse_plan(int layout, int M, int N, int K, bool allow_split) {
+  struct Coarse { int tile; double one, two, fixed, thin, start; bool slices; };
+  static const Coarse tiles[] = {{T128, 0.0091, 0., 3.0, 1.04, 4.9, true}, {T256_NARROW, 0.0167, 0., 8.0, 0., 0., true},
+                                 {T256, 0.0197, 0., 9.7, 0., 0., true}, {T128_PAIR, 0.0126, 0.0188, 1.5, 1.17, 5.4, true},
+                                 {T64, 0.0047, 0.0071, 1.3, 1.3, 3.9, true}, {T128, 0.0112, 0., 2.05, 1.25, 4.75, false}};
   const double bytes = 2e-6 * ((double)N * K + (double)M * K);
-  const bool thin = M <= 128, nn = layout == NN;
-  SplitPlan best{T64, 1, K, 0};
+  const bool thin = M <= 128, nn = layout == NN, half_lines = K % 64 != 0;
+  SplitPlan best = slices_of(T64, M, N, K, 1);
   double best_time = 1e30;
-  const bool half_lines = K % 64 != 0;
-  if ((long)((M + 31) / 32) * ((N + 31) / 32) <= 256) {
+  if (tiles_of(T32, M, N) <= 256) {
     best_time = !thin ? 0.0018 * K + 3.0 : (nn ? 0.0022 : 0.0014) * K + 2.9 + 0.26e-6 * N * K;
     best.tile = T32;
   }
-  for (int i = 0; i < 6; i++) {
-    const Tile& t = tiles[i];
-    if (t.bm == 256 && M < 192) continue;
-    const double per_index = thin ? t.thin : 1., memory = thin ? bytes / (!nn ? 4.9 : i == T64 ? 4.5 : 5.9) + t.start : bytes / 4.9 + 8.4;
-    for (int sp : slices) {
-      if (sp > 1 && (!allow_split || K / sp < 256 || i == T128_SHALLOW)) break;
-      const int slice = sp == 1 ? K : ((K + 63) / 64 + sp - 1) / sp * 64, split = sp == 1 ? 1 : (K + slice - 1) / slice;
-      const long n = (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * split;
-      if (i == T128_PAIR && n <= 256) continue;
-      const double lines1 = half_lines && i == T64 ? 1.08 : 1., lines2 = half_lines && i == T64 ? 1.38 : 1.;
-      const double one = slice * t.c1 * per_index * lines1 + t.fixed, two = slice * t.c2 * per_index * lines2 + t.fixed;
+  for (const Coarse& t : tiles) {
+    if (kTileCost[t.tile].bm == 256 && M < 192) continue;
+    const double per_index = thin ? t.thin : 1., memory = thin ? bytes / (!nn ? 4.9 : t.tile == T64 ? 4.5 : 5.9) + t.start : bytes / 4.9 + 8.4;
+    for (int sp : kSlices) {
+      if (sp > 1 && (!allow_split || K / sp < 256 || !t.slices)) break;
+      const SplitPlan plan = slices_of(t.tile, M, N, K, sp);
+      const long n = tiles_of(t.tile, M, N) * plan.split;
+      if (t.tile == T128_PAIR && n <= 256) continue;
+      const bool slow = half_lines && t.tile == T64;
+      const double one = plan.slice * t.one * per_index * (slow ? 1.08 : 1.) + t.fixed, two = plan.slice * t.two * per_index * (slow ? 1.38 : 1.) + t.fixed;
       double time;
-      if (t.per_cu == 1) time = (double)((n + 255) / 256) * one;
+      if (t.two == 0.) time = (double)((n + 255) / 256) * one;
       else time = (double)(n / 512) * two + (n % 512 == 0 ? 0. : n % 512 <= 256 ? one : two);
       time = (time < memory ? memory : time) + 0.02 * time;       // (equally memory-bound: the one that computes faster)
-      if (split > 1) time = (thin ? 1.03 : 1.12) * (time + 3.8 + 0.303e-6 * split * M * N * sizeof(float));
-      if (time < best_time) {
-        best_time = time;
-        best = SplitPlan{i, split, slice, split > 1 ? kSplitHead + (size_t)split * M * N * sizeof(float) : 0};
-      }
+      if (plan.split > 1) time = (thin ? 1.03 : 1.12) * (time + 3.8 + 0.303e-6 * plan.split * M * N * sizeof(float));
+      if (time < best_time) { best_time = time; best = plan; }
+    }
+  }
+  return best;
+}
+static bool one_round(int M, int N) { return (long)((M + 255) / 256) * ((N + 255) / 256) <= 256; }
+static SplitPlan product_plan(int layout, int M, int N, int K, bool allow_split) {
+  const SplitPlan coarse = coarse_plan(layout, M, N, K, allow_split);
+  // Long products of 64 large tiles or more run at the power limit, where the tile that moves the fewest bytes is level or ahead
+  // whatever else it costs ([1024, 4096] x 22016 (NT) in four slices of 256 x 256 158.8 us, in two of 256 x 128 160.9).
+  if (K > 24576 && tiles_of(T256, M, N) >= 64) return coarse;
+  SplitPlan best = coarse;
+  const double coarse_time = product_time(kTileCost[coarse.tile], layout, M, N, K, tiles_of(coarse.tile, M, N) * coarse.split, coarse.slice, coarse.split);
+  double best_time = 1e30;
+  for (int i = T32; i <= T256; i++) {
+    const TileCost& t = kTileCost[i];
+    const long tiles = tiles_of(i, M, N);
+    if (i == T32 && tiles > 256) continue;
+    if (t.bm > 128 && M <= t.bm / 2) continue;
+    if (i == T128X192 && layout == NT && K % 64) continue;        // (rows across two lines: up to 1.8 times the modelled time)
+    for (int sp : kSlices) {
+      if (sp > 1 && (!allow_split || i == T32 || K / sp < 256)) break;
+      const SplitPlan plan = slices_of(i, M, N, K, sp);
+      const double time = product_time(t, layout, M, N, K, tiles * plan.split, plan.slice, plan.split);
+      // (its times of 32 x 32 tiles err most, those of the two largest of the new tiles least; up to 128 rows the coarse one is good)
+      const double must = coarse.tile == T32 ? 0.8 : M <= 128 ? 0.85 : i == T256X128 || i == T192 ? 0.96 : 0.9;
+      if (time < must * coarse_time && time < best_time) { best_time = time; best = plan; }
     }
   }
   return best;
@@ -1362,42 +1481,66 @@ static hipError_t launch_small(const GemmParams& p0, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int BM, int BN, bool AKC, bool BKC, int KD, int RING>
-static hipError_t launch_bf16_split(const GemmParams& p0, const SplitPlan& plan, void* ws, hipStream_t s) {
+template <int BM, int BN>
+static GemmParams with_tiles(const GemmParams& p0) {
   GemmParams p = p0;
   p.tiles_m = (p.M + BM - 1) / BM;
   p.tiles_n = (p.N + BN - 1) / BN;
+  return p;
+}
+// The slices of a product on `kern`, then their sum.
+static hipError_t launch_slices(void (*kern)(GemmParams), unsigned threads, size_t smem, GemmParams p, const SplitPlan& plan, void* ws, hipStream_t s) {
+  const void* const R = p.R;
+  void* const C = p.C;
+  const long ldc = p.ldc;
   p.split = plan.split; p.split_k = plan.slice;
   float* const parts = reinterpret_cast<float*>(static_cast<char*>(ws) + kSplitHead);
   p.C = parts; p.ldc = p.N; p.sCo = (long)p.M * p.N; p.sCi = 0; p.R = nullptr;
   p.sAo = p.sAi = p.sBo = p.sBi = 0;
-  constexpr size_t smem = (size_t)(RING >= 3 ? RING : (KD == 32 ? STAGES : 2)) * (BM + BN) * KD * sizeof(bf16_t);
-  auto kern = gemm_bf16_split_kernel<BM, BN, AKC, BKC, KD, RING>;
-  static AttrOnce once;
-  if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_m * p.tiles_n * plan.split)), dim3(256), smem, s, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_m * p.tiles_n * plan.split)), dim3(threads), smem, s, p);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   const long nv = (long)p.M * (p.N / 8);
-  hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, s, parts,
-                     plan.split, p.M, p.N, static_cast<const bf16_t*>(p0.R), static_cast<bf16_t*>(p0.C), p0.ldc);
+  hipLaunchKernelGGL(split_sum_kernel, dim3((unsigned)((nv + 255) / 256)), dim3(256), 0, s, parts, plan.split, p.M, p.N,
+                     static_cast<const bf16_t*>(R), static_cast<bf16_t*>(C), ldc);
   return hipGetLastError();
 }
 
-template <int BM, int BN, bool BKC, int RING>
-static hipError_t launch_product(const GemmParams& p, const SplitPlan& plan, void* ws, hipStream_t s) {
-  return plan.split > 1 ? launch_bf16_split<BM, BN, true, BKC, 64, RING>(p, plan, ws, s)
-                        : launch_bf16<BM, BN, true, BKC, bf16_t, 64, RING>(p, 1, s);
+// Tiles whose waves copy and multiply (256 x 256 and 256 x 192, two 64-deep slots).
+template <int BM, int BN, bool BKC>
+static hipError_t launch_product(const GemmParams& p0, const SplitPlan& plan, void* ws, hipStream_t s) {
+  if (plan.split == 1) return launch_bf16<BM, BN, true, BKC, bf16_t, 64, 0>(p0, 1, s);
+  constexpr size_t smem = (size_t)2 * (BM + BN) * 64 * sizeof(bf16_t);
+  auto kern = gemm_bf16_split_kernel<BM, BN, true, BKC, 64, 0>;
+  static AttrOnce once;
+  if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
+  return launch_slices(kern, 256, smem, with_tiles<BM, BN>(p0), plan, ws, s);
+}
+// Tiles with waves of their own for the copies, on RING 64-deep slots.
+template <int BM, int BN, bool BKC, int RING, int WGS = 1>
+static hipError_t launch_copiers(const GemmParams& p0, const SplitPlan& plan, void* ws, hipStream_t s) {
+  const GemmParams p = with_tiles<BM, BN>(p0);
+  constexpr size_t smem = (size_t)RING * (BM + BN) * 64 * sizeof(bf16_t);
+  static_assert(WGS * smem <= 160 * 1024, "LDS budget of one gfx950 compute unit");
+  auto kern = plan.split > 1 ? gemm_bf16_copiers_split_kernel<BM, BN, BKC, RING, WGS> : gemm_bf16_copiers_kernel<BM, BN, BKC, RING, WGS>;
+  static AttrOnce once[2];
+  if (hipError_t e = once[plan.split > 1].set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
+  if (plan.split > 1) return launch_slices(kern, 512, smem, p, plan, ws, s);
+  hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(512), smem, s, p);
+  return hipGetLastError();
 }
 template <bool BKC>
 static hipError_t dispatch_product(const GemmParams& p, const SplitPlan& plan, void* ws, hipStream_t s) {
   switch (plan.tile) {
-    case T128_DEEP: return launch_product<128, 128, BKC, 4>(p, plan, ws, s);
-    case T256_NARROW: return launch_product<256, 192, BKC, 0>(p, plan, ws, s);
-    case T256: return launch_product<256, 256, BKC, 0>(p, plan, ws, s);
-    case T128_PAIR: return launch_product<128, 128, BKC, 0>(p, plan, ws, s);
-    case T64: return launch_product<64, 64, BKC, 4>(p, plan, ws, s);
-    case T128_SHALLOW: return launch_bf16<128, 128, true, BKC, bf16_t, 32>(p, 1, s);
     case T32: return launch_small<BKC>(p, s);
+    case T64: return launch_copiers<64, 64, BKC, 4, 2>(p, plan, ws, s);
+    case T128X64: return launch_copiers<128, 64, BKC, 6>(p, plan, ws, s);
+    case T128: return launch_copiers<128, 128, BKC, 4>(p, plan, ws, s);
+    case T128_PAIR: return launch_copiers<128, 128, BKC, 2, 2>(p, plan, ws, s);
+    case T128X192: return launch_copiers<128, 192, BKC, 4>(p, plan, ws, s);
+    case T256X128: return launch_copiers<256, 128, BKC, 3>(p, plan, ws, s);
+    case T192: return launch_copiers<192, 192, BKC, 3>(p, plan, ws, s);
+    case T256_NARROW: return launch_product<256, 192, BKC>(p, plan, ws, s);
+    case T256: return launch_product<256, 256, BKC>(p, plan, ws, s);
   }
   return hipErrorInvalidValue;
 }

@@ -177,6 +177,31 @@ def test_gemm_tile_and_slice_choices(layout, mnk):
         assert torch.all(out[:, N:] == 7.0)
 
 
+@pytest.mark.parametrize("layout,mnk", [
+    (tbp.NN, (400, 4760, 64)), (tbp.NT, (2312, 872, 72)), (tbp.NN, (16, 3280, 5264)), (tbp.NT, (72, 3424, 2792)),        # 128 x 128, in slices
+    (tbp.NN, (416, 8440, 64)), (tbp.NT, (392, 8952, 64)),                                                                 # two of them per compute unit
+    (tbp.NN, (1040, 3744, 320)), (tbp.NT, (2440, 1640, 960)), (tbp.NN, (288, 3928, 4000)), (tbp.NT, (152, 5936, 5056)),   # 128 x 192
+    (tbp.NN, (408, 2352, 512)), (tbp.NT, (2832, 328, 464)), (tbp.NN, (328, 920, 2808)), (tbp.NT, (1912, 144, 2520)),      # 128 x 64
+    (tbp.NN, (1448, 5768, 144)), (tbp.NT, (1064, 7520, 160)), (tbp.NN, (144, 8344, 3112)), (tbp.NT, (136, 8608, 3376)),   # 192 x 192
+    (tbp.NN, (1744, 3488, 800)), (tbp.NT, (456, 8200, 720)), (tbp.NN, (168, 5904, 4416)), (tbp.NT, (408, 2976, 4040)),    # 256 x 128
+    (tbp.NN, (16, 8904, 8)), (tbp.NT, (16, 8648, 72)), (tbp.NN, (24, 80, 2408)), (tbp.NT, (16, 72, 4720))])               # 64 x 64
+def test_gemm_tiles_with_copying_waves(layout, mnk):
+    """Every tile whose copies are started by waves of their own, with the contraction whole and in slices (which end in a
+    shorter one), from one slot (rings of up to six then run past the end at once) to many; ragged in M, N and K, with a
+    residual.  The same bits from call to call.  Tolerance: one bf16 rounding of the result (2^-8 of the element at most)."""
+    M, N, K = mnk
+    _say(f"gemm, copying waves layout={layout} M,N,K={mnk}")
+    A, B = _rnd(19, "A", (M, K), "bf16"), _rnd(19, "B", (N, K) if layout == tbp.NT else (K, N), "bf16")
+    R = _rnd(19, "R", (M, N), "bf16", 4.0)
+    a64, b64 = A.astype(np.float64), B.astype(np.float64)
+    ref = ops.linear_p1(a64, b64) if layout == tbp.NT else ops.linear_fwd(a64, b64)
+    dA, dB, dR = to_dev(A, "bf16"), to_dev(B, "bf16"), to_dev(R, "bf16")
+    for workspace in (True, None):
+        got = tbp.tbp_gemm(layout, dA, dB, R=dR, alpha=0.5, workspace=workspace)
+        assert max_rel(to_np(got), 0.5 * ref + R) < 4.5e-3
+        assert torch.equal(got, tbp.tbp_gemm(layout, dA, dB, R=dR, alpha=0.5, workspace=workspace))
+
+
 def test_gemm_strided_views_and_empty():
     # operands that are column blocks of wider matrices (leading dimension > row length), as the stage uses them
     dtype = "bf16"
