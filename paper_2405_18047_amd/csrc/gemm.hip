@@ -40,6 +40,8 @@ struct GemmParams {
   // contraction cut into `split` slices of split_k indices, one workgroup per (tile, slice) (see SplitPlan); slice i leaves
   // its partial product at C + i * sCo
   int split, split_k;
+  const void* gu;               // see GemmArgs
+  PairEpilogue pair;            // paired columns (gemm_bf16_pairs_kernel)
 };
 
 constexpr int BK = 32;                     // contraction depth of one LDS slot
@@ -631,6 +633,14 @@ __global__ __launch_bounds__(256) void gemm_bf16_split_kernel(GemmParams p) {
 }
 
 constexpr int kSmallSlots = 4;                 // ring slots per wave of the small-output kernel
+constexpr int kPairSlots = 3;                  // the same with two images of B per slot
+
+// d(silu(gate) * up) for an output derivative v
+__device__ __forceinline__ void swiglu_backward(float v, float gate, float up, float& dgate, float& dup) {
+  const float s = 1.f / (1.f + __expf(-gate));
+  dgate = v * up * s * (1.f + gate * (1.f - s));
+  dup = v * gate * s;
+}
 
 // Outputs of at most one 32 x 32 tile per compute unit (storage-type NN / NT products of short micro-batches).  What bounds
 // such a product is latency: a workgroup has few slots to walk, and every barrier and every slot that is not yet in flight
@@ -639,7 +649,7 @@ constexpr int kSmallSlots = 4;                 // ring slots per wave of the sma
 // the LDS (added in wave order), and 12 slots on their way at once.
 // Measured against 64 x 64 tiles (us): [128, 256] x 256 4.2 -> 3.7, x 768 6.0 -> 4.2, x 1376 8.4 -> 4.7, [256, 1024] x 5504
 // 14.5 -> 11.9, [64, 4096] x 4096 22 -> 11; at more than one tile per compute unit it loses ([200, 1536] x 512 5.4 -> 6.9).
-template <bool BKC>
+template <bool BKC, bool SWIGLU>
 __global__ __launch_bounds__(256) void gemm_bf16_small_kernel(GemmParams p) {
   using TA = OperandTile<32, true, 64>;
   using TB = OperandTile<32, BKC, 64>;
@@ -684,6 +694,18 @@ __global__ __launch_bounds__(256) void gemm_bf16_small_kernel(GemmParams p) {
     slot_next = slot_next + 1 == NS ? 0 : slot_next + 1;
     krem -= 4 * KD;
   };
+  const int col = n0 + (lane & 31);
+  float gate[4], up[4];
+  if constexpr (SWIGLU) {                     // what the epilogue reads, requested before everything else
+    const bf16_t* const gu = reinterpret_cast<const bf16_t*>(p.gu);
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      const int row = m0 + 8 * wave + 4 * (lane >> 5) + q;
+      const long idx = row < p.M && col < p.N ? (long)row * p.ldc + col : 0;
+      gate[q] = (float)gu[idx];
+      up[q] = (float)gu[idx + p.N];
+    }
+  }
   f32x16 acc;
 #pragma unroll
   for (int e = 0; e < 16; e++) acc[e] = 0.f;
@@ -717,7 +739,6 @@ __global__ __launch_bounds__(256) void gemm_bf16_small_kernel(GemmParams p) {
   // each wave adds up and stores 8 rows: registers 4 w .. 4 w + 3 are rows 8 w + 4 (lane / 32) + 0..3
   const bf16_t* R = reinterpret_cast<const bf16_t*>(p.R);
   bf16_t* C = reinterpret_cast<bf16_t*>(p.C);
-  const int col = n0 + (lane & 31);
 #pragma unroll
   for (int q = 0; q < 4; q++) {
     const int e = 4 * wave + q, row = m0 + 8 * wave + 4 * (lane >> 5) + q;
@@ -727,8 +748,127 @@ __global__ __launch_bounds__(256) void gemm_bf16_small_kernel(GemmParams p) {
     if (row >= p.M || col >= p.N) continue;
     const long idx = (long)row * p.ldc + col;
     v *= p.alpha;
+    if constexpr (SWIGLU) {
+      float dg, du;
+      swiglu_backward(v, gate[q], up[q], dg, du);
+      C[idx] = (bf16_t)dg;
+      C[idx + p.N] = (bf16_t)du;
+      continue;
+    }
     if (R) v += (float)R[idx];
     C[idx] = (bf16_t)v;
+  }
+}
+
+// The same for a product whose columns c and c + (a fixed distance) go into one result: gate and up of the SwiGLU (the distance
+// is the FFN width), or the two halves of a head that the rotary embedding turns (half the head width).  A workgroup takes 32
+// columns and their 32 partners, a lane holds both, and what would be a launch of its own over [rows, columns] becomes a few
+// instructions here, on values that have not been rounded yet.  Launches are what a micro-batch this small costs: SwiGLU and
+// rotation were 2.8 of 72 us each in a layer of d 256, f 688 on 128 tokens.
+__global__ __launch_bounds__(256) void gemm_bf16_pairs_kernel(GemmParams p) {
+  using TA = OperandTile<32, true, 64>;
+  using TB = OperandTile<32, false, 64>;
+  constexpr int KD = 64, NS = kPairSlots, L = 12, SLOT = 12288;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  lds_u8* const lds = LDS_PTR(unsigned char, smem_raw);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  lds_u8* const ring = lds + wave * (NS * SLOT);
+  const uint32_t ring0 = (uint32_t)(uintptr_t)lds + wave * (NS * SLOT);
+  int tm_i, tn_i;
+  tile_of_block(blockIdx.x, p.tiles_m, p.tiles_n, tm_i, tn_i);
+  const PairEpilogue& pe = p.pair;
+  // first column (its partner is `distance` further) and the end of the first columns of this group (a head, or all gate columns)
+  const int m0 = tm_i * 32, group = tn_i * 32 / pe.distance;
+  const int n0 = tn_i * 32 + group * pe.distance, n_end = (2 * group + 1) * pe.distance;
+  const bf16_t* A = reinterpret_cast<const bf16_t*>(p.A);
+  const bf16_t* B = reinterpret_cast<const bf16_t*>(p.B);
+  unsigned a_goff[4], b_goff[4];
+  int a_kidx[4], b_kidx[4];
+#pragma unroll
+  for (int i = 0; i < 4; i++) {
+    TA::copy_plan(i, lane, p.lda, m0, p.M, a_goff[i], a_kidx[i]);
+    TB::copy_plan(i, lane, p.ldb, n0, n_end, b_goff[i], b_kidx[i]);
+  }
+  const int k0 = wave * KD;                   // this wave's slots: k0, k0 + 4 KD, ...
+  uint64_t a_next = reinterpret_cast<uint64_t>(A + (long)m0 * p.lda + k0);
+  uint64_t b_next = reinterpret_cast<uint64_t>(B + n0 + (long)k0 * p.ldb);
+  int slot_next = 0, krem = p.K - k0;
+  const int nk = krem > 0 ? (krem + 4 * KD - 1) / (4 * KD) : 0;
+  auto issue = [&]() {                        // past the end: every lane out of range, zeros, no traffic
+    const u32x4 dA = make_desc(reinterpret_cast<const void*>(a_next)), dB = make_desc(reinterpret_cast<const void*>(b_next)),
+                dP = make_desc(reinterpret_cast<const void*>(b_next + (uint64_t)pe.distance * 2));
+    const uint32_t base = ring0 + slot_next * SLOT;
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+      dma16(base + i * 1024, dA, a_kidx[i] < krem ? a_goff[i] : kOob);
+      dma16(base + 4096 + i * 1024, dB, b_kidx[i] < krem ? b_goff[i] : kOob);
+      dma16(base + 8192 + i * 1024, dP, b_kidx[i] < krem ? b_goff[i] : kOob);
+    }
+    a_next += (uint64_t)(4 * KD * 2);
+    b_next += (uint64_t)(4 * KD * p.ldb * 2);
+    slot_next = slot_next + 1 == NS ? 0 : slot_next + 1;
+    krem -= 4 * KD;
+  };
+  f32x16 acc[2];
+#pragma unroll
+  for (int e = 0; e < 16; e++) { acc[0][e] = 0.f; acc[1][e] = 0.f; }
+  if (nk > 0) {
+#pragma unroll
+    for (int t = 0; t < NS - 1; t++) issue();
+    for (int t = 0; t < nk; t++) {
+      wait_vmem<(NS - 2) * L>();              // this wave's slot t has landed
+      asm volatile("" ::: "memory");          // (its fragments must not be fetched earlier)
+      __builtin_amdgcn_sched_barrier(0);
+      lds_u8* const ia = ring + (t % NS) * SLOT;
+      issue();                                // slot t + NS - 1 in the place of slot t - 1, whose fragments have been used
+      bf16x8 fa[4], fb[4], fp[4];
+#pragma unroll
+      for (int v = 0; v < 4; v++) {
+        fa[v] = read_frag<32, true>(ia + TA::frag_base(lane, 0, TA::variant(v, 0)) + TA::frag_step(v, 0));
+        fb[v] = read_frag<32, false>(ia + 4096 + TB::frag_base(lane, 0, TB::variant(v, 0)) + TB::frag_step(v, 0));
+        fp[v] = read_frag<32, false>(ia + 8192 + TB::frag_base(lane, 0, TB::variant(v, 0)) + TB::frag_step(v, 0));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int v = 0; v < 4; v++) {
+        acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[v], fb[v], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[v], fp[v], acc[1], 0, 0, 0);
+      }
+    }
+    wait_vmem<0>();                           // (the empty copies issued past the end)
+  }
+  __syncthreads();                            // every wave is done with its ring
+  LDS_AS float* const part = reinterpret_cast<LDS_AS float*>(lds);
+#pragma unroll
+  for (int h = 0; h < 2; h++)
+#pragma unroll
+    for (int e = 0; e < 16; e++) part[((h * 4 + wave) * 16 + e) * 64 + lane] = acc[h][e];
+  __syncthreads();
+  bf16_t* C = reinterpret_cast<bf16_t*>(p.C);
+  const int col = n0 + (lane & 31);
+#pragma unroll
+  for (int q = 0; q < 4; q++) {
+    const int e = 4 * wave + q, row = m0 + 8 * wave + 4 * (lane >> 5) + q;
+    float v[2];
+#pragma unroll
+    for (int h = 0; h < 2; h++) {
+      v[h] = part[(h * 64 + e) * 64 + lane];
+#pragma unroll
+      for (int w = 1; w < 4; w++) v[h] += part[((h * 4 + w) * 16 + e) * 64 + lane];
+    }
+    if (row >= p.M || col >= n_end) continue;
+    const long idx = (long)row * p.ldc + col;
+    if (pe.m) {
+      reinterpret_cast<bf16_t*>(pe.m)[(long)row * pe.distance + col] = (bf16_t)(v[0] / (1.f + __expf(-v[0])) * v[1]);
+    } else if (group < pe.rotated) {
+      const float2 t = pe.rope[(long)(row % pe.seq) * pe.distance + (col - 2 * group * pe.distance)];
+      const float x = v[0], y = v[1];
+      v[0] = x * t.x - y * t.y;
+      v[1] = x * t.y + y * t.x;
+    }
+    C[idx] = (bf16_t)v[0];
+    C[idx + pe.distance] = (bf16_t)v[1];
   }
 }
 
@@ -889,7 +1029,7 @@ struct OperandTileF32 {
   }
 };
 
-template <int BM, int BN, bool AKC, bool BKC, int WK, int KD, int NS>
+template <int BM, int BN, bool AKC, bool BKC, int WK, int KD, int NS, bool SWIGLU>
 __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(GemmParams p) {
   using TA = OperandTileF32<BM, AKC, KD>;
   using TB = OperandTileF32<BN, BKC, KD>;
@@ -1018,6 +1158,34 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(GemmParams p) {
   // whole MFMA tile at a time: one value at a time, between stores that the compiler must take to alias the next load, old
   // values made an accumulating [2616, 4084] x 64 product 66 us (now 38), and P and delta the 16 x [512, 512] x 64 product of a
   // score gradient 40 us (now 15).  The overwriting kernel keeps a branch of its own: sharing this one cost it 20-30 %.
+  if constexpr (SWIGLU) {                           // gate and up in, their derivatives out
+    const float* const gu = reinterpret_cast<const float*>(p.gu);
+#pragma unroll
+    for (int i = 0; i < TM; i++)
+#pragma unroll
+      for (int j = 0; j < TN; j++) {
+        const int col = n0 + (wn * TN + j) * 32 + (lane & 31);
+        float gate[NE], up[NE];
+#pragma unroll
+        for (int e = 0; e < NE; e++) {
+          const int row = row_of(i, e);
+          const long idx = row < p.M && col < p.N ? (long)row * p.ldc + col : 0;
+          gate[e] = gu[idx];
+          up[e] = gu[idx + p.N];
+        }
+#pragma unroll
+        for (int e = 0; e < NE; e++) {
+          const int row = row_of(i, e);
+          float dg, du;
+          swiglu_backward(p.alpha * acc[i][j][e], gate[e], up[e], dg, du);
+          if (row < p.M && col < p.N) {
+            C[(long)row * p.ldc + col] = dg;
+            C[(long)row * p.ldc + col + p.N] = du;
+          }
+        }
+      }
+    return;
+  }
   if ((p.accumulate || R) && !(p.accumulate && R && !delta)) {
     const float* const src = R ? R : C;
 #pragma unroll
@@ -1108,7 +1276,7 @@ struct SmallTileF32 {
   }
 };
 
-template <bool AKC, bool BKC>
+template <bool AKC, bool BKC, bool SWIGLU>
 __global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmParams p) {
   using TA = SmallTileF32<AKC>;
   using TB = SmallTileF32<BKC>;
@@ -1201,6 +1369,14 @@ __global__ __launch_bounds__(256) void gemm_f32_small_kernel(GemmParams p) {
   const float* const R = p.R ? reinterpret_cast<const float*>(p.R) + zo * p.sCo + zi * p.sCi : nullptr;
   const long idx = (long)row * p.ldc + col;
   v *= p.alpha;
+  if constexpr (SWIGLU) {
+    const float* const gu = reinterpret_cast<const float*>(p.gu);
+    float dg, du;
+    swiglu_backward(v, gu[idx], gu[idx + p.N], dg, du);
+    C[idx] = dg;
+    C[idx + p.N] = du;
+    return;
+  }
   if (p.delta) {
     v = (!p.delta_causal || col <= row) ? R[idx] * (v - p.delta[zo * p.sDo + zi * p.sDi + (long)row * p.ldd]) : 0.f;
   } else {
@@ -1468,13 +1644,13 @@ SplitPlan gemm_split_plan(int dtype, int layout, int M, int N, int K, int out_f3
   return plan.split > 1 ? plan : none;
 }
 
-template <bool BKC>
+template <bool BKC, bool SWIGLU = false>
 static hipError_t launch_small(const GemmParams& p0, hipStream_t s) {
   GemmParams p = p0;
   p.tiles_m = (p.M + 31) / 32;
   p.tiles_n = (p.N + 31) / 32;
   constexpr size_t smem = (size_t)4 * kSmallSlots * 8192;
-  auto kern = gemm_bf16_small_kernel<BKC>;
+  auto kern = gemm_bf16_small_kernel<BKC, SWIGLU>;
   static AttrOnce once;
   if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(256), smem, s, p);
@@ -1739,14 +1915,14 @@ static bool f32_mfma_ok(const GemmArgs& g) {
          g.lda < (1 << 22) && g.ldb < (1 << 22);
 }
 
-template <int BM, int BN, bool AKC, bool BKC, int WK, int KD, int NS>
+template <int BM, int BN, bool AKC, bool BKC, int WK, int KD, int NS, bool SWIGLU = false>
 static hipError_t launch_f32(const GemmParams& p0, int batch, hipStream_t s) {
   GemmParams p = p0;
   p.tiles_m = (p.M + BM - 1) / BM;
   p.tiles_n = (p.N + BN - 1) / BN;
   constexpr size_t smem = (size_t)NS * (BM + BN) * KD * sizeof(float);
   static_assert(smem <= 160 * 1024, "LDS budget of one gfx950 compute unit");
-  auto kern = gemm_f32_mfma_kernel<BM, BN, AKC, BKC, WK, KD, NS>;
+  auto kern = gemm_f32_mfma_kernel<BM, BN, AKC, BKC, WK, KD, NS, SWIGLU>;
   static AttrOnce once;
   if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)batch), dim3(256), smem, s, p);
@@ -1768,9 +1944,10 @@ static hipError_t launch_f32_small(int layout, const GemmParams& p0, int batch, 
   p.tiles_m = (p.M + 15) / 16;
   p.tiles_n = (p.N + 15) / 16;
   constexpr size_t smem = (size_t)4 * kSmallSlots * 4096;
-  auto kern = layout == NN ? gemm_f32_small_kernel<true, false> : layout == NT ? gemm_f32_small_kernel<true, true> : gemm_f32_small_kernel<false, false>;
-  static AttrOnce once[3];
-  if (hipError_t e = once[layout].set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
+  auto kern = p.gu ? gemm_f32_small_kernel<true, true, true> : layout == NN ? gemm_f32_small_kernel<true, false, false>
+              : layout == NT ? gemm_f32_small_kernel<true, true, false> : gemm_f32_small_kernel<false, false, false>;
+  static AttrOnce once[4];
+  if (hipError_t e = once[p.gu ? 3 : layout].set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)(p.tiles_m * p.tiles_n), 1, (unsigned)batch), dim3(256), smem, s, p);
   return hipGetLastError();
 }
@@ -1805,7 +1982,7 @@ static int f32_tile(int M, int N, int K, int batch) {
 static hipError_t dispatch_f32(int layout, const GemmParams& p, int batch, hipStream_t s) {
   switch (f32_tile(p.M, p.N, p.K, batch)) {
     case 16: return launch_f32_small(layout, p, batch, s);
-    case 32: return launch_f32_layout<32, 32, 4, 128, 2>(layout, p, batch, s);
+    case 32: return p.gu ? launch_f32<32, 32, true, true, 4, 128, 2, true>(p, batch, s) : launch_f32_layout<32, 32, 4, 128, 2>(layout, p, batch, s);
     case 64: return launch_f32_layout<64, 64, 1, 64, 2>(layout, p, batch, s);
   }
   return launch_f32_layout<128, 128, 1, 32, 2>(layout, p, batch, s);
@@ -1823,6 +2000,41 @@ int gemm_row_tile(int dtype, const GemmArgs& g) {
   return !g.a_panel && large_tiles(g) ? 256 : 128;
 }
 
+static SplitPlan plan_of(const GemmArgs& g) {
+  SplitPlan plan = product_plan(g.layout, g.M, g.N, g.K, g.ws && reinterpret_cast<uintptr_t>(g.ws) % 256 == 0);
+  if (plan.bytes > g.ws_bytes) plan = product_plan(g.layout, g.M, g.N, g.K, false);
+  return plan;
+}
+
+// Where the epilogue pays: fp32 products of at most two 32 x 32 tiles per compute unit (256 tokens, d 256, f 688: 5.6 us and 3.0 for the
+// SwiGLU, now 6.4; 512 tokens, d 1024, f 2752 level) and bf16 ones on 32 x 32 tiles (128 tokens: 4.1 and 2.9, now 4.6).  On long micro-batches it gains nothing: the larger tiles have no second
+// workgroup under whose work the three passes over memory could hide, and they run at the power limit.
+bool gemm_swiglu_p1_fuses(int dtype, const GemmArgs& g) {
+  if (g.layout != NT || g.batch != 1 || g.M <= 0 || g.N <= 0 || g.K <= 0) return false;
+  if (dtype == 0) return f32_mfma_ok(g) && (long)((g.M + 31) / 32) * ((g.N + 31) / 32) <= 512 && f32_tile(g.M, g.N, g.K, 1) <= 32;
+  return one_round(g.M, g.N) && plan_of(g).tile == T32;
+}
+
+// One launch for an NN product of at most 256 tiles of 32 x 32 and what follows it on pairs of its columns.
+bool gemm_pairs_fuse(int dtype, const GemmArgs& g, int distance) {
+  return dtype == 1 && g.layout == NN && g.batch == 1 && g.M > 0 && g.K > 0 && distance % 8 == 0 && g.N % (2 * distance) == 0 &&
+         (distance % 32 == 0 || g.N == 2 * distance) && one_round(g.M, g.N) && plan_of(g).tile == T32;
+}
+hipError_t gemm_pairs(const GemmArgs& g, const PairEpilogue& pair, hipStream_t s) {
+  GemmParams p{};
+  p.A = g.A; p.B = g.B; p.C = g.C;
+  p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc;
+  p.M = g.M; p.N = g.N; p.K = g.K;
+  p.pair = pair;
+  p.tiles_m = (g.M + 31) / 32;
+  p.tiles_n = (g.N / 2 + 31) / 32;
+  constexpr size_t smem = (size_t)4 * kPairSlots * 12288;
+  static AttrOnce once;
+  if (hipError_t e = once.set(reinterpret_cast<const void*>(gemm_bf16_pairs_kernel), smem); e != hipSuccess) return e;
+  hipLaunchKernelGGL(gemm_bf16_pairs_kernel, dim3((unsigned)(p.tiles_m * p.tiles_n)), dim3(256), smem, s, p);
+  return hipGetLastError();
+}
+
 hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;     // empty product: nothing to write
   GemmParams p{};
@@ -1834,6 +2046,11 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   p.alpha = g.alpha; p.accumulate = g.accumulate; p.causal = g.causal;
   p.delta = g.delta; p.ldd = g.ldd; p.sDo = g.sDo; p.sDi = g.sDi; p.delta_causal = g.delta_causal;
   p.causal_fill = g.delta && g.delta_causal ? g.causal_fill : 0;
+  p.gu = g.gu;
+  if (g.gu) {
+    if (!gemm_swiglu_p1_fuses(dtype, g)) return hipErrorInvalidValue;
+    if (dtype == 1) return launch_small<true, true>(p, s);
+  }
   if (dtype == 0) {
     if (g.a_panel) return hipErrorInvalidValue;
     switch (g.layout) {
@@ -1863,8 +2080,7 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
   const long tiles_big = (long)tiles_m * tiles_n * g.batch;
   const bool big = large_tiles(g);
   if (!g.out_f32 && g.batch == 1 && g.causal == CAUSAL_NONE && !g.delta && g.layout != TN && one_round(g.M, g.N)) {
-    SplitPlan plan = product_plan(g.layout, g.M, g.N, g.K, g.ws && reinterpret_cast<uintptr_t>(g.ws) % 256 == 0);
-    if (plan.bytes > g.ws_bytes) plan = product_plan(g.layout, g.M, g.N, g.K, false);
+    const SplitPlan plan = plan_of(g);
     return g.layout == NN ? dispatch_product<false>(p, plan, g.ws, s) : dispatch_product<true>(p, plan, g.ws, s);
   }
   if (!g.out_f32 && g.batch == 1 && g.causal == CAUSAL_NONE && !g.delta && g.layout != TN && narrow_tiles_pay(g.M, g.N, g.K))

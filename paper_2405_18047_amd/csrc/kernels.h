@@ -52,6 +52,18 @@ struct GemmArgs {
   // A[(m / kPanel) * a_panel + k * lda + m % kPanel] with lda == kPanel, so that the K x kPanel slab an output tile
   // contracts over is one contiguous stream.  0: plain [K, lda] matrix.  Such a product runs on kPanel-wide tiles.
   long a_panel;
+  // SwiGLU backward fused into the epilogue of dm = dx Wd^T ([M, N] = [tokens, f]), where gemm_swiglu_p1_fuses: gate and up, C
+  // receives their derivatives; both [M, 2 N] with leading dimension ldc, up behind gate.
+  const void* gu;
+};
+// An NN product whose columns c and c + distance go into one result (see gemm_pairs_fuse): with m set, gate and up columns of a
+// SwiGLU (distance = f; m [M, distance] receives silu(gate) * up); otherwise heads of 2 * distance columns, the first `rotated`
+// of which leave rotated (rope: table [seq][distance], row r at position r % seq).
+struct PairEpilogue {
+  int distance;
+  void* m;
+  const float2* rope;
+  int seq, rotated;
 };
 constexpr int kPanel = 128;
 // elements of one (sequence, head) entry of the fused attention's dS^T scratch, stored in such panels
@@ -75,6 +87,9 @@ inline GemmArgs gemm_args(int layout, int M, int N, int K, const void* A, long l
 
 // dtype: 0 = fp32 storage, 1 = bf16 storage (matches tbp_dtype).
 hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s);
+bool gemm_swiglu_p1_fuses(int dtype, const GemmArgs& g);
+bool gemm_pairs_fuse(int dtype, const GemmArgs& g, int distance);
+hipError_t gemm_pairs(const GemmArgs& g, const PairEpilogue& pair, hipStream_t s);
 // Rows of the output tiles that gemm() runs a product with a causal contraction (K_END, K_BEGIN) on.
 int gemm_row_tile(int dtype, const GemmArgs& g);
 

@@ -239,13 +239,14 @@ GemmArgs head_gemm(const Dims& c, int layout, int M, int N, int K) {
 
 // A linear-layer product of the forward or backward-p1 pass: handed the stage's scratch when its output is small
 // enough for the contraction to be split over several workgroups per tile.
-hipError_t linear_gemm(tbp_stage* st, GemmArgs g, hipStream_t s) {
+GemmArgs with_scratch(tbp_stage* st, GemmArgs g) {
   if (st->y.ws_split_bytes) {
     g.ws = st->ws(st->y.ws_split);
     g.ws_bytes = st->y.ws_split_bytes;
   }
-  return tbp::gemm(st->c.dtype, g, s);
+  return g;
 }
+hipError_t linear_gemm(tbp_stage* st, const GemmArgs& g, hipStream_t s) { return tbp::gemm(st->c.dtype, with_scratch(st, g), s); }
 
 tbp_status run_forward(tbp_stage* st, int mb, int slot, const void* x_in, void* x_out, hipStream_t s) {
   const Dims& c = st->c;
@@ -274,8 +275,13 @@ tbp_status run_forward(tbp_stage* st, int mb, int slot, const void* x_in, void* 
       void* P = st->aslot(l, A_P, slot);
       void* a = st->wslab(l, W_A, mb);
       TBP_HIP(l == 0 ? first_norm(x0, st->g1[l], h1) : tbp::rmsnorm_fwd(dt, T, d, c.eps, x0, st->g1[l], h1, s));
-      TBP_HIP(linear_gemm(st, gemm_args(tbp::NN, T, 3 * d, d, h1, d, st->w_qkv[l], 3 * d, qkv, 3 * d), s));
-      TBP_HIP(tbp::rope(dt, T, c.S, 2 * c.H, c.dh, 3 * d, (const float2*)st->ws(st->y.ws_rope), 0, qkv, s));
+      const GemmArgs gqkv = with_scratch(st, gemm_args(tbp::NN, T, 3 * d, d, h1, d, st->w_qkv[l], 3 * d, qkv, 3 * d));
+      if (tbp::gemm_pairs_fuse(dt, gqkv, c.dh / 2)) {
+        TBP_HIP(tbp::gemm_pairs(gqkv, {c.dh / 2, nullptr, (const float2*)st->ws(st->y.ws_rope), c.S, 2 * c.H}, s));
+      } else {
+        TBP_HIP(tbp::gemm(dt, gqkv, s));
+        TBP_HIP(tbp::rope(dt, T, c.S, 2 * c.H, c.dh, 3 * d, (const float2*)st->ws(st->y.ws_rope), 0, qkv, s));
+      }
       if (c.fused) {
         TBP_HIP(tbp::attention_fwd(c.B, c.H, c.S, c.dh, c.causal, qkv, 3 * d, a, d, (float*)st->aslot(l, A_LSE, slot), s));
       } else {
@@ -309,8 +315,13 @@ tbp_status run_forward(tbp_stage* st, int mb, int slot, const void* x_in, void* 
     void* gu = st->aslot(l, A_GU, slot);
     void* m = st->wslab(l, W_M, mb);
     TBP_HIP(l == 0 && !c.attn ? first_norm(x1, st->g2[l], h2) : tbp::rmsnorm_fwd(dt, T, d, c.eps, x1, st->g2[l], h2, s));
-    TBP_HIP(linear_gemm(st, gemm_args(tbp::NN, T, 2 * f, d, h2, d, st->w_gu[l], 2 * f, gu, 2 * f), s));
-    TBP_HIP(tbp::swiglu_fwd(dt, T, f, gu, m, s));
+    const GemmArgs ggu = with_scratch(st, gemm_args(tbp::NN, T, 2 * f, d, h2, d, st->w_gu[l], 2 * f, gu, 2 * f));
+    if (tbp::gemm_pairs_fuse(dt, ggu, f)) {
+      TBP_HIP(tbp::gemm_pairs(ggu, {f, m, nullptr, 1, 0}, s));
+    } else {
+      TBP_HIP(tbp::gemm(dt, ggu, s));
+      TBP_HIP(tbp::swiglu_fwd(dt, T, f, gu, m, s));
+    }
     {  // x2 = x1 + m Wd, written where the next layer (or the caller) wants its input
       void* dst = (l + 1 < c.L) ? (c.attn ? st->x0_of(l + 1, mb, slot) : st->x1_of(l + 1, mb, slot)) : x_out;
       GemmArgs g = gemm_args(tbp::NN, T, d, f, m, f, st->w_d[l], d, dst, d);
@@ -345,8 +356,14 @@ tbp_status run_p1(tbp_stage* st, int mb, int slot, const void* dy, void* dx, hip
     // where this layer's input gradient goes: previous layer's dx2 slab, or the caller
     void* dx_out = (l > 0) ? st->wslab(l - 1, W_DX2, mb) : dx;
     // dm = dx2 Wd^T
-    TBP_HIP(linear_gemm(st, gemm_args(tbp::NT, T, f, d, dx2, d, st->w_d[l], d, dm, f), s));
-    TBP_HIP(tbp::swiglu_p1(dt, T, f, dm, gu, dgu, s));
+    GemmArgs gdm = with_scratch(st, gemm_args(tbp::NT, T, f, d, dx2, d, st->w_d[l], d, dm, f));
+    if (tbp::gemm_swiglu_p1_fuses(dt, gdm)) {
+      gdm.gu = gu; gdm.C = dgu; gdm.ldc = 2 * f;
+      TBP_HIP(tbp::gemm(dt, gdm, s));
+    } else {
+      TBP_HIP(tbp::gemm(dt, gdm, s));
+      TBP_HIP(tbp::swiglu_p1(dt, T, f, dm, gu, dgu, s));
+    }
     // dh2 = [dg, du] Wgu^T
     TBP_HIP(linear_gemm(st, gemm_args(tbp::NT, T, d, 2 * f, dgu, 2 * f, st->w_gu[l], 2 * f, dh, d), s));
     void* dx1 = c.attn ? st->wslab(l, W_DX1, mb) : dx_out;

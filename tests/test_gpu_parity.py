@@ -724,6 +724,33 @@ def test_fused_attention_on_few_and_many_workgroups(seq, nb, H, dh, causal):
             assert max_rel(blk, ref) < 1.5e-2, (name, recompute)
 
 
+@pytest.mark.parametrize("shape", [
+    # bf16 on 32 x 32 tiles: an FFN width and a number of tokens that are no multiple of 32; heads of two and of four tiles; an FFN
+    # narrower than a tile; 256 tiles of gate and up, and 272 (not fused); a head width that is never fused; no attention
+    si.StageShape("pairs_64", 1, 128, 2, 64, 200, 40, 1, 2, "bf16", 71), si.StageShape("pairs_128", 2, 256, 2, 128, 344, 72, 1, 1, "bf16", 72),
+    si.StageShape("pairs_thin", 1, 128, 2, 64, 24, 8, 2, 1, "bf16", 73), si.StageShape("pairs_256", 1, 64, 1, 64, 2048, 64, 1, 1, "bf16", 74),
+    si.StageShape("pairs_272", 1, 64, 1, 64, 2176, 64, 1, 1, "bf16", 75), si.StageShape("pairs_96", 1, 192, 2, 96, 264, 48, 1, 1, "bf16", 76),
+    si.StageShape("pairs_mlp", 1, 128, 0, 0, 264, 56, 1, 2, "bf16", 77),
+    # fp32: the SwiGLU backward in the epilogue of 16 and 32 wide tiles, ragged; 544 tiles, 64 and 128 wide ones (not fused)
+    si.StageShape("swiglu_16", 1, 64, 1, 64, 100, 36, 1, 1, "f32", 78), si.StageShape("swiglu_32", 1, 128, 2, 64, 1060, 100, 2, 1, "f32", 79),
+    si.StageShape("swiglu_544", 1, 128, 0, 0, 1060, 508, 1, 1, "f32", 82),
+    si.StageShape("swiglu_64", 1, 128, 0, 0, 2100, 500, 1, 1, "f32", 80), si.StageShape("swiglu_128", 1, 64, 0, 0, 4100, 2052, 1, 1, "f32", 81)],
+    ids=lambda s: s.name)
+def test_elementwise_steps_inside_products(shape):
+    """Rotation and SwiGLU in the products before them, where products are small enough: whole
+    stages against the oracle on both sides of the line, twice on one stage (the second pass finds the buffers used)."""
+    _say(f"fused elementwise {shape.name}")
+    params, xs, dys = _stage_inputs(shape)
+    outs, dxs, grads = run_oracle(shape, params, xs, dys)
+    st = make_gpu_stage(shape, params)
+    for _ in range(2):
+        g_out = [st.forward(m, to_dev(x, shape.dtype)) for m, x in enumerate(xs)]
+        g_dx = [st.backward_p1(m, to_dev(d, shape.dtype)) for m, d in enumerate(dys)]
+        st.backward_p2(range(len(xs)), tbp.TBP_P2_KCONCAT, accumulate=False)
+        compare_stage(shape, g_out, g_dx, st.grads, outs, dxs, grads, stage_tolerance(shape.dtype), shape.name)
+    st.close()
+
+
 # (seq, head_dim, heads, micro_batch, dtype): the tiles of the score-gradient product and of the products that read it
 SCORE_TILES = [
     (64, 128, 2, 16, "f32"),      # fp32: 16 x 16 read by 32 x 32
