@@ -82,8 +82,8 @@ typedef enum { TBP_P2_LOOP = 0, TBP_P2_KCONCAT = 1 } tbp_p2_mode;
  *   FUSED         one forward kernel and one backward kernel that never write scores or probabilities: only the
  *                 row log-sum-exp [batch, heads, seq] is stashed and p1 rebuilds the probabilities from it
  *                 (bf16 storage, head_dim 64 or 128; TBP_EINVAL otherwise).  p1's dq comes from a product with dS^T, which
- *                 the first pass writes to the workspace, or, on large grids where that is faster, as with
- *                 FUSED_RECOMPUTE (no dS^T workspace is asked for then);
+ *                 the first pass writes to the workspace, or, where that is faster, as with FUSED_RECOMPUTE (on
+ *                 large grids no dS^T workspace is asked for then);
  *   FUSED_RECOMPUTE  FUSED, with a backward whose dq always comes from a second pass over the keys that rebuilds the scores
  *                 and dP: three more products per tile, no dS^T workspace (batch * heads * seq^2 storage-type
  *                 elements); same availability rule as FUSED;
@@ -268,7 +268,7 @@ tbp_status tbp_attention_fwd(int dtype, int batch, int n_heads, int seq, int hea
  * [batch*seq, ld_dqkv], from qkv, the forward's out and lse, and d_out = derivative of out (out and d_out dense:
  * ld_out == n_heads*head_dim).  The probabilities are rebuilt from lse; dS = P * (dP - rowsum(d_out * out)).
  * scratch: device, 256-byte aligned, >= tbp_attention_p1_scratch_bytes(batch, n_heads, seq) (row sums and room for
- * dS^T, which large grids leave unused; the size grows with each argument, so scratch for the largest call serves all).
+ * dS^T, which many grids leave unused; the size grows with each argument, so scratch for the largest call serves all).
  * tbp_attention_p1_recompute is the same operation with dq from a recompute pass (see TBP_ATTN_FUSED_RECOMPUTE): its
  * scratch holds the row sums only, tbp_attention_p1_recompute_scratch_bytes(batch, n_heads, seq) bytes. */
 size_t tbp_attention_p1_scratch_bytes(int batch, int n_heads, int seq);

@@ -1,9 +1,9 @@
 // GEMM kernels for gfx950 (MI355X).
 //
 // bf16 path: C = alpha * op(A) op(B) on the 32x32x16 bf16 MFMA instruction, fp32 accumulation.
-//   One workgroup = 4 wavefronts (2 x 2), block tile BM x BN (256 x 256, 256 x 192, 128 x 128 or 64 x 64, chosen per
-//   product by how well the tiles fill the 256 compute units), contraction consumed in slices of 32 through a 4-slot LDS
-//   ring, or in slices of 64 through two slots (four for the small tiles) where the contraction index is contiguous in
+//   One workgroup = 4 multiplying wavefronts (2 x 2) and, on the NN / NT tiles up to 256 x 128, 4 that only copy; block tile
+//   BM x BN (64 x 64 to 256 x 256, chosen per product by modelled time), contraction consumed in slices of 32 through a 4-slot
+//   LDS ring, or in slices of 64 through two to six slots where the contraction index is contiguous in
 //   memory, filled by asynchronous global -> LDS copies (no staging registers) that stay in flight while the previous
 //   slices are multiplied.  The smallest outputs run on 32 x 32 tiles that the four waves share, each through its own ring.
 //   Outputs with too few tiles cut the contraction over several workgroups per tile (scratch memory, a second launch).
@@ -1734,6 +1734,38 @@ static bool narrow_tiles_pay(int M, int N, int K) {
   return narrow > 1.08 * now;
 }
 
+// The first part of a product of more than one round of large tiles that is cut: whole rounds of them, in whole tile columns (or
+// rows, if there are more of those).
+static void cut_of(int M, int N, int& head_m, int& head_n) {
+  const int tiles_m = (M + 255) / 256, tiles_n = (N + 255) / 256;
+  const long whole = (long)tiles_m * tiles_n / 256 * 256;
+  head_m = tiles_n >= tiles_m ? M : (int)(whole / tiles_n) * 256;
+  head_n = tiles_n >= tiles_m ? (int)(whole / tiles_m) * 256 : N;
+}
+// Storage-type NN / NT products of one to six rounds of large tiles: how they run, by the modelled time of the parts.  What they
+// would run on otherwise (256 x 192 tiles where narrow_tiles_pay, else cut or plain) stays unless a choice is 5 % faster.
+// 3048 random products of one to three rounds in turn with what was here: 5.3 % faster on average, 2 of them more than 3 % slower; 1227 of
+// three to six rounds 1.7 %, 1.  [1024, 22016] x 4096 (NN) 197 us on 256 x 192 tiles, cut into a round of
+// large tiles and 88 tiles' worth of smaller ones 184.
+enum Rounds { R_DEFAULT, R_CUT, R_256X128 };
+static Rounds rounds_of(int layout, int M, int N, int K) {
+  const long large = tiles_of(T256, M, N);
+  if (large <= 256 || large >= 1600 || M < 256 || N < 256 || K <= 256) return R_DEFAULT;
+  auto time = [&](int tile, int m, int n) { return product_time(kTileCost[tile], layout, m, n, K, tiles_of(tile, m, n), K, 1); };
+  int head_m, head_n;
+  cut_of(M, N, head_m, head_n);
+  const int rest_m = head_m < M ? M - head_m : M, rest_n = head_n < N ? N - head_n : N;
+  const bool cuts = large % 256 != 0 && head_m > 0 && head_n > 0 && (head_m < M || head_n < N);
+  double cut = 1e30;
+  if (cuts) cut = time(T256, head_m, head_n) + time(product_plan(layout, rest_m, rest_n, K, false).tile, rest_m, rest_n) + 2.;
+  double now = time(T256, M, N);
+  if (narrow_tiles_pay(M, N, K)) now = time(T256_NARROW, M, N);
+  else if (cuts && large % 256 <= 192) now = cut;
+  const double wide = time(T256X128, M, N);
+  if (cut <= wide) return cut < 0.95 * now ? R_CUT : R_DEFAULT;
+  return wide < 0.95 * now ? R_256X128 : R_DEFAULT;
+}
+
 // Slot depth by layout and tile size: operands with a contiguous contraction index get the 64-deep slots on the
 // large tiles (whole cache lines per tile row: up to 8 % faster); on the small tiles, which run two or three
 // workgroups per compute unit and overlap that way, the 4-slot ring of 32-deep slots stays ahead.
@@ -1762,7 +1794,7 @@ static bool narrow_tiles_pay(int M, int N, int K) {
 // CU to cover the first one's waits, and a 32-deep slot of a 128 x 128 tile is multiplied in 256 clocks, so the three slots
 // that a ring of four keeps in flight cover under 800 clocks of memory latency; four 64-deep slots (128 KiB of LDS; eight 32-deep
 // ones where the contraction index is strided in memory) cover three times 512.  Measured on [1024, 4096] outputs when they
-// ran here (product_plan's T128_DEEP is the same kernel): K = 12288 (NT) 126 -> 107 us, K = 22016 (NT) 237 -> 216 us, K = 11008
+// ran here (the same tile with copying waves, product_plan's T128, has taken them since): K = 12288 (NT) 126 -> 107 us, K = 22016 (NT) 237 -> 216 us, K = 11008
 // (NN) 104 -> 93 us; a ring of eight 32-deep slots gains 3 %, three 64-deep slots lose 5 %, five (all 160 KiB) lose too.
 template <typename OutT>
 static hipError_t dispatch_small_deep(int layout, const GemmParams& p, hipStream_t s) {
@@ -2083,7 +2115,13 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
     const SplitPlan plan = plan_of(g);
     return g.layout == NN ? dispatch_product<false>(p, plan, g.ws, s) : dispatch_product<true>(p, plan, g.ws, s);
   }
-  if (!g.out_f32 && g.batch == 1 && g.causal == CAUSAL_NONE && !g.delta && g.layout != TN && narrow_tiles_pay(g.M, g.N, g.K))
+  const bool linear = !g.out_f32 && g.batch == 1 && g.causal == CAUSAL_NONE && !g.delta && g.layout != TN;
+  const Rounds rounds = linear ? rounds_of(g.layout, g.M, g.N, g.K) : R_DEFAULT;
+  if (rounds == R_256X128) {
+    const SplitPlan plan{T256X128, 1, g.K, 0};
+    return g.layout == NN ? dispatch_product<false>(p, plan, nullptr, s) : dispatch_product<true>(p, plan, nullptr, s);
+  }
+  if (linear && rounds != R_CUT && narrow_tiles_pay(g.M, g.N, g.K))
     return g.layout == NN ? launch_bf16<256, 192, true, false, bf16_t, TBP_NARROW_KD, TBP_NARROW_RING>(p, 1, s)
                           : launch_bf16<256, 192, true, true, bf16_t, TBP_NARROW_KD, TBP_NARROW_RING>(p, 1, s);
   // a weight gradient by itself: large tiles (below, with the last round on smaller ones where it is at most three quarters
@@ -2129,7 +2167,7 @@ hipError_t gemm(int dtype, const GemmArgs& g, hipStream_t s) {
     return launch_bf16<256, 192, false, false, float, 32>(q, 1, s);
   };
   if (big && g.batch == 1 && g.causal == CAUSAL_NONE && tiles_big > 256 && rem != 0 &&
-      (rem <= 128 || (has_narrow && rem <= 192))) {
+      (rem <= 128 || (has_narrow && rem <= 192) || rounds == R_CUT)) {
     const long whole = tiles_big - rem;
     const size_t ce = g.out_f32 ? 4 : 2;
     GemmParams a = p, b = p;

@@ -202,6 +202,27 @@ def test_gemm_tiles_with_copying_waves(layout, mnk):
         assert torch.equal(got, tbp.tbp_gemm(layout, dA, dB, R=dR, alpha=0.5, workspace=workspace))
 
 
+@pytest.mark.parametrize("layout,mnk", [
+    (tbp.NN, (6168, 2896, 280)), (tbp.NT, (7320, 2408, 272)),              # cut along M into a round of large tiles and the rest
+    (tbp.NN, (1312, 11248, 272)), (tbp.NT, (872, 16704, 312)),             # along N
+    (tbp.NN, (6520, 2336, 336)), (tbp.NT, (2232, 10848, 288)),             # 256 x 128 tiles
+    (tbp.NN, (3080, 6272, 264)), (tbp.NT, (2640, 8208, 512)),              # 256 x 192 tiles
+    (tbp.NN, (1304, 16800, 264)), (tbp.NT, (3928, 8096, 264))])            # as before: cut; large tiles
+def test_gemm_of_several_rounds(layout, mnk):
+    """Storage-type products of more than one round of large tiles, every way they run, ragged, with a residual and an output in
+    a wider matrix whose other columns stay untouched.  Tolerance: one bf16 rounding of the result."""
+    M, N, K = mnk
+    _say(f"gemm rounds layout={layout} M,N,K={mnk}")
+    A, B = _rnd(20, "A", (M, K), "bf16"), _rnd(20, "B", (N, K) if layout == tbp.NT else (K, N), "bf16")
+    R = _rnd(20, "R", (M, N + 16), "bf16", 4.0)
+    ref = ops.linear_p1(A, B) if layout == tbp.NT else ops.linear_fwd(A, B)          # (fp32 sums of at most 512 terms: 1e-6)
+    dA, dB, dR = to_dev(A, "bf16"), to_dev(B, "bf16"), to_dev(R, "bf16")
+    out = torch.full((M, N + 16), 7.0, dtype=torch.bfloat16, device=DEV)
+    tbp.tbp_gemm(layout, dA, dB, C_out=out[:, :N], R=dR[:, :N], alpha=0.5, workspace=True)
+    assert max_rel(to_np(out[:, :N]), (0.5 * ref + R[:, :N]).astype(np.float64)) < 4.5e-3
+    assert torch.all(out[:, N:] == 7.0)
+
+
 def test_gemm_strided_views_and_empty():
     # operands that are column blocks of wider matrices (leading dimension > row length), as the stage uses them
     dtype = "bf16"
