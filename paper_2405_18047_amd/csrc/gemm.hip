@@ -455,6 +455,36 @@ __device__ __forceinline__ void gemm_bf16_tile(const GemmParams& p, int tm_i, in
   // a wave-wide store covers whole rows when LPR divides 64 and consecutive rows otherwise (WN = 96).
   constexpr int LPR = WN / V, NVEC = 32 * LPR;
   static_assert(NVEC % 64 == 0, "a strip must be a whole number of wave-wide stores");
+  if constexpr (sizeof(OutT) == 4 && !ACC) {
+    // fp32 goes out as it lies in the accumulators: 32 lanes are 32 consecutive floats of a row, a whole cache line, so the way
+    // through LDS below would gain no larger pieces.  All weight gradients of a 7B layer, K 512 297 -> 288 us, K 1024 450 -> 437,
+    // K 2048 730 -> 719; of four MLP blocks of d 2048, K 2048 508 -> 497.
+    const bool whole = m0 + BM <= p.M && n0 + BN <= p.N;
+    const int row0 = m0 + wm * WM + 4 * (lane >> 5), col0 = n0 + wn * WN + (lane & 31);
+    float* const out = reinterpret_cast<float*>(C) + (long)row0 * p.ldc + col0;
+    if (whole) {
+#pragma unroll
+      for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          float* const row = out + (long)(i * 32 + 8 * (e >> 2) + (e & 3)) * p.ldc;
+#pragma unroll
+          for (int j = 0; j < TN; j++) row[j * 32] = p.alpha * acc[i][j][e];
+        }
+    } else {
+#pragma unroll
+      for (int i = 0; i < TM; i++)
+#pragma unroll
+        for (int e = 0; e < 16; e++) {
+          const int r = i * 32 + 8 * (e >> 2) + (e & 3);
+          float* const row = out + (long)r * p.ldc;
+#pragma unroll
+          for (int j = 0; j < TN; j++)
+            if (row0 + r < p.M && col0 + j * 32 < p.N) row[j * 32] = p.alpha * acc[i][j][e];
+        }
+    }
+    return;
+  }
   // fp32 +=: the old value that store u of strip i adds is requested where store u of strip i - 1 has used its own, so a
   // whole strip of requests is in flight (without branches: lanes outside the output read the tile's first element).
   // Read in place, one at a time, they made an accumulating round of 256 large tiles 22 us longer than an overwriting one;
@@ -1512,8 +1542,8 @@ static hipError_t launch_bf16_causal_pair(const GemmParams& p0, int batch, hipSt
 // holds for 4 to 20 % faster, depending on how well it knows the two.  On 3900 products (M 16-4096, N 128-27648, K 64-27648, weights that no cache holds) the plan costs 0.9 % more
 // than the fastest of all tiles and slices on average, and is more than 6 % slower than the coarse one on 6 of them; the coarse
 // one alone costs 2.5 %, `product_time` alone 0.7 % with a tail of 1.3-fold misses ([16, 2560] x 3264 (NN) 13.4 us for 9.6).
-// us, with the 4-wave kernels and the coarse plan that were here / now: [256, 22016] x 4096 (NN) 71 / 57 (256 x 128), [360, 4096] x 11008
-// (NT) 52 / 46, [256, 4096] x 4096 (NN) 19.6 / 16.7 (64 x 64), [2000, 1152] x 3456 (NT) 27.3 / 23.6 (128 x 128), [1024, 4096] x 11008 (NN)
+// us, with the 4-wave kernels and the coarse plan that were here / now: [256, 22016] x 4096 (NN) 71 / 58 (128 x 192), [360, 4096] x 11008
+// (NT) 54 / 47 (192 x 192 in five slices), [256, 4096] x 4096 (NN) 19.6 / 16.7 (64 x 64), [2000, 1152] x 3456 (NT) 27.3 / 23.6 (128 x 128), [1024, 4096] x 11008 (NN)
 // 90 / 87.
 enum ProductTile { T32, T64, T128X64, T128, T128_PAIR, T128X192, T256X128, T192, T256_NARROW, T256 };
 struct TileCost {
