@@ -556,9 +556,9 @@ def kernel_rates(shape, tbp, torch, dev, tdt, probe=False) -> dict:
             r = res["attention_p1_fused"]
             r["TFLOP/s_live_causal_half"] = round(flops_live / (r["us"] * 1e-6) / 1e12, 1)
             r["frac_of_bf16_mfma_peak"] = round(r["TFLOP/s_live_causal_half"] / PEAK_BF16_TFLOPS, 4)
-            r["what"] = ("fused attention backward (softmax backward inside), per layer and micro-batch: row dot + dK/dV kernel "
-                         "+ dQ, by the recompute pass on large grids, else as a product with the dS^T that the first kernel "
-                         "writes; GB/s on the algorithmic bytes")
+            r["what"] = ("fused attention backward (softmax backward inside), per layer and micro-batch: dQ by the recompute pass "
+                         "(with the row sums) + dK/dV kernel, or, on some grids, row sums, dK/dV kernel and dQ as a product with "
+                         "the dS^T that it writes; GB/s on the algorithmic bytes")
         else:
             causal_bytes = 3 * B * H * (S * (S + 1) // 2) * e      # live lower triangle only
 

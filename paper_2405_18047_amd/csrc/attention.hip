@@ -244,11 +244,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int e = 0; e < 16; e++) ot[t][e] *= alpha;
       m = mnew;
     }
+    // (SPLIT 2: a wave whose keys have all scored -inf so far has no reference point yet, and the query's other wave may: zeros)
+    const float ref = SPLIT == 2 && m == -INFINITY ? 0.f : m;
     bf16x8 pb[2 * NT], vf[DT];
     auto elements = [&](int e0, int e1) {               // exponentials of elements e0 .. e1 - 1 of the lane's 16 NT
 #pragma unroll
       for (int e = e0; e < e1; e++) {
-        const float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e >> 4][e & 15], p.scale_log2e, -m));
+        const float pe = __builtin_amdgcn_exp2f(__builtin_fmaf(st[e >> 4][e & 15], p.scale_log2e, -ref));
         st[e >> 4][e & 15] = pe;
         l[e & 1] += pe;
         if (e % 8 == 7) pb[e >> 3] = pack8(st[e >> 4], (e >> 3) & 1);

@@ -772,6 +772,32 @@ def test_elementwise_steps_inside_products(shape):
     st.close()
 
 
+@pytest.mark.parametrize("dh", [64, 128])
+def test_fused_attention_forward_with_keys_out_of_range(dh):
+    """A whole 32-key tile whose scores overflow to -inf: one of the two waves of a query then has nothing to add, and the rows
+    are those of the other keys alone."""
+    _say(f"attention fwd, scores of -inf dh={dh}")
+    seq, H = 96, 2
+    d = H * dh
+    q, k, v = (_rnd(50, n, (seq, d), "bf16") for n in ("q", "k", "v"))
+    q = np.abs(q)
+    q[:, ::dh] = 1e30                                   # the first column of each head
+    k[:, ::dh] = 0.
+    k[32:64, ::dh] = -1e30                              # keys 32..63: scores of -1e60 = -inf in fp32
+    keep = np.r_[0:32, 64:96]
+    qkv = to_dev(np.concatenate([q, k, v], axis=1), "bf16")
+    out, lse2 = tbp.tbp_attention_fwd(qkv, seq, H, dh, False)
+    q0 = q.astype(np.float64)
+    q0[:, ::dh] = 0.
+    for h in range(H):
+        c = slice(h * dh, (h + 1) * dh)
+        s = q0[:, c] @ k[keep][:, c].astype(np.float64).T / np.sqrt(dh)
+        p = np.exp(s - s.max(axis=1, keepdims=True))
+        ref = (p / p.sum(axis=1, keepdims=True)) @ v[keep][:, c].astype(np.float64)
+        assert max_rel(to_np(out)[:, c], ref) < 1e-2
+    assert torch.all(torch.isfinite(lse2))
+
+
 # (seq, head_dim, heads, micro_batch, dtype): the tiles of the score-gradient product and of the products that read it
 SCORE_TILES = [
     (64, 128, 2, 16, "f32"),      # fp32: 16 x 16 read by 32 x 32
