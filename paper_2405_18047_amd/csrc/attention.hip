@@ -235,7 +235,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     mx *= p.scale_log2e;                                // scale > 0: the maximum commutes with it
     if (__any(mx > m + kSlack)) {
       const float mnew = fmaxf(m, fmaxf(mx, xor32(mx)));
-      const float alpha = __builtin_amdgcn_exp2f(m - mnew);    // first block: m = -inf, exp2(-inf) = 0
+      // First block: m = -inf, exp2(-inf) = 0.  (SPLIT 2: so also for a lane that is here because of its neighbours while its own
+      // query's keys have all scored -inf so far: -inf - -inf would make NaN of the zeros that it holds.)
+      const float alpha = __builtin_amdgcn_exp2f(m - (SPLIT == 2 && mnew == -INFINITY ? 0.f : mnew));
       l[0] *= alpha;
       l[1] *= alpha;
 #pragma unroll
@@ -308,7 +310,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   float lq = (l[0] + l[1]) + xor32(l[0] + l[1]);
   if constexpr (SPLIT == 2) {
     // the two waves of a query: what the second one summed, brought to the common reference point, joins the first one's.
-    // (The first tile of a row always has a visible key; a second wave that saw none has m = -inf and adds nothing.)
+    // (A wave that saw no key of the query, or only such as score -inf, has m = -inf and zeros, and adds nothing.)
     static_assert(BQ * EROW + 1024 <= SLOT && QW * DT * 4096 <= SLOT, "output tile, statistics and partial sums side by side");
     LDS_AS float* const part = reinterpret_cast<LDS_AS float*>(lds + SLOT) + wq * (DT * 1024);
     LDS_AS float* const stat = reinterpret_cast<LDS_AS float*>(lds + BQ * EROW) + wq * 128;

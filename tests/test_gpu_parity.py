@@ -798,6 +798,41 @@ def test_fused_attention_forward_with_keys_out_of_range(dh):
     assert torch.all(torch.isfinite(lse2))
 
 
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("causal", [True, False])
+@pytest.mark.parametrize("seq,query,tile", [
+    (96, 70, 1), (96, 95, 1), (96, 40, 0), (96, 33, 0),        # the second, the first wave has no other keys of the query (with the mask)
+    (160, 150, 1), (160, 110, 1), (160, 159, 0), (160, 75, 0),                  # it meets finite keys in its next tile
+    (160, 150, 3)])                                             # it has met finite keys before
+def test_fused_attention_forward_with_keys_out_of_range_of_one_query(seq, query, tile, causal, dh):
+    """One 32-key tile scores -inf for one query alone: its neighbours of the same wave have a finite maximum there and move the
+    reference point.  The query's row is the result over its other keys, and the rows beside it are unaffected."""
+    _say(f"attention fwd, one query out of range seq={seq} query={query} tile={tile} causal={causal} dh={dh}")
+    H = 2
+    d = H * dh
+    q, k, v = (_rnd(51, n, (seq, d), "bf16") for n in ("q", "k", "v"))
+    q[:, ::dh] = 0.                                     # the first column of each head scores nothing ...
+    k[:, ::dh] = 0.
+    q[query, ::dh] = 1e30                               # ... but for this query and these keys: -1e60 = -inf in fp32
+    k[32 * tile:32 * (tile + 1), ::dh] = -1e30
+    out, lse2 = tbp.tbp_attention_fwd(to_dev(np.concatenate([q, k, v], axis=1), "bf16"), seq, H, dh, causal)
+    q64, k64, v64 = (t.astype(np.float64) for t in (q, k, v))
+    ref, ref_lse = np.empty((seq, d)), np.empty((H, seq))
+    for h in range(H):
+        c = slice(h * dh, (h + 1) * dh)
+        s = q64[:, c] @ k64[:, c].T / np.sqrt(dh)
+        s[s < -1e40] = -np.inf
+        if causal:
+            s[np.triu_indices(seq, 1)] = -np.inf
+        top = s.max(axis=1, keepdims=True)
+        p = np.exp(s - top)
+        ref[:, c] = (p / p.sum(axis=1, keepdims=True)) @ v64[:, c]
+        ref_lse[h] = (top[:, 0] + np.log(p.sum(axis=1))) / np.log(2.)
+    assert max_rel(to_np(out), ref) < 1e-2
+    assert max_rel(to_np(out)[query], ref[query]) < 1e-2
+    assert max_rel(lse2.cpu().numpy().reshape(H, seq), ref_lse) < 1e-4
+
+
 # (seq, head_dim, heads, micro_batch, dtype): the tiles of the score-gradient product and of the products that read it
 SCORE_TILES = [
     (64, 128, 2, 16, "f32"),      # fp32: 16 x 16 read by 32 x 32
