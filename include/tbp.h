@@ -207,6 +207,11 @@ size_t tbp_gemm_workspace_bytes(int dtype, int layout, int M, int N, int K, int 
 tbp_status tbp_gemm_ws(int dtype, int layout, int M, int N, int K, float alpha, const void* A, int lda,
                        const void* B, int ldb, void* C, int ldc, int out_f32, int accumulate, const void* R,
                        void* workspace, size_t workspace_bytes, void* stream);
+/* How such a product runs when tbp_gemm_ws is given workspace_bytes of workspace (0: none): rows and columns of the output
+ * tile of a workgroup, workgroups that share a compute unit, and slices of the contraction (host only; for tests and
+ * measurements).  TBP_EINVAL for products that are not of this kind. */
+tbp_status tbp_gemm_plan(int layout, int M, int N, int K, size_t workspace_bytes, int* tile_rows, int* tile_cols,
+                         int* workgroups_per_cu, int* slices);
 tbp_status tbp_rmsnorm_fwd(int dtype, int rows, int d, float eps, const void* x, const void* g, void* y,
                            void* stream);
 /* RMSNorm backward, split as Section 3.1 splits every parametrised module.  The backward-p1 half,

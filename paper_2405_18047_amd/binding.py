@@ -12,7 +12,7 @@ import torch
 
 __all__ = [
     "TBP_F32", "TBP_BF16", "TBP_P2_LOOP", "TBP_P2_KCONCAT", "TBP_ATTN_AUTO", "TBP_ATTN_MATERIALISED", "TBP_ATTN_FUSED", "TBP_ATTN_FUSED_RECOMPUTE", "TBP_GAIN_PARTIALS", "TBP_GAIN_LITERAL", "NN", "NT", "TN", "TbpError", "lib", "library_path",
-    "tbp_config", "tbp_stash_query", "Stage", "tbp_gemm", "tbp_rmsnorm_fwd", "tbp_rmsnorm_p1", "tbp_rmsnorm_p1_partials", "tbp_gain_partials_sum", "tbp_rmsnorm_p1_static", "tbp_rmsnorm_gain_p2", "tbp_swiglu_fwd",
+    "tbp_config", "tbp_stash_query", "Stage", "tbp_gemm", "tbp_gemm_plan", "tbp_rmsnorm_fwd", "tbp_rmsnorm_p1", "tbp_rmsnorm_p1_partials", "tbp_gain_partials_sum", "tbp_rmsnorm_p1_static", "tbp_rmsnorm_gain_p2", "tbp_swiglu_fwd",
     "tbp_swiglu_p1", "tbp_rope_table", "tbp_rope", "tbp_softmax_fwd", "tbp_softmax_p1", "tbp_version",
     "tbp_attention_fwd", "tbp_attention_p1",
     "config_from_shape",
@@ -78,6 +78,7 @@ def lib() -> C.CDLL:
                                                    C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_size_t, C.c_void_p]
         L.tbp_gemm_workspace_bytes.argtypes = [C.c_int] * 6
         L.tbp_gemm_workspace_bytes.restype = C.c_size_t
+        L.tbp_gemm_plan.argtypes = [C.c_int] * 4 + [C.c_size_t] + [C.POINTER(C.c_int)] * 4
         L.tbp_rmsnorm_fwd.argtypes = [C.c_int, C.c_int, C.c_int, C.c_float] + [C.c_void_p] * 4
         L.tbp_rmsnorm_p1.argtypes = [C.c_int, C.c_int, C.c_int, C.c_float] + [C.c_void_p] * 8
         L.tbp_rmsnorm_partial_rows.argtypes = [C.c_int] * 3
@@ -266,6 +267,16 @@ def tbp_gemm(layout: int, A: torch.Tensor, B: torch.Tensor, *, out_f32: bool = F
         _check(lib().tbp_gemm_ws(dt, layout, M, N, K, alpha, _ptr(A), ld(A), _ptr(B), ld(B), _ptr(C_out), ld(C_out),
                                  f32, 1 if accumulate else 0, _ptr(R), _ptr(workspace), workspace.numel(), _stream()))
     return C_out
+
+
+def tbp_gemm_plan(layout: int, M: int, N: int, K: int, workspace_bytes: int | None = None) -> tuple[int, int, int, int]:
+    """(tile rows, tile columns, workgroups per compute unit, slices) of a bf16 NN / NT product; None: with all the
+    workspace that it asks for."""
+    if workspace_bytes is None:
+        workspace_bytes = lib().tbp_gemm_workspace_bytes(TBP_BF16, layout, M, N, K, 0)
+    out = [C.c_int() for _ in range(4)]
+    _check(lib().tbp_gemm_plan(layout, M, N, K, workspace_bytes, *(C.byref(o) for o in out)))
+    return tuple(o.value for o in out)
 
 
 def tbp_rmsnorm_fwd(x, g, eps):

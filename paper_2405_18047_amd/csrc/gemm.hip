@@ -1539,9 +1539,10 @@ static hipError_t launch_bf16_causal_pair(const GemmParams& p0, int batch, hipSt
 // whose output is at most one round of 256 x 256 tiles.  Two models of a product's time, fitted to different data:
 // `coarse_plan` knows six tiles, with constants of its own for up to 128 rows, and errs little where it errs; `product_time` knows all
 // of them and more of what a product's time depends on.  The plan is the coarse one unless the other model has a choice that it
-// holds for 4 to 20 % faster, depending on how well it knows the two.  On 3900 products (M 16-4096, N 128-27648, K 64-27648, weights that no cache holds) the plan costs 0.9 % more
-// than the fastest of all tiles and slices on average, and is more than 6 % slower than the coarse one on 6 of them; the coarse
-// one alone costs 2.5 %, `product_time` alone 0.7 % with a tail of 1.3-fold misses ([16, 2560] x 3264 (NN) 13.4 us for 9.6).
+// holds for 4 to 30 % faster, depending on how well it knows the two.  On 3900 products (M 16-4096, N 128-27648, K 64-27648, weights that no
+// cache holds) the coarse one alone costs 2.5 % more than the fastest of all tiles and slices on average, `product_time` alone 0.7 % with
+// a tail of 1.3-fold misses ([16, 2560] x 3264 (NN) 13.4 us for 9.6).  On 2900 products where the two disagree (M 8-4096, N 256-12288, K 256-12288
+// and some to 60000, operands that take turns) the plan is 10 % faster than the coarse one on average and more than 6 % slower on 48.
 // us, with the 4-wave kernels and the coarse plan that were here / now: [256, 22016] x 4096 (NN) 71 / 58 (128 x 192), [360, 4096] x 11008
 // (NT) 54 / 47 (192 x 192 in five slices), [256, 4096] x 4096 (NN) 19.6 / 16.7 (64 x 64), [2000, 1152] x 3456 (NT) 27.3 / 23.6 (128 x 128), [1024, 4096] x 11008 (NN)
 // 90 / 87.
@@ -1574,7 +1575,12 @@ static const TileCost kTileCost[] = {
 // across two cache lines.  Slices add a second launch and the partial products.
 static double product_time(const TileCost& t, int layout, int M, int N, int K, long n, int slice, int split) {
   const double slower = 1. + ((layout == NN ? N : K) % 64 ? t.half_b : 0.) + (layout == NN && K % 64 ? t.half_a : 0.);
-  const double work = slice * t.index * slower;
+  // 256 x 128 tiles: long slices run at the power limit, which the tile that fetches the most bytes for its size meets first.  Time over what
+  // the rest of the model says, slices of 2-4 K / 4-6 / 6-8 / 8-12 / over 12 K indices: 0.87 / 0.98 / 1.02 / 1.05 / 1.12, NT with rows at
+  // multiples of less than 64 bytes 0.98 / 1.03 / 1.14 / 1.25 / 1.25-1.44; 256 x 256 tiles go from 0.93 to 1.0 ([592, 10616] x 10248 (NT)
+  // 203 us, in two slices of 256 x 256 170; [2304, 3328] x 28416 (NN) 392 and 365).
+  const double late = &t != &kTileCost[T256X128] || slice <= 4096 ? 1. : 1. + (layout == NT && K % 32 ? 0.25 : 0.12) * fmin(1., (slice - 4096) / 4096.);
+  const double work = slice * t.index * slower * late;
   double time;
   if (t.per_cu == 1) {
     const long rest = n % 256;
@@ -1599,7 +1605,9 @@ static long tiles_of(int tile, int M, int N) {
   const TileCost& t = kTileCost[tile];
   return (long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
 }
-// The model, in us, fitted to 2500 (shape, tile, slices) triples, M 64-2048, N 256-22016, K 256-22016: a round of 256 workgroups of
+// The coarse model, in us.  Its constants are those of kernels without copying waves, which the tiles up to 128 x 128 ran on before:
+// they price a product too high there, by a factor that differs little between these tiles.  Fitted to 2500 (shape, tile,
+// slices) triples, M 64-2048, N 256-22016, K 256-22016: a round of 256 workgroups of
 // K / slices indices costs `one` per index (`two` with two workgroups on a compute unit) and a fixed part, but at least the time
 // of reading both operands once at 4.9 TB/s plus 8.4; slices add 3.8 and 0.30 per MB of partial products, and must gain 12 % (3 % up to 128 rows).
 // Up to 128 rows the weight is read for one row of tiles, from HBM, and the tiles differ in the rate at which they
@@ -1608,24 +1616,27 @@ static long tiles_of(int tile, int M, int N) {
 // (`thin`).  Fitted to 510 products, M 8-128, N 256-24000, K 64-16000, weights that no cache holds.
 // Rows of K that are no multiple of 64 cost the 64 x 64 tiles, which fetch the most per product, 8 % on a CU of their own and 38 %
 // beside a second one.
+static double coarse_time_of_32(int layout, int M, int N, int K) {
+  return M > 128 ? 0.0018 * K + 3.0 : (layout == NN ? 0.0022 : 0.0014) * K + 2.9 + 0.26e-6 * N * K;
+}
 static SplitPlan coarse_plan(int layout, int M, int N, int K, bool allow_split) {
-  struct Coarse { int tile; double one, two, fixed, thin, start; bool slices; };
-  static const Coarse tiles[] = {{T128, 0.0091, 0., 3.0, 1.04, 4.9, true}, {T256_NARROW, 0.0167, 0., 8.0, 0., 0., true},
-                                 {T256, 0.0197, 0., 9.7, 0., 0., true}, {T128_PAIR, 0.0126, 0.0188, 1.5, 1.17, 5.4, true},
-                                 {T64, 0.0047, 0.0071, 1.3, 1.3, 3.9, true}, {T128, 0.0112, 0., 2.05, 1.25, 4.75, false}};
+  struct Coarse { int tile; double one, two, fixed, thin, start; };
+  static const Coarse tiles[] = {{T128, 0.0091, 0., 3.0, 1.04, 4.9}, {T256_NARROW, 0.0167, 0., 8.0, 0., 0.},
+                                 {T256, 0.0197, 0., 9.7, 0., 0.}, {T128_PAIR, 0.0126, 0.0188, 1.5, 1.17, 5.4},
+                                 {T64, 0.0047, 0.0071, 1.3, 1.3, 3.9}};
   const double bytes = 2e-6 * ((double)N * K + (double)M * K);
   const bool thin = M <= 128, nn = layout == NN, half_lines = K % 64 != 0;
   SplitPlan best = slices_of(T64, M, N, K, 1);
   double best_time = 1e30;
   if (tiles_of(T32, M, N) <= 256) {
-    best_time = !thin ? 0.0018 * K + 3.0 : (nn ? 0.0022 : 0.0014) * K + 2.9 + 0.26e-6 * N * K;
+    best_time = coarse_time_of_32(layout, M, N, K);
     best.tile = T32;
   }
   for (const Coarse& t : tiles) {
     if (kTileCost[t.tile].bm == 256 && M < 192) continue;
     const double per_index = thin ? t.thin : 1., memory = thin ? bytes / (!nn ? 4.9 : t.tile == T64 ? 4.5 : 5.9) + t.start : bytes / 4.9 + 8.4;
     for (int sp : kSlices) {
-      if (sp > 1 && (!allow_split || K / sp < 256 || !t.slices)) break;
+      if (sp > 1 && (!allow_split || K / sp < 256)) break;
       const SplitPlan plan = slices_of(t.tile, M, N, K, sp);
       const long n = tiles_of(t.tile, M, N) * plan.split;
       if (t.tile == T128_PAIR && n <= 256) continue;
@@ -1644,11 +1655,10 @@ static SplitPlan coarse_plan(int layout, int M, int N, int K, bool allow_split) 
 static bool one_round(int M, int N) { return (long)((M + 255) / 256) * ((N + 255) / 256) <= 256; }
 static SplitPlan product_plan(int layout, int M, int N, int K, bool allow_split) {
   const SplitPlan coarse = coarse_plan(layout, M, N, K, allow_split);
-  // Long products of 64 large tiles or more run at the power limit, where the tile that moves the fewest bytes is level or ahead
-  // whatever else it costs ([1024, 4096] x 22016 (NT) in four slices of 256 x 256 158.8 us, in two of 256 x 128 160.9).
-  if (K > 24576 && tiles_of(T256, M, N) >= 64) return coarse;
   SplitPlan best = coarse;
-  const double coarse_time = product_time(kTileCost[coarse.tile], layout, M, N, K, tiles_of(coarse.tile, M, N) * coarse.split, coarse.slice, coarse.split);
+  double coarse_time = product_time(kTileCost[coarse.tile], layout, M, N, K, tiles_of(coarse.tile, M, N) * coarse.split, coarse.slice, coarse.split);
+  // (32 x 32 tiles of few rows: the coarse model knows them better.  [24, 584] x 3912 (NT) 6.5 us, 9.9 modelled here, in eleven slices of 64 x 64 8.4)
+  if (coarse.tile == T32 && M <= 128) coarse_time = fmin(coarse_time, coarse_time_of_32(layout, M, N, K));
   double best_time = 1e30;
   for (int i = T32; i <= T256; i++) {
     const TileCost& t = kTileCost[i];
@@ -1660,18 +1670,35 @@ static SplitPlan product_plan(int layout, int M, int N, int K, bool allow_split)
       if (sp > 1 && (!allow_split || i == T32 || K / sp < 256)) break;
       const SplitPlan plan = slices_of(i, M, N, K, sp);
       const double time = product_time(t, layout, M, N, K, tiles * plan.split, plan.slice, plan.split);
-      // (its times of 32 x 32 tiles err most, those of the two largest of the new tiles least; up to 128 rows the coarse one is good)
-      const double must = coarse.tile == T32 ? 0.8 : M <= 128 ? 0.85 : i == T256X128 || i == T192 ? 0.96 : 0.9;
+      // Its times of 32 x 32 tiles err most, those of the two largest of the new tiles least, but for up to 192 rows, where these are
+      // mostly padding ([176, 9280] x 4160 (NN) 32.6 us on five slices of 192 x 192, modelled 32.3; 26.7 on 64 x 64, modelled 39.0).  Up to 128
+      // rows the coarse plan is good, and 64 x 64 tiles that read a large weight unsliced in its place lose ([64, 11928] x 11320 (NT)
+      // 100 us, two slices of 128 x 128 86).
+      const double must = coarse.tile == T32 ? 0.8 : M <= 128 ? (i == T64 && sp == 1 && coarse.tile != T64 ? 0.7 : 0.85)
+                          : M <= 192 && t.bm >= 192 ? 0.8 : i == T256X128 || i == T192 ? 0.96 : 0.9;
       if (time < must * coarse_time && time < best_time) { best_time = time; best = plan; }
     }
   }
   return best;
+}
+// The plan where `ws_bytes` of scratch are at hand.
+static SplitPlan plan_within(int layout, int M, int N, int K, size_t ws_bytes) {
+  const SplitPlan plan = product_plan(layout, M, N, K, ws_bytes > 0);
+  return plan.bytes > ws_bytes ? product_plan(layout, M, N, K, false) : plan;
 }
 SplitPlan gemm_split_plan(int dtype, int layout, int M, int N, int K, int out_f32, int batch) {
   const SplitPlan none{0, 1, 0, 0};
   if (dtype != 1 || out_f32 || batch != 1 || layout == TN || !one_round(M, N)) return none;
   const SplitPlan plan = product_plan(layout, M, N, K, true);
   return plan.split > 1 ? plan : none;
+}
+
+bool gemm_plan(int layout, int M, int N, int K, size_t ws_bytes, int* tile_rows, int* tile_cols, int* per_cu, int* slices) {
+  if ((layout != NN && layout != NT) || M <= 0 || N <= 0 || !one_round(M, N)) return false;
+  const SplitPlan plan = plan_within(layout, M, N, K, ws_bytes);
+  const TileCost& t = kTileCost[plan.tile];
+  *tile_rows = t.bm; *tile_cols = t.bn; *per_cu = t.per_cu; *slices = plan.split;
+  return true;
 }
 
 template <bool BKC, bool SWIGLU = false>
@@ -2063,9 +2090,7 @@ int gemm_row_tile(int dtype, const GemmArgs& g) {
 }
 
 static SplitPlan plan_of(const GemmArgs& g) {
-  SplitPlan plan = product_plan(g.layout, g.M, g.N, g.K, g.ws && reinterpret_cast<uintptr_t>(g.ws) % 256 == 0);
-  if (plan.bytes > g.ws_bytes) plan = product_plan(g.layout, g.M, g.N, g.K, false);
-  return plan;
+  return plan_within(g.layout, g.M, g.N, g.K, g.ws && reinterpret_cast<uintptr_t>(g.ws) % 256 == 0 ? g.ws_bytes : 0);
 }
 
 // Where the epilogue pays: fp32 products of at most two 32 x 32 tiles per compute unit (256 tokens, d 256, f 688: 5.6 us and 3.0 for the

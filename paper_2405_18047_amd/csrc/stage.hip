@@ -667,6 +667,14 @@ size_t tbp_gemm_workspace_bytes(int dtype, int layout, int M, int N, int K, int 
   return tbp::gemm_split_plan(dtype, layout, M, N, K, out_f32, 1).bytes;
 }
 
+tbp_status tbp_gemm_plan(int layout, int M, int N, int K, size_t workspace_bytes, int* tile_rows, int* tile_cols,
+                         int* workgroups_per_cu, int* slices) {
+  if (!tile_rows || !tile_cols || !workgroups_per_cu || !slices) return fail(TBP_EINVAL, "outputs must be non-null");
+  if (layout < 0 || K < 0 || !tbp::gemm_plan(layout, M, N, K, workspace_bytes, tile_rows, tile_cols, workgroups_per_cu, slices))
+    return fail(TBP_EINVAL, "not an NN or NT product of at most 256 tiles of 256 x 256");
+  return TBP_OK;
+}
+
 tbp_status tbp_gemm(int dtype, int layout, int M, int N, int K, float alpha, const void* A, int lda, const void* B,
                     int ldb, void* C, int ldc, int out_f32, int accumulate, const void* R, void* stream) {
   return tbp_gemm_ws(dtype, layout, M, N, K, alpha, A, lda, B, ldb, C, ldc, out_f32, accumulate, R, nullptr, 0, stream);

@@ -243,3 +243,24 @@ int main() {
     assert all(longest <= 2**31 - 64 for _, longest in got.values())
     assert got[2048, 300] == (2, 150 * 2048) and got[2048, 1] == (1, 2048)          # ordinary sets: the runs themselves
     assert got[1 << 24, 128] == (2, 64 << 24) and got[1 << 24, 300][0] == 6
+
+
+@pytest.mark.parametrize("layout,mnk,slower", [
+    # measured, us: what the slower choice takes, and the faster one
+    (tbp.NT, (592, 10616, 10248), (256, 128, 1)),        # 203, 170: two slices of 256 x 256
+    (tbp.NN, (2304, 3328, 28416), (256, 128, 1)),        # 392, 365: the same
+    (tbp.NT, (24, 584, 3912), (64, 64, 11)),             # 8.4, 6.5: 32 x 32, whole
+    (tbp.NN, (176, 9280, 4160), (192, 192, 5)),          # 32.6, 27.2: 128 x 128, whole
+    (tbp.NT, (64, 11928, 11320), (64, 64, 1))])          # 100, 86: two slices of 128 x 128
+def test_gemm_plan_avoids_choices_that_measured_slower(layout, mnk, slower):
+    rows, cols, per_cu, slices = tbp.tbp_gemm_plan(layout, *mnk)
+    assert (rows, cols, slices) != slower
+    assert 1 <= per_cu <= 2 and 1 <= slices <= 16
+    # without scratch nothing is cut
+    assert tbp.tbp_gemm_plan(layout, *mnk, 0)[3] == 1
+
+
+def test_gemm_plan_refuses_other_products():
+    for layout, M, N, K in ((tbp.TN, 64, 64, 64), (tbp.NN, 0, 64, 64), (tbp.NN, 64, 64, -1), (7, 64, 64, 64), (tbp.NN, 8192, 8192, 64)):
+        with pytest.raises(tbp.TbpError):
+            tbp.tbp_gemm_plan(layout, M, N, K, 0)
