@@ -1653,7 +1653,7 @@ static SplitPlan coarse_plan(int layout, int M, int N, int K, bool allow_split) 
   return best;
 }
 static bool one_round(int M, int N) { return (long)((M + 255) / 256) * ((N + 255) / 256) <= 256; }
-static SplitPlan product_plan(int layout, int M, int N, int K, bool allow_split) {
+static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) {
   const SplitPlan coarse = coarse_plan(layout, M, N, K, allow_split);
   SplitPlan best = coarse;
   double coarse_time = product_time(kTileCost[coarse.tile], layout, M, N, K, tiles_of(coarse.tile, M, N) * coarse.split, coarse.slice, coarse.split);
@@ -1680,6 +1680,17 @@ static SplitPlan product_plan(int layout, int M, int N, int K, bool allow_split)
     }
   }
   return best;
+}
+// The search above costs 2 us of host time, a sixth of what a small product takes from call to call, and a program runs the same few
+// products over and over: each thread keeps its last plans (a function of these five numbers alone), one per slot.
+static SplitPlan product_plan(int layout, int M, int N, int K, bool allow_split) {
+  struct Slot { int layout, M, N, K; bool allow_split; SplitPlan plan; };
+  static thread_local Slot slots[128];                              // (M is 0 in a slot that holds nothing)
+  uint32_t h = (uint32_t)M * 0x9E3779B1u + (uint32_t)N * 0x85EBCA6Bu + (uint32_t)K * 0xC2B2AE35u + (uint32_t)(2 * layout + allow_split) * 0x27D4EB2Fu;
+  Slot& slot = slots[(h ^ h >> 15) * 0x9E3779B1u >> 25];
+  if (M <= 0 || slot.M != M || slot.N != N || slot.K != K || slot.layout != layout || slot.allow_split != allow_split)
+    slot = Slot{layout, M, N, K, allow_split, search_plan(layout, M, N, K, allow_split)};
+  return slot.plan;
 }
 // The plan where `ws_bytes` of scratch are at hand.
 static SplitPlan plan_within(int layout, int M, int N, int K, size_t ws_bytes) {

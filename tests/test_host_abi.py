@@ -1,7 +1,9 @@
 """CPU-only checks of the C ABI: the library loads, exports what the header declares, and its host logic
 (configuration checks, stash sizing, state machine) behaves without any GPU work being launched."""
+import concurrent.futures
 import ctypes as C
 import os
+import random
 import re
 import subprocess
 
@@ -258,6 +260,21 @@ def test_gemm_plan_avoids_choices_that_measured_slower(layout, mnk, slower):
     assert 1 <= per_cu <= 2 and 1 <= slices <= 16
     # without scratch nothing is cut
     assert tbp.tbp_gemm_plan(layout, *mnk, 0)[3] == 1
+
+
+def test_gemm_plan_is_the_same_however_often_and_wherever_it_is_asked_for():
+    """Threads keep plans that they have found: many more products than they keep, in several orders and threads."""
+    rng = random.Random(5)
+    cases = [(rng.choice((tbp.NN, tbp.NT)), 8 * rng.randint(1, 500), 8 * rng.randint(1, 1000), 8 * rng.randint(0, 1000)) for _ in range(900)]
+    cases = [c for c in cases if -(-c[1] // 256) * -(-c[2] // 256) <= 256]
+    ask = lambda c: (tbp.tbp_gemm_plan(*c), tbp.tbp_gemm_plan(*c, 0), tbp.lib().tbp_gemm_workspace_bytes(tbp.TBP_BF16, *c, 0))
+    want = {c: ask(c) for c in cases}
+    for c in rng.sample(cases, len(cases)) + cases[::-1]:
+        assert ask(c) == want[c], c
+    with concurrent.futures.ThreadPoolExecutor(4) as pool:
+        assert list(pool.map(ask, cases + cases)) == [want[c] for c in cases + cases]
+    for (layout, M, N, K), ((_, _, _, slices), (_, _, _, one), need) in want.items():
+        assert one == 1 and (need == 0) == (slices == 1) and need >= (slices > 1) * slices * M * N * 4
 
 
 def test_gemm_plan_refuses_other_products():
