@@ -200,9 +200,10 @@ tbp_status tbp_gemm(int dtype, int layout, int M, int N, int K, float alpha, con
  * 256 x 256 may not fill the chip with one workgroup per tile; given `workspace` (device, 256-byte aligned, at least
  * tbp_gemm_workspace_bytes(...) bytes) the contraction is cut into slices, one workgroup per tile and slice, whose fp32
  * partial products go to the workspace and are added in a fixed order by a second launch (the result does not depend on
- * timing).  tbp_gemm_workspace_bytes returns 0 for a product that would not be cut; workspace may then be NULL.  Nothing
- * in the workspace has to be initialised; calls that share a workspace must not overlap.  The stage gives its
- * forward and backward-p1 linear products such a workspace out of its arena (Section 3.1: dX = dY W^T). */
+ * timing).  tbp_gemm_workspace_bytes returns 0 for a product that would not be cut, or where the slices gain less than a
+ * workspace of its own and a second launch cost a caller; workspace may then be NULL.  Nothing in the workspace has to be
+ * initialised; calls that share a workspace must not overlap.  The stage gives its forward and backward-p1 linear
+ * products such a workspace out of its arena (Section 3.1: dX = dY W^T). */
 size_t tbp_gemm_workspace_bytes(int dtype, int layout, int M, int N, int K, int out_f32);
 tbp_status tbp_gemm_ws(int dtype, int layout, int M, int N, int K, float alpha, const void* A, int lda,
                        const void* B, int ldb, void* C, int ldc, int out_f32, int accumulate, const void* R,

@@ -1704,6 +1704,16 @@ SplitPlan gemm_split_plan(int dtype, int layout, int M, int N, int K, int out_f3
   return plan.split > 1 ? plan : none;
 }
 
+// What a caller is told to bring for one product.  A call that allocates its workspace and starts two kernels takes 15 us of host time
+// and one without 10.5, so a product that takes less than 15 in one launch is left whole unless the coarse model cuts it as well:
+// [160, 416] x 4168 (NN), called in a row, 15 us in eleven slices (7 of them on the GPU) and 12.0 whole.  (The stage, whose
+// scratch is there in any case, goes by gemm_split_plan.)
+size_t gemm_workspace_bytes(int dtype, int layout, int M, int N, int K, int out_f32) {
+  const SplitPlan plan = gemm_split_plan(dtype, layout, M, N, K, out_f32, 1);
+  if (plan.split == 1 || coarse_plan(layout, M, N, K, true).split > 1) return plan.bytes;
+  const SplitPlan whole = product_plan(layout, M, N, K, false);
+  return product_time(kTileCost[whole.tile], layout, M, N, K, tiles_of(whole.tile, M, N), K, 1) < 15. ? 0 : plan.bytes;
+}
 bool gemm_plan(int layout, int M, int N, int K, size_t ws_bytes, int* tile_rows, int* tile_cols, int* per_cu, int* slices) {
   if ((layout != NN && layout != NT) || M <= 0 || N <= 0 || !one_round(M, N)) return false;
   const SplitPlan plan = plan_within(layout, M, N, K, ws_bytes);

@@ -75,6 +75,8 @@ constexpr size_t attn_ds_elems(int seq) { return (size_t)((seq + kPanel - 1) / k
 struct SplitPlan { int tile, split, slice; size_t bytes; };
 constexpr size_t kSplitHead = 1024;           // unused: part of the size that tbp_gemm_workspace_bytes has always told callers
 SplitPlan gemm_split_plan(int dtype, int layout, int M, int N, int K, int out_f32, int batch);
+// Scratch that a caller who would have to allocate it is told to bring for one such product: 0 also where slices gain too little.
+size_t gemm_workspace_bytes(int dtype, int layout, int M, int N, int K, int out_f32);
 // How gemm() runs a storage-type bf16 NN / NT product of at most one round of 256 x 256 tiles that is given ws_bytes of scratch:
 // output tile, workgroups per compute unit that its LDS allows, slices.  false: another product.
 bool gemm_plan(int layout, int M, int N, int K, size_t ws_bytes, int* tile_rows, int* tile_cols, int* per_cu, int* slices);

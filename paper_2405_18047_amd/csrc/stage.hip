@@ -664,7 +664,7 @@ static tbp_status check_dtype(int dtype) {
 
 size_t tbp_gemm_workspace_bytes(int dtype, int layout, int M, int N, int K, int out_f32) {
   if (M <= 0 || N <= 0 || K <= 0 || layout < 0 || layout > 2) return 0;
-  return tbp::gemm_split_plan(dtype, layout, M, N, K, out_f32, 1).bytes;
+  return tbp::gemm_workspace_bytes(dtype, layout, M, N, K, out_f32);
 }
 
 tbp_status tbp_gemm_plan(int layout, int M, int N, int K, size_t workspace_bytes, int* tile_rows, int* tile_cols,

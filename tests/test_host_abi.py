@@ -262,6 +262,16 @@ def test_gemm_plan_avoids_choices_that_measured_slower(layout, mnk, slower):
     assert tbp.tbp_gemm_plan(layout, *mnk, 0)[3] == 1
 
 
+def test_no_workspace_for_products_that_take_less_than_its_allocation():
+    # called in a row, us, with a workspace of its own in slices / whole: 15 / 12.0, 15 / 14.7
+    for mnk in ((160, 416, 4168), (352, 360, 4552)):
+        assert tbp.lib().tbp_gemm_workspace_bytes(tbp.TBP_BF16, tbp.NN, *mnk, 0) == 0
+        assert tbp.tbp_gemm_plan(tbp.NN, *mnk)[3] == 1
+        assert tbp.tbp_gemm_plan(tbp.NN, *mnk, 1 << 30)[3] > 1          # scratch that is there is used
+    for layout, mnk in ((tbp.NT, (360, 4096, 11008)), (tbp.NN, (112, 728, 8120))):
+        assert tbp.lib().tbp_gemm_workspace_bytes(tbp.TBP_BF16, layout, *mnk, 0) > 0
+
+
 def test_gemm_plan_is_the_same_however_often_and_wherever_it_is_asked_for():
     """Threads keep plans that they have found: many more products than they keep, in several orders and threads."""
     rng = random.Random(5)
