@@ -1542,7 +1542,7 @@ static hipError_t launch_bf16_causal_pair(const GemmParams& p0, int batch, hipSt
 // holds for 4 to 30 % faster, depending on how well it knows the two.  On 3900 products (M 16-4096, N 128-27648, K 64-27648, weights that no
 // cache holds) the coarse one alone costs 2.5 % more than the fastest of all tiles and slices on average, `product_time` alone 0.7 % with
 // a tail of 1.3-fold misses ([16, 2560] x 3264 (NN) 13.4 us for 9.6).  On 2900 products where the two disagree (M 8-4096, N 256-12288, K 256-12288
-// and some to 60000, operands that take turns) the plan is 10 % faster than the coarse one on average and more than 6 % slower on 48.
+// and some to 60000, operands that take turns) the plan is 10 % faster than the coarse one on average and more than 6 % slower on 44.
 // us, with the 4-wave kernels and the coarse plan that were here / now: [256, 22016] x 4096 (NN) 71 / 58 (128 x 192), [360, 4096] x 11008
 // (NT) 54 / 47 (192 x 192 in five slices), [256, 4096] x 4096 (NN) 19.6 / 16.7 (64 x 64), [2000, 1152] x 3456 (NT) 27.3 / 23.6 (128 x 128), [1024, 4096] x 11008 (NN)
 // 90 / 87.
@@ -1673,9 +1673,11 @@ static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) 
       // Its times of 32 x 32 tiles err most, those of the two largest of the new tiles least, but for up to 192 rows, where these are
       // mostly padding ([176, 9280] x 4160 (NN) 32.6 us on five slices of 192 x 192, modelled 32.3; 26.7 on 64 x 64, modelled 39.0).  Up to 128
       // rows the coarse plan is good, and 64 x 64 tiles that read a large weight unsliced in its place lose ([64, 11928] x 11320 (NT)
-      // 100 us, two slices of 128 x 128 86).
+      // 100 us, two slices of 128 x 128 86).  Short slices on 256 x 128 are level with two 128 x 128 workgroups per compute unit where it
+      // holds them for 7 % faster ([2032, 2624] x 848 (NT) 18.8 us and 18.4).
       const double must = coarse.tile == T32 ? 0.8 : M <= 128 ? (i == T64 && sp == 1 && coarse.tile != T64 ? 0.7 : 0.85)
-                          : M <= 192 && t.bm >= 192 ? 0.8 : i == T256X128 || i == T192 ? 0.96 : 0.9;
+                          : M <= 192 && t.bm >= 192 ? 0.8 : i == T256X128 && plan.slice < 1024 ? 0.85
+                          : i == T256X128 || i == T192 ? 0.96 : 0.9;
       if (time < must * coarse_time && time < best_time) { best_time = time; best = plan; }
     }
   }
