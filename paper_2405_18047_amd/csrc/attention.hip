@@ -392,7 +392,9 @@ struct AttnBwdParams {
 // KEYS = 64, for grids that leave compute units idle: two left waves per 32 keys, each on one tile of a 64-query step, and the
 // right waves take both tiles per iteration: half the iterations per workgroup, twice the workgroups (and the transposed
 // fragments of Q and dO, read for half the keys, weigh twice as much: about 10 % slower per key and query).
-template <int DH, bool WRITE_DST, int KEYS>
+// ROPE is fixed at compile time: a branch on the table in the stores kept the reads of a row from overlapping the stores of the one
+// before, 185 us instead of 181 at B 2, H 32, S 2048, dh 128 without a table, and 123.6 instead of 120.7 in the dq pass.
+template <int DH, bool WRITE_DST, int KEYS, bool ROPE>
 __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p) {
   using HT = HeadTile<DH>;
   constexpr int KS = DH / 16, DT = DH / 32, BQ = 64;
@@ -690,7 +692,7 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
       if (krow < p.S) {
         bf16_t* const out = p.dqkv + (tok0 + krow) * p.ld_dqkv + d + h * DH + 8 * piece;
         bf16x8 vk = *reinterpret_cast<const LDS_AS bf16x8*>(edk + row * EROW + 16 * piece);
-        if (p.rope) {                                         // rotated back: the other half of the row is in LDS as well
+        if constexpr (ROPE) {                                 // rotated back: the other half of the row is in LDS as well
           const bf16x8 other = *reinterpret_cast<const LDS_AS bf16x8*>(edk + row * EROW + 16 * (piece ^ (LPR / 2)));
           const float2* const tb = p.rope + (long)krow * (DH / 2) + 8 * (piece & (LPR / 2 - 1));
           const float sgn = piece < LPR / 2 ? 1.f : -1.f;
@@ -717,8 +719,9 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
 // atomically, and the result is bit-reproducible.  Workgroup = 4 waves x 32 queries, K and V blocks double-buffered
 // through LDS exactly as in the forward; SPLIT = 2 as there.
 // It runs before the pass over the queries, because it has a query's rows of dout in registers: delta = rowsum(dout * out) costs
-// it one more image, which arrives beside the first key block, instead of a launch that reads both tensors (11 of 285 us at
-// B 2, H 32, S 2048, dh 128; 5 of 82 at B 4, H 12, S 1000, dh 64).
+// it one more image, which arrives beside the first key block, instead of a launch that reads both tensors.  Kernel times, us: B 2, H 32,
+// S 2048, dh 128 105.0 and a row dot of 11.2 before, now 108.7; B 2, H 40, S 1816, dh 64, unmasked 117.5 and 7.0, now 119.2 (the lane's pieces
+// of the row by plain loads beside the first copies, without image and barriers: no faster).
 struct AttnDqParams {
   const bf16_t* qkv; long ld_qkv;
   const bf16_t* dout; long ld_do;
@@ -731,7 +734,7 @@ struct AttnDqParams {
   float scale, scale_log2e;
 };
 
-template <int DH, int SPLIT>
+template <int DH, int SPLIT, bool ROPE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dq_kernel(AttnDqParams p) {
   using HT = HeadTile<DH>;
   constexpr int KS = DH / 16, DT = DH / 32, BKV = 64, BQ = 128 / SPLIT, QW = 4 / SPLIT;
@@ -911,7 +914,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   for (int t = 0; t < DT; t++)
 #pragma unroll
     for (int e = 0; e < 16; e++) dqt[t][e] *= p.scale;
-  if (p.rope) {
+  if constexpr (ROPE) {
     const float2* const tb = p.rope + (long)(qlive ? query : 0) * (DH / 2) + 4 * g;
 #pragma unroll
     for (int t = 0; t < DT / 2; t++)
@@ -988,9 +991,9 @@ hipError_t attention_fwd(int batch, int n_heads, int seq, int head_dim, int caus
 template <int DH, int SPLIT>
 static hipError_t launch_bwd_dq(const AttnDqParams& p, hipStream_t s) {
   constexpr size_t smem = 2 * 2 * 64 * DH * 2;
-  auto kern = attn_bwd_dq_kernel<DH, SPLIT>;
-  static AttrOnce once;
-  if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
+  auto kern = p.rope ? attn_bwd_dq_kernel<DH, SPLIT, true> : attn_bwd_dq_kernel<DH, SPLIT, false>;
+  static AttrOnce once[2];
+  if (hipError_t e = once[p.rope != nullptr].set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)(p.H * p.B), (unsigned)((p.S * SPLIT + 127) / 128)), dim3(256), smem, s, p);
   return hipGetLastError();
 }
@@ -1013,9 +1016,9 @@ static bool short_key_blocks(long heads, int seq, int causal) {
 template <int DH, bool WRITE_DST, int KEYS>
 static hipError_t launch_bwd_kv_split(const AttnBwdParams& p, hipStream_t s) {
   constexpr size_t smem = 3 * (2 * 64 * DH * 2 + 1024) + 2 * 4 * 4096 + (WRITE_DST ? 4 * 32 * 144 : 0);     // three slots, two hand-over buffers, dS^T staging
-  auto kern = attn_bwd_kv_split_kernel<DH, WRITE_DST, KEYS>;
-  static AttrOnce once;
-  if (hipError_t e = once.set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
+  auto kern = p.rope && !WRITE_DST ? attn_bwd_kv_split_kernel<DH, WRITE_DST, KEYS, !WRITE_DST> : attn_bwd_kv_split_kernel<DH, WRITE_DST, KEYS, false>;
+  static AttrOnce once[2];
+  if (hipError_t e = once[p.rope != nullptr].set(reinterpret_cast<const void*>(kern), smem); e != hipSuccess) return e;
   hipLaunchKernelGGL(kern, dim3((unsigned)(p.H * p.B), (unsigned)((p.S + KEYS - 1) / KEYS)), dim3(512), smem, s, p);
   return hipGetLastError();
 }
@@ -1024,7 +1027,7 @@ hipError_t attention_p1(int batch, int n_heads, int seq, int head_dim, int causa
                         const void* out, const void* d_out, long ld_out, const float* lse, void* dqkv, long ld_dqkv,
                         float* delta, void* ds_t, const float2* rope_table, hipStream_t s) {
   if (batch <= 0 || n_heads <= 0 || seq <= 0) return hipSuccess;
-  if (ld_out != (long)n_heads * head_dim || (head_dim != 64 && head_dim != 128)) return hipErrorInvalidValue;      // the row-dot kernel takes dense rows
+  if (ld_out != (long)n_heads * head_dim || (head_dim != 64 && head_dim != 128)) return hipErrorInvalidValue;      // out and d_out are read with the one leading dimension
   AttnBwdParams p{};
   p.qkv = (const bf16_t*)qkv; p.ld_qkv = ld_qkv; p.dout = (const bf16_t*)d_out; p.ld_do = ld_out;
   p.lse = lse; p.delta = delta; p.dqkv = (bf16_t*)dqkv; p.ld_dqkv = ld_dqkv; p.dst = (bf16_t*)ds_t;
