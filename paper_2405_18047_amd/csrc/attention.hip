@@ -505,7 +505,7 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
         for (int u = 0; u < 2; u++)
 #pragma unroll
           for (int t = 0; t < 8; t++) { kp[u][t] = (bf16_t)pv[8 * u + t]; ks[u][t] = (bf16_t)sv[8 * u + t]; }
-        lds_u8* const out = my_hand + (it & 1) * HAND;
+        lds_u8* const out = my_hand + ((TPI == 1 ? tile : it) & 1) * HAND;      // (the same parity; by `it` the loops of KEYS 128 ran 3 % slower)
         *reinterpret_cast<LDS_AS bf16x8*>(out) = kp[0];
         *reinterpret_cast<LDS_AS bf16x8*>(out + 1024) = kp[1];
         *reinterpret_cast<LDS_AS bf16x8*>(out + 2048) = ks[0];
@@ -607,16 +607,17 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
   __syncthreads();
   __syncthreads();                                            // the left waves have read their K and V rows
   for (int it = 0; it <= nt; it++) {
+    const int tp = t0 + TPI * it;                             // the (first) tile the left waves are on
     if (it > 0 && has_cols) {
 #pragma unroll
       for (int tq = 0; tq < TPI; tq++) {
-        const int tile = t0 + TPI * (it - 1) + tq;
+        const int tile = tp - TPI + tq;
         lds_u8* const qimg = lds + (((tile >> 1) - step0) % 3) * SLOT + (tile & 1) * HALF;
         lds_u8* const dimg = qimg + IMG;
         // this wave's 32 head-dim columns of dO^T and Q^T (two k-steps of 16 queries), then every key block's P and dS, each
         // fetched one key block ahead of its MFMAs (pinned, as on the left)
         bf16x8 fo_d[2], fo_q[2], kp[2][2], ks[2][2];
-        const lds_u8* const in = hand + ((it - 1) & 1) * HAND + tq * (KB * 4096) + lane * 16;
+        const lds_u8* const in = hand + ((TPI == 1 ? tile : it - 1) & 1) * HAND + tq * (KB * 4096) + lane * 16;
         auto fetch = [&](int kbk) {
 #pragma unroll
           for (int u = 0; u < 2; u++) {
@@ -641,9 +642,8 @@ __global__ __launch_bounds__(512) void attn_bwd_kv_split_kernel(AttnBwdParams p)
       }
     }
     if constexpr (TPI == 1) {
-      // the left waves are on tile tp.  Step (tp + 1) / 2 + 1 is what they start two barriers from now, when tp is odd: it was
-      // issued three barriers ago and only the issue after it may still be in flight
-      const int tp = t0 + it;
+      // Step (tp + 1) / 2 + 1 is what the left waves start two barriers from now, when tp is odd: it was issued three
+      // barriers ago and only the issue after it may still be in flight
       if (tp & 1) wait_vmem<OPS>();
       __syncthreads();
       // after this barrier nobody reads the step before tp / 2 any more (tp even): its slot takes step tp / 2 + 2
