@@ -1,4 +1,4 @@
-"""Helpers shared by the GPU parity tests: upload seeded inputs, run the oracle, compare."""
+"""Helpers and lists shared by the GPU parity tests: upload seeded inputs, run the oracle, compare."""
 from __future__ import annotations
 
 import numpy as np
@@ -9,6 +9,31 @@ import paper_2405_18047_amd as tbp
 import seeded_inputs as si
 
 DEV = "cuda:0"
+
+# (layout, (M, N, K), (tile rows, tile columns, workgroups per compute unit, slices)): storage-type products for every tile of the bf16 product
+# plan, whole and (but for 32 x 32) in slices that end in a shorter one, in both layouts
+PRODUCT_TILES = [
+    (tbp.NN, (136, 1032, 2760), (32, 32, 1, 1)), (tbp.NT, (8, 4104, 4104), (32, 32, 1, 1)),
+    (tbp.NN, (16, 8904, 8), (64, 64, 2, 1)), (tbp.NT, (16, 8648, 72), (64, 64, 2, 1)), (tbp.NN, (328, 920, 2808), (64, 64, 2, 2)),
+    (tbp.NN, (24, 80, 2408), (64, 64, 2, 8)), (tbp.NT, (16, 72, 4720), (64, 64, 2, 15)),
+    (tbp.NN, (408, 2352, 512), (128, 64, 1, 1)), (tbp.NT, (2832, 328, 464), (128, 64, 1, 1)), (tbp.NN, (584, 520, 2800), (128, 64, 1, 5)),
+    (tbp.NT, (1912, 144, 2520), (128, 64, 1, 5)), (tbp.NT, (456, 664, 2456), (128, 64, 1, 5)),
+    (tbp.NN, (400, 4760, 64), (128, 128, 2, 1)), (tbp.NN, (416, 8440, 64), (128, 128, 2, 1)), (tbp.NN, (1744, 3488, 800), (128, 128, 2, 1)),
+    (tbp.NT, (392, 8952, 64), (128, 128, 2, 1)), (tbp.NT, (456, 8200, 720), (128, 128, 2, 1)), (tbp.NN, (136, 5872, 4120), (128, 128, 2, 5)),
+    (tbp.NT, (2024, 72, 8016), (128, 128, 2, 16)),
+    (tbp.NN, (144, 8344, 3112), (128, 128, 1, 1)), (tbp.NN, (3640, 520, 72), (128, 128, 1, 1)), (tbp.NT, (2312, 872, 72), (128, 128, 1, 1)),
+    (tbp.NT, (136, 8608, 3376), (128, 128, 1, 1)), (tbp.NN, (16, 3280, 5264), (128, 128, 1, 8)), (tbp.NT, (72, 3424, 2792), (128, 128, 1, 5)),
+    (tbp.NT, (408, 2976, 4040), (128, 128, 1, 2)),
+    (tbp.NN, (1040, 3744, 320), (128, 192, 1, 1)), (tbp.NT, (2440, 1640, 960), (128, 192, 1, 1)), (tbp.NN, (288, 3928, 4000), (128, 192, 1, 4)),
+    (tbp.NN, (168, 5904, 4416), (128, 192, 1, 4)), (tbp.NT, (152, 5936, 5056), (128, 192, 1, 4)),
+    (tbp.NN, (2552, 2312, 1032), (256, 128, 1, 1)), (tbp.NT, (2696, 1456, 1032), (256, 128, 1, 1)), (tbp.NN, (920, 1400, 4904), (256, 128, 1, 5)),
+    (tbp.NT, (936, 1328, 4744), (256, 128, 1, 4)),
+    (tbp.NN, (1448, 5768, 144), (192, 192, 1, 1)), (tbp.NT, (1064, 7520, 160), (192, 192, 1, 1)), (tbp.NN, (1296, 976, 4952), (192, 192, 1, 6)),
+    (tbp.NT, (520, 2200, 4128), (192, 192, 1, 6)),
+    (tbp.NN, (1736, 4904, 368), (256, 192, 1, 1)), (tbp.NT, (1936, 4440, 368), (256, 192, 1, 1)), (tbp.NN, (984, 2056, 4472), (256, 192, 1, 5)),
+    (tbp.NT, (1240, 3224, 3232), (256, 192, 1, 3)),
+    (tbp.NN, (2576, 4712, 384), (256, 256, 1, 1)), (tbp.NT, (2192, 5400, 392), (256, 256, 1, 1)), (tbp.NN, (2120, 2000, 4144), (256, 256, 1, 3)),
+    (tbp.NT, (2224, 1936, 4168), (256, 256, 1, 3))]
 
 
 def to_dev(a: np.ndarray, dtype: str) -> torch.Tensor:

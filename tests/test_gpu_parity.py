@@ -11,7 +11,7 @@ import oracle
 from oracle import ops
 import paper_2405_18047_amd as tbp
 import seeded_inputs as si
-from gpu_util import DEV, compare_stage, make_gpu_stage, max_rel, run_oracle, stage_tolerance, to_dev, to_np
+from gpu_util import DEV, PRODUCT_TILES, compare_stage, make_gpu_stage, max_rel, run_oracle, stage_tolerance, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -155,14 +155,15 @@ def test_gemm_with_split_contraction(layout, mnk):
     (264, 1032, 1000), (264, 1032, 5512),                         # 64 x 64 tiles; the last in slices
     (1000, 2056, 3080), (1032, 1032, 4104),                       # 128 x 128 tiles, one per compute unit; in slices
     (1688, 1560, 400), (2040, 2040, 8),                           # the same with a short contraction
-    (2000, 3464, 1160), (360, 4088, 5512),                        # 128 x 128 tiles, two per compute unit; few, long
-    (264, 22008, 1032), (264, 11016, 4104),                       # 256 x 192 tiles; in slices
-    (40, 11000, 4104), (24, 16696, 6088), (8, 4104, 4104),        # one row of tiles: by layout 128 x 128 or 64 x 64, or 32 x 32, in slices
+    (2000, 3464, 1160), (360, 4088, 5512),                        # 256 x 128 tiles; by layout 192 x 192 or 128 x 128 in slices
+    (264, 22008, 1032), (264, 11016, 4104),                       # 192 x 192 tiles; in slices
+    (40, 11000, 4104), (24, 16696, 6088), (8, 4104, 4104),        # one row of tiles: by layout 128 x 128 in slices, 64 x 64 or 32 x 32
     (1032, 4088, 8200), (4088, 4088, 1096)])                      # 256 x 256 tiles in slices (ragged last slice); unsliced
 def test_gemm_tile_and_slice_choices(layout, mnk):
-    """Storage-type products of at most one round of large tiles: every tile size, with and without the contraction cut
-    into slices whose partial products a second launch adds up, ragged in M, N, K and in the last slice; output in a wider
-    matrix whose other columns stay untouched.  Tolerance: one bf16 rounding of the result (2^-8 of the element at most)."""
+    """Storage-type products of at most one round of large tiles: small and large tiles, with and without the contraction cut
+    into slices whose partial products a second launch adds up, ragged in M, N, K and in the last slice (every tile:
+    PRODUCT_TILES); output in a wider matrix whose other columns stay untouched.  Tolerance: one bf16 rounding of the
+    result (2^-8 of the element at most)."""
     M, N, K = mnk
     _say(f"gemm tiles layout={layout} M,N,K={mnk}")
     A, B = _rnd(18, "A", (M, K), "bf16"), _rnd(18, "B", (N, K) if layout == tbp.NT else (K, N), "bf16")
@@ -177,18 +178,12 @@ def test_gemm_tile_and_slice_choices(layout, mnk):
         assert torch.all(out[:, N:] == 7.0)
 
 
-@pytest.mark.parametrize("layout,mnk", [
-    (tbp.NN, (400, 4760, 64)), (tbp.NT, (2312, 872, 72)), (tbp.NN, (16, 3280, 5264)), (tbp.NT, (72, 3424, 2792)),        # 128 x 128, in slices
-    (tbp.NN, (416, 8440, 64)), (tbp.NT, (392, 8952, 64)),                                                                 # two of them per compute unit
-    (tbp.NN, (1040, 3744, 320)), (tbp.NT, (2440, 1640, 960)), (tbp.NN, (288, 3928, 4000)), (tbp.NT, (152, 5936, 5056)),   # 128 x 192
-    (tbp.NN, (408, 2352, 512)), (tbp.NT, (2832, 328, 464)), (tbp.NN, (328, 920, 2808)), (tbp.NT, (1912, 144, 2520)),      # 128 x 64
-    (tbp.NN, (1448, 5768, 144)), (tbp.NT, (1064, 7520, 160)), (tbp.NN, (144, 8344, 3112)), (tbp.NT, (136, 8608, 3376)),   # 192 x 192
-    (tbp.NN, (1744, 3488, 800)), (tbp.NT, (456, 8200, 720)), (tbp.NN, (168, 5904, 4416)), (tbp.NT, (408, 2976, 4040)),    # 256 x 128
-    (tbp.NN, (16, 8904, 8)), (tbp.NT, (16, 8648, 72)), (tbp.NN, (24, 80, 2408)), (tbp.NT, (16, 72, 4720))])               # 64 x 64
-def test_gemm_tiles_with_copying_waves(layout, mnk):
-    """Every tile whose copies are started by waves of their own, with the contraction whole and in slices (which end in a
-    shorter one), from one slot (rings of up to six then run past the end at once) to many; ragged in M, N and K, with a
-    residual.  The same bits from call to call.  Tolerance: one bf16 rounding of the result (2^-8 of the element at most)."""
+@pytest.mark.parametrize("layout,mnk,plan", PRODUCT_TILES)
+def test_gemm_tiles_with_copying_waves(layout, mnk, plan):
+    """Every tile of the plan, those whose copies are started by waves of their own and the others, with the contraction whole and in
+    slices (which end in a shorter one), from one slot (rings of up to six then run past the end at once) to many; ragged in M,
+    N and K, with a residual; then without scratch.  The same bits from call to call.  Tolerance: one bf16 rounding of the
+    result (2^-8 of the element at most)."""
     M, N, K = mnk
     _say(f"gemm, copying waves layout={layout} M,N,K={mnk}")
     A, B = _rnd(19, "A", (M, K), "bf16"), _rnd(19, "B", (N, K) if layout == tbp.NT else (K, N), "bf16")
@@ -196,7 +191,9 @@ def test_gemm_tiles_with_copying_waves(layout, mnk):
     a64, b64 = A.astype(np.float64), B.astype(np.float64)
     ref = ops.linear_p1(a64, b64) if layout == tbp.NT else ops.linear_fwd(a64, b64)
     dA, dB, dR = to_dev(A, "bf16"), to_dev(B, "bf16"), to_dev(R, "bf16")
-    for workspace in (True, None):
+    scratch = torch.empty(1024 + plan[3] * M * N * 4, dtype=torch.uint8, device=DEV)
+    assert tbp.tbp_gemm_plan(layout, *mnk, scratch.numel()) == plan
+    for workspace in (scratch, None):
         got = tbp.tbp_gemm(layout, dA, dB, R=dR, alpha=0.5, workspace=workspace)
         assert max_rel(to_np(got), 0.5 * ref + R) < 4.5e-3
         assert torch.equal(got, tbp.tbp_gemm(layout, dA, dB, R=dR, alpha=0.5, workspace=workspace))

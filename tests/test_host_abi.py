@@ -11,6 +11,7 @@ import pytest
 
 import paper_2405_18047_amd as tbp
 import seeded_inputs as si
+from gpu_util import PRODUCT_TILES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -261,6 +262,17 @@ def test_gemm_plan_avoids_choices_that_measured_slower(layout, mnk, slower):
     assert 1 <= per_cu <= 2 and 1 <= slices <= 16
     # without scratch nothing is cut
     assert tbp.tbp_gemm_plan(layout, *mnk, 0)[3] == 1
+
+
+def test_product_tiles_list_runs_what_it_names():
+    """The shapes that the GPU tests run tile by tile: the plan takes the tile and the slices that each is listed for, and every tile
+    is there in both layouts, whole and (but for 32 x 32) in slices."""
+    for layout, mnk, plan in PRODUCT_TILES:
+        assert tbp.tbp_gemm_plan(layout, *mnk, 1024 + plan[3] * mnk[0] * mnk[1] * 4) == plan, (layout, mnk)
+    got = {(layout, plan[:3], plan[3] > 1) for layout, _, plan in PRODUCT_TILES}
+    tiles = {(64, 64, 2), (128, 64, 1), (128, 128, 1), (128, 128, 2), (128, 192, 1), (256, 128, 1), (192, 192, 1), (256, 192, 1), (256, 256, 1)}
+    layouts = (tbp.NN, tbp.NT)
+    assert got == {(lo, t, cut) for lo in layouts for t in tiles for cut in (False, True)} | {(lo, (32, 32, 1), False) for lo in layouts}
 
 
 def test_no_workspace_for_products_that_take_less_than_its_allocation():
