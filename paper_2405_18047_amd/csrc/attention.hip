@@ -1053,8 +1053,7 @@ hipError_t attention_p1(int batch, int n_heads, int seq, int head_dim, int causa
     return head_dim == 128 ? launch_bwd_kv_split<128, false, 128>(p, s) : launch_bwd_kv_split<64, false, 128>(p, s);
   }
   if (e = head_rowdot(1, batch * seq, n_heads, head_dim, d_out, out, delta, s); e != hipSuccess) return e;
-  e = head_dim == 128 ? launch_bwd_kv_split<128, true, 128>(p, s) : launch_bwd_kv_split<64, true, 128>(p, s);
-  if (e != hipSuccess) return e;
+  if (e = launch_bwd_kv_split<128, true, 128>(p, s); e != hipSuccess) return e;      // (head_dim 64 is always rebuilt)
   // dq = scale * dS k = scale * (dS^T)^T k per (sequence, head): contraction over keys, causal: keys <= query
   const long d = (long)n_heads * head_dim;
   GemmArgs g = gemm_args(TN, seq, head_dim, seq, ds_t, kPanel, (const char*)qkv + d * 2, ld_qkv, dqkv, ld_dqkv);

@@ -155,18 +155,18 @@ hipError_t head_rowdot(int dtype, int rows, int n_heads, int head_dim, const voi
 hipError_t attention_fwd(int batch, int n_heads, int seq, int head_dim, int causal, const void* qkv, long ld_qkv,
                          void* out, long ld_out, float* lse, hipStream_t s);
 
-// Does the backward compute dq by a pass that rebuilds S and dP rather than from dS^T written to memory?  At head_dim 64, where
-// the two products that the pass adds are cheap (on 769 to 1023 workgroups of 128 keys of a short sequence dS^T has been kept,
-// B 4, H 85, S 264 74 / 60: a test holds the two forms apart there);
-// at head_dim 128 where the grid is small (its workgroups can be halved, a product over 128 x 128 tiles cannot) or the
-// sequence long: short ones write little dS^T per workgroup.  Whole backward, us, dS^T / rebuilt; dh 128, causal: B 1, H 32, S 256
-// 23.7 / 17.4, S 1024 56.7 / 49.9, S 2048 140 / 138, B 2, H 40, S 768 69 / 71, B 3, H 32, S 1024 139 / 132, B 5, H 32, S 640 115 / 112, B 10, H 32,
-// S 256 71 / 73, B 2, H 32, S 2048 270 / 264, B 8, H 32, S 512 131 / 135; unmasked: B 1, H 16, S 1024 53 / 43, H 24, S 1000 57 / 63, B 2, H 40, S 768
-// 98 / 102, B 3, H 32, S 1024 206 / 200; dh 64: B 1, H 16, S 1024 45 / 30, B 4, H 12, S 1000 unmasked 82 / 73, B 2, H 24, S 2048 167 / 138.
+// Does the backward compute dq by a pass that rebuilds S and dP rather than from dS^T written to memory?  At head_dim 64 always: the
+// two products that the pass adds are cheap there.  At head_dim 128 where the grid is small (its workgroups can be halved, a
+// product over 128 x 128 tiles cannot) or the sequence long: short ones write little dS^T per workgroup.  Whole backward, us,
+// dS^T / rebuilt; dh 128, causal: B 1, H 32, S 256 23.7 / 17.4, S 1024 56.7 / 49.9, S 2048 140 / 138, B 2, H 40, S 768 69 / 71, B 3, H 32, S 1024
+// 139 / 132, B 5, H 32, S 640 115 / 112, B 10, H 32, S 256 71 / 73, B 2, H 32, S 2048 270 / 264, B 8, H 32, S 512 131 / 135; unmasked: B 1, H 16, S 1024
+// 53 / 43, H 24, S 1000 57 / 63, B 2, H 40, S 768 98 / 102, B 3, H 32, S 1024 206 / 200; dh 64: B 1, H 16, S 1024 45 / 30, B 4, H 12, S 1000 unmasked
+// 82 / 73, B 2, H 24, S 2048 167 / 138, B 4, H 85, S 264 73 / 58 (unmasked 80 / 72), B 31, H 32, S 128 61 / 55, B 26, H 32, S 40 34 / 30, B 5, H 40, S 504
+// 75 / 64.
 inline bool attn_rebuilds_dq(int batch, int n_heads, int seq, int head_dim, int causal) {
   const long w = (long)batch * n_heads * ((seq + 127) / 128);
-  if (w >= 1024) return head_dim == 64 || seq > 512;
-  if (head_dim == 64) return w <= 768 || seq > 512;
+  if (head_dim == 64) return true;
+  if (w >= 1024) return seq > 512;
   return causal ? w <= 512 || seq > 768 : w <= 128 || (w >= 512 && seq > 768);
 }
 
