@@ -79,11 +79,11 @@ typedef enum { TBP_P2_LOOP = 0, TBP_P2_KCONCAT = 1 } tbp_p2_mode;
 /* Attention is a functional operation: no backward-p2, everything it keeps is released in backward-p1 (Section 4.2).
  *   MATERIALISED  scores -> softmax -> P v as separate products; the probabilities P [batch, heads, seq, seq] are
  *                 stashed from forward to p1 (any dtype, any head_dim);
- *   FUSED         one forward kernel and one backward kernel that never write scores or probabilities: only the
- *                 row log-sum-exp [batch, heads, seq] is stashed and p1 rebuilds the probabilities from it
- *                 (bf16 storage, head_dim 64 or 128; TBP_EINVAL otherwise).  p1's dq comes from a product with dS^T, which
- *                 the first pass writes to the workspace, or, where that is faster, as with FUSED_RECOMPUTE (on
- *                 large grids no dS^T workspace is asked for then);
+ *   FUSED         one forward kernel and two backward kernels (and a product, below) that never write scores or
+ *                 probabilities: only the row log-sum-exp [batch, heads, seq] is stashed and p1 rebuilds the
+ *                 probabilities from it (bf16 storage, head_dim 64 or 128; TBP_EINVAL otherwise).  p1's dq comes, where
+ *                 that is faster, as with FUSED_RECOMPUTE, and otherwise from a product with dS^T, which the dk / dv
+ *                 kernel writes to the workspace (no dS^T workspace is asked for where it does not);
  *   FUSED_RECOMPUTE  FUSED, with a backward whose dq always comes from a second pass over the keys that rebuilds the scores
  *                 and dP: three more products per tile, no dS^T workspace (batch * heads * seq^2 storage-type
  *                 elements); same availability rule as FUSED;

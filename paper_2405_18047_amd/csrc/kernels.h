@@ -155,7 +155,8 @@ hipError_t head_rowdot(int dtype, int rows, int n_heads, int head_dim, const voi
 hipError_t attention_fwd(int batch, int n_heads, int seq, int head_dim, int causal, const void* qkv, long ld_qkv,
                          void* out, long ld_out, float* lse, hipStream_t s);
 
-// Does the backward compute dq by a pass that rebuilds S and dP rather than from dS^T written to memory?  At head_dim 64 always: the
+// Does the backward compute dq by a pass that rebuilds S and dP rather than from dS^T written to memory (for which a stage then has
+// no room)?  At head_dim 64 always: the
 // two products that the pass adds are cheap there.  At head_dim 128 where the grid is small (its workgroups can be halved, a
 // product over 128 x 128 tiles cannot) or the sequence long: short ones write little dS^T per workgroup.  Whole backward, us,
 // dS^T / rebuilt; dh 128, causal: B 1, H 32, S 256 23.7 / 17.4, S 1024 56.7 / 49.9, S 2048 140 / 138, B 2, H 40, S 768 69 / 71, B 3, H 32, S 1024
@@ -168,12 +169,6 @@ inline bool attn_rebuilds_dq(int batch, int n_heads, int seq, int head_dim, int 
   if (head_dim == 64) return true;
   if (w >= 1024) return seq > 512;
   return causal ? w <= 512 || seq > 768 : w <= 128 || (w >= 512 && seq > 768);
-}
-
-// Does a stage ask for room for dS^T?  (By the size of the grid alone, and also for small grids that have stopped writing it: the
-// sizes that a configuration's owner was told have not changed with that.)
-inline bool attn_asks_for_ds(int batch, int n_heads, int seq, int head_dim) {
-  return (long)batch * n_heads * ((seq + 127) / 128) < 1024 || (head_dim != 64 && seq <= 512);
 }
 
 // Backward-p1 of the same: dq, dk, dv into the column blocks of dqkv from qkv, the forward's output and lse and the

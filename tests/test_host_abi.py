@@ -55,10 +55,10 @@ def test_stash_sizes_follow_the_stash_rule():
             assert fused["a_stash_bytes"] == L * M * T * ((5 * d + 2 * f) * 2 + s.n_heads * 4)
             assert fused["w_stash_bytes"] == got["w_stash_bytes"]
             assert _sizes(s)["a_stash_bytes"] == fused["a_stash_bytes"]       # AUTO picks it for bf16, head_dim 128
-            # dq by a recompute pass: the same stash, and the dS^T workspace (batch * heads * seq^2 elements) is gone
+            # dq by a recompute pass, which these stages take by themselves: the same stash, no dS^T workspace
             lean = _sizes(s, attention=tbp.TBP_ATTN_FUSED_RECOMPUTE)
             assert lean["a_stash_bytes"] == fused["a_stash_bytes"] and lean["w_stash_bytes"] == fused["w_stash_bytes"]
-            assert fused["workspace_bytes"] - lean["workspace_bytes"] == s.micro_batch * s.n_heads * s.seq * s.seq * 2
+            assert fused["workspace_bytes"] == lean["workspace_bytes"]
         # gain gradients computed in p2: each norm's input moves from the forward->p1 slots to slabs kept until p2 and
         # the derivative of its output is kept as well; the fp32 partials disappear
         lit = _sizes(s, gain_grad=tbp.TBP_GAIN_LITERAL)
@@ -70,13 +70,16 @@ def test_stash_sizes_follow_the_stash_rule():
     s = si.CONFIGS["llama7b_s1024"]
     assert _sizes(s, act_slots=1)["a_stash_bytes"] * 4 == _sizes(s)["a_stash_bytes"]
     assert _sizes(s, act_slots=1)["w_stash_bytes"] == _sizes(s)["w_stash_bytes"]
-    # where the backward rebuilds dq on its own account, no dS^T workspace is asked for: from 1024 workgroups of 128 keys on,
-    # at head_dim 128 above 512 keys
-    for heads, dh, seq, batch, rebuilt in ((32, 128, 2048, 2, True), (31, 128, 2048, 2, False), (32, 128, 512, 8, False), (32, 128, 520, 8, True),
-                                           (32, 64, 128, 32, True), (32, 64, 128, 31, False), (32, 64, 512, 8, True)):
-        s = si.StageShape("dst", 1, heads * dh, heads, dh, 256, seq, batch, 1, "bf16", 1)
+    # where the backward rebuilds dq on its own account, no dS^T workspace is asked for: at head_dim 64; at 128 on up to 512
+    # workgroups of 128 keys (unmasked 128), above 768 keys, or 512 from 1024 workgroups on
+    for heads, dh, seq, batch, causal, rebuilt in (
+            (32, 128, 2048, 2, True, True), (31, 128, 2048, 2, True, True), (32, 128, 512, 8, True, False), (32, 128, 520, 8, True, True),
+            (32, 128, 512, 4, True, True), (33, 128, 512, 4, True, False), (33, 128, 520, 6, True, False), (40, 128, 776, 2, True, True),
+            (16, 128, 1024, 1, False, True), (17, 128, 1024, 1, False, False), (32, 128, 1024, 2, False, True), (32, 128, 768, 3, False, False),
+            (32, 64, 128, 32, True, True), (32, 64, 128, 31, True, True), (32, 64, 512, 8, True, True), (32, 64, 512, 6, False, True)):
+        s = si.StageShape("dst", 1, heads * dh, heads, dh, 256, seq, batch, 1, "bf16", 1, causal=causal)
         saved = _sizes(s, attention=tbp.TBP_ATTN_FUSED)["workspace_bytes"] - _sizes(s, attention=tbp.TBP_ATTN_FUSED_RECOMPUTE)["workspace_bytes"]
-        assert saved == (0 if rebuilt else batch * heads * seq * ((seq + 127) // 128 * 128) * 2), (heads, dh, seq, batch)
+        assert saved == (0 if rebuilt else batch * heads * seq * ((seq + 127) // 128 * 128) * 2), (heads, dh, seq, batch, causal)
         # the single operation's scratch stays large enough for any smaller call
         assert tbp.lib().tbp_attention_p1_scratch_bytes(batch, heads, seq) >= batch * heads * seq * seq * 2
     # 13B stage: everything fits the 288 GB of one MI355X
