@@ -1684,14 +1684,15 @@ static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) 
   return best;
 }
 // The search above costs 2 us of host time, a sixth of what a small product takes from call to call, and a program runs the same few
-// products over and over: each thread keeps its last plans (a function of these five numbers alone), one per slot.
+// products over and over: each thread keeps its last plans (a function of these five numbers alone), one per slot.  The plans of a product
+// with and without scratch, which a workspace query and the call after it ask for in turn, have slots of their own.
 static SplitPlan product_plan(int layout, int M, int N, int K, bool allow_split) {
-  struct Slot { int layout, M, N, K; bool allow_split; SplitPlan plan; };
-  static thread_local Slot slots[128];                              // (M is 0 in a slot that holds nothing)
-  uint32_t h = (uint32_t)M * 0x9E3779B1u + (uint32_t)N * 0x85EBCA6Bu + (uint32_t)K * 0xC2B2AE35u + (uint32_t)(2 * layout + allow_split) * 0x27D4EB2Fu;
-  Slot& slot = slots[(h ^ h >> 15) * 0x9E3779B1u >> 25];
-  if (M <= 0 || slot.M != M || slot.N != N || slot.K != K || slot.layout != layout || slot.allow_split != allow_split)
-    slot = Slot{layout, M, N, K, allow_split, search_plan(layout, M, N, K, allow_split)};
+  struct Slot { int layout, M, N, K; SplitPlan plan; };
+  static thread_local Slot slots[2][128];                           // (M is 0 in a slot that holds nothing)
+  uint32_t h = (uint32_t)M * 0x9E3779B1u + (uint32_t)N * 0x85EBCA6Bu + (uint32_t)K * 0xC2B2AE35u + (uint32_t)layout * 0x27D4EB2Fu;
+  Slot& slot = slots[allow_split][(h ^ h >> 15) * 0x9E3779B1u >> 25];
+  if (M <= 0 || slot.M != M || slot.N != N || slot.K != K || slot.layout != layout)
+    slot = Slot{layout, M, N, K, search_plan(layout, M, N, K, allow_split)};
   return slot.plan;
 }
 // The plan where `ws_bytes` of scratch are at hand.
