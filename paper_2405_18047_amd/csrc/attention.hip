@@ -1035,7 +1035,7 @@ hipError_t attention_p1(int batch, int n_heads, int seq, int head_dim, int causa
   p.scale = 1.f / sqrtf((float)head_dim);
   p.scale_log2e = 1.4426950408889634f * p.scale;
   hipError_t e;
-  if (!ds_t || attn_rebuilds_dq(batch, n_heads, seq, head_dim, causal)) {
+  if (!ds_t || attn_rebuilds_dq(batch, n_heads, seq, head_dim, causal, rope_table != nullptr)) {
     const long heads = (long)batch * n_heads;
     // us of the whole backward, 128 / 64 queries per workgroup of the dq pass; causal: B 1, H 32, dh 128, S 256 23.5 / 21.1, S 1024
     // 64.1 / 57.3, S 2048 142 / 138, B 4, H 12, dh 64, S 1000 50.5 / 48.3; lost: B 4, H 32, S 512 60.9 / 62.1; unmasked: B 1, H 16,

@@ -166,10 +166,15 @@ hipError_t attention_fwd(int batch, int n_heads, int seq, int head_dim, int caus
 // us, dS^T / rebuilt, dh 64: B 1, H 16, S 1024 45 / 30, B 4, H 12, S 1000 unmasked 82 / 73, B 2, H 24, S 2048 167 / 138, B 4, H 85, S 264 73 / 58
 // (unmasked 80 / 72), B 31, H 32, S 128 61 / 55, B 26, H 32, S 40 34 / 30, B 5, H 40, S 504 75 / 64; dh 128, 1024 workgroups: B 2, H 32, S 2048
 // 270 / 264, B 8, H 32, S 512 131 / 135.
-inline bool attn_rebuilds_dq(int batch, int n_heads, int seq, int head_dim, int causal) {
+//
+// `rotates`: dq and dk have to leave rotated back, as a stage asks for, which the rebuilt form does on the way and dS^T by one more
+// launch.  The rebuilt form then is ahead on most of those grids as well: 1200 shapes with that launch; causal 257-576 workgroups above S 512
+// 1.00-1.19, 577-1023 above S 768 1.09-1.29; unmasked up to 128 workgroups 1.29-1.61, 512-1023 above S 768 1.05-1.17, 129-256 above S 1024 0.85-1.06.
+inline bool attn_rebuilds_dq(int batch, int n_heads, int seq, int head_dim, int causal, bool rotates) {
   const long w = (long)batch * n_heads * ((seq + 127) / 128);
   if (head_dim == 64) return true;
   if (w >= 1024) return seq > 512;
+  if (rotates) return causal ? w <= 512 || seq > 768 : w <= 128 || (w >= 512 && seq > 768);
   if (!causal) return w <= 128 || (w > 768 ? seq > 768 : w > 640 ? seq > 896 : w >= 512 && seq > 1408);
   if (w <= 256) return true;
   if (seq <= 512) return w <= 512;
@@ -182,7 +187,7 @@ inline bool attn_rebuilds_dq(int batch, int n_heads, int seq, int head_dim, int 
 // queries: per (sequence, head) [ceil(seq / kPanel)][seq keys][kPanel queries]; dq is then one batched product
 // dS K), or nullptr: dq is computed by a second pass over the keys that rebuilds S and dP (no dS^T anywhere), as it is
 // with attn_rebuilds_dq in any case (ds_t is then not touched).  rope_table (may be null): q and k are rotated, and dq and dk
-// leave rotated back.
+// leave rotated back (`rotates`).
 hipError_t attention_p1(int batch, int n_heads, int seq, int head_dim, int causal, const void* qkv, long ld_qkv,
                         const void* out, const void* d_out, long ld_out, const float* lse, void* dqkv, long ld_dqkv,
                         float* delta, void* ds_t, const float2* rope_table, hipStream_t s);

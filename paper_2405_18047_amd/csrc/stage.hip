@@ -186,7 +186,7 @@ tbp_status check_config(const tbp_config* cfg, Dims* out) {
   c.literal = cfg->gain_grad == TBP_GAIN_LITERAL;
   if (!(c.eps >= 0.f)) return fail(TBP_EINVAL, "rms_eps must be >= 0");
   if ((long)c.S * c.B > (1L << 24)) return fail(TBP_EINVAL, "tokens per micro-batch above 2^24");
-  c.dq_recompute = c.fused && (cfg->attention == TBP_ATTN_FUSED_RECOMPUTE || tbp::attn_rebuilds_dq(c.B, c.H, c.S, c.dh, c.causal));
+  c.dq_recompute = c.fused && (cfg->attention == TBP_ATTN_FUSED_RECOMPUTE || tbp::attn_rebuilds_dq(c.B, c.H, c.S, c.dh, c.causal, true));
   c.T = c.S * c.B;
   *out = c;
   return TBP_OK;

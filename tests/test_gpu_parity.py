@@ -698,10 +698,12 @@ def test_stage_inputs_at_any_address(shape, gain_grad):
 @pytest.mark.parametrize("seq,nb,H,dh,causal,rebuilt", [
     (264, 4, 86, 64, True, True), (264, 4, 85, 64, True, True),             # head_dim 64; the last key block ragged
     (264, 4, 86, 128, False, False),                                        # 1032 workgroups, but short
-    (520, 5, 41, 128, False, True), (520, 4, 51, 128, True, False)])         # 1025 and 1020
+    (520, 5, 41, 128, False, True), (520, 4, 51, 128, True, False),          # 1025 and 1020
+    (904, 1, 40, 128, True, True), (904, 1, 41, 128, True, False),          # 320 and 328
+    (512, 2, 33, 128, True, True), (520, 1, 52, 128, True, False)])         # 264 and 260, on both sides of 512 keys
 def test_fused_attention_backward_on_many_workgroups(seq, nb, H, dh, causal, rebuilt):
-    """At head_dim 64, and at head_dim 128 on four workgroups of 128 keys per compute unit or more above 512 keys, dq comes from the
-    recompute pass also where there is room for dS^T: both sides of the lines against the oracle's values.  Where it does, and
+    """At head_dim 64, and at head_dim 128 on small grids and for long sequences on large ones, dq comes from the
+    recompute pass also where there is room for dS^T: both sides of lines against the oracle's values.  Where it does, and
     only there, the bits are those of the call that asks for the pass."""
     _say(f"attention p1 on many workgroups seq={seq} B={nb} H={H} dh={dh} causal={causal}")
     d = H * dh

@@ -70,15 +70,12 @@ def test_stash_sizes_follow_the_stash_rule():
     s = si.CONFIGS["llama7b_s1024"]
     assert _sizes(s, act_slots=1)["a_stash_bytes"] * 4 == _sizes(s)["a_stash_bytes"]
     assert _sizes(s, act_slots=1)["w_stash_bytes"] == _sizes(s)["w_stash_bytes"]
-    # where the backward rebuilds dq on its own account, no dS^T workspace is asked for: both sides of every line
+    # where the backward rebuilds dq on its own account, no dS^T workspace is asked for: at head_dim 64; at 128 on up to 512
+    # workgroups of 128 keys (unmasked 128), above 768 keys (unmasked from 512 workgroups on), or 512 from 1024 workgroups on
     for heads, dh, seq, batch, causal, rebuilt in (
-            (32, 128, 2048, 2, True, True), (32, 128, 512, 8, True, False), (32, 128, 520, 8, True, True), (31, 128, 2048, 2, True, True),
-            (32, 128, 768, 1, True, True), (64, 128, 512, 2, True, True), (33, 128, 512, 4, True, False),
-            (40, 128, 896, 1, True, False), (40, 128, 904, 1, True, True), (41, 128, 904, 1, True, False), (41, 128, 520, 2, True, False),
-            (36, 128, 2048, 1, True, False), (37, 128, 2048, 1, True, True), (49, 128, 768, 2, True, False), (45, 128, 776, 2, True, True),
-            (16, 128, 1024, 1, False, True), (17, 128, 1024, 1, False, False), (31, 128, 2048, 1, False, False), (32, 128, 2048, 1, False, True),
-            (48, 128, 1408, 1, False, False), (48, 128, 1416, 1, False, True), (50, 128, 896, 2, False, False), (41, 128, 904, 2, False, True),
-            (55, 128, 896, 2, False, True), (64, 128, 768, 2, False, False),
+            (32, 128, 2048, 2, True, True), (31, 128, 2048, 2, True, True), (32, 128, 512, 8, True, False), (32, 128, 520, 8, True, True),
+            (32, 128, 512, 4, True, True), (33, 128, 512, 4, True, False), (33, 128, 520, 6, True, False), (40, 128, 776, 2, True, True),
+            (16, 128, 1024, 1, False, True), (17, 128, 1024, 1, False, False), (32, 128, 1024, 2, False, True), (32, 128, 768, 3, False, False),
             (32, 64, 128, 32, True, True), (32, 64, 128, 31, True, True), (32, 64, 512, 8, True, True), (32, 64, 512, 6, False, True)):
         s = si.StageShape("dst", 1, heads * dh, heads, dh, 256, seq, batch, 1, "bf16", 1, causal=causal)
         saved = _sizes(s, attention=tbp.TBP_ATTN_FUSED)["workspace_bytes"] - _sizes(s, attention=tbp.TBP_ATTN_FUSED_RECOMPUTE)["workspace_bytes"]
