@@ -1656,9 +1656,11 @@ static bool one_round(int M, int N) { return (long)((M + 255) / 256) * ((N + 255
 static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) {
   const SplitPlan coarse = coarse_plan(layout, M, N, K, allow_split);
   SplitPlan best = coarse;
-  double coarse_time = product_time(kTileCost[coarse.tile], layout, M, N, K, tiles_of(coarse.tile, M, N) * coarse.split, coarse.slice, coarse.split);
+  const long coarse_wgs = tiles_of(coarse.tile, M, N) * coarse.split;
+  double coarse_time = product_time(kTileCost[coarse.tile], layout, M, N, K, coarse_wgs, coarse.slice, coarse.split);
   // (32 x 32 tiles of few rows: the coarse model knows them better.  [24, 584] x 3912 (NT) 6.5 us, 9.9 modelled here, in eleven slices of 64 x 64 8.4)
   if (coarse.tile == T32 && M <= 128) coarse_time = fmin(coarse_time, coarse_time_of_32(layout, M, N, K));
+  const bool few_pairs = coarse.tile == T128_PAIR && coarse_wgs > 256 && coarse_wgs <= 288;
   double best_time = 1e30;
   for (int i = T32; i <= T256; i++) {
     const TileCost& t = kTileCost[i];
@@ -1675,9 +1677,13 @@ static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) 
       // rows the coarse plan is good, and 64 x 64 tiles that read a large weight unsliced in its place lose ([64, 11928] x 11320 (NT)
       // 100 us, two slices of 128 x 128 86).  Short slices on 256 x 128 are level with two 128 x 128 workgroups per compute unit where it
       // holds them for 7 % faster ([2032, 2624] x 848 (NT) 18.8 us and 18.4).
-      const double must = coarse.tile == T32 ? 0.8 : M <= 128 ? (i == T64 && sp == 1 && coarse.tile != T64 ? 0.7 : 0.85)
-                          : M <= 192 && t.bm >= 192 ? 0.8 : i == T256X128 && plan.slice < 1024 ? 0.85
-                          : i == T256X128 || i == T192 ? 0.96 : 0.9;
+      // Where two 128 x 128 workgroups share up to 32 of the compute units, this model prices all of them like that: 257 to 288 workgroups
+      // take 0.78 of its time (weights in the cache; 0.83 from HBM), 181 to 256 0.98 (1.11).  [2496, 1592] x 1000 (NT) 18.5 us, modelled 24.0, on
+      // 256 x 128 20.7.  (It prices 64 x 64 tiles likewise, but 44 of 48 such products that leave them are faster for it.)
+      const double must = fmin(few_pairs ? 0.75 : 1.,
+                               coarse.tile == T32 ? 0.8 : M <= 128 ? (i == T64 && sp == 1 && coarse.tile != T64 ? 0.7 : 0.85)
+                               : M <= 192 && t.bm >= 192 ? 0.8 : i == T256X128 && plan.slice < 1024 ? 0.85
+                               : i == T256X128 || i == T192 ? 0.96 : 0.9);
       if (time < must * coarse_time && time < best_time) { best_time = time; best = plan; }
     }
   }
@@ -1685,7 +1691,8 @@ static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) 
 }
 // The search above costs 2 us of host time, a sixth of what a small product takes from call to call, and a program runs the same few
 // products over and over: each thread keeps its last plans (a function of these five numbers alone), one per slot.  The plans of a product
-// with and without scratch, which a workspace query and the call after it ask for in turn, have slots of their own.
+// with and without scratch, which a workspace query and the call after it ask for in turn, have slots of their own (in one, they threw each
+// other out: 3.1 us for the two, at worst 5.2, instead of 2.2).
 static SplitPlan product_plan(int layout, int M, int N, int K, bool allow_split) {
   struct Slot { int layout, M, N, K; SplitPlan plan; };
   static thread_local Slot slots[2][128];                           // (M is 0 in a slot that holds nothing)

@@ -26,7 +26,7 @@ PRODUCT_TILES = [
     (tbp.NT, (408, 2976, 4040), (128, 128, 1, 2)),
     (tbp.NN, (1040, 3744, 320), (128, 192, 1, 1)), (tbp.NT, (2440, 1640, 960), (128, 192, 1, 1)), (tbp.NN, (288, 3928, 4000), (128, 192, 1, 4)),
     (tbp.NN, (168, 5904, 4416), (128, 192, 1, 4)), (tbp.NT, (152, 5936, 5056), (128, 192, 1, 4)),
-    (tbp.NN, (2552, 2312, 1032), (256, 128, 1, 1)), (tbp.NT, (2696, 1456, 1032), (256, 128, 1, 1)), (tbp.NN, (920, 1400, 4904), (256, 128, 1, 5)),
+    (tbp.NN, (2552, 2312, 1032), (256, 128, 1, 1)), (tbp.NT, (2104, 2064, 1056), (256, 128, 1, 1)), (tbp.NN, (920, 1400, 4904), (256, 128, 1, 5)),
     (tbp.NT, (936, 1328, 4744), (256, 128, 1, 4)),
     (tbp.NN, (1448, 5768, 144), (192, 192, 1, 1)), (tbp.NT, (1064, 7520, 160), (192, 192, 1, 1)), (tbp.NN, (1296, 976, 4952), (192, 192, 1, 6)),
     (tbp.NT, (520, 2200, 4128), (192, 192, 1, 6)),
