@@ -1658,7 +1658,9 @@ static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) 
   SplitPlan best = coarse;
   const long coarse_wgs = tiles_of(coarse.tile, M, N) * coarse.split;
   double coarse_time = product_time(kTileCost[coarse.tile], layout, M, N, K, coarse_wgs, coarse.slice, coarse.split);
-  // (32 x 32 tiles of few rows: the coarse model knows them better.  [24, 584] x 3912 (NT) 6.5 us, 9.9 modelled here, in eleven slices of 64 x 64 8.4)
+  // 32 x 32 tiles of few rows: the coarse model knows them better, those it chose ([24, 584] x 3912 (NT) 6.5 us, 9.9 modelled here, in eleven
+  // slices of 64 x 64 8.4) as well as those in place of another choice ([72, 2240] x 5312 (NN) in the steps of an MLP 14.2 to 21.5 us, 13.0 modelled
+  // here, 17.7 there; in six slices of 64 x 64 12.6 to 18.6 with their sum).
   if (coarse.tile == T32 && M <= 128) coarse_time = fmin(coarse_time, coarse_time_of_32(layout, M, N, K));
   const bool few_pairs = coarse.tile == T128_PAIR && coarse_wgs > 256 && coarse_wgs <= 288;
   double best_time = 1e30;
@@ -1671,7 +1673,8 @@ static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) 
     for (int sp : kSlices) {
       if (sp > 1 && (!allow_split || i == T32 || K / sp < 256)) break;
       const SplitPlan plan = slices_of(i, M, N, K, sp);
-      const double time = product_time(t, layout, M, N, K, tiles * plan.split, plan.slice, plan.split);
+      double time = product_time(t, layout, M, N, K, tiles * plan.split, plan.slice, plan.split);
+      if (i == T32 && M <= 128) time = fmax(time, coarse_time_of_32(layout, M, N, K));
       // Its times of 32 x 32 tiles err most, those of the two largest of the new tiles least, but for up to 192 rows, where these are
       // mostly padding ([176, 9280] x 4160 (NN) 32.6 us on five slices of 192 x 192, modelled 32.3; 26.7 on 64 x 64, modelled 39.0).  Up to 128
       // rows the coarse plan is good, and 64 x 64 tiles that read a large weight unsliced in its place lose ([64, 11928] x 11320 (NT)

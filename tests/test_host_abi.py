@@ -256,6 +256,7 @@ int main() {
     (tbp.NT, (592, 10616, 10248), (256, 128, 1)),        # 203, 170: two slices of 256 x 256
     (tbp.NN, (2304, 3328, 28416), (256, 128, 1)),        # 392, 365: the same
     (tbp.NT, (24, 584, 3912), (64, 64, 11)),             # 8.4, 6.5: 32 x 32, whole
+    (tbp.NN, (72, 2240, 5312), (32, 32, 1)),             # 14.2-21.5, 12.6-18.6 (in steps): six slices of 64 x 64
     (tbp.NN, (176, 9280, 4160), (192, 192, 5)),          # 32.6, 27.2: 128 x 128, whole
     (tbp.NT, (2032, 2624, 848), (256, 128, 1)),          # 18.8, 18.4: 128 x 128, whole
     (tbp.NT, (2496, 1592, 1000), (256, 128, 1)),         # 20.7, 18.5: 128 x 128, whole
