@@ -957,7 +957,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 // Workgroups of 128 queries (keys) of a launch; and is the chip short of them?  Up to one per compute unit it is; with the
-// causal mask, whose longest workgroup works eight times as long as the shortest (or more), up to two.
+// causal mask, whose longest workgroup works eight times as long as the shortest (or more), up to two.  (Lines set at head_dim 128; at 64
+// halves would pay on somewhat larger grids too: B 3, H 24, S 512, causal, 288 workgroups, forward 11.5 / 10.0 us.)
 static long query_groups(long heads, int seq) { return heads * ((seq + 127) / 128); }
 static bool few_query_groups(long heads, int seq) { const long w = query_groups(heads, seq); return w <= 256 || (w <= 512 && seq > 896); }
 

@@ -1541,8 +1541,9 @@ static hipError_t launch_bf16_causal_pair(const GemmParams& p0, int batch, hipSt
 // of them and more of what a product's time depends on.  The plan is the coarse one unless the other model has a choice that it
 // holds for 4 to 30 % faster, depending on how well it knows the two.  On 3900 products (M 16-4096, N 128-27648, K 64-27648, weights that no
 // cache holds) the coarse one alone costs 2.5 % more than the fastest of all tiles and slices on average, `product_time` alone 0.7 % with
-// a tail of 1.3-fold misses ([16, 2560] x 3264 (NN) 13.4 us for 9.6).  On 2900 products where the two disagree (M 8-4096, N 256-12288, K 256-12288
-// and some to 60000, operands that take turns) the plan is 10 % faster than the coarse one on average and more than 6 % slower on 44.
+// a tail of 1.3-fold misses ([16, 2560] x 3264 (NN) 13.4 us for 9.6).  On 3717 products (M 64-4096, N and K 256-12288; weights from HBM / from
+// the cache) the plan with scratch costs 1.5 / 1.4 % more than the fastest, the coarse one 4.6 / 3.9 %; against the 4-wave kernels and the
+// coarse plan of before it is 5.8 / 6.4 % faster on average and more than 6 % slower on 3 / 15.
 // us, with the 4-wave kernels and the coarse plan that were here / now: [256, 22016] x 4096 (NN) 71 / 58 (128 x 192), [360, 4096] x 11008
 // (NT) 54 / 47 (192 x 192 in five slices), [256, 4096] x 4096 (NN) 19.6 / 16.7 (64 x 64), [2000, 1152] x 3456 (NT) 27.3 / 23.6 (128 x 128), [1024, 4096] x 11008 (NN)
 // 90 / 87.
