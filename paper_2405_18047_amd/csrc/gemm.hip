@@ -1664,6 +1664,10 @@ static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) 
   // here, 17.7 there; in six slices of 64 x 64 12.6 to 18.6 with their sum).
   if (coarse.tile == T32 && M <= 128) coarse_time = fmin(coarse_time, coarse_time_of_32(layout, M, N, K));
   const bool few_pairs = coarse.tile == T128_PAIR && coarse_wgs > 256 && coarse_wgs <= 288;
+  // 64 x 64 tiles that it prices likewise (below) and that narrow outputs of split cache lines had better keep: N up to 256, time on the other
+  // choice (128 x 64) over theirs 1.10-1.14 (K 1100-1400; from HBM 1.10), 1.06 (900-1100) and 1.06-1.10 (1400-1800); level or less for
+  // other K, and for wider outputs (500 tall ones of 257 to 290 workgroups; [4648, 216] x 1552 (NT), 292, 11.8 and 13.6).  [5448, 192] x 1248 (NT) 10.4 us, on 128 x 64 13.5.
+  if (coarse.tile == T64 && coarse.split == 1 && coarse_wgs > 256 && coarse_wgs <= 300 && N <= 256 && K % 64 && K >= 900 && K < 1800) return coarse;
   double best_time = 1e30;
   for (int i = T32; i <= T256; i++) {
     const TileCost& t = kTileCost[i];
@@ -1683,7 +1687,8 @@ static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) 
       // holds them for 7 % faster ([2032, 2624] x 848 (NT) 18.8 us and 18.4).
       // Where two 128 x 128 workgroups share up to 32 of the compute units, this model prices all of them like that: 257 to 288 workgroups
       // take 0.78 of its time (weights in the cache; 0.83 from HBM), 181 to 256 0.98 (1.11).  [2496, 1592] x 1000 (NT) 18.5 us, modelled 24.0, on
-      // 256 x 128 20.7.  (It prices 64 x 64 tiles likewise, but 44 of 48 such products that leave them are faster for it.)
+      // 256 x 128 20.7.  (It prices 64 x 64 tiles likewise, but apart from narrow
+      // outputs, see above, 44 of 48 such products that leave them are faster for it.)
       const double must = fmin(few_pairs ? 0.75 : 1.,
                                coarse.tile == T32 ? 0.8 : M <= 128 ? (i == T64 && sp == 1 && coarse.tile != T64 ? 0.7 : 0.85)
                                : M <= 192 && t.bm >= 192 ? 0.8 : i == T256X128 && plan.slice < 1024 ? 0.85

@@ -260,6 +260,7 @@ int main() {
     (tbp.NN, (176, 9280, 4160), (192, 192, 5)),          # 32.6, 27.2: 128 x 128, whole
     (tbp.NT, (2032, 2624, 848), (256, 128, 1)),          # 18.8, 18.4: 128 x 128, whole
     (tbp.NT, (2496, 1592, 1000), (256, 128, 1)),         # 20.7, 18.5: 128 x 128, whole
+    (tbp.NT, (5448, 192, 1248), (128, 64, 1)),           # 13.5, 10.4: 64 x 64, whole
     (tbp.NT, (64, 11928, 11320), (64, 64, 1))])          # 100, 86: two slices of 128 x 128
 def test_gemm_plan_avoids_choices_that_measured_slower(layout, mnk, slower):
     rows, cols, per_cu, slices = tbp.tbp_gemm_plan(layout, *mnk)
