@@ -1724,17 +1724,17 @@ SplitPlan gemm_split_plan(int dtype, int layout, int M, int N, int K, int out_f3
 }
 
 // What a caller is told to bring for one product.  A call that allocates its workspace and starts two kernels takes 14 us of host time
-// and one without 10, so a product that takes less than 16 in one launch (32 x 32 tiles: by either model, and less still where the L2
-// holds the weight) is left whole unless the coarse model cuts it as well.  From call to call, us, in slices / whole: [160, 416] x 4168 (NN) 15 /
-// 12, [136, 376] x 6696 (NT) 13.6 / 9.8, [176, 928] x 4712 (NN) 14.2 / 10.9.  Of 7400 drawn products 2 are slower for a workspace then, 16 with
-// a line at 15 by the second model alone.  (The stage, whose scratch is there in any case, goes by gemm_split_plan.)
+// and one without 10, so a product that is modelled to take less than 15.6 in one launch (16.7 on 32 x 32 tiles, less where the L2 holds the
+// weight) is left whole unless the coarse model cuts it as well.  From call to call, us, in slices / whole: [160, 416] x 4168 (NN) 15 / 12,
+// [136, 376] x 6696 (NT) 13.6 / 9.8, [176, 928] x 4712 (NN) 14.2 / 10.9; above the lines [280, 376] x 7048 (NN) 14.3 / 21.3, [312, 616] x 6296 (NN)
+// 13.9 / 19.8.  Of 7400 drawn products 3 are slower for a workspace, and 7 that would gain more than 10 % by one go without.  (The stage, whose
+// scratch is there in any case, goes by gemm_split_plan.)
 size_t gemm_workspace_bytes(int dtype, int layout, int M, int N, int K, int out_f32) {
   const SplitPlan plan = gemm_split_plan(dtype, layout, M, N, K, out_f32, 1);
   if (plan.split == 1 || coarse_plan(layout, M, N, K, true).split > 1) return plan.bytes;
   const int whole = product_plan(layout, M, N, K, false).tile;
-  double time = product_time(kTileCost[whole], layout, M, N, K, tiles_of(whole, M, N), K, 1);
-  if (whole == T32) time = fmin(time, coarse_time_of_32(layout, M, N, K));
-  return time < 16. ? 0 : plan.bytes;
+  const double time = product_time(kTileCost[whole], layout, M, N, K, tiles_of(whole, M, N), K, 1);
+  return time < (whole == T32 ? 16.7 : 15.6) ? 0 : plan.bytes;
 }
 bool gemm_plan(int layout, int M, int N, int K, size_t ws_bytes, int* tile_rows, int* tile_cols, int* per_cu, int* slices) {
   if ((layout != NN && layout != NT) || M <= 0 || N <= 0 || !one_round(M, N)) return false;
