@@ -1663,7 +1663,7 @@ static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) 
   // slices of 64 x 64 8.4) as well as those in place of another choice ([72, 2240] x 5312 (NN) in the steps of an MLP 14.2 to 21.5 us, 13.0 modelled
   // here, 17.7 there; in six slices of 64 x 64 12.6 to 18.6 with their sum).
   if (coarse.tile == T32 && M <= 128) coarse_time = fmin(coarse_time, coarse_time_of_32(layout, M, N, K));
-  const bool few_pairs = coarse.tile == T128_PAIR && coarse_wgs > 256 && coarse_wgs <= 288;
+  const bool few_pairs = coarse.tile == T128_PAIR && coarse_wgs > 256 && coarse_wgs <= 288 && M > 850;
   // 64 x 64 tiles that it prices likewise (below) and that narrow outputs of split cache lines had better keep: N up to 256, time on the other
   // choice (128 x 64) over theirs 1.10-1.14 (K 1100-1400; from HBM 1.10), 1.06 (900-1100) and 1.06-1.10 (1400-1800); level or less for
   // other K, and for wider outputs (500 tall ones of 257 to 290 workgroups; [4648, 216] x 1552 (NT), 292, 11.8 and 13.6).  [5448, 192] x 1248 (NT) 10.4 us, on 128 x 64 13.5.
@@ -1681,17 +1681,19 @@ static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) 
       double time = product_time(t, layout, M, N, K, tiles * plan.split, plan.slice, plan.split);
       if (i == T32 && M <= 128) time = fmax(time, coarse_time_of_32(layout, M, N, K));
       // Its times of 32 x 32 tiles err most, those of the two largest of the new tiles least, but for up to 192 rows, where these are
-      // mostly padding ([176, 9280] x 4160 (NN) 32.6 us on five slices of 192 x 192, modelled 32.3; 26.7 on 64 x 64, modelled 39.0).  Up to 128
+      // mostly padding ([176, 9280] x 4160 (NN) 32.6 us on five slices of 192 x 192, modelled 32.3; 26.7 on 64 x 64, modelled 39.0; less so in NT,
+      // [168, 9712] x 4440 on five such slices 1.2 times as fast as on 128 x 128).  Up to 128
       // rows the coarse plan is good, and 64 x 64 tiles that read a large weight unsliced in its place lose ([64, 11928] x 11320 (NT)
       // 100 us, two slices of 128 x 128 86).  Short slices on 256 x 128 are level with two 128 x 128 workgroups per compute unit where it
       // holds them for 7 % faster ([2032, 2624] x 848 (NT) 18.8 us and 18.4).
       // Where two 128 x 128 workgroups share up to 32 of the compute units, this model prices all of them like that: 257 to 288 workgroups
-      // take 0.78 of its time (weights in the cache; 0.83 from HBM), 181 to 256 0.98 (1.11).  [2496, 1592] x 1000 (NT) 18.5 us, modelled 24.0, on
-      // 256 x 128 20.7.  (It prices 64 x 64 tiles likewise, but apart from narrow
-      // outputs, see above, 44 of 48 such products that leave them are faster for it.)
-      const double must = fmin(few_pairs ? 0.75 : 1.,
+      // take 0.78 of its time (weights in the cache; 0.83 from HBM), 181 to 256 0.98 (1.11).  Outputs of more than 850 rows that leave them for 256 x 128
+      // tiles modelled less than 25 % faster lose ([2496, 1592] x 1000 (NT) 18.5 us, modelled 24.0, on 256 x 128 20.7; 9 of 10 such by 1 to 10 %); lower ones,
+      // and all that leave them for 128 x 192, gain.  (It prices 64 x 64 tiles likewise, but apart from narrow outputs, see above, 44 of 48 such
+      // products that leave them are faster for it.)
+      const double must = fmin(few_pairs && t.bm > 128 ? 0.75 : 1.,
                                coarse.tile == T32 ? 0.8 : M <= 128 ? (i == T64 && sp == 1 && coarse.tile != T64 ? 0.7 : 0.85)
-                               : M <= 192 && t.bm >= 192 ? 0.8 : i == T256X128 && plan.slice < 1024 ? 0.85
+                               : M <= 192 && t.bm >= 192 ? (layout == NN ? 0.8 : 0.9) : i == T256X128 && plan.slice < 1024 ? 0.85
                                : i == T256X128 || i == T192 ? 0.96 : 0.9);
       if (time < must * coarse_time && time < best_time) { best_time = time; best = plan; }
     }
