@@ -159,10 +159,10 @@ hipError_t attention_fwd(int batch, int n_heads, int seq, int head_dim, int caus
 // no room)?  At head_dim 64 always: the two products that the pass adds are cheap there.  At head_dim 128 by the number of
 // workgroups of 128 keys and the length: small grids rebuild (their workgroups can be halved, a product over 128 x 128 tiles
 // cannot), and so do long sequences on many workgroups (short ones write little dS^T per workgroup); between, where the pass has an
-// unfilled second round, dS^T is faster.  Time of the whole backward on dS^T over rebuilt, 900 shapes; causal: up to 256 workgroups
-// 1.08-1.34, 257-512 up to S 512 1.02-1.08; S 513-896 on 257-320 0.93-1.00, above 1.04-1.10; longer than 512 on 321-576 0.92-1.03 (B 3,
-// H 8, S 2088 112.6 us and 119.6); longer than 768 on 577-1023 1.00-1.11; unmasked: up to 128 workgroups 1.24-1.40, 129-256 0.82-1.10, 257-511
-// 0.91-1.06; S 769-1408 on 512-640 0.91-1.06 (B 4, H 16, S 1104 179.9 us and 190.6), above 1.01-1.10; on 641-768 up to S 896 0.97, above 0.99-1.08.
+// unfilled second round, dS^T is faster.  Time of the whole backward on dS^T over rebuilt, 1160 shapes; causal: up to 256 workgroups
+// 1.08-1.34, 257-512 up to S 512 1.02-1.08; S 513-896 on 257-320 0.93-1.00, above 1.04-1.10; longer than 512 on 321-576 0.90-1.04 (B 3,
+// H 8, S 2088 112.6 us and 119.6), but longer than 3072 on 321-384 0.97-1.09, 1.05 on average (B 3, H 4, S 3936 211
+// us and 193); longer than 768 on 577-1023 1.00-1.11; unmasked: up to 128 workgroups 1.24-1.40, 129-256 0.82-1.10, 257-511 0.91-1.06; S 769-1408 on 512-640 0.91-1.06 (B 4, H 16, S 1104 179.9 us and 190.6), above 1.01-1.10; on 641-768 up to S 896 0.97, above 0.99-1.08.
 // us, dS^T / rebuilt, dh 64: B 1, H 16, S 1024 45 / 30, B 4, H 12, S 1000 unmasked 82 / 73, B 2, H 24, S 2048 167 / 138, B 4, H 85, S 264 73 / 58
 // (unmasked 80 / 72), B 31, H 32, S 128 61 / 55, B 26, H 32, S 40 34 / 30, B 5, H 40, S 504 75 / 64; dh 128, 1024 workgroups: B 2, H 32, S 2048
 // 270 / 264, B 8, H 32, S 512 131 / 135.
@@ -178,7 +178,7 @@ inline bool attn_rebuilds_dq(int batch, int n_heads, int seq, int head_dim, int 
   if (!causal) return w <= 128 || (w > 768 ? seq > 768 : w > 640 ? seq > 896 : w >= 512 && seq > 1408);
   if (w <= 256) return true;
   if (seq <= 512) return w <= 512;
-  return w <= 320 ? seq > 896 : w > 576 && seq > 768;
+  return w <= 320 ? seq > 896 : w <= 384 ? seq > 3072 : w > 576 && seq > 768;
 }
 
 // Backward-p1 of the same: dq, dk, dv into the column blocks of dqkv from qkv, the forward's output and lse and the
