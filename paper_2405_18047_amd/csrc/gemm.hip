@@ -1666,7 +1666,8 @@ static SplitPlan search_plan(int layout, int M, int N, int K, bool allow_split) 
   const bool few_pairs = coarse.tile == T128_PAIR && coarse_wgs > 256 && coarse_wgs <= 288 && M > 850;
   // 64 x 64 tiles that it prices likewise (below) and that narrow outputs of split cache lines had better keep: N up to 256, time on the other
   // choice (128 x 64) over theirs 1.10-1.14 (K 1100-1400; from HBM 1.10), 1.06 (900-1100) and 1.06-1.10 (1400-1800); level or less for
-  // other K, and for wider outputs (500 tall ones of 257 to 290 workgroups; [4648, 216] x 1552 (NT), 292, 11.8 and 13.6).  [5448, 192] x 1248 (NT) 10.4 us, on 128 x 64 13.5.
+  // other K, and for wider outputs (500 tall ones of 257 to 290 workgroups; [4648, 216] x 1552 (NT), 292 of them, 11.8 us and 13.6).
+  // [5448, 192] x 1248 (NT) 10.4 us, on 128 x 64 13.5.
   if (coarse.tile == T64 && coarse.split == 1 && coarse_wgs > 256 && coarse_wgs <= 300 && N <= 256 && K % 64 && K >= 900 && K < 1800) return coarse;
   double best_time = 1e30;
   for (int i = T32; i <= T256; i++) {
