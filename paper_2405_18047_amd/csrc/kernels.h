@@ -155,17 +155,17 @@ hipError_t head_rowdot(int dtype, int rows, int n_heads, int head_dim, const voi
 hipError_t attention_fwd(int batch, int n_heads, int seq, int head_dim, int causal, const void* qkv, long ld_qkv,
                          void* out, long ld_out, float* lse, hipStream_t s);
 
-// Does the backward compute dq by a pass that rebuilds S and dP rather than from dS^T written to memory (for which a stage then has
-// no room)?  At head_dim 64 always: the two products that the pass adds are cheap there.  At head_dim 128 by the number of
-// workgroups of 128 keys and the length: small grids rebuild (their workgroups can be halved, a product over 128 x 128 tiles
-// cannot), and so do long sequences on many workgroups (short ones write little dS^T per workgroup); between, where the pass has an
-// unfilled second round, dS^T is faster.  Time of the whole backward on dS^T over rebuilt, 1160 shapes; causal: up to 256 workgroups
-// 1.08-1.34, 257-512 up to S 512 1.02-1.08; S 513-896 on 257-320 0.93-1.00, above 1.04-1.10; longer than 512 on 321-576 0.90-1.04 (B 3,
-// H 8, S 2088 112.6 us and 119.6), but longer than 3072 on 321-384 0.97-1.09, 1.05 on average (B 3, H 4, S 3936 211
-// us and 193); longer than 768 on 577-1023 1.00-1.11; unmasked: up to 128 workgroups 1.24-1.40, 129-256 0.82-1.10, 257-511 0.91-1.06; S 769-1408 on 512-640 0.91-1.06 (B 4, H 16, S 1104 179.9 us and 190.6), above 1.01-1.10; on 641-768 up to S 896 0.97, above 0.99-1.08.
-// us, dS^T / rebuilt, dh 64: B 1, H 16, S 1024 45 / 30, B 4, H 12, S 1000 unmasked 82 / 73, B 2, H 24, S 2048 167 / 138, B 4, H 85, S 264 73 / 58
-// (unmasked 80 / 72), B 31, H 32, S 128 61 / 55, B 26, H 32, S 40 34 / 30, B 5, H 40, S 504 75 / 64; dh 128, 1024 workgroups: B 2, H 32, S 2048
-// 270 / 264, B 8, H 32, S 512 131 / 135.
+// Does the backward compute dq by a pass that rebuilds S and dP rather than from dS^T written to memory (for which a stage then has no
+// room)?  At head_dim 64 always: the two products that the pass adds are cheap there.  At head_dim 128 by the number of workgroups of 128
+// keys and the length: small grids rebuild (their workgroups can be halved, a product over 128 x 128 tiles cannot), and so do long
+// sequences on many workgroups (short ones write little dS^T per workgroup); between, where the pass has an unfilled second round, dS^T is
+// faster.  Time of the whole backward on dS^T over rebuilt, 1160 shapes; causal: up to 256 workgroups 1.08-1.34, 257-512 up to S 512
+// 1.02-1.08; S 513-896 on 257-320 0.93-1.00, above 1.04-1.10; longer than 512 on 321-576 0.90-1.04 (B 3, H 8, S 2088 112.6 us and 119.6),
+// but longer than 3072 on 321-384 0.97-1.09, 1.05 on average (B 3, H 4, S 3936 211 us and 193); longer than 768 on 577-1023 1.00-1.11;
+// unmasked: up to 128 workgroups 1.24-1.40, 129-256 0.82-1.10, 257-511 0.91-1.06; S 769-1408 on 512-640 0.91-1.06 (B 4, H 16, S 1104 179.9
+// us and 190.6), above 1.01-1.10; on 641-768 up to S 896 0.97, above 0.99-1.08. us, dS^T / rebuilt, dh 64: B 1, H 16, S 1024 45 / 30, B 4,
+// H 12, S 1000 unmasked 82 / 73, B 2, H 24, S 2048 167 / 138, B 4, H 85, S 264 73 / 58 (unmasked 80 / 72), B 31, H 32, S 128 61 / 55, B 26,
+// H 32, S 40 34 / 30, B 5, H 40, S 504 75 / 64; dh 128, 1024 workgroups: B 2, H 32, S 2048 270 / 264, B 8, H 32, S 512 131 / 135.
 //
 // `rotates`: dq and dk have to leave rotated back, as a stage asks for, which the rebuilt form does on the way and dS^T by one more
 // launch.  The rebuilt form then is ahead on most of those grids as well: 1200 shapes with that launch; causal 257-576 workgroups above S 512
